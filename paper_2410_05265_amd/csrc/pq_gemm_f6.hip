@@ -864,6 +864,17 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
 {
     const int64_t gm = (M + 127) / 128;
     const int forced_tile = forced_f6_tile();
+    // Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
+    // tiles was measured at 5 us + 0.33 us per 128-channel stage and round (0.5 with every CU busy) + its output; the
+    // kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
+    // 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).
+    if (forced_tile == -1) {
+        const int64_t tiles = gm * ((N + 255) / 256);
+        const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
+        const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
+                                     (double)M * N * 2 / 4.2e6;
+        if (gemm_ksplit_f6_cost_us(M, N, K) < 0.97 * persistent_us) return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st);
+    }
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn

@@ -1,0 +1,344 @@
+// Products whose output has too few large tiles for 256 CUs (from about a dozen tokens to a few thousand
+// output tiles' worth): K is split over the wavefronts of a workgroup.
+//
+// The persistent and the tiled kernels give every CU one large tile and one wavefront per SIMD; with few tokens
+// most CUs have no tile, and those that do walk K alone, waiting for one load after the other.  Here a workgroup
+// of 8 or 16 wavefronts owns one small tile of the output (32 to 96 tokens x 32 to 96 channels, chosen so that
+// the tiles go round the CUs once), every wavefront multiplies its own run of K for the whole tile, and the
+// partial tiles are added through LDS at the end: no planes in memory, no second launch, no barrier in the main
+// loop.  What bounds it is the rate at which a CU takes its operands in: (tokens + channels) x K codes per tile
+// at 95-120 KB/us with eight wavefronts (four reach 80-95), so the rule that picks the tile minimises that sum
+// over the rounds.
+#include <hip/hip_fp16.h>
+
+#include <type_traits>
+
+#include "pq_internal.h"
+
+namespace pq {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) uint8_t* lds_u8;
+
+constexpr int kMaxLds = 160 * 1024;
+
+// Each XCD takes a contiguous run of tiles, row tiles fastest: the tiles that share weights meet in one L2.
+__device__ __forceinline__ int xcd_run(int b, int total)
+{
+    const int x = b & 7, idx = b >> 3, q = total >> 3, rem = total & 7;
+    return x * q + (x < rem ? x : rem) + idx;
+}
+
+// What the epilogue multiplies by and adds: one static step or the tokens' own (srow), and the zero-point's
+// per-channel integers (zcorr), as in the tiled kernel.
+struct Epilogue {
+    const float* sw;
+    float sx;
+    const float* srow;
+    const int32_t* zcorr;
+    __half* out;
+    int32_t* acc_out;
+};
+
+// LDS bytes of the partial tiles: one copy per wavefront where that fits, else one per pair of wavefronts.
+template <int TI, int CJ, int W>
+struct Partial {
+    static constexpr int kPitch = 128 * CJ + 16;              // a token's 32 CJ sums, padded (bank spread)
+    static constexpr int kCopy = 32 * TI * kPitch;
+    static constexpr int kSteps = 32 * CJ * 8 + 32 * TI * 4;  // channel steps, zero-point integers, token steps
+    static constexpr bool kPairs = W * kCopy + kSteps > kMaxLds;
+    static constexpr int kCopies = kPairs ? W / 2 : W;
+    static constexpr int kBytes = kCopies * kCopy;
+    static_assert(kBytes + kSteps <= kMaxLds, "partial tiles do not fit LDS");
+};
+
+// Adds the W partial tiles (sums of 2^SHIFT acc, register v of lane l: token l % 32, channel 8 (v / 4) + 4 (l / 32)
+// + v % 4) and writes the tile.  steps_at: LDS offset of the steps, filled by the caller before the first barrier here.
+template <typename ACC, int TI, int CJ, int W, int SHIFT>
+__device__ __forceinline__ void reduce_and_store(ACC (&acc)[CJ][TI], uint8_t* smem, int steps_at, const Epilogue& ep, int m0, int n0,
+                                                 int M, int N)
+{
+    using P = Partial<TI, CJ, W>;
+    using V4 = typename std::conditional<std::is_same<ACC, v16f>::value, v4f, v4i>::type;
+    typedef __attribute__((address_space(3))) V4* lds4;
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto at = [&](int copy, int i, int j, int q) {
+        return (lds4)(lds_u8)(smem + copy * P::kCopy + (32 * i + r) * P::kPitch + (32 * j + 8 * q + 4 * g) * 4);
+    };
+    auto put = [&](int copy) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < CJ; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *at(copy, i, j, q) = (V4){acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+    };
+    if constexpr (P::kPairs) {
+        if (wave >= W / 2) put(wave - W / 2);
+        __syncthreads();
+        if (wave < W / 2) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < CJ; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const V4 t = *at(wave, i, j, q);
+                        *at(wave, i, j, q) = (V4){acc[j][i][4 * q] + t.x, acc[j][i][4 * q + 1] + t.y, acc[j][i][4 * q + 2] + t.z,
+                                                  acc[j][i][4 * q + 3] + t.w};
+                    }
+        }
+    } else {
+        put(wave);
+    }
+    __syncthreads();
+    const float* steps = reinterpret_cast<const float*>(smem + steps_at);
+    constexpr int UPR = 8 * CJ, ITEMS = 32 * TI * UPR;        // four channels of a token per item
+#pragma unroll
+    for (int it0 = 0; it0 < ITEMS; it0 += 64 * W) {
+        const int it = it0 + tid;
+        if (ITEMS % (64 * W) != 0 && it >= ITEMS) break;
+        const int row = it / UPR, u = it % UPR, m = m0 + row, n = n0 + 4 * u;
+        V4 s = *(lds4)(lds_u8)(smem + row * P::kPitch + u * 16);
+#pragma unroll
+        for (int c = 1; c < P::kCopies; ++c) s += *(lds4)(lds_u8)(smem + c * P::kCopy + row * P::kPitch + u * 16);
+        if (m >= M || n >= N) continue;
+        const int64_t o = (int64_t)m * N + n;
+        if (ep.acc_out) {
+            const v4i a = {(int)s.x >> SHIFT, (int)s.y >> SHIFT, (int)s.z >> SHIFT, (int)s.w >> SHIFT};
+            *reinterpret_cast<v4i*>(ep.acc_out + o) = a;
+        }
+        if (ep.out) {
+            // the tiled kernels' two roundings: fp32(2^SHIFT' acc) * (sw * (step / 2^SHIFT')) with SHIFT' = 8 for 4-bit
+            // codes, 4 for 8-bit ones; the fp32 sums of the 6-bit instruction carry no factor, theirs goes to the step
+            constexpr int kFold = SHIFT == 0 ? 8 : SHIFT;
+            const float f = (ep.srow ? steps[64 * CJ + row] : ep.sx) * (1.0f / (float)(1 << kFold));
+            const v4f c = *reinterpret_cast<const v4f*>(steps + 4 * u);
+            float c0 = mul_rn(c.x, f), c1 = mul_rn(c.y, f), c2 = mul_rn(c.z, f), c3 = mul_rn(c.w, f);
+            if constexpr (SHIFT == 0) { c0 *= 256.0f; c1 *= 256.0f; c2 *= 256.0f; c3 *= 256.0f; }
+            if constexpr (SHIFT != 0) {
+                if (ep.zcorr) {
+                    const v4i z = *reinterpret_cast<const v4i*>(steps + 32 * CJ + 4 * u);
+                    s.x += z.x << SHIFT; s.y += z.y << SHIFT; s.z += z.z << SHIFT; s.w += z.w << SHIFT;
+                }
+            }
+            const __half2 lo = __floats2half2_rn(mul_rn((float)s.x, c0), mul_rn((float)s.y, c1));
+            const __half2 hi = __floats2half2_rn(mul_rn((float)s.z, c2), mul_rn((float)s.w, c3));
+            v2i val;
+            val.x = *reinterpret_cast<const int*>(&lo);
+            val.y = *reinterpret_cast<const int*>(&hi);
+            *reinterpret_cast<v2i*>(ep.out + o) = val;
+        }
+    }
+}
+
+// The tile's steps: requested at the start of the kernel, one value per thread, and written to LDS in front of the
+// reduction's barrier, so that no memory latency is left for the end.
+template <int TI, int CJ>
+struct Steps {
+    float s, t;
+    int z;
+    __device__ __forceinline__ void request(const Epilogue& ep, int m0, int n0, int M, int N)
+    {
+        const int tid = threadIdx.x;
+        s = t = 0.0f;
+        z = 0;
+        if (tid < 32 * CJ) {
+            const int n = n0 + tid < N ? n0 + tid : N - 1;
+            s = ep.sw[n];
+            if (ep.zcorr) z = ep.zcorr[n];
+        }
+        if (ep.srow && tid < 32 * TI) t = ep.srow[m0 + tid < M ? m0 + tid : M - 1];
+    }
+    __device__ __forceinline__ void deposit(uint8_t* at) const
+    {
+        const int tid = threadIdx.x;
+        float* p = reinterpret_cast<float*>(at);
+        if (tid < 32 * CJ) {
+            p[tid] = s;
+            reinterpret_cast<int*>(p)[32 * CJ + tid] = z;
+        }
+        if (tid < 32 * TI) p[64 * CJ + tid] = t;
+    }
+};
+
+// ---- prepacked operands (f6 tiles).  Every plane of a block is one contiguous load of a wavefront, so the operands
+// go straight from memory to the registers the matrix instruction reads: a ring of U stages of 128 channels, each
+// slot refilled as soon as its matrix instructions have been issued.
+template <int TI, int CJ, int W, int U>
+__global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6, Epilogue ep,
+                                                          int M, int N, int K, int GM)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    using P = Partial<TI, CJ, W>;
+    constexpr int kBlock = 3072, kP1 = 1024, kP2 = 1536, kP3 = 2048;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t l16 = (uint32_t)lane * 16u, l8 = (uint32_t)lane * 8u;
+    const int tile = xcd_run((int)blockIdx.x, (int)gridDim.x);
+    const int mt = tile % GM, nt = tile / GM, m0 = mt * (32 * TI), n0 = nt * (32 * CJ);
+    const int nk = K >> 7, RBX = (M + 31) >> 5, RBW = (N + 31) >> 5;
+    const int k0 = (int)((int64_t)nk * wave / W), k1 = (int)((int64_t)nk * (wave + 1) / W), n = k1 - k0;
+
+    Steps<TI, CJ> steps;
+    steps.request(ep, m0, n0, M, N);
+
+    const uint8_t *xp[TI], *wp[CJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        const int rb = mt * TI + i < RBX ? mt * TI + i : RBX - 1;
+        xp[i] = x6 + ((size_t)k0 * RBX + rb) * kBlock;
+    }
+#pragma unroll
+    for (int j = 0; j < CJ; ++j) {
+        const int rb = nt * CJ + j < RBW ? nt * CJ + j : RBW - 1;
+        wp[j] = w6 + ((size_t)k0 * RBW + rb) * kBlock;
+    }
+    v8i a[U][2][TI], b[U][2][CJ];
+    v16f acc[CJ][TI];
+#pragma unroll
+    for (int j = 0; j < CJ; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.0f;
+
+    auto image = [&](const uint8_t* blk, int st, v8i& d) {
+        if (st == 0) {
+            const v4i t = *reinterpret_cast<const v4i*>(blk + l16);
+            const v2i u = *reinterpret_cast<const v2i*>(blk + kP1 + l8);
+            d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w; d[4] = u.x; d[5] = u.y;
+        } else {
+            const v2i u = *reinterpret_cast<const v2i*>(blk + kP2 + l8);
+            const v4i t = *reinterpret_cast<const v4i*>(blk + kP3 + l16);
+            d[0] = u.x; d[1] = u.y; d[2] = t.x; d[3] = t.y; d[4] = t.z; d[5] = t.w;
+        }
+    };
+    auto load_step = [&](auto slotc, auto stc, int s) {
+        constexpr int slot = decltype(slotc)::value, st = decltype(stc)::value;
+#pragma unroll
+        for (int j = 0; j < CJ; ++j) image(wp[j] + (size_t)s * RBW * kBlock, st, b[slot][st][j]);
+#pragma unroll
+        for (int i = 0; i < TI; ++i) image(xp[i] + (size_t)s * RBX * kBlock, st, a[slot][st][i]);
+    };
+    auto multiply = [&](auto slotc, auto stc) {
+        constexpr int slot = decltype(slotc)::value, st = decltype(stc)::value;
+#pragma unroll
+        for (int j = 0; j < CJ; ++j)
+#pragma unroll
+            for (int i = 0; i < TI; ++i)      // formats 3, 3: E3M2 both; no scales
+                acc[j][i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[slot][st][j], a[slot][st][i], acc[j][i], 3, 3, 0, 0, 0, 0);
+    };
+    auto S0 = std::integral_constant<int, 0>{};
+    auto S1 = std::integral_constant<int, 1>{};
+    auto stage = [&](auto slotc) { multiply(slotc, S0); multiply(slotc, S1); };
+    auto stage_refill = [&](auto slotc, int s) {
+        multiply(slotc, S0);
+        load_step(slotc, S0, s);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(slotc, S1);
+        load_step(slotc, S1, s);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (n > 0) {
+        load_step(S0, S0, 0);
+        load_step(S0, S1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (U == 1) {
+            int s = 0;
+            for (; s + 1 < n; ++s) stage_refill(S0, s + 1);
+            stage(S0);
+        } else {
+            if (n > 1) {
+                load_step(S1, S0, 1);
+                load_step(S1, S1, 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            int s = 0;
+            for (; s + 3 < n; s += 2) {
+                stage_refill(S0, s + 2);
+                stage_refill(S1, s + 3);
+            }
+            const int left = n - s;                       // 1, 2 or 3
+            if (left == 3) stage_refill(S0, s + 2); else stage(S0);
+            if (left >= 2) stage(S1);
+            if (left == 3) stage(S0);
+        }
+    }
+    steps.deposit(smem + P::kBytes);
+    reduce_and_store<v16f, TI, CJ, W, 0>(acc, smem, P::kBytes, ep, m0, n0, M, N);
+}
+
+template <int TI, int CJ, int W, int U>
+int launch_f6_tile(const void* x6, const void* w6, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
+{
+    using P = Partial<TI, CJ, W>;
+    constexpr size_t lds = P::kBytes + P::kSteps;
+    const int GM = (int)((M + 32 * TI - 1) / (32 * TI)), GN = (int)((N + 32 * CJ - 1) / (32 * CJ));
+    auto kern = k_gemm_f6_ksplit<TI, CJ, W, U>;
+    static std::atomic<uint64_t> lds_ok{0};
+    if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN)), dim3(64 * W), lds, st, static_cast<const uint8_t*>(x6),
+                       static_cast<const uint8_t*>(w6), ep, (int)M, (int)N, (int)K, GM);
+    return hip_status(hipGetLastError());
+}
+
+// Tile of a launch and its estimated time in microseconds.  Per tile: the reduction and the epilogue (in proportion
+// to the tile), and per 128-channel stage of K the operands' way into the CU; tiles go round 256 CUs.  Fitted to
+// sweeps over 12 shapes (17 to 1111 tokens, K 4096 and 14336), within about 10 % of what was measured: 0.035 us per
+// stage and 32-row block of the tile.
+struct Plan {
+    int ti, cj;
+    double us;
+};
+
+template <int COUNT, typename COST>
+Plan best_plan(const int (&tiles)[COUNT][2], int64_t M, int64_t N, int64_t K, COST cost)
+{
+    Plan best{0, 0, 1e300};
+    for (const auto& t : tiles) {
+        const int64_t count = ((M + 32 * t[0] - 1) / (32 * t[0])) * ((N + 32 * t[1] - 1) / (32 * t[1]));
+        if (count > (1 << 20)) continue;
+        const double fill = count < 256 ? (double)count / 256 : 1.0;
+        const double us = 1.5 + (double)((count + 255) / 256) * cost(t[0], t[1], (double)(K / 128), fill) + (double)M * N * 2 / 4.2e6;
+        if (us < best.us) best = Plan{t[0], t[1], us};
+    }
+    return best;
+}
+
+constexpr int kTilesF6[][2] = {{1, 1}, {1, 2}, {2, 2}, {3, 2}, {2, 3}, {4, 2}, {2, 4}};
+
+Plan plan_f6(int64_t M, int64_t N, int64_t K)
+{
+    return best_plan(kTilesF6, M, N, K, [](int ti, int cj, double nk, double) { return 0.5 + 0.3 * ti * cj + 0.035 * (ti + cj) * nk; });
+}
+
+}  // namespace
+
+// Estimated microseconds; a large number where the kernel does not take the shape.
+double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K) { return plan_f6(M, N, K).us; }
+
+int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st)
+{
+    const Epilogue ep{sw, sx, nullptr, nullptr, static_cast<__half*>(out), acc};
+    const Plan p = plan_f6(M, N, K);
+    switch (p.ti * 10 + p.cj) {
+        case 11: return launch_f6_tile<1, 1, 8, 2>(x6, w6, ep, M, N, K, st);
+        case 12: return launch_f6_tile<1, 2, 8, 2>(x6, w6, ep, M, N, K, st);
+        case 22: return launch_f6_tile<2, 2, 8, 1>(x6, w6, ep, M, N, K, st);
+        case 32: return launch_f6_tile<3, 2, 8, 1>(x6, w6, ep, M, N, K, st);
+        case 23: return launch_f6_tile<2, 3, 8, 1>(x6, w6, ep, M, N, K, st);
+        case 42: return launch_f6_tile<4, 2, 8, 1>(x6, w6, ep, M, N, K, st);
+        case 24: return launch_f6_tile<2, 4, 8, 1>(x6, w6, ep, M, N, K, st);
+        default: return PQ_ERR_UNSUPPORTED;
+    }
+}
+
+}  // namespace pq

@@ -74,6 +74,11 @@ int launch_repack_f6(const void* codes, int64_t R, int64_t K, void* out, hipStre
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                    int32_t* acc, hipStream_t st);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
+// Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
+// number where the shape is not taken) and the launch.
+double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K);
+int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st);
 
 // forced tile configurations (sweeps and tests): previous value, or -2 for an unknown one
 int set_gemm_tile(int tile);

@@ -1,0 +1,71 @@
+"""GPU parity of the small-tile products that split K over a workgroup's wavefronts (outputs of few tiles).
+
+Accumulators are exact integers whatever the order of the partial sums, so they equal the oracle's, and the fp16
+outputs equal those of the large-tile kernels bit for bit.  Shapes: every tile size the rule picks, with ragged last
+tiles in both directions, fewer 128-channel stages than wavefronts (most wavefronts then add zeros), stage counts the
+wavefronts do not share evenly (one to four each, the prologue and both tails of the two-stage ring), and the longest
+row.
+"""
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2410_05265_amd import synth
+from pq_testlib import dev, host, ulp_diff
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pq():
+    import paper_2410_05265_amd.binding as b
+    b.lib()
+    return b
+
+
+def operands(M, N, K):
+    return (synth.random_packed(M, K, seed=M + K), synth.random_packed(N, K, seed=N + K, stream=7),
+            synth.random_scales(N, seed=N), np.float32(0.2173))
+
+
+# tokens, channels out, channels in; the tile the rule picks (32-row blocks of tokens x of channels)
+SHAPES_F6 = [(1, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (5, 80, 4224),      # 1 x 1
+             (33, 4112, 128), (40, 4240, 2304),                                                                   # 1 x 2
+             (33, 8208, 384), (100, 4176, 1152),                                                                  # 2 x 2
+             (100, 8208, 128), (190, 6032, 1280),                                                                 # 2 x 3
+             (70, 12304, 128), (333, 4096, 1152),                                                                 # 3 x 2
+             (131, 8208, 384),                                                                                    # 2 x 4
+             (100, 12304, 256), (500, 4080, 1024)]                                                                # 4 x 2
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES_F6)
+def test_prepacked_product(pq, M, N, K):
+    xq, wq, sw, sx = operands(M, N, K)
+    x6, w6 = pq.pq_repack_f6(dev(xq)), pq.pq_repack_f6(dev(wq))
+    acc_ref = O.gemm_i64(O.unpack(xq), O.unpack(wq))
+    out, acc = pq.pq_w4a4_gemm_f6(x6, w6, dev(sw), float(sx), M, N, K, want_acc=True)
+    assert np.array_equal(host(acc).astype(np.int64), acc_ref)
+    assert ulp_diff(host(out), O.epilogue(acc_ref, sx, sw)).max() <= 1
+    prev = pq.pq_set_gemm_f6_tile(2)
+    try:
+        big, _ = pq.pq_w4a4_gemm_f6(x6, w6, dev(sw), float(sx), M, N, K)
+    finally:
+        pq.pq_set_gemm_f6_tile(prev)
+    assert np.array_equal(host(big).view(np.uint16), host(out).view(np.uint16))
+    # each output alone
+    only, none = pq.pq_w4a4_gemm_f6(x6, w6, dev(sw), float(sx), M, N, K)
+    assert none is None and np.array_equal(host(only).view(np.uint16), host(out).view(np.uint16))
+    none, only = pq.pq_w4a4_gemm_f6(x6, w6, dev(sw), float(sx), M, N, K, want_out=False, want_acc=True)
+    assert none is None and np.array_equal(host(only), host(acc))
+
+
+def test_prepacked_extreme_codes_on_the_longest_row(pq):
+    """All codes -8 at the largest K: every partial sum and the total stay exact in fp32 (below 2^24)."""
+    M, N, K = 40, 64, 262016                     # the largest multiple of 128 the product accepts
+    x6 = pq.pq_repack_f6(dev(np.full((M, K // 2), 0x88, dtype=np.uint8)))
+    w6 = pq.pq_repack_f6(dev(np.full((N, K // 2), 0x88, dtype=np.uint8)))
+    sw = synth.random_scales(N, seed=1)
+    out, acc = pq.pq_w4a4_gemm_f6(x6, w6, dev(sw), 1e-5, M, N, K, want_acc=True)
+    assert (host(acc) == 64 * K).all()
+    assert ulp_diff(host(out), O.epilogue(np.full((M, N), 64 * K, dtype=np.int64), np.float32(1e-5), sw)).max() <= 1
