@@ -82,6 +82,28 @@ int pick_with_planes(int64_t M, int64_t N, int64_t K, size_t plane_bytes, int32_
     return kernel;
 }
 
+// Whether a 4-bit product goes to the kernel that splits K over the wavefronts of a workgroup (one launch, no planes)
+// instead of `kernel`, the choice above: by the estimates of both sides, against the tiled kernel (split with the planes
+// of this call, or whole) and against two or more streaming launches.  Measured, before -> after: 64 x 4096 x 14336
+// 14.6 -> 11.8 us (with planes; 39 without), 200 x 6144 x 4096 13.9 -> 11.4, 128 x 4096 x 4096 12.5 -> 6.4, 24 x 14336 x
+// 4096 12.6 -> 8.2, 32 x 4096 x 4096 8.8 -> 4.2; 500 x 4096 x 4096 would go 14.7 -> 16.3 and stays.  One streaming launch
+// (up to 16 tokens) is level or ahead and always stays.
+bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes)
+{
+    if (g_variant != 0) return false;
+    double other;
+    if (kernel == 2) {
+        other = pq::gemm_tiled_cost_us(M, N, K, plane_bytes);
+    } else if (kernel == 1) {
+        const int launches = pq::stream_mfma_launches(M, N, K, 4);
+        if (launches < 2) return false;
+        other = launches * (2.5 + (double)(N * (K / 2)) / 5.0e6);
+    } else {
+        return false;
+    }
+    return pq::gemm_ksplit_i8_cost_us(M, N, K) < 0.97 * other;
+}
+
 // Whether pq_linear takes the fused launch (every workgroup rotates and quantizes the few rows for itself)
 // when the shape allows it, rather than a quantizer launch and a product launch.  Measured with cold weights
 // on 8 to 117 MB matrices: without rotation the fused launch is level or ahead up to 32768 channels in all
@@ -154,7 +176,10 @@ int pq_w4a4_gemm_ws(const void* xq_packed, const void* wq_packed, const float* w
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (g_variant == 3)
         return pq::launch_gemm_simple(xq_packed, wq_packed, w_scale, act_scale, M, N, K, out_f16, acc_i32, st);
-    switch (pick_with_planes(M, N, K, workspace ? workspace_bytes : 0)) {
+    const int kernel = pick_with_planes(M, N, K, workspace ? workspace_bytes : 0);
+    if (take_ksplit(kernel, M, N, K, workspace ? workspace_bytes : 0))
+        return pq::launch_gemm_ksplit_i8(xq_packed, wq_packed, w_scale, act_scale, nullptr, nullptr, M, N, K, out_f16, acc_i32, st);
+    switch (kernel) {
         case 4:
             return pq::launch_decode(nullptr, xq_packed, wq_packed, w_scale, act_scale, 1, M, N, K, out_f16, acc_i32,
                                      nullptr, st);
@@ -370,6 +395,10 @@ int pq_gemm_dynamic_ws(const void* xq, int32_t bits, const void* wq_packed, cons
     if (few == 4)
         return pq::launch_decode(nullptr, xq, wq_packed, w_scale, 1.0f, 1, M, N, K, out_f16, acc_i32, nullptr,
                                  static_cast<hipStream_t>(stream), row_scale, bits);
+    // (the size limits of the tiled kernel's per-token form)
+    if (bits == 4 && K <= 65536 && M * K < ((int64_t)1 << 32) && take_ksplit(few, M, N, K, workspace ? workspace_bytes : 0))
+        return pq::launch_gemm_ksplit_i8(xq, wq_packed, w_scale, 1.0f, row_scale, nullptr, M, N, K, out_f16, acc_i32,
+                                         static_cast<hipStream_t>(stream));
     if (few == 1)
         return pq::launch_stream_mfma(xq, wq_packed, w_scale, 1.0f, M, N, K, out_f16, acc_i32,
                                       static_cast<hipStream_t>(stream), row_scale, bits);
@@ -524,6 +553,8 @@ int pq_w4a4_gemm_zp_ws(const void* xq_packed, const void* wq_packed, const float
     if (few == 4)
         return pq::launch_decode(nullptr, xq_packed, wq_packed, w_scale, act_scale, 1, M, N, K, out_f16, acc_i32,
                                  nullptr, st, nullptr, 4, zp_corr);
+    if (take_ksplit(few, M, N, K, workspace ? workspace_bytes : 0))
+        return pq::launch_gemm_ksplit_i8(xq_packed, wq_packed, w_scale, act_scale, nullptr, zp_corr, M, N, K, out_f16, acc_i32, st);
     if (few == 1)
         return pq::launch_stream_mfma(xq_packed, wq_packed, w_scale, act_scale, M, N, K, out_f16, acc_i32, st, nullptr,
                                       4, zp_corr);

@@ -275,6 +275,103 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __rest
     reduce_and_store<v16f, TI, CJ, W, 0>(acc, smem, P::kBytes, ep, m0, n0, M, N);
 }
 
+// ---- packed nibbles (canonical operands) on the INT8 matrix instruction.  Rows lie K/2 bytes apart, and a load whose
+// neighbouring lanes sit in different rows runs at one lane per clock, so the bytes go to LDS first, 64 contiguous
+// ones per row and stage (four lanes each), in a ring of NS stages that belongs to the wavefront alone (no barrier);
+// read back in the instruction's layout and expanded as in the tiled kernel.
+__device__ __forceinline__ void dma16(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
+{
+    // 16 bytes per lane from memory to LDS (lane l lands at lds_addr + 16 l); base and lds_addr are wavefront-uniform.
+    // Inline assembly so that the compiler places no waits of its own for it; the waits are counted by hand.
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_offset), "s"(base), "s"(lds_addr) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+template <int TI, int CJ, int W, int NS>
+__global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, Epilogue ep,
+                                                          int M, int N, int K, int GM)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    using P = Partial<TI, CJ, W>;
+    constexpr int kStage = (TI + CJ) * 2048, PIECES = (TI + CJ) * 2;          // 32 rows x 64 bytes per block
+    const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = xcd_run((int)blockIdx.x, (int)gridDim.x);
+    const int mt = tile % GM, nt = tile / GM, m0 = mt * (32 * TI), n0 = nt * (32 * CJ);
+    const int nk = K >> 7, Kb = K >> 1;
+    const int k0 = (int)((int64_t)nk * wave / W), k1 = (int)((int64_t)nk * (wave + 1) / W), n = k1 - k0;
+
+    Steps<TI, CJ> steps;
+    steps.request(ep, m0, n0, M, N);
+
+    // piece p: 16 rows; lane l fetches row l / 4, the 16-byte chunk that belongs at position l % 4: chunk c of row t
+    // sits at position c ^ ((t / 4) % 4), which spreads the reads of 32 rows over all banks
+    uint32_t off[PIECES];
+#pragma unroll
+    for (int p = 0; p < PIECES; ++p) {
+        const bool is_w = p < 2 * CJ;
+        int row = (is_w ? n0 + p * 16 : m0 + (p - 2 * CJ) * 16) + (lane >> 2);
+        const int last = (is_w ? N : M) - 1;
+        row = row < last ? row : last;
+        off[p] = (uint32_t)row * (uint32_t)Kb + (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 16);
+    }
+    const uint32_t ring = (uint32_t)(uintptr_t)(lds_u8)(smem + wave * (NS * kStage));
+    const uint8_t *xk = xq + (size_t)k0 * 64, *wk = wq + (size_t)k0 * 64;
+    auto request = [&](int s, int slot) {
+#pragma unroll
+        for (int p = 0; p < PIECES; ++p)
+            dma16((p < 2 * CJ ? wk : xk) + (size_t)s * 64, off[p], ring + slot * kStage + p * 1024);
+    };
+    const int swr = (r >> 2) & 3;
+    const int rd0 = r * 64 + ((g ^ swr) << 4), rd1 = r * 64 + (((2 + g) ^ swr) << 4);
+
+    v16i acc[CJ][TI];
+#pragma unroll
+    for (int j = 0; j < CJ; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][i][v] = 0;
+
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < n) request(s, s);
+    int slot = 0;
+    for (int s = 0; s < n; ++s) {
+        // stage s has landed when at most the NS - 1 stages behind it are outstanding; near the end there are fewer
+        if (s + NS - 1 < n) wait_vm<(NS - 1) * PIECES>();
+        else wait_vm<0>();
+        typedef __attribute__((address_space(3))) const uint8_t* lds_cu8;
+        lds_cu8 st = (lds_cu8)(lds_u8)(smem + wave * (NS * kStage) + slot * kStage);
+        v4i p[2][TI + CJ];
+#pragma unroll
+        for (int b = 0; b < TI + CJ; ++b) {
+            p[0][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 2048 + rd0);
+            p[1][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 2048 + rd1);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the slot has been read: it can be refilled)
+        if (s + NS < n) request(s + NS, slot);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            v4i e[TI + CJ], o[TI + CJ];
+#pragma unroll
+            for (int b = 0; b < TI + CJ; ++b) unpack16(p[kk][b], e[b], o[b]);
+#pragma unroll
+            for (int j = 0; j < CJ; ++j)
+#pragma unroll
+                for (int i = 0; i < TI; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(e[j], e[CJ + i], acc[j][i], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < CJ; ++j)
+#pragma unroll
+                for (int i = 0; i < TI; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o[j], o[CJ + i], acc[j][i], 0, 0, 0);
+        }
+    }
+    __syncthreads();                     // every wavefront is done with its ring: partial tiles and steps take its place
+    steps.deposit(smem + P::kBytes);
+    reduce_and_store<v16i, TI, CJ, W, 8>(acc, smem, P::kBytes, ep, m0, n0, M, N);
+}
+
 template <int TI, int CJ, int W, int U>
 int launch_f6_tile(const void* x6, const void* w6, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
 {
@@ -286,6 +383,22 @@ int launch_f6_tile(const void* x6, const void* w6, const Epilogue& ep, int64_t M
     if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN)), dim3(64 * W), lds, st, static_cast<const uint8_t*>(x6),
                        static_cast<const uint8_t*>(w6), ep, (int)M, (int)N, (int)K, GM);
+    return hip_status(hipGetLastError());
+}
+
+template <int TI, int CJ, int W, int NS>
+int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
+{
+    using P = Partial<TI, CJ, W>;
+    constexpr size_t ring = (size_t)W * NS * (TI + CJ) * 2048;
+    constexpr size_t lds = ring > (size_t)(P::kBytes + P::kSteps) ? ring : (size_t)(P::kBytes + P::kSteps);
+    static_assert(lds <= (size_t)kMaxLds, "ring too large");
+    const int GM = (int)((M + 32 * TI - 1) / (32 * TI)), GN = (int)((N + 32 * CJ - 1) / (32 * CJ));
+    auto kern = k_gemm_i8_ksplit<TI, CJ, W, NS>;
+    static std::atomic<uint64_t> lds_ok{0};
+    if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN)), dim3(64 * W), lds, st, static_cast<const uint8_t*>(xq),
+                       static_cast<const uint8_t*>(wq), ep, (int)M, (int)N, (int)K, GM);
     return hip_status(hipGetLastError());
 }
 
@@ -313,16 +426,34 @@ Plan best_plan(const int (&tiles)[COUNT][2], int64_t M, int64_t N, int64_t K, CO
 }
 
 constexpr int kTilesF6[][2] = {{1, 1}, {1, 2}, {2, 2}, {3, 2}, {2, 3}, {4, 2}, {2, 4}};
+constexpr int kTilesI8[][2] = {{1, 1}, {1, 2}, {2, 2}, {3, 2}, {2, 3}};
 
 Plan plan_f6(int64_t M, int64_t N, int64_t K)
 {
     return best_plan(kTilesF6, M, N, K, [](int ti, int cj, double nk, double) { return 0.5 + 0.3 * ti * cj + 0.035 * (ti + cj) * nk; });
 }
 
+// Packed nibbles: the expansion and the INT8 instructions weigh in, 0.089 / 0.125 / 0.17 / 0.25 us per stage for tiles
+// of 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few.
+Plan plan_i8(int64_t M, int64_t N, int64_t K)
+{
+    return best_plan(kTilesI8, M, N, K, [](int ti, int cj, double nk, double fill) {
+        const int area = ti * cj;
+        return 0.5 + 0.25 * area + (area == 1 ? 0.089 : (area == 2 ? 0.125 : (area == 4 ? 0.17 : 0.25))) * (0.7 + 0.3 * fill) * nk;
+    });
+}
+
 }  // namespace
 
 // Estimated microseconds; a large number where the kernel does not take the shape.
 double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K) { return plan_f6(M, N, K).us; }
+
+double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K)
+{
+    // (sums of 256 acc in int32, 32-bit byte offsets of the rows)
+    if (K % 128 != 0 || K >= 131072 || M * (K / 2) >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return 1e300;
+    return plan_i8(M, N, K).us;
+}
 
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st)
@@ -337,6 +468,21 @@ int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float
         case 23: return launch_f6_tile<2, 3, 8, 1>(x6, w6, ep, M, N, K, st);
         case 42: return launch_f6_tile<4, 2, 8, 1>(x6, w6, ep, M, N, K, st);
         case 24: return launch_f6_tile<2, 4, 8, 1>(x6, w6, ep, M, N, K, st);
+        default: return PQ_ERR_UNSUPPORTED;
+    }
+}
+
+int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float sx, const float* srow, const int32_t* zcorr, int64_t M,
+                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st)
+{
+    const Epilogue ep{sw, sx, srow, zcorr, static_cast<__half*>(out), acc};
+    const Plan p = plan_i8(M, N, K);
+    switch (p.ti * 10 + p.cj) {
+        case 11: return launch_i8_tile<1, 1, 16, 2>(xq, wq, ep, M, N, K, st);
+        case 12: return launch_i8_tile<1, 2, 8, 3>(xq, wq, ep, M, N, K, st);
+        case 22: return launch_i8_tile<2, 2, 8, 2>(xq, wq, ep, M, N, K, st);
+        case 32: return launch_i8_tile<3, 2, 8, 2>(xq, wq, ep, M, N, K, st);
+        case 23: return launch_i8_tile<2, 3, 8, 2>(xq, wq, ep, M, N, K, st);
         default: return PQ_ERR_UNSUPPORTED;
     }
 }

@@ -812,10 +812,11 @@ bool pick_dual(int64_t M, int64_t N, int* n1_out, int* n2_out)
 // (per 128-channel stage: 0.27-0.33 for a 64 x 128 tile, 0.42 for 128 x 128, 0.77 for 256 x 128, 1.35
 // for 256 x 256; 3.5 fixed for the unsplit launch, 5.8 for the split pair; partial planes written
 // and read back at ~4 TB/s).  S = 1: the unsplit kernel is cheaper or the workspace holds no two planes.
-void plan_splitk(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool force, int* bm_out, int* s_out)
+void plan_splitk(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool force, int* bm_out, int* s_out, double* us_out = nullptr)
 {
     *bm_out = 128;
     *s_out = 1;
+    if (us_out) *us_out = 1e300;
     if (K % 128 != 0 || N % 8 != 0 || M * N >= ((int64_t)1 << 31)) return;
     const int64_t nk = K / 128;
     if (force) {   // as many runs as fit, up to 5 (an odd count: uneven runs); the lowest tile that covers M
@@ -834,7 +835,7 @@ void plan_splitk(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool force, i
             const int64_t rounds = (tiles * S + 255) / 256;
             const double cost = 5.8 + (double)rounds * (double)((nk + S - 1) / S) * tk +
                                 (2.0 * S * plane_bytes + (double)M * N * 2) / 4.0e6;
-            if (cost < best) { best = cost; *bm_out = bm; *s_out = S; }
+            if (cost < best) { best = cost; *bm_out = bm; *s_out = S; if (us_out) *us_out = cost; }
         }
     }
 }
@@ -886,6 +887,16 @@ double gemm_unsplit_cost_us(int64_t M, int64_t N, int64_t K)
         if (cost < best) best = cost;
     }
     return best;
+}
+
+double gemm_tiled_cost_us(int64_t M, int64_t N, int64_t K, size_t ws_bytes)
+{
+    if (forced_tile() != -1) return 0.0;
+    int bm, S;
+    double split = 1e300;
+    if (ws_bytes > 0) plan_splitk(M, N, K, ws_bytes, false, &bm, &S, &split);
+    const double whole = gemm_unsplit_cost_us(M, N, K);
+    return split < whole ? split : whole;
 }
 
 size_t gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force)

@@ -55,8 +55,10 @@ int launch_gemm_mfma(const void* xq, const void* wq, const float* sw, float sx, 
 // a smaller one gets fewer planes or the unsplit launch.  force: split whenever K has two runs of two
 // stages and ws holds two planes (tests); PQ_ERR_UNSUPPORTED if not.
 size_t gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force = false);
-// the cost model's microseconds for the unsplit tiled launch (used to choose between kernels)
+// the cost model's microseconds for the unsplit tiled launch (used to choose between kernels), and for what the tiled
+// kernel would do with `ws_bytes` of scratch memory (split or not); 0 while a tile is forced
 double gemm_unsplit_cost_us(int64_t M, int64_t N, int64_t K);
+double gemm_tiled_cost_us(int64_t M, int64_t N, int64_t K, size_t ws_bytes);
 int launch_gemm_mfma_ws(const void* xq, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K,
                         void* out, int32_t* acc, void* ws, size_t ws_bytes, bool force, hipStream_t st);
 int launch_probe_mfma(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink,
@@ -75,10 +77,13 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
                    int32_t* acc, hipStream_t st);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
-// number where the shape is not taken) and the launch.
+// number where the shape is not taken) and the launches.  srow, zcorr as in the tiled kernel, or NULL.
 double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K);
+double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K);
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st);
+int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float sx, const float* srow, const int32_t* zcorr, int64_t M,
+                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st);
 
 // forced tile configurations (sweeps and tests): previous value, or -2 for an unknown one
 int set_gemm_tile(int tile);

@@ -60,6 +60,67 @@ def test_prepacked_product(pq, M, N, K):
     assert none is None and np.array_equal(host(only), host(acc))
 
 
+# the same for packed nibbles; from 17 tokens on (fewer take a weight-streaming kernel)
+SHAPES_I8 = [(17, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (20, 80, 4224),        # 1 x 1
+             (33, 4112, 128), (40, 4240, 2304),                                                                     # 1 x 2
+             (33, 8208, 384), (100, 4176, 1152),                                                                    # 2 x 2
+             (100, 8208, 384), (190, 6032, 1280),                                                                   # 2 x 3
+             (70, 12304, 384), (333, 4080, 1152)]                                                                   # 3 x 2
+
+
+def forced(pq, variant, fn, *a, **kw):
+    prev = pq.pq_set_gemm_variant(variant)
+    try:
+        return fn(*a, **kw)
+    finally:
+        pq.pq_set_gemm_variant(prev)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES_I8)
+def test_packed_product_with_every_epilogue(pq, M, N, K):
+    xq, wq, sw, sx = operands(M, N, K)
+    x, w, s = dev(xq), dev(wq), dev(sw)
+    acc_ref = O.gemm_i64(O.unpack(xq), O.unpack(wq))
+    out, acc = pq.pq_w4a4_gemm(x, w, s, float(sx), want_acc=True)
+    assert np.array_equal(host(acc).astype(np.int64), acc_ref)
+    assert ulp_diff(host(out), O.epilogue(acc_ref, sx, sw)).max() <= 1
+    tiled, _ = forced(pq, 2, pq.pq_w4a4_gemm, x, w, s, float(sx))
+    assert np.array_equal(host(tiled).view(np.uint16), host(out).view(np.uint16))
+    none, only = pq.pq_w4a4_gemm(x, w, s, float(sx), want_out=False, want_acc=True)
+    assert none is None and np.array_equal(host(only), host(acc))
+    # the tokens' own steps
+    srow = dev((0.05 + 0.4 * np.random.default_rng(M).random(M)).astype(np.float32))
+    dyn, acc = pq.pq_gemm_dynamic(x, 4, w, s, srow, want_acc=True)
+    tiled, _ = forced(pq, 2, pq.pq_gemm_dynamic, x, 4, w, s, srow)
+    assert np.array_equal(host(acc).astype(np.int64), acc_ref)
+    assert np.array_equal(host(tiled).view(np.uint16), host(dyn).view(np.uint16))
+    # a zero-point's per-channel integers
+    corr = pq.pq_zero_point_correction(w, 3)
+    zp, acc = pq.pq_w4a4_gemm_zp(x, w, s, float(sx), corr, want_acc=True)
+    tiled, _ = forced(pq, 2, pq.pq_w4a4_gemm_zp, x, w, s, float(sx), corr)
+    assert np.array_equal(host(acc).astype(np.int64), acc_ref)
+    assert np.array_equal(host(tiled).view(np.uint16), host(zp).view(np.uint16))
+
+
+def test_packed_extreme_codes_on_the_longest_row(pq):
+    """All codes -8 at the largest K: the int32 sums of 256 acc hold 256 * 64 * K."""
+    M, N, K = 40, 64, 130944
+    x, w = (dev(np.full((r, K // 2), 0x88, dtype=np.uint8)) for r in (M, N))
+    sw = synth.random_scales(N, seed=1)
+    out, acc = pq.pq_w4a4_gemm(x, w, dev(sw), 1e-5, want_acc=True)
+    assert (host(acc) == 64 * K).all()
+    assert ulp_diff(host(out), O.epilogue(np.full((M, N), 64 * K, dtype=np.int64), np.float32(1e-5), sw)).max() <= 1
+
+
+def test_limits_of_the_per_token_form_stay(pq):
+    """Rows longer than 65536 channels were refused with per-token steps and still are."""
+    import torch
+    K = 65536 + 128
+    x, w = (torch.zeros((r, K // 2), dtype=torch.uint8, device="cuda") for r in (40, 64))
+    with pytest.raises(RuntimeError, match="PQ_ERR_UNSUPPORTED"):
+        pq.pq_gemm_dynamic(x, 4, w, torch.ones(64, device="cuda"), torch.ones(40, device="cuda"))
+
+
 def test_prepacked_extreme_codes_on_the_longest_row(pq):
     """All codes -8 at the largest K: every partial sum and the total stay exact in fp32 (below 2^24)."""
     M, N, K = 40, 64, 262016                     # the largest multiple of 128 the product accepts
