@@ -697,6 +697,15 @@ int pq_rotate_quant_f6(const void* x_f16, int64_t M, int64_t K, int32_t had_bloc
 // rotation blocks beyond what the tile-writing quantizer handles go through the canonical codes
 static bool f6_needs_codes(int64_t M, int64_t K, int32_t had_block) { return !pq::quant_f6_supported(M, K, had_block); }
 
+// Both forms of the codes: one launch for blocks of 4096 channels, else the codes and a repack.
+static int quant_codes_and_tiles(const void* x, int64_t M, int64_t K, int32_t had_block, float act_scale, uint8_t* tiles, uint8_t* nibbles,
+                                 hipStream_t st)
+{
+    if (pq::rotate4096_mfma_supported(K, had_block)) return pq::launch_rotate4096_mfma(x, M, K, act_scale, tiles, nibbles, st);
+    const int rc = pq_rotate_quant(x, M, K, had_block, act_scale, nibbles, st);
+    return rc == PQ_OK ? pq::launch_repack_f6(nibbles, M, K, tiles, st) : rc;
+}
+
 size_t pq_linear_f6_workspace_bytes(int64_t M, int64_t K, int32_t had_block)
 {
     if (M <= 0 || K <= 0 || (K % 128) != 0) return 0;
@@ -728,8 +737,7 @@ int pq_linear_f6(const void* x_f16, const void* w_tiles, const float* w_scale, f
         rc = pq::launch_quant_f6(x_f16, M, K, had_block, act_scale, tiles, nullptr, st);
     } else {
         uint8_t* nibbles = tiles + ((pq::f6_tiles_bytes(M, K) + 255) & ~(size_t)255);
-        rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, nibbles, stream);
-        if (rc == PQ_OK) rc = pq::launch_repack_f6(nibbles, M, K, tiles, st);
+        rc = quant_codes_and_tiles(x_f16, M, K, had_block, act_scale, tiles, nibbles, st);
     }
     if (rc != PQ_OK) return rc;
     return pq::launch_gemm_f6(tiles, w_tiles, w_scale, act_scale, M, N, K, out_f16, nullptr, st);
@@ -761,8 +769,7 @@ int pq_linear2_f6(const void* x_f16, const void* w_tiles_a, const float* w_scale
         rc = pq::launch_quant_f6(x_f16, M, K, had_block, act_scale, tiles, nullptr, st);
     } else {
         uint8_t* nibbles = tiles + ((pq::f6_tiles_bytes(M, K) + 255) & ~(size_t)255);
-        rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, nibbles, stream);
-        if (rc == PQ_OK) rc = pq::launch_repack_f6(nibbles, M, K, tiles, st);
+        rc = quant_codes_and_tiles(x_f16, M, K, had_block, act_scale, tiles, nibbles, st);
     }
     if (rc != PQ_OK) return rc;
     rc = pq::launch_gemm_f6(tiles, w_tiles_a, w_scale_a, act_scale, M, N_a, K, out_a_f16, nullptr, st);

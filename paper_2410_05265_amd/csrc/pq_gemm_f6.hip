@@ -339,6 +339,108 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
     });
 }
 
+// Rotation blocks of 4096 channels: H_4096 = H_32 x H_128, so a token's 128-channel blocks are first multiplied by H_128
+// on the matrix pipe, as above but with the 32 blocks of ONE token as the columns, and the five outer stages are fp32
+// butterflies between the lanes that hold the blocks.  With butterflies alone and a repack behind them the rotation of a
+// prepacked layer was two launches, bound by vector instructions and by launch latency (1111 x 4096: 9.8 + 5.5 us);
+// this is one launch that writes tiles, nibbles, or both.
+//
+// A workgroup of 16 wavefronts takes four tokens, four wavefronts each: wavefront n of a token computes the output
+// channels 32 n .. 32 n + 31 of every block (8 matrix instructions), so that a handful of tokens still keeps a CU busy.
+// The codes meet in LDS (8 bytes per lane: lane (block b, half g) holds channels 32 n + 16 g ..), and one thread per register
+// image or per 16 bytes of nibbles writes them out; four tokens side by side make 64-byte runs of a tile's planes.
+constexpr int kCodePitch = 80;     // LDS bytes per 128-channel block of codes: 64 + 16 (bank spread, 16-byte aligned)
+
+template <bool STREAM>
+__global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __restrict__ x, int64_t row_base, int64_t M, int K,
+                                                                  rq::StaticStep steps, uint8_t* __restrict__ tiles,
+                                                                  uint8_t* __restrict__ nibbles)
+{
+    __shared__ __align__(16) uint8_t stage_all[4 * 32 * kXPitch];
+    __shared__ __align__(16) uint8_t codes_all[4 * 32 * kCodePitch];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tok = wave >> 2, n = wave & 3;
+    const int64_t row0 = row_base + (int64_t)blockIdx.y * 4;
+    const int kt0 = blockIdx.x * 32;                         // first 128-channel block of this rotation block
+    uint8_t* stg = stage_all + tok * (32 * kXPitch);
+    // ---- the token's 4096 channels into LDS, one row of 128 channels per block: this wavefront's quarter
+    {
+        const int64_t row = row0 + tok;
+        const bool in_row = row < M;
+        const uint8_t* base = reinterpret_cast<const uint8_t*>(x + ((in_row ? row : 0) * K + (int64_t)kt0 * 128));
+        v4i raw[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int b = 8 * n + 4 * p + (lane >> 4);
+            raw[p] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(base + b * 256 + (lane & 15) * 16));
+            if (!in_row) raw[p] = (v4i){0, 0, 0, 0};         // tokens past the end: zero codes
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+            *(__attribute__((address_space(3))) v4i*)(stg + (8 * n + 4 * p + (lane >> 4)) * kXPitch + (lane & 15) * 16) = raw[p];
+    }
+    // ---- the H operand (see above): sign = parity of popcount(i & j), j = 32 n + l % 32, i = 16 s + 8 (l / 32) + 0..7
+    const int j = lane & 31, g = lane >> 5;
+    uint32_t hreg[2][4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t lo = __builtin_popcount((2 * d) & j & 7) & 1, hi = __builtin_popcount((2 * d + 1) & j & 7) & 1;
+        const uint32_t base = 0x3C003C00u ^ (lo << 15) ^ (hi << 31);
+        const uint32_t f0 = (uint32_t)(g & (j >> 3)) & 1u, f1 = f0 ^ ((uint32_t)(j >> 4) & 1u);
+        hreg[0][d] = base ^ (f0 * 0x80008000u);
+        hreg[1][d] = base ^ (f1 * 0x80008000u);
+    }
+    __syncthreads();
+    // ---- blocks x H_128: lane l ends with block l % 32, channels 32 n + 8 (v / 4) + 4 (l / 32) + v % 4
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    static_for6<0, 8>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        const v4i xi = *(__attribute__((address_space(3))) const v4i*)(stg + j * kXPitch + 32 * s + 16 * g);
+        const uint32_t flip = (__builtin_popcount((s >> 1) & n) & 1) ? 0x80008000u : 0u;      // wavefront-uniform
+        const v4i hi4 = {(int)(hreg[s & 1][0] ^ flip), (int)(hreg[s & 1][1] ^ flip), (int)(hreg[s & 1][2] ^ flip), (int)(hreg[s & 1][3] ^ flip)};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, hi4), __builtin_bit_cast(v8h, xi), acc, 0, 0, 0);
+    });
+    // ---- the outer stages: between blocks, i.e. between lanes
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = acc[i];
+    rq::lane_stage<0>(v, lane);
+    rq::lane_stage<1>(v, lane);
+    rq::lane_stage<2>(v, lane);
+    rq::lane_stage<3>(v, lane);
+    rq::lane_stage<4>(v, lane);
+    // ---- quantize; the half-wavefronts trade so that a lane has 16 consecutive channels (as in the kernel above)
+    const uint32_t w01 = rq::quant_pack8<false>(v, v, steps.mult, steps.step);
+    const uint32_t w23 = rq::quant_pack8<false>(v + 8, v + 8, steps.mult, steps.step);
+    const auto sw = __builtin_amdgcn_permlane32_swap(w01, w23, false, false);
+    const uint32_t mine = sw[0], theirs = sw[1];
+    const v2i two = {(int)__builtin_amdgcn_perm(theirs, mine, 0x05040100u), (int)__builtin_amdgcn_perm(theirs, mine, 0x07060302u)};
+    *(__attribute__((address_space(3))) v2i*)(codes_all + tok * (32 * kCodePitch) + j * kCodePitch + n * 16 + g * 8) = two;
+    __syncthreads();
+    // ---- out: 512 register images (four tokens side by side) by the first half of the workgroup, 512 pieces of 16 bytes of
+    // nibbles by the other half (by all in turn if only one of the two is wanted, which leaves the rest idle)
+    const int half = tid >> 9, id = tid & 511;
+    if (tiles && half == 0) {
+        const int t = id & 3, part = id >> 2, b = part >> 2, st = (part >> 1) & 1, gg = part & 1;
+        const v4i p = *(__attribute__((address_space(3))) const v4i*)(codes_all + t * (32 * kCodePitch) + b * kCodePitch + st * 32 + gg * 16);
+        const int64_t row = row0 + t, RB = (M + 31) >> 5;    // (row < 32 RB: the grid covers whole row blocks)
+        uint64_t w[3];
+        image_of_nibbles(p, w);
+        store_image<STREAM>(tiles + ((int64_t)(kt0 + b) * RB + (row >> 5)) * kChunkF6, (int)(row & 31) + 32 * gg, st, w);
+    }
+    if (nibbles && half == 1) {
+        const int t = id >> 7, piece = id & 127, b = piece >> 2;
+        if (row0 + t < M) {
+            const v4i p = *(__attribute__((address_space(3))) const v4i*)(codes_all + t * (32 * kCodePitch) + b * kCodePitch + (piece & 3) * 16);
+            v4i* at = reinterpret_cast<v4i*>(nibbles + (row0 + t) * (K >> 1) + (int64_t)kt0 * 64 + piece * 16);
+            if constexpr (STREAM) __builtin_nontemporal_store(p, at);
+            else *at = p;
+        }
+    }
+}
+
 __device__ __forceinline__ int xcd_run(int b, int total)   // each XCD takes a contiguous run of tiles
 {
     const int x = b & 7, idx = b >> 3, q = total >> 3, rem = total & 7;
@@ -806,6 +908,28 @@ int launch_rotate128_mfma(const void* x, int64_t R, int64_t K, float act_scale, 
         else hipLaunchKernelGGL((k_rotate128_quant_mfma<W, 1, false>), grid, dim3(64 * W), 0, st, xp, (int)R, (int)K, steps, tp, np);
     }
     return hip_status(hipGetLastError());
+}
+
+// 4096-point blocks.  The choice depends on the row alone, so every call on the same input sees the same codes.  (The same
+// kernel with fewer outer stages is level with the butterflies at 2048 points and behind at 1024: 0.92-1.09 x.)
+// out (tiles) or nibbles may be NULL, not both.
+bool rotate4096_mfma_supported(int64_t K, int32_t h) { return h == 4096 && (K % 4096) == 0 && K <= (1 << 24); }
+
+int launch_rotate4096_mfma(const void* x, int64_t R, int64_t K, float act_scale, void* tiles, void* nibbles, hipStream_t st)
+{
+    const rq::StaticStep steps{(float)(1.0 / ((double)act_scale * 64.0)), act_scale};
+    const bool stream = (tiles ? (int64_t)f6_tiles_bytes(R, K) : R * (K / 2)) <= rq::kStreamBelow;   // (the larger output)
+    uint8_t *tp = static_cast<uint8_t*>(tiles), *np = static_cast<uint8_t*>(nibbles);
+    const int64_t rows = tiles ? (R + 31) / 32 * 32 : R;             // a tile's rows past the end are zero codes
+    for (int64_t r0 = 0; r0 < rows; r0 += 131072) {                  // grid.y is limited to 65535 per launch
+        const int64_t mm = rows - r0 < 131072 ? rows - r0 : 131072;
+        const dim3 grid((unsigned)(K / 4096), (unsigned)((mm + 3) / 4));
+        if (stream) hipLaunchKernelGGL((k_rotate4096_quant_mfma<true>), grid, dim3(1024), 0, st, static_cast<const __half*>(x), r0, R, (int)K, steps, tp, np);
+        else hipLaunchKernelGGL((k_rotate4096_quant_mfma<false>), grid, dim3(1024), 0, st, static_cast<const __half*>(x), r0, R, (int)K, steps, tp, np);
+        const int rc = hip_status(hipGetLastError());
+        if (rc != PQ_OK) return rc;
+    }
+    return PQ_OK;
 }
 
 int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_scale, void* out, void* nibbles, hipStream_t st)

@@ -231,6 +231,38 @@ def test_rotation_of_128_point_blocks_on_the_matrix_pipe(pq, M, K):
         assert np.all(np.abs(t - (np.minimum(got[at], want[at]) + 0.5)) <= 1e-3)
 
 
+@pytest.mark.parametrize("M,K,h", [(1, 4096, 4096), (5, 4096, 4096), (33, 8192, 4096), (66, 12288, 4096), (1030, 4096, 4096), (37, 6144, 2048)])
+def test_rotation_of_4096_point_blocks_on_the_matrix_pipe(pq, M, K, h):
+    """4096-point blocks: 128-point products on the matrix pipe, the outer stages between lanes (2048-point blocks stay with
+    the butterflies).  Against the oracle's fp64 rotation, codes differ only at rounding ties; the tiles of the prepacked
+    layer are the same codes, rows past the end zero.  Token counts that are no multiple of 4 or 32, one to three blocks
+    per row; the last rows are one-hot and constant (their rotations are known in closed form, exact in fp32)."""
+    x = synth.activations(M, K, seed=3 * M + K)
+    x[-1] = 0
+    x[-1, K - h + 77] = np.float16(3.0)                       # +-3 / sqrt(h) in the last block
+    if M > 1:
+        x[-2] = np.float16(0.25)                              # 0.25 sqrt(h) in the first channel of every block
+    y = O.rotate(x, h)
+    sx = np.float32(np.abs(y).max() / 7.0)
+    want = O.quantize(y, sx)
+    codes = host(pq.pq_rotate_quant(dev(x), h, float(sx)))
+    w6 = pq.pq_repack_f6(dev(synth.random_packed(16, K, seed=1, stream=7)))
+    ws = torch.full((pq.pq_linear_f6_workspace_bytes(M, K, h),), 0x77, dtype=torch.uint8, device="cuda")
+    pq.pq_linear_f6(dev(x), w6, dev(synth.random_scales(16)), float(sx), h, workspace=ws)
+    tiles = pq.pq_f6_tiles_bytes(M, K)
+    assert np.array_equal(host(ws)[:tiles], tiles_by_definition(O.unpack(codes)))
+    off = (tiles + 255) // 256 * 256
+    assert np.array_equal(host(ws)[off:off + M * K // 2].reshape(M, K // 2), codes)
+    got = O.unpack(codes).astype(np.int32)
+    diff = got - want.astype(np.int32)
+    at = np.nonzero(diff)
+    assert at[0].size <= 1e-3 * diff.size
+    if at[0].size:
+        assert np.all(np.abs(diff[at]) == 1)
+        t = y[at] / np.float64(sx)
+        assert np.all(np.abs(t - (np.minimum(got[at], want[at]) + 0.5)) <= 1e-3)
+
+
 def test_outputs_larger_than_the_l2s(pq):
     """A launch whose codes or images exceed 32 MiB writes them with ordinary stores, a smaller one streams them
     out: same bytes either way.  17000 x 4096 unrotated: 34.8 MB of nibbles, 52 MB of images; codes against the
