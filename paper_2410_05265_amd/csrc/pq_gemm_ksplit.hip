@@ -3,12 +3,11 @@
 //
 // The persistent and the tiled kernels give every CU one large tile and one wavefront per SIMD; with few tokens
 // most CUs have no tile, and those that do walk K alone, waiting for one load after the other.  Here a workgroup
-// of 8 or 16 wavefronts owns one small tile of the output (32 to 96 tokens x 32 to 96 channels, chosen so that
+// of 4 to 16 wavefronts owns one small tile of the output (32 to 128 tokens x 32 to 128 channels, chosen so that
 // the tiles go round the CUs once), every wavefront multiplies its own run of K for the whole tile, and the
 // partial tiles are added through LDS at the end: no planes in memory, no second launch, no barrier in the main
-// loop.  What bounds it is the rate at which a CU takes its operands in: (tokens + channels) x K codes per tile
-// at 95-120 KB/us with eight wavefronts (four reach 80-95), so the rule that picks the tile minimises that sum
-// over the rounds.
+// loop.  What bounds it is the rate at which a CU takes its operands in, (tokens + channels) x K codes per tile at
+// 80-100 KB/us, so the rule that picks the tile minimises that sum over the rounds.
 #include <hip/hip_fp16.h>
 
 #include <type_traits>
@@ -170,7 +169,10 @@ struct Steps {
 
 // ---- prepacked operands (f6 tiles).  Every plane of a block is one contiguous load of a wavefront, so the operands
 // go straight from memory to the registers the matrix instruction reads: a ring of U stages of 128 channels, each
-// slot refilled as soon as its matrix instructions have been issued.
+// slot refilled as soon as its matrix instructions have been issued.  Four wavefronts: with eight the loads come in
+// 15 % faster, but twice the partial tiles have to pass through LDS (333 x 4096 x 4096: 9.8 against 9.5 us, 128 x
+// 14336 x 4096: 12.5 against 11.6), and two or three of the smaller workgroups share a CU (64 x 64 tiles in two
+// rounds: 13.0 against 11.7).  A second stage in the ring of the larger tiles: 3 % slower.
 template <int TI, int CJ, int W, int U>
 __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6, Epilogue ep,
                                                           int M, int N, int K, int GM)
@@ -402,44 +404,51 @@ int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M
     return hip_status(hipGetLastError());
 }
 
-// Tile of a launch and its estimated time in microseconds.  Per tile: the reduction and the epilogue (in proportion
-// to the tile), and per 128-channel stage of K the operands' way into the CU; tiles go round 256 CUs.  Fitted to
-// sweeps over 12 shapes (17 to 1111 tokens, K 4096 and 14336), within about 10 % of what was measured: 0.035 us per
-// stage and 32-row block of the tile.
+// Tile of a launch and its estimated time in microseconds.  Per 128-channel stage of K the operands' way into the CU,
+// and per tile the reduction and the epilogue (in proportion to the tile), which overlap another tile's stages where
+// several workgroups fit a CU; tiles go round 256 CUs.  Fitted to sweeps over 12 shapes (17 to 1111 tokens, K 4096 and
+// 14336), within about 10 % of what was measured.
 struct Plan {
     int ti, cj;
     double us;
 };
 
+struct TileShape {
+    int ti, cj, resident;      // 32-row blocks of tokens and of channels; workgroups a CU holds at a time
+};
+
 template <int COUNT, typename COST>
-Plan best_plan(const int (&tiles)[COUNT][2], int64_t M, int64_t N, int64_t K, COST cost)
+Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t K, double per_area, COST stage_us)
 {
     Plan best{0, 0, 1e300};
-    for (const auto& t : tiles) {
-        const int64_t count = ((M + 32 * t[0] - 1) / (32 * t[0])) * ((N + 32 * t[1] - 1) / (32 * t[1]));
+    for (const TileShape& t : tiles) {
+        const int64_t count = ((M + 32 * t.ti - 1) / (32 * t.ti)) * ((N + 32 * t.cj - 1) / (32 * t.cj));
         if (count > (1 << 20)) continue;
+        const int64_t rounds = (count + 255) / 256;
         const double fill = count < 256 ? (double)count / 256 : 1.0;
-        const double us = 1.5 + (double)((count + 255) / 256) * cost(t[0], t[1], (double)(K / 128), fill) + (double)M * N * 2 / 4.2e6;
-        if (us < best.us) best = Plan{t[0], t[1], us};
+        const double us = 1.5 + (double)rounds * (double)(K / 128) * stage_us(t, fill) +
+                          (double)((rounds + t.resident - 1) / t.resident) * (0.5 + per_area * t.ti * t.cj) + (double)M * N * 2 / 4.2e6;
+        if (us < best.us) best = Plan{t.ti, t.cj, us};
     }
     return best;
 }
 
-constexpr int kTilesF6[][2] = {{1, 1}, {1, 2}, {2, 2}, {3, 2}, {2, 3}, {4, 2}, {2, 4}};
-constexpr int kTilesI8[][2] = {{1, 1}, {1, 2}, {2, 2}, {3, 2}, {2, 3}};
+constexpr TileShape kTilesF6[] = {{1, 1, 4}, {1, 2, 3}, {2, 2, 2}, {3, 2, 1}, {2, 3, 1}, {4, 2, 1}, {2, 4, 1}};
+constexpr TileShape kTilesI8[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {3, 2, 1}, {2, 3, 1}};
 
+// Prepacked: 0.035 us per stage and 32-row block of the tile (3 KiB at 85 KB/us).
 Plan plan_f6(int64_t M, int64_t N, int64_t K)
 {
-    return best_plan(kTilesF6, M, N, K, [](int ti, int cj, double nk, double) { return 0.5 + 0.3 * ti * cj + 0.035 * (ti + cj) * nk; });
+    return best_plan(kTilesF6, M, N, K, 0.3, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
 }
 
 // Packed nibbles: the expansion and the INT8 instructions weigh in, 0.089 / 0.125 / 0.17 / 0.25 us per stage for tiles
 // of 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few.
 Plan plan_i8(int64_t M, int64_t N, int64_t K)
 {
-    return best_plan(kTilesI8, M, N, K, [](int ti, int cj, double nk, double fill) {
-        const int area = ti * cj;
-        return 0.5 + 0.25 * area + (area == 1 ? 0.089 : (area == 2 ? 0.125 : (area == 4 ? 0.17 : 0.25))) * (0.7 + 0.3 * fill) * nk;
+    return best_plan(kTilesI8, M, N, K, 0.25, [](const TileShape& t, double fill) {
+        const int area = t.ti * t.cj;
+        return (area == 1 ? 0.089 : (area == 2 ? 0.125 : (area == 4 ? 0.17 : 0.25))) * (0.7 + 0.3 * fill);
     });
 }
 
@@ -461,13 +470,13 @@ int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float
     const Epilogue ep{sw, sx, nullptr, nullptr, static_cast<__half*>(out), acc};
     const Plan p = plan_f6(M, N, K);
     switch (p.ti * 10 + p.cj) {
-        case 11: return launch_f6_tile<1, 1, 8, 2>(x6, w6, ep, M, N, K, st);
-        case 12: return launch_f6_tile<1, 2, 8, 2>(x6, w6, ep, M, N, K, st);
-        case 22: return launch_f6_tile<2, 2, 8, 1>(x6, w6, ep, M, N, K, st);
-        case 32: return launch_f6_tile<3, 2, 8, 1>(x6, w6, ep, M, N, K, st);
-        case 23: return launch_f6_tile<2, 3, 8, 1>(x6, w6, ep, M, N, K, st);
-        case 42: return launch_f6_tile<4, 2, 8, 1>(x6, w6, ep, M, N, K, st);
-        case 24: return launch_f6_tile<2, 4, 8, 1>(x6, w6, ep, M, N, K, st);
+        case 11: return launch_f6_tile<1, 1, 4, 2>(x6, w6, ep, M, N, K, st);
+        case 12: return launch_f6_tile<1, 2, 4, 2>(x6, w6, ep, M, N, K, st);
+        case 22: return launch_f6_tile<2, 2, 4, 1>(x6, w6, ep, M, N, K, st);
+        case 32: return launch_f6_tile<3, 2, 4, 1>(x6, w6, ep, M, N, K, st);
+        case 23: return launch_f6_tile<2, 3, 4, 1>(x6, w6, ep, M, N, K, st);
+        case 42: return launch_f6_tile<4, 2, 4, 1>(x6, w6, ep, M, N, K, st);
+        case 24: return launch_f6_tile<2, 4, 4, 1>(x6, w6, ep, M, N, K, st);
         default: return PQ_ERR_UNSUPPORTED;
     }
 }
