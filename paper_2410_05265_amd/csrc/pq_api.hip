@@ -772,6 +772,8 @@ int pq_linear2_f6(const void* x_f16, const void* w_tiles_a, const float* w_scale
         rc = quant_codes_and_tiles(x_f16, M, K, had_block, act_scale, tiles, nibbles, st);
     }
     if (rc != PQ_OK) return rc;
+    if (N_a == N_b)
+        return pq::launch_gemm_f6(tiles, w_tiles_a, w_scale_a, act_scale, M, N_a, K, out_a_f16, nullptr, st, w_tiles_b, w_scale_b, out_b_f16);
     rc = pq::launch_gemm_f6(tiles, w_tiles_a, w_scale_a, act_scale, M, N_a, K, out_a_f16, nullptr, st);
     if (rc != PQ_OK) return rc;
     return pq::launch_gemm_f6(tiles, w_tiles_b, w_scale_b, act_scale, M, N_b, K, out_b_f16, nullptr, st);

@@ -812,20 +812,38 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
 // order, so with GM x nA = GM x nB = the number of CUs every CU computes one tile of each width and none idles
 // through a partial last round (gate/up: 14336 = 16 x 512 + 16 x 384); a workgroup of the second list starts as
 // soon as one of the first has issued its last stores, and loads while those drain.
-template <int CM, bool MIXED>
+// `two`: a second matrix of the same size for the same tokens (gate and up): the workgroups behind the first matrix's are
+// the second's, so a CU goes on with it as soon as its share of the first is done, instead of at the end of the launch.
+struct SecondF6 {
+    const uint8_t* w6;
+    const float* sw;
+    __half* out;
+};
+
+// (TWO is a template parameter: one more branch and the arguments cost a single product 0.2 us)
+template <int CM, bool MIXED, bool TWO>
 __global__ __launch_bounds__(256) void k_gemm_f6(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6,
                                                 const float* __restrict__ sw, float sx, int M, int N, int K,
                                                 int GM, int nA, int nB, int GA, __half* __restrict__ out,
-                                                int32_t* __restrict__ acc_out)
+                                                int32_t* __restrict__ acc_out, SecondF6 two)
 {
+    const int workgroups = TWO ? (int)gridDim.x >> 1 : (int)gridDim.x;      // of one matrix
+    int bid = (int)blockIdx.x;
+    if constexpr (TWO) {
+        if (bid >= workgroups) {
+            bid -= workgroups;
+            w6 = two.w6;
+            sw = two.sw;
+            out = two.out;
+        }
+    }
     if constexpr (MIXED) {
-        if ((int)blockIdx.x < GA)
-            f6_persistent<CM>(x6, w6, sw, sx, M, N, K, GM, nA, 0, (int)blockIdx.x, GA, out, acc_out);
+        if (bid < GA)
+            f6_persistent<CM>(x6, w6, sw, sx, M, N, K, GM, nA, 0, bid, GA, out, acc_out);
         else
-            f6_persistent<CM - 1>(x6, w6, sw, sx, M, N, K, GM, nB, nA * (128 * CM), (int)blockIdx.x - GA,
-                                  (int)gridDim.x - GA, out, acc_out);
+            f6_persistent<CM - 1>(x6, w6, sw, sx, M, N, K, GM, nB, nA * (128 * CM), bid - GA, workgroups - GA, out, acc_out);
     } else {
-        f6_persistent<CM>(x6, w6, sw, sx, M, N, K, GM, nA, 0, (int)blockIdx.x, (int)gridDim.x, out, acc_out);
+        f6_persistent<CM>(x6, w6, sw, sx, M, N, K, GM, nA, 0, bid, workgroups, out, acc_out);
     }
 }
 
@@ -962,7 +980,7 @@ constexpr size_t lds_bytes_f6(int ci) { return (size_t)ring_of(ci) * kStageA + 4
 
 template <int CM, bool MIXED>
 int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, int nA, int nB,
-              void* out, int32_t* acc, hipStream_t st)
+              void* out, int32_t* acc, SecondF6 two, hipStream_t st)
 {
     const int GM = (int)((M + 127) / 128);
     const int64_t ta = (int64_t)GM * nA, tb = (int64_t)GM * nB;
@@ -970,12 +988,17 @@ int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t
     const int GB = (int)(tb < kPersistentWorkgroups ? tb : kPersistentWorkgroups);
     constexpr size_t lds = lds_bytes_f6(CM);
     static_assert(lds <= 160 * 1024, "LDS ring and staging too large");
-    static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(k_gemm_f6<CM, MIXED>), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
-    hipLaunchKernelGGL((k_gemm_f6<CM, MIXED>), dim3((unsigned)(GA + GB)), dim3(256), lds, st, static_cast<const uint8_t*>(x6),
-                       static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, nA, nB, GA,
-                       static_cast<__half*>(out), acc);
-    return hip_status(hipGetLastError());
+    auto launch = [&](auto twoc) {
+        constexpr bool kTwo = decltype(twoc)::value;
+        auto kern = k_gemm_f6<CM, MIXED, kTwo>;
+        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per kTwo)
+        if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
+        hipLaunchKernelGGL(kern, dim3((unsigned)((kTwo ? 2 : 1) * (GA + GB))), dim3(256), lds, st, static_cast<const uint8_t*>(x6),
+                           static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, nA, nB, GA,
+                           static_cast<__half*>(out), acc, two);
+        return hip_status(hipGetLastError());
+    };
+    return two.w6 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 }  // namespace
 
@@ -983,9 +1006,12 @@ int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t
 // 384 b; the choice minimises the estimated time of the busiest CU (a tile costs a fixed part plus a part
 // proportional to its width).
 // pq_set_gemm_f6_tile: 2, 4 force one width, 3 the mix where N allows one (else 384 wide).
+// w6b != NULL: a second [N, K] matrix on the same tokens, in the same launch (two of the small-tile kernel).
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                   int32_t* acc, hipStream_t st)
+                   int32_t* acc, hipStream_t st, const void* w6b, const float* swb, void* outb)
 {
+    const SecondF6 two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb)};
+    const int64_t mats = w6b ? 2 : 1;                                // matrices whose tiles follow one another
     const int64_t gm = (M + 127) / 128;
     const int forced_tile = forced_f6_tile();
     // Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
@@ -993,17 +1019,20 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     // kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
     // 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).
     if (forced_tile == -1) {
-        const int64_t tiles = gm * ((N + 255) / 256);
+        const int64_t tiles = mats * gm * ((N + 255) / 256);
         const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
         const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
-                                     (double)M * N * 2 / 4.2e6;
-        if (gemm_ksplit_f6_cost_us(M, N, K) < 0.97 * persistent_us) return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st);
+                                     (double)(mats * M) * N * 2 / 4.2e6;
+        if (mats * gemm_ksplit_f6_cost_us(M, N, K) < 0.97 * persistent_us) {
+            const int rc = launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st);
+            return rc != PQ_OK || !w6b ? rc : launch_gemm_ksplit_f6(x6, w6b, swb, sx, M, N, K, outb, nullptr, st);
+        }
     }
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn
         const int64_t G = kPersistentWorkgroups;
-        return (double)((tiles_a + G - 1) / G) * ca + (double)((tiles_b + G - 1) / G) * cb;
+        return (double)((mats * tiles_a + G - 1) / G) * ca + (double)((mats * tiles_b + G - 1) / G) * cb;
     };
     int best_ci = 4, best_a = 0, best_b = 0;
     double best = 1e300;
@@ -1024,11 +1053,11 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
             if (c < bar) { bar = c; best_a = (int)a; best_b = (int)b; }
         }
     }
-    if (best_a > 0) return launch_f6<4, true>(x6, w6, sw, sx, M, N, K, best_a, best_b, out, acc, st);
+    if (best_a > 0) return launch_f6<4, true>(x6, w6, sw, sx, M, N, K, best_a, best_b, out, acc, two, st);
     const int gn = (int)((N + 128 * best_ci - 1) / (128 * best_ci));
-    if (best_ci == 2) return launch_f6<2, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, st);
-    if (best_ci == 3) return launch_f6<3, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, st);
-    return launch_f6<4, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, st);
+    if (best_ci == 2) return launch_f6<2, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
+    if (best_ci == 3) return launch_f6<3, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
+    return launch_f6<4, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
 }
 
 }  // namespace pq

@@ -76,7 +76,7 @@ bool quant_f6_supported(int64_t R, int64_t K, int32_t h);
 int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_scale, void* out, void* nibbles, hipStream_t st);
 int launch_repack_f6(const void* codes, int64_t R, int64_t K, void* out, hipStream_t st);
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                   int32_t* acc, hipStream_t st);
+                   int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
 // number where the shape is not taken) and the launches.  srow, zcorr as in the tiled kernel, or NULL.

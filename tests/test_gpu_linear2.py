@@ -71,6 +71,30 @@ def test_two_matrices_prepacked(pq, M, K, Na, Nb, h):
         assert np.array_equal(host(got).view(np.uint16), host(canon).view(np.uint16))
 
 
+# equal heights: one launch for both (256-wide tiles in one and in several rounds, 384, 512, the mix of 512 and 384, a last
+# tile that is ragged in both directions), or the small tiles, one after the other
+@pytest.mark.parametrize("M,K,N", [(1030, 256, 4096), (2048, 128, 8208), (2048, 128, 6144), (4000, 256, 2064), (2000, 128, 14336), (40, 640, 272), (300, 384, 1040)])
+def test_two_matrices_of_one_height_prepacked(pq, M, K, N):
+    x = dev(synth.activations(M, K, seed=M + K))
+    ws = [dev(synth.random_packed(N, K, seed=N + i, stream=7)) for i in (0, 1)]
+    steps = [dev(synth.random_scales(N, seed=N + i)) for i in (0, 1)]
+    tiles = [pq.pq_repack_f6(w) for w in ws]
+    a, b, work = pq.pq_linear2_f6(x, tiles[0], steps[0], tiles[1], steps[1], 0.21, 1)
+    xq = pq.pq_rotate_quant(x, 1, 0.21)
+    for got, w, s in ((a, ws[0], steps[0]), (b, ws[1], steps[1])):
+        want, _ = pq.pq_w4a4_gemm(xq, w, s, 0.21)
+        assert np.array_equal(host(got).view(np.uint16), host(want).view(np.uint16))
+    # forced widths take the same launch
+    for tile in (2, 3, 4):
+        prev = pq.pq_set_gemm_f6_tile(tile)
+        try:
+            fa, fb, _ = pq.pq_linear2_f6(x, tiles[0], steps[0], tiles[1], steps[1], 0.21, 1)
+        finally:
+            pq.pq_set_gemm_f6_tile(prev)
+        assert np.array_equal(host(fa).view(np.uint16), host(a).view(np.uint16))
+        assert np.array_equal(host(fb).view(np.uint16), host(b).view(np.uint16))
+
+
 def test_argument_errors(pq):
     import torch
     x, sx, wa, swa, wb, swb = layer(1, 512, 32, 32, 1, seed=3)
