@@ -1,9 +1,9 @@
-// Products whose output has too few large tiles for 256 CUs (from about a dozen tokens to a few thousand
-// output tiles' worth): K is split over the wavefronts of a workgroup.
+// Products whose output has too few large tiles for 256 CUs (from a handful of tokens to a few hundred): K is split
+// over the wavefronts of a workgroup.
 //
 // The persistent and the tiled kernels give every CU one large tile and one wavefront per SIMD; with few tokens
 // most CUs have no tile, and those that do walk K alone, waiting for one load after the other.  Here a workgroup
-// of 4 to 16 wavefronts owns one small tile of the output (32 to 128 tokens x 32 to 128 channels, chosen so that
+// of 4 or 8 wavefronts owns one small tile of the output (32 to 128 tokens x 32 to 128 channels, chosen so that
 // the tiles go round the CUs once), every wavefront multiplies its own run of K for the whole tile, and the
 // partial tiles are added through LDS at the end: no planes in memory, no second launch, no barrier in the main
 // loop.  What bounds it is the rate at which a CU takes its operands in, (tokens + channels) x K codes per tile at
@@ -278,9 +278,10 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __rest
 }
 
 // ---- packed nibbles (canonical operands) on the INT8 matrix instruction.  Rows lie K/2 bytes apart, and a load whose
-// neighbouring lanes sit in different rows runs at one lane per clock, so the bytes go to LDS first, 64 contiguous
-// ones per row and stage (four lanes each), in a ring of NS stages that belongs to the wavefront alone (no barrier);
-// read back in the instruction's layout and expanded as in the tiled kernel.
+// neighbouring lanes sit in different rows runs at one lane per clock, so the bytes go to LDS first, 128 contiguous ones
+// per row and stage (a whole cache line, eight lanes each), in a ring of NS stages that belongs to the wavefront alone (no
+// barrier); read back in the instruction's layout and expanded as in the tiled kernel.  Stages of 64 bytes a row, half
+// lines, measured 8-22 % slower at every size (64 x 4096 x 14336: 11.9 against 9.3 us, 333 x 4096 x 4096: 11.7 against 10.7).
 __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
 {
     // 16 bytes per lane from memory to LDS (lane l lands at lds_addr + 16 l); base and lds_addr are wavefront-uniform.
@@ -295,37 +296,50 @@ __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __rest
 {
     extern __shared__ __align__(16) uint8_t smem[];
     using P = Partial<TI, CJ, W>;
-    constexpr int kStage = (TI + CJ) * 2048, PIECES = (TI + CJ) * 2;          // 32 rows x 64 bytes per block
+    constexpr int kStage = (TI + CJ) * 4096, PIECES = (TI + CJ) * 4;          // 32 rows x 128 bytes (256 channels) per block
     const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = xcd_run((int)blockIdx.x, (int)gridDim.x);
     const int mt = tile % GM, nt = tile / GM, m0 = mt * (32 * TI), n0 = nt * (32 * CJ);
-    const int nk = K >> 7, Kb = K >> 1;
+    const int nk = (K + 255) >> 8, Kb = K >> 1;
     const int k0 = (int)((int64_t)nk * wave / W), k1 = (int)((int64_t)nk * (wave + 1) / W), n = k1 - k0;
+    // K an odd multiple of 128: the last stage of the row has only 128 channels; this wavefront's stages that are whole
+    const int whole = (K & 128) && k1 == nk && n > 0 ? n - 1 : n;
 
     Steps<TI, CJ> steps;
     steps.request(ep, m0, n0, M, N);
 
-    // piece p: 16 rows; lane l fetches row l / 4, the 16-byte chunk that belongs at position l % 4: chunk c of row t
-    // sits at position c ^ ((t / 4) % 4), which spreads the reads of 32 rows over all banks
+    // piece p: 8 rows; lane l fetches row l / 8, the 16-byte chunk that belongs at position l % 8: chunk c of row t sits
+    // at position c ^ ((t / 2) % 8), which spreads the reads of 32 rows over all banks
     uint32_t off[PIECES];
+    const int chunk[2] = {(lane & 7) ^ (lane >> 4), (lane & 7) ^ (4 | (lane >> 4))};       // even and odd pieces
 #pragma unroll
     for (int p = 0; p < PIECES; ++p) {
-        const bool is_w = p < 2 * CJ;
-        int row = (is_w ? n0 + p * 16 : m0 + (p - 2 * CJ) * 16) + (lane >> 2);
+        const bool is_w = p < 4 * CJ;
+        int row = (is_w ? n0 + p * 8 : m0 + (p - 4 * CJ) * 8) + (lane >> 3);
         const int last = (is_w ? N : M) - 1;
         row = row < last ? row : last;
-        off[p] = (uint32_t)row * (uint32_t)Kb + (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 16);
+        off[p] = (uint32_t)row * (uint32_t)Kb + (uint32_t)(chunk[p & 1] * 16);
     }
+    // in a half stage the lanes of the upper four chunks re-read the lower ones (in bounds; never multiplied)
+    const uint32_t back[2] = {chunk[0] >= 4 ? 64u : 0u, chunk[1] >= 4 ? 64u : 0u};
     const uint32_t ring = (uint32_t)(uintptr_t)(lds_u8)(smem + wave * (NS * kStage));
-    const uint8_t *xk = xq + (size_t)k0 * 64, *wk = wq + (size_t)k0 * 64;
+    const uint8_t *xk = xq + (size_t)k0 * 128, *wk = wq + (size_t)k0 * 128;
     auto request = [&](int s, int slot) {
+        if (s < whole) {
 #pragma unroll
-        for (int p = 0; p < PIECES; ++p)
-            dma16((p < 2 * CJ ? wk : xk) + (size_t)s * 64, off[p], ring + slot * kStage + p * 1024);
+            for (int p = 0; p < PIECES; ++p)
+                dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p], ring + slot * kStage + p * 1024);
+        } else {
+#pragma unroll
+            for (int p = 0; p < PIECES; ++p)
+                dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p] - back[p & 1], ring + slot * kStage + p * 1024);
+        }
     };
-    const int swr = (r >> 2) & 3;
-    const int rd0 = r * 64 + ((g ^ swr) << 4), rd1 = r * 64 + (((2 + g) ^ swr) << 4);
+    const int swr = (r >> 1) & 7;
+    int rd[4];                                                                // 16-byte chunk 2 kk + g of the lane's row
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) rd[kk] = r * 128 + (((2 * kk + g) ^ swr) << 4);
 
     v16i acc[CJ][TI];
 #pragma unroll
@@ -335,30 +349,21 @@ __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __rest
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[j][i][v] = 0;
 
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-        if (s < n) request(s, s);
-    int slot = 0;
-    for (int s = 0; s < n; ++s) {
-        // stage s has landed when at most the NS - 1 stages behind it are outstanding; near the end there are fewer
-        if (s + NS - 1 < n) wait_vm<(NS - 1) * PIECES>();
-        else wait_vm<0>();
-        typedef __attribute__((address_space(3))) const uint8_t* lds_cu8;
-        lds_cu8 st = (lds_cu8)(lds_u8)(smem + wave * (NS * kStage) + slot * kStage);
-        v4i p[2][TI + CJ];
+    typedef __attribute__((address_space(3))) const uint8_t* lds_cu8;
+    v4i p[2][2][TI + CJ];                 // packed operands of a stage: [128 channels][64 channels][block]
+    auto fetch = [&](lds_cu8 st, int h) {
 #pragma unroll
         for (int b = 0; b < TI + CJ; ++b) {
-            p[0][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 2048 + rd0);
-            p[1][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 2048 + rd1);
+            p[h][0][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 4096 + rd[2 * h]);
+            p[h][1][b] = *(__attribute__((address_space(3))) const v4i*)(st + b * 4096 + rd[2 * h + 1]);
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the slot has been read: it can be refilled)
-        if (s + NS < n) request(s + NS, slot);
-        slot = slot + 1 == NS ? 0 : slot + 1;
+    };
+    auto multiply = [&](int h) {
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             v4i e[TI + CJ], o[TI + CJ];
 #pragma unroll
-            for (int b = 0; b < TI + CJ; ++b) unpack16(p[kk][b], e[b], o[b]);
+            for (int b = 0; b < TI + CJ; ++b) unpack16(p[h][kk][b], e[b], o[b]);
 #pragma unroll
             for (int j = 0; j < CJ; ++j)
 #pragma unroll
@@ -368,6 +373,28 @@ __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __rest
 #pragma unroll
                 for (int i = 0; i < TI; ++i) acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o[j], o[CJ + i], acc[j][i], 0, 0, 0);
         }
+    };
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < n) request(s, s);
+    int slot = 0;
+    for (int s = 0; s < whole; ++s) {
+        // stage s has landed when at most the NS - 1 stages behind it are outstanding; near the end there are fewer
+        if (s + NS - 1 < n) wait_vm<(NS - 1) * PIECES>();
+        else wait_vm<0>();
+        lds_cu8 st = (lds_cu8)(lds_u8)(smem + wave * (NS * kStage) + slot * kStage);
+        fetch(st, 0);
+        fetch(st, 1);                                            // (in flight while the first half is multiplied)
+        multiply(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the slot has been read: it can be refilled)
+        if (s + NS < n) request(s + NS, slot);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+        multiply(1);
+    }
+    if (whole < n) {
+        wait_vm<0>();
+        fetch((lds_cu8)(lds_u8)(smem + wave * (NS * kStage) + slot * kStage), 0);
+        multiply(0);
     }
     __syncthreads();                     // every wavefront is done with its ring: partial tiles and steps take its place
     steps.deposit(smem + P::kBytes);
@@ -392,7 +419,7 @@ template <int TI, int CJ, int W, int NS>
 int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
 {
     using P = Partial<TI, CJ, W>;
-    constexpr size_t ring = (size_t)W * NS * (TI + CJ) * 2048;
+    constexpr size_t ring = (size_t)W * NS * (TI + CJ) * 4096;
     constexpr size_t lds = ring > (size_t)(P::kBytes + P::kSteps) ? ring : (size_t)(P::kBytes + P::kSteps);
     static_assert(lds <= (size_t)kMaxLds, "ring too large");
     const int GM = (int)((M + 32 * TI - 1) / (32 * TI)), GN = (int)((N + 32 * CJ - 1) / (32 * CJ));
@@ -442,14 +469,18 @@ Plan plan_f6(int64_t M, int64_t N, int64_t K)
     return best_plan(kTilesF6, M, N, K, 0.3, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
 }
 
-// Packed nibbles: the expansion and the INT8 instructions weigh in, 0.089 / 0.125 / 0.17 / 0.25 us per stage for tiles
-// of 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few.
+// Packed nibbles: the expansion and the INT8 instructions weigh in, 0.063 / 0.105 / 0.15 / 0.215 us per stage for tiles of
+// 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few; and no less than the weights' way from
+// memory (2.8 us + bytes at 6.3 TB/s).
 Plan plan_i8(int64_t M, int64_t N, int64_t K)
 {
-    return best_plan(kTilesI8, M, N, K, 0.25, [](const TileShape& t, double fill) {
+    Plan p = best_plan(kTilesI8, M, N, K, 0.25, [](const TileShape& t, double fill) {
         const int area = t.ti * t.cj;
-        return (area == 1 ? 0.089 : (area == 2 ? 0.125 : (area == 4 ? 0.17 : 0.25))) * (0.7 + 0.3 * fill);
+        return (area == 1 ? 0.063 : (area == 2 ? 0.105 : (area == 4 ? 0.15 : 0.215))) * (0.7 + 0.3 * fill);
     });
+    const double stream_us = 2.8 + (double)(N * (K / 2)) / 6.3e6;
+    if (p.us < stream_us) p.us = stream_us;
+    return p;
 }
 
 }  // namespace
@@ -487,11 +518,11 @@ int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float
     const Epilogue ep{sw, sx, srow, zcorr, static_cast<__half*>(out), acc};
     const Plan p = plan_i8(M, N, K);
     switch (p.ti * 10 + p.cj) {
-        case 11: return launch_i8_tile<1, 1, 16, 2>(xq, wq, ep, M, N, K, st);
-        case 12: return launch_i8_tile<1, 2, 8, 3>(xq, wq, ep, M, N, K, st);
-        case 22: return launch_i8_tile<2, 2, 8, 2>(xq, wq, ep, M, N, K, st);
-        case 32: return launch_i8_tile<3, 2, 8, 2>(xq, wq, ep, M, N, K, st);
-        case 23: return launch_i8_tile<2, 3, 8, 2>(xq, wq, ep, M, N, K, st);
+        case 11: return launch_i8_tile<1, 1, 8, 2>(xq, wq, ep, M, N, K, st);
+        case 12: return launch_i8_tile<1, 2, 4, 2>(xq, wq, ep, M, N, K, st);
+        case 22: return launch_i8_tile<2, 2, 4, 2>(xq, wq, ep, M, N, K, st);
+        case 32: return launch_i8_tile<3, 2, 4, 2>(xq, wq, ep, M, N, K, st);
+        case 23: return launch_i8_tile<2, 3, 4, 2>(xq, wq, ep, M, N, K, st);
         default: return PQ_ERR_UNSUPPORTED;
     }
 }
