@@ -281,6 +281,14 @@ int pq_linear2(const void* x_f16, const void* wq_a, const float* w_scale_a, int6
     if (rc != PQ_OK) return rc;
     const size_t codes = pq_linear_workspace_bytes(M, K);
     uint8_t* planes = static_cast<uint8_t*>(workspace) + codes;
+    const size_t plane_bytes = workspace_bytes - codes;
+    // Both products on the kernel that splits K over a workgroup's wavefronts: one launch for the two.  Two launches of
+    // few tiles leave the chip half empty twice and pay the launch and the reduction twice (32 tokens, 4096 -> 2 x 1024:
+    // 10.5 -> 6.8 us with the quantizer, 64 tokens, 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).
+    auto small = [&](int64_t N) { return take_ksplit(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes); };
+    if (small(N_a) && small(N_b) && pq::gemm_ksplit_i8_cost_us(M, N_a + N_b, K) < 1e9)
+        return pq::launch_gemm_ksplit_i8(workspace, wq_a, w_scale_a, act_scale, nullptr, nullptr, M, N_a, K, out_a_f16, nullptr,
+                                         static_cast<hipStream_t>(stream), wq_b, w_scale_b, N_b, out_b_f16);
     rc = pq_w4a4_gemm_ws(workspace, wq_a, w_scale_a, act_scale, M, N_a, K, out_a_f16, nullptr, planes, workspace_bytes - codes, stream);
     if (rc != PQ_OK) return rc;
     return pq_w4a4_gemm_ws(workspace, wq_b, w_scale_b, act_scale, M, N_b, K, out_b_f16, nullptr, planes, workspace_bytes - codes, stream);

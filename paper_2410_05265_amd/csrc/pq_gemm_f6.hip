@@ -1006,7 +1006,7 @@ int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t
 // 384 b; the choice minimises the estimated time of the busiest CU (a tile costs a fixed part plus a part
 // proportional to its width).
 // pq_set_gemm_f6_tile: 2, 4 force one width, 3 the mix where N allows one (else 384 wide).
-// w6b != NULL: a second [N, K] matrix on the same tokens, in the same launch (two of the small-tile kernel).
+// w6b != NULL: a second [N, K] matrix on the same tokens, in the same launch.
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                    int32_t* acc, hipStream_t st, const void* w6b, const float* swb, void* outb)
 {
@@ -1017,16 +1017,16 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     // Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
     // tiles was measured at 5 us + 0.33 us per 128-channel stage and round (0.5 with every CU busy) + its output; the
     // kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
-    // 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).
+    // 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).  Two
+    // matrices count as one of twice the height on either side (two launches of few tiles -> one, with the quantizer:
+    // 128 tokens, 4096 -> 2 x 4096: 15.6 -> 11.9 us, 512 tokens, 4096 -> 2 x 1024: 17.1 -> 13.4).
     if (forced_tile == -1) {
         const int64_t tiles = mats * gm * ((N + 255) / 256);
         const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
         const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
                                      (double)(mats * M) * N * 2 / 4.2e6;
-        if (mats * gemm_ksplit_f6_cost_us(M, N, K) < 0.97 * persistent_us) {
-            const int rc = launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st);
-            return rc != PQ_OK || !w6b ? rc : launch_gemm_ksplit_f6(x6, w6b, swb, sx, M, N, K, outb, nullptr, st);
-        }
+        if (gemm_ksplit_f6_cost_us(M, mats * N, K) < 0.97 * persistent_us)
+            return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
     }
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {

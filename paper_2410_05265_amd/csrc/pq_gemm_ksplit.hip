@@ -43,6 +43,34 @@ struct Epilogue {
     int32_t* acc_out;
 };
 
+// A second weight matrix on the same tokens, in the same launch: its tiles follow the `first` tiles of the first one.
+struct Second {
+    const uint8_t* w;
+    const float* sw;
+    __half* out;
+    int N, first;
+};
+
+// This workgroup's tile within its matrix; w, ep and N become those of the second matrix where the tile is in that one.
+template <bool TWO>
+__device__ __forceinline__ int own_tile(const Second& two, const uint8_t* __restrict__& w, Epilogue& ep, int& N)
+{
+    int b = (int)blockIdx.x, total = (int)gridDim.x;
+    if constexpr (TWO) {
+        if (b >= two.first) {
+            b -= two.first;
+            total -= two.first;
+            w = two.w;
+            ep.sw = two.sw;
+            ep.out = two.out;
+            N = two.N;
+        } else {
+            total = two.first;
+        }
+    }
+    return xcd_run(b, total);
+}
+
 // LDS bytes of the partial tiles: one copy per wavefront where that fits, else one per pair of wavefronts.
 template <int TI, int CJ, int W>
 struct Partial {
@@ -173,9 +201,9 @@ struct Steps {
 // 15 % faster, but twice the partial tiles have to pass through LDS (333 x 4096 x 4096: 9.8 against 9.5 us, 128 x
 // 14336 x 4096: 12.5 against 11.6), and two or three of the smaller workgroups share a CU (64 x 64 tiles in two
 // rounds: 13.0 against 11.7).  A second stage in the ring of the larger tiles: 3 % slower.
-template <int TI, int CJ, int W, int U>
+template <int TI, int CJ, int W, int U, bool TWO>
 __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6, Epilogue ep,
-                                                          int M, int N, int K, int GM)
+                                                          int M, int N, int K, int GM, Second two)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     using P = Partial<TI, CJ, W>;
@@ -183,7 +211,7 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __rest
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t l16 = (uint32_t)lane * 16u, l8 = (uint32_t)lane * 8u;
-    const int tile = xcd_run((int)blockIdx.x, (int)gridDim.x);
+    const int tile = own_tile<TWO>(two, w6, ep, N);
     const int mt = tile % GM, nt = tile / GM, m0 = mt * (32 * TI), n0 = nt * (32 * CJ);
     const int nk = K >> 7, RBX = (M + 31) >> 5, RBW = (N + 31) >> 5;
     const int k0 = (int)((int64_t)nk * wave / W), k1 = (int)((int64_t)nk * (wave + 1) / W), n = k1 - k0;
@@ -290,16 +318,16 @@ __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t lane_offset,
 }
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-template <int TI, int CJ, int W, int NS>
+template <int TI, int CJ, int W, int NS, bool TWO>
 __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, Epilogue ep,
-                                                          int M, int N, int K, int GM)
+                                                          int M, int N, int K, int GM, Second two)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     using P = Partial<TI, CJ, W>;
     constexpr int kStage = (TI + CJ) * 4096, PIECES = (TI + CJ) * 4;          // 32 rows x 128 bytes (256 channels) per block
     const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = xcd_run((int)blockIdx.x, (int)gridDim.x);
+    const int tile = own_tile<TWO>(two, wq, ep, N);
     const int mt = tile % GM, nt = tile / GM, m0 = mt * (32 * TI), n0 = nt * (32 * CJ);
     const int nk = (K + 255) >> 8, Kb = K >> 1;
     const int k0 = (int)((int64_t)nk * wave / W), k1 = (int)((int64_t)nk * (wave + 1) / W), n = k1 - k0;
@@ -401,34 +429,38 @@ __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __rest
     reduce_and_store<v16i, TI, CJ, W, 8>(acc, smem, P::kBytes, ep, m0, n0, M, N);
 }
 
-template <int TI, int CJ, int W, int U>
-int launch_f6_tile(const void* x6, const void* w6, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
+template <typename KERN>
+int launch_tiles(KERN kern, std::atomic<uint64_t>& lds_ok, size_t lds, int tm, int tn, int threads, const void* x, const void* w,
+                 const Epilogue& ep, int64_t M, int64_t N, int64_t K, Second two, hipStream_t st)
 {
-    using P = Partial<TI, CJ, W>;
-    constexpr size_t lds = P::kBytes + P::kSteps;
-    const int GM = (int)((M + 32 * TI - 1) / (32 * TI)), GN = (int)((N + 32 * CJ - 1) / (32 * CJ));
-    auto kern = k_gemm_f6_ksplit<TI, CJ, W, U>;
-    static std::atomic<uint64_t> lds_ok{0};
+    const int GM = (int)((M + tm - 1) / tm), GN = (int)((N + tn - 1) / tn), GN2 = two.w ? (two.N + tn - 1) / tn : 0;
     if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN)), dim3(64 * W), lds, st, static_cast<const uint8_t*>(x6),
-                       static_cast<const uint8_t*>(w6), ep, (int)M, (int)N, (int)K, GM);
+    two.first = GM * GN;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(GM * (GN + GN2))), dim3((unsigned)threads), lds, st, static_cast<const uint8_t*>(x),
+                       static_cast<const uint8_t*>(w), ep, (int)M, (int)N, (int)K, GM, two);
     return hip_status(hipGetLastError());
 }
 
+template <int TI, int CJ, int W, int U>
+int launch_f6_tile(const void* x6, const void* w6, const Epilogue& ep, int64_t M, int64_t N, int64_t K, const Second& two, hipStream_t st)
+{
+    using P = Partial<TI, CJ, W>;
+    constexpr size_t lds = P::kBytes + P::kSteps;
+    static std::atomic<uint64_t> lds_ok[2] = {{0}, {0}};
+    if (two.w) return launch_tiles(k_gemm_f6_ksplit<TI, CJ, W, U, true>, lds_ok[1], lds, 32 * TI, 32 * CJ, 64 * W, x6, w6, ep, M, N, K, two, st);
+    return launch_tiles(k_gemm_f6_ksplit<TI, CJ, W, U, false>, lds_ok[0], lds, 32 * TI, 32 * CJ, 64 * W, x6, w6, ep, M, N, K, two, st);
+}
+
 template <int TI, int CJ, int W, int NS>
-int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M, int64_t N, int64_t K, hipStream_t st)
+int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M, int64_t N, int64_t K, const Second& two, hipStream_t st)
 {
     using P = Partial<TI, CJ, W>;
     constexpr size_t ring = (size_t)W * NS * (TI + CJ) * 4096;
     constexpr size_t lds = ring > (size_t)(P::kBytes + P::kSteps) ? ring : (size_t)(P::kBytes + P::kSteps);
     static_assert(lds <= (size_t)kMaxLds, "ring too large");
-    const int GM = (int)((M + 32 * TI - 1) / (32 * TI)), GN = (int)((N + 32 * CJ - 1) / (32 * CJ));
-    auto kern = k_gemm_i8_ksplit<TI, CJ, W, NS>;
-    static std::atomic<uint64_t> lds_ok{0};
-    if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN)), dim3(64 * W), lds, st, static_cast<const uint8_t*>(xq),
-                       static_cast<const uint8_t*>(wq), ep, (int)M, (int)N, (int)K, GM);
-    return hip_status(hipGetLastError());
+    static std::atomic<uint64_t> lds_ok[2] = {{0}, {0}};
+    if (two.w) return launch_tiles(k_gemm_i8_ksplit<TI, CJ, W, NS, true>, lds_ok[1], lds, 32 * TI, 32 * CJ, 64 * W, xq, wq, ep, M, N, K, two, st);
+    return launch_tiles(k_gemm_i8_ksplit<TI, CJ, W, NS, false>, lds_ok[0], lds, 32 * TI, 32 * CJ, 64 * W, xq, wq, ep, M, N, K, two, st);
 }
 
 // Tile of a launch and its estimated time in microseconds.  Per 128-channel stage of K the operands' way into the CU,
@@ -485,7 +517,8 @@ Plan plan_i8(int64_t M, int64_t N, int64_t K)
 
 }  // namespace
 
-// Estimated microseconds; a large number where the kernel does not take the shape.
+// Estimated microseconds; a large number where the kernel does not take the shape.  (Two matrices in one launch: N is the
+// sum of their heights.)
 double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K) { return plan_f6(M, N, K).us; }
 
 double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K)
@@ -496,33 +529,36 @@ double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K)
 }
 
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                          int32_t* acc, hipStream_t st)
+                          int32_t* acc, hipStream_t st, const void* w6b, const float* swb, int64_t Nb, void* outb)
 {
     const Epilogue ep{sw, sx, nullptr, nullptr, static_cast<__half*>(out), acc};
-    const Plan p = plan_f6(M, N, K);
+    const Second two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb), (int)Nb, 0};
+    const Plan p = plan_f6(M, N + Nb, K);
     switch (p.ti * 10 + p.cj) {
-        case 11: return launch_f6_tile<1, 1, 4, 2>(x6, w6, ep, M, N, K, st);
-        case 12: return launch_f6_tile<1, 2, 4, 2>(x6, w6, ep, M, N, K, st);
-        case 22: return launch_f6_tile<2, 2, 4, 1>(x6, w6, ep, M, N, K, st);
-        case 32: return launch_f6_tile<3, 2, 4, 1>(x6, w6, ep, M, N, K, st);
-        case 23: return launch_f6_tile<2, 3, 4, 1>(x6, w6, ep, M, N, K, st);
-        case 42: return launch_f6_tile<4, 2, 4, 1>(x6, w6, ep, M, N, K, st);
-        case 24: return launch_f6_tile<2, 4, 4, 1>(x6, w6, ep, M, N, K, st);
+        case 11: return launch_f6_tile<1, 1, 4, 2>(x6, w6, ep, M, N, K, two, st);
+        case 12: return launch_f6_tile<1, 2, 4, 2>(x6, w6, ep, M, N, K, two, st);
+        case 22: return launch_f6_tile<2, 2, 4, 1>(x6, w6, ep, M, N, K, two, st);
+        case 32: return launch_f6_tile<3, 2, 4, 1>(x6, w6, ep, M, N, K, two, st);
+        case 23: return launch_f6_tile<2, 3, 4, 1>(x6, w6, ep, M, N, K, two, st);
+        case 42: return launch_f6_tile<4, 2, 4, 1>(x6, w6, ep, M, N, K, two, st);
+        case 24: return launch_f6_tile<2, 4, 4, 1>(x6, w6, ep, M, N, K, two, st);
         default: return PQ_ERR_UNSUPPORTED;
     }
 }
 
 int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float sx, const float* srow, const int32_t* zcorr, int64_t M,
-                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st)
+                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st, const void* wqb, const float* swb, int64_t Nb,
+                          void* outb)
 {
     const Epilogue ep{sw, sx, srow, zcorr, static_cast<__half*>(out), acc};
-    const Plan p = plan_i8(M, N, K);
+    const Second two{static_cast<const uint8_t*>(wqb), swb, static_cast<__half*>(outb), (int)Nb, 0};
+    const Plan p = plan_i8(M, N + Nb, K);
     switch (p.ti * 10 + p.cj) {
-        case 11: return launch_i8_tile<1, 1, 8, 2>(xq, wq, ep, M, N, K, st);
-        case 12: return launch_i8_tile<1, 2, 4, 2>(xq, wq, ep, M, N, K, st);
-        case 22: return launch_i8_tile<2, 2, 4, 2>(xq, wq, ep, M, N, K, st);
-        case 32: return launch_i8_tile<3, 2, 4, 2>(xq, wq, ep, M, N, K, st);
-        case 23: return launch_i8_tile<2, 3, 4, 2>(xq, wq, ep, M, N, K, st);
+        case 11: return launch_i8_tile<1, 1, 8, 2>(xq, wq, ep, M, N, K, two, st);
+        case 12: return launch_i8_tile<1, 2, 4, 2>(xq, wq, ep, M, N, K, two, st);
+        case 22: return launch_i8_tile<2, 2, 4, 2>(xq, wq, ep, M, N, K, two, st);
+        case 32: return launch_i8_tile<3, 2, 4, 2>(xq, wq, ep, M, N, K, two, st);
+        case 23: return launch_i8_tile<2, 3, 4, 2>(xq, wq, ep, M, N, K, two, st);
         default: return PQ_ERR_UNSUPPORTED;
     }
 }

@@ -79,13 +79,16 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
                    int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
-// number where the shape is not taken) and the launches.  srow, zcorr as in the tiled kernel, or NULL.
+// number where the shape is not taken) and the launches.  srow, zcorr as in the tiled kernel, or NULL.  w.b != NULL: a
+// second matrix [Nb, K] on the same tokens in the same launch, outputs without acc, srow and zcorr.
 double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K);
 double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K);
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                          int32_t* acc, hipStream_t st);
+                          int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, int64_t Nb = 0,
+                          void* outb = nullptr);
 int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float sx, const float* srow, const int32_t* zcorr, int64_t M,
-                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st);
+                          int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st, const void* wqb = nullptr,
+                          const float* swb = nullptr, int64_t Nb = 0, void* outb = nullptr);
 
 // forced tile configurations (sweeps and tests): previous value, or -2 for an unknown one
 int set_gemm_tile(int tile);

@@ -33,12 +33,14 @@ def layer(M, K, Na, Nb, h, seed):
 
 
 # (M, K, N_a, N_b, had_block): one token to a small prefill; heights that make 1, 2 or 4 rows per wavefront;
-# N_a not a multiple of the rows a workgroup takes at a time; 5 tokens and 64 tokens leave the fused launch
+# N_a not a multiple of the rows a workgroup takes at a time; 5 tokens and 64 tokens leave the fused launch; the last
+# row: both products in one launch of small tiles, of several sizes, the second matrix taller or a single ragged tile
 CASES = [(1, 512, 256, 256, 1), (1, 4096, 1008, 528, 1), (2, 2048, 4096, 2064, 128), (4, 1024, 16, 8192, 64),
          (1, 8192, 14336, 14336, 1), (3, 4096, 9008, 9008, 4096), (1, 14336, 2048, 1040, 128),
          (1, 4096, 14336, 14336, 1),      # gate and up of Llama-3-8B at one token: the launch bench.py times
 
-         (5, 1024, 528, 272, 128), (64, 1024, 528, 272, 1), (16, 4096, 1024, 512, 128)]
+         (5, 1024, 528, 272, 128), (64, 1024, 528, 272, 1), (16, 4096, 1024, 512, 128),
+         (24, 4096, 272, 1040, 1), (40, 1152, 4240, 16, 128), (100, 640, 48, 8208, 1), (300, 384, 2064, 2064, 1)]
 
 
 @pytest.mark.parametrize("M,K,Na,Nb,h", CASES)
@@ -72,7 +74,7 @@ def test_two_matrices_prepacked(pq, M, K, Na, Nb, h):
 
 
 # equal heights: one launch for both (256-wide tiles in one and in several rounds, 384, 512, the mix of 512 and 384, a last
-# tile that is ragged in both directions), or the small tiles, one after the other
+# tile that is ragged in both directions), the small tiles among them
 @pytest.mark.parametrize("M,K,N", [(1030, 256, 4096), (2048, 128, 8208), (2048, 128, 6144), (4000, 256, 2064), (2000, 128, 14336), (40, 640, 272), (300, 384, 1040)])
 def test_two_matrices_of_one_height_prepacked(pq, M, K, N):
     x = dev(synth.activations(M, K, seed=M + K))
