@@ -58,7 +58,7 @@ const char* pq_status_str(int status);
  * For every row m and every block b of had_block consecutive channels
  *     y[m, b*h + j] = sum_i x[m, b*h + i] * H_h[i][j] / sqrt(h),
  *     H_h[i][j] = (-1)^popcount(i & j)            (Sylvester order; fp32 sums: butterflies, or for blocks of
- *                                                  128 a product with H_128 on the matrix pipe),
+ *                                                  128 and 4096 a product with H_128 on the matrix pipe),
  *     q = clamp(round_half_even(y / act_scale), -8, 7).
  * had_block: 0 or 1 = no rotation; otherwise a power of two in [2, 16384] that
  *            divides K.  With had_block <= 1 the codes are exactly
@@ -73,9 +73,10 @@ int pq_rotate_quant(const void* x_f16, int64_t M, int64_t K, int32_t had_block,
  * O2 for the two step sizes).
  *     acc[m,n] = sum_k xq[m,k] * wq[n,k]              (exact, int32)
  *     out[m,n] = fp16(acc[m,n] * (act_scale * w_scale[n]))   (fp32 multiply, RNE)
- * The kernel is chosen from M: weight-streaming kernels for M <= 16 (decode: 4-bit dot
- * products on packed nibbles for M <= 8, small matrix tiles up to 16 or 32), an INT8-MFMA tiled
- * kernel otherwise (prefill).  The tiled kernel carries 256 * acc in int32, which is exact for
+ * The kernel is chosen from the shape: weight-streaming kernels for M <= 16 (decode: 4-bit dot
+ * products on packed nibbles for M <= 8, small matrix tiles up to 16 or 32), an INT8-MFMA kernel of
+ * small tiles whose K is split over the wavefronts of a workgroup where the output has few tiles, an
+ * INT8-MFMA tiled kernel otherwise (prefill).  The last two carry 256 * acc in int32, which is exact for
  * K < 131072; longer rows with more than 8 tokens return PQ_ERR_UNSUPPORTED.
  * xq_packed in  [M,K/2] uint8 canonical.      wq_packed in [N,K/2] uint8 canonical.
  * w_scale   in  [N] fp32, 16-byte aligned.    act_scale: static step size of xq.
@@ -95,7 +96,9 @@ int pq_w4a4_gemm(const void* xq_packed, const void* wq_packed, const float* w_sc
  * pq_w4a4_gemm_workspace_bytes: what the cost model's choice needs for the shape, 0 where it would
  *   not split (one launch of a weight-streaming kernel serves, up to 16 tokens; or the output has
  *   enough tiles).  Host only.  With that much the split launch also takes over from two or more
- *   weight-streaming launches (17 to 32 tokens, very long rows) on matrices of 8 MB and more.
+ *   weight-streaming launches (17 to 32 tokens, very long rows) on matrices of 8 MB and more.  Where an
+ *   estimate puts the small-tile kernel of pq_w4a4_gemm ahead of the split launch (4-bit codes, most shapes
+ *   up to 128 tokens) that kernel runs and the workspace stays untouched.
  * workspace: device memory, 256-byte aligned, or NULL; workspace_bytes may be smaller than asked
  *   for (fewer planes, or the unsplit kernel) or larger (the rest is untouched).  Its contents on
  *   return are unspecified.  Calls that share a workspace must be ordered on one stream.
@@ -131,7 +134,8 @@ int pq_linear(const void* x_f16, const void* wq_packed, const float* w_scale,
  * their own channel steps and their own outputs [M, N_a] and [M, N_b].  Outputs equal those of two pq_linear
  * calls bit for bit.  Where pq_linear would take its fused launch (few tokens), one launch streams both
  * matrices, which saves the fixed cost of a launch (several microseconds where a matrix takes 4-8);
- * otherwise one pq_rotate_quant and two products.  N_a, N_b: multiples of 16; K, had_block, workspace
+ * otherwise one pq_rotate_quant and two products, which share a launch where both take the small-tile
+ * kernel of pq_w4a4_gemm.  N_a, N_b: multiples of 16; K, had_block, workspace
  * (pq_linear_workspace_bytes(M, K), or more for the split launch of the larger product) as for pq_linear.
  */
 int pq_linear2(const void* x_f16, const void* wq_a, const float* w_scale_a, int64_t N_a, void* out_a_f16,
@@ -235,7 +239,8 @@ int pq_rotate_quant_f6(const void* x_f16, int64_t M, int64_t K, int32_t had_bloc
 
 /* The whole layer on that instruction, for weights repacked beforehand (the prepacked twin of
  * pq_linear): pq_rotate_quant_f6, then pq_w4a4_gemm_f6, on one stream: two launches.  Rotation blocks
- * beyond 512 channels take pq_rotate_quant, pq_repack_f6 and pq_w4a4_gemm_f6: three.  The codes behind
+ * of 4096 channels take two launches as well (the quantizer writes tiles and nibbles together), other blocks
+ * beyond 512 channels pq_rotate_quant, pq_repack_f6 and pq_w4a4_gemm_f6: three.  The codes behind
  * the tiles are those of pq_rotate_quant bit for bit, the outputs those of pq_linear.
  * workspace: device memory, 256-byte aligned, pq_linear_f6_workspace_bytes(M,K,had_block) bytes; on
  * return it holds the activations' tiles (pq_f6_tiles_bytes(M,K)), and behind them, rounded up to 256,
@@ -248,7 +253,7 @@ int pq_linear_f6(const void* x_f16, const void* w_tiles, const float* w_scale,
                  void* out_f16, void* workspace, size_t workspace_bytes, void* stream);
 
 /* pq_linear2 on the prepacked path: two weight matrices as f6 tiles on the same tokens (gate_proj and up_proj),
- * X rotated, quantized and written as tiles once, two products.  Outputs equal those of two pq_linear_f6 calls
+ * X rotated, quantized and written as tiles once, two products (in one launch where N_a = N_b).  Outputs equal those of two pq_linear_f6 calls
  * (and of pq_linear2 on the canonical weights) bit for bit.  Arguments as for pq_linear_f6; workspace of
  * pq_linear_f6_workspace_bytes(M, K, had_block). */
 int pq_linear2_f6(const void* x_f16, const void* w_tiles_a, const float* w_scale_a, int64_t N_a, void* out_a_f16,
@@ -270,7 +275,9 @@ int pq_linear_prepacked(const void* x_f16, const void* wq_tiled, const float* w_
  * automatic choice for given codes: dot products up to 4 tokens (8 on matrices under 12 MB; with
  * int8 activations 2, 4 and 6 on matrices over 24 MB, over 12 MB and smaller), matrix tiles up to
  * 16 (up to 32 in two launches where a cost estimate puts that ahead of the tiled kernel: outputs
- * of few tiles), tiled beyond.  Every kernel gives the same accumulators and the same fp16 outputs
+ * of few tiles), tiled beyond; and with 4-bit activation codes the small tiles that split K over the
+ * wavefronts of a workgroup in place of the last two where an estimate puts them ahead (up to 16
+ * tokens: K <= 4096 and matrices under 24 MB).  No variant number forces these.  Every kernel gives the same accumulators and the same fp16 outputs
  * bit for bit.
  * Returns the previous value, or -1 if `variant` is unknown.  An atomic integer: safe to call from
  * any thread, but a product call running concurrently on another thread may see either value.
@@ -345,7 +352,7 @@ int pq_rotate_quant_dynamic(const void* x_f16, int64_t M, int64_t K, int32_t had
 
 /* out[m,n] = fp16(acc[m,n] * (row_scale[m] * w_scale[n])), acc as in pq_w4a4_gemm (bits = 4) or
  * pq_w4a8_gemm (bits = 8).  K % 128 == 0, K <= 65536.  M <= 8 takes the weight-streaming decode
- * kernel (when the rows fit LDS), everything else the MFMA tiled kernel.
+ * kernel (when the rows fit LDS), everything else the MFMA kernels (bits = 4: chosen as in pq_w4a4_gemm).
  */
 int pq_gemm_dynamic(const void* xq, int32_t bits, const void* wq_packed, const float* w_scale,
                     const float* row_scale, int64_t M, int64_t N, int64_t K,
@@ -442,7 +449,7 @@ int pq_zero_point_correction(const void* wq_packed, int64_t N, int64_t K, int32_
 
 /* out[m,n] = fp16((acc[m,n] + zp_corr[n]) * (act_scale * w_scale[n])); acc_i32, if given, receives
  * the raw accumulators (without the correction).  K % 128 == 0, K <= 32768; M <= 8 takes the
- * weight-streaming kernel, larger M the MFMA tiled kernel.
+ * weight-streaming kernel, larger M the MFMA kernels (chosen as in pq_w4a4_gemm).
  */
 int pq_w4a4_gemm_zp(const void* xq_packed, const void* wq_packed, const float* w_scale,
                     float act_scale, const int32_t* zp_corr, int64_t M, int64_t N, int64_t K,
