@@ -276,8 +276,8 @@ int pq_linear_prepacked(const void* x_f16, const void* wq_tiled, const float* w_
  * int8 activations 2, 4 and 6 on matrices over 24 MB, over 12 MB and smaller), matrix tiles up to
  * 16 (up to 32 in two launches where a cost estimate puts that ahead of the tiled kernel: outputs
  * of few tiles), tiled beyond; and with 4-bit activation codes the small tiles that split K over the
- * wavefronts of a workgroup in place of the last two where an estimate puts them ahead (up to 16
- * tokens: K <= 4096 and matrices under 24 MB).  No variant number forces these.  Every kernel gives the same accumulators and the same fp16 outputs
+ * wavefronts of a workgroup in place of two streaming launches and of tiled where an estimate puts
+ * them ahead.  No variant number forces these.  Every kernel gives the same accumulators and the same fp16 outputs
  * bit for bit.
  * Returns the previous value, or -1 if `variant` is unknown.  An atomic integer: safe to call from
  * any thread, but a product call running concurrently on another thread may see either value.

@@ -87,20 +87,19 @@ int pick_with_planes(int64_t M, int64_t N, int64_t K, size_t plane_bytes, int32_
 // against two or more streaming launches the estimates of both sides decide.  Measured before -> after, warm weights:
 // 64 x 4096 x 14336 14.6 -> 9.2 us (with planes; 39 without), 200 x 6144 x 4096 13.9 -> 11.0, 128 x 4096 x 4096 12.5 -> 5.9,
 // 24 x 14336 x 4096 12.8 -> 7.5, 32 x 4096 x 4096 8.8 -> 4.1; weights from HBM: 48 x 4096 x 14336 14.9 -> 11.8.
-// One streaming launch (up to 16 tokens) loses where rows are short and the matrix small, with warm and with cold weights
-// (16 x 4096 x 4096 4.9 -> 4.0 and 5.3 -> 5.2 us, 13 x 11008 x 4096 7.9 -> 6.6 and 8.4 -> 7.3); on longer rows or larger
-// matrices it reads cold weights faster (16 x 4096 x 14336 9.6 against 10.9, 13 x 14336 x 4096 8.0 against 8.1) and stays.
+// One streaming launch (up to 16 tokens) stays: it loses with warm weights (16 x 4096 x 4096 4.9 against 4.0 us, 13 x
+// 11008 x 4096 7.9 against 6.6) but reads cold ones faster (with the quantizer, 13 tokens, 4096 -> 4096 7.7 against 8.2 us,
+// 2048 -> 20480 10.8 against 12.1, 14336 -> 4096 product 9.6 against 10.9; 4096 -> 11008 alone 11.0 against 10.4).
 bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes)
 {
     if (g_variant != 0) return false;
-    const int64_t weight_bytes = N * (K / 2);
     double other;
     if (kernel == 2) {
         other = pq::gemm_tiled_cost_us(M, N, K, plane_bytes);
     } else if (kernel == 1) {
         const int launches = pq::stream_mfma_launches(M, N, K, 4);
-        if (launches == 1) return K <= 4096 && weight_bytes < 24000000;
-        other = launches * (2.5 + (double)weight_bytes / 5.0e6);
+        if (launches < 2) return false;
+        other = launches * (2.5 + (double)(N * (K / 2)) / 5.0e6);
     } else {
         return false;
     }

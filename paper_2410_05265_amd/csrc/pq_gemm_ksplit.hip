@@ -1,4 +1,4 @@
-// Products whose output has too few large tiles for 256 CUs (from a handful of tokens to a few hundred): K is split
+// Products whose output has too few large tiles for 256 CUs (up to a few hundred tokens): K is split
 // over the wavefronts of a workgroup.
 //
 // The persistent and the tiled kernels give every CU one large tile and one wavefront per SIMD; with few tokens

@@ -60,9 +60,8 @@ def test_prepacked_product(pq, M, N, K):
     assert none is None and np.array_equal(host(only), host(acc))
 
 
-# the same for packed nibbles (up to 16 tokens: rows of at most 4096 channels; longer ones take a weight-streaming kernel)
-SHAPES_I8 = [(9, 48, 256), (16, 1040, 4096), (5, 4112, 1280),                                                          # 1 x 1
-             (17, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (20, 80, 4224),        # 1 x 1
+# the same for packed nibbles; from 17 tokens on (fewer take a weight-streaming kernel)
+SHAPES_I8 = [(17, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (20, 80, 4224),        # 1 x 1
              (33, 4112, 128), (40, 4240, 2304),                                                                     # 1 x 2
              (33, 8208, 384), (100, 4176, 1152),                                                                    # 2 x 2
              (100, 8208, 384), (190, 6032, 1280),                                                                   # 2 x 3
