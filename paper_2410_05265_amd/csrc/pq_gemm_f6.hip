@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
 // on the matrix pipe, as above but with the 32 blocks of ONE token as the columns, and the five outer stages are fp32
 // butterflies between the lanes that hold the blocks.  With butterflies alone and a repack behind them the rotation of a
 // prepacked layer was two launches, bound by vector instructions and by launch latency (1111 x 4096: 9.8 + 5.5 us);
-// this is one launch that writes tiles, nibbles, or both.
+// this is one launch that writes tiles, nibbles, or both (10.1 us).
 //
 // A workgroup of 16 wavefronts takes four tokens, four wavefronts each: wavefront n of a token computes the output
 // channels 32 n .. 32 n + 31 of every block (8 matrix instructions), so that a handful of tokens still keeps a CU busy.
