@@ -61,7 +61,7 @@ __device__ __forceinline__ int bitrev(int x, int bits)
 }
 
 // MODE 0: packed codes are given (xq_in); 1: rows are fp16, quantized with exact ties (log2h == 0)
-// or rotated with blocks of 2^log2h <= 2048 first; 2: rotated with blocks of 4096.
+// or rotated with blocks of 2^log2h <= 2048 first; 2: rotated with blocks of 4096 (on the matrix pipe).
 // One workgroup of 16 wavefronts per CU; a wavefront owns RPW weight rows at a time and has
 // RPW * CB 16-byte loads in flight; MP = padded M.
 // ABITS = 8 (given codes only): the activation codes are int8 in the grouped order (16 even
@@ -75,7 +75,6 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
                                                uint8_t* __restrict__ xq_out, const float* __restrict__ srow,
                                                const int32_t* __restrict__ zcorr, DecodeSecond two)
 {
-    constexpr int G = MODE == 2 ? 2 : 1;
     static_assert(ABITS == 4 || (ABITS == 8 && MODE == 0), "8-bit activations: given codes only");
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -85,10 +84,11 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
     const int cpr = (Kb + 1023) >> 10;   // KiB chunks per row
     const int groups = N / RPW, gstride = gridDim.x * 16;
     int gid = blockIdx.x * 16 + wave;
-    // LDS: [MP][Ka] codes | rotation scratch | [M][K] fp16 rows (fused modes only)
+    // LDS: [MP][Ka] codes | rotation scratch | [M][K] fp16 rows (fused modes only; 4096-point blocks: every 128 channels
+    // padded to rq::kXPitch bytes)
     uint8_t* xs = smem;
     const int xch_off = (MP * Ka + 15) & ~15;
-    const int xraw_off = xch_off + (MODE == 0 ? 16 : G * kChunk * 4);
+    const int xraw_off = xch_off + (MODE == 1 ? kChunk * 4 : 16);
 
     // ---- 1. first pieces of the activation rows (ordinary loads, issued before the weights:
     // loads complete in order, so waiting for these leaves the weight loads in flight)
@@ -96,6 +96,7 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
     const uint8_t* xsrc = MODE == 0 ? xq_in : reinterpret_cast<const uint8_t*>(x);
     const int pieces = (MODE == 0 ? M * Ka : M * K * 2) >> 4;   // 16-byte pieces
     uint8_t* xdst = MODE == 0 ? xs : smem + xraw_off;
+    auto staged_at = [](int i) { return MODE == 2 ? (i >> 4) * rq::kXPitch + (i & 15) * 16 : i * 16; };   // LDS place of piece i
     v4i xr[XB];
 #pragma unroll
     for (int u = 0; u < XB; ++u) {
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
 #pragma unroll
     for (int u = 0; u < XB; ++u) {
         const int i = tid + 1024 * u;   // pieces past the end land in the (still unused) scratch: no branch
-        uint8_t* d = i < pieces ? xdst + i * 16 : smem + xch_off;
+        uint8_t* d = i < pieces ? xdst + staged_at(i) : smem + xch_off;
         *(__attribute__((address_space(3))) v4i*)d = xr[u];
     }
     for (int base = 1024 * XB; base < pieces; base += 1024 * XB) {
@@ -192,16 +193,30 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
 #pragma unroll
         for (int u = 0; u < XB; ++u) {
             const int i = base + tid + 1024 * u;
-            uint8_t* d = i < pieces ? xdst + i * 16 : smem + xch_off;
+            uint8_t* d = i < pieces ? xdst + staged_at(i) : smem + xch_off;
             *(__attribute__((address_space(3))) v4i*)d = xr[u];
         }
     }
     rq::lds_sync();
-    if constexpr (MODE != 0) {
+    if constexpr (MODE == 2) {
+        // four wavefronts per block of 4096 channels, four blocks at a time (rows are contiguous: block u of all rows has
+        // its codes at 2048 u).  Fused call with cold weights, butterflies by four of the wavefronts -> this: 1 x 4096 -> 4096
+        // 7.9 -> 4.8 us, 2 x 4096 -> 4096 12.3 -> 5.6, 1 x 16384 -> 4096 24.6 -> 10.8.
+        const int n = wave & 3, units = (M * K) >> 12;
+        for (int u = wave >> 2; u < units; u += 4) {
+            uint32_t q[2];
+            rq::rotate4096_quarter(xdst + u * (32 * rq::kXPitch), n, lane, rq::StaticStep{mult, sx}, q);
+            auto at = (rq::lds_u32_ptr)(xs + u * 2048 + (lane & 31) * 64 + n * 16 + (lane >> 5) * 8);
+            at[0] = q[0];
+            at[1] = q[1];
+        }
+        rq::lds_sync();
+    }
+    if constexpr (MODE == 1) {
         // four groups of 256 threads take chunks in turn; with a cross-wavefront exchange
         // (blocks > 512) the scratch is shared, so only the first group works
         const int sg = wave >> 2, stid = tid & 255;
-        const int nch = (K + G * kChunk - 1) / (G * kChunk), items = M * nch;
+        const int nch = (K + kChunk - 1) / kChunk, items = M * nch;
         const bool serial = log2h > 9;
         for (int it0 = 0; it0 < items; it0 += serial ? 1 : 4) {
             const int it = serial ? it0 : it0 + sg;
@@ -212,10 +227,9 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
             auto scratch = (rq::lds_f32_ptr)(smem + xch_off);
             if (!serial && !active) continue;   // no barriers inside: idle groups skip the arithmetic
             if (log2h == 0)
-                rq::rotate_quant_chunk<G, true>(src, K, (int64_t)c * G * kChunk, 0, mult, sx, dst, scratch, stid, active);
+                rq::rotate_quant_chunk<1, true>(src, K, (int64_t)c * kChunk, 0, mult, sx, dst, scratch, stid, active);
             else
-                rq::rotate_quant_chunk<G, false>(src, K, (int64_t)c * G * kChunk, log2h, mult, sx, dst, scratch, stid,
-                                                 active);
+                rq::rotate_quant_chunk<1, false>(src, K, (int64_t)c * kChunk, log2h, mult, sx, dst, scratch, stid, active);
         }
         rq::lds_sync();
     }
@@ -314,9 +328,8 @@ int launch_one(const __half* x, const uint8_t* xq_in, const uint8_t* wq, const f
                int log2h, int M, int N, int K, __half* out, int32_t* acc, uint8_t* xq_out, hipStream_t st,
                const float* srow, const int32_t* zcorr, const DecodeSecond& two)
 {
-    constexpr int G = MODE == 2 ? 2 : 1;
     const size_t lds = (((size_t)MP * (ABITS == 8 ? K : K / 2) + 15) & ~(size_t)15) +
-                       (MODE == 0 ? 16 : (size_t)G * kChunk * 4 + (size_t)M * K * 2);
+                       (MODE == 0 ? 16 : (MODE == 1 ? (size_t)kChunk * 4 + (size_t)M * K * 2 : 16 + (size_t)M * (K / 128) * rq::kXPitch));
     auto kern = k_decode<RPW, CB, MP, MODE, ABITS>;
     static std::atomic<uint64_t> lds_ok{0};
     if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_ok) != PQ_OK)
@@ -385,6 +398,7 @@ bool decode_supported(int64_t M, int64_t N, int64_t K, int32_t h, int32_t abits)
     }
     if (!(M >= 1 && M <= (h < 0 ? 8 : 4) && (N % 16) == 0 && K <= 131072 && h <= 2 * kChunk && N <= (1 << 30)))
         return false;
+    // (4096-point blocks use less: 16 bytes of scratch and 1/16 more for the rows)
     const int64_t mp = M == 1 ? 1 : (M <= 4 ? 4 : 8), g = h <= kChunk ? 1 : 2;
     const int64_t fused = h >= 0 ? M * K * 2 + g * kChunk * 4 : 16;
     return mp * (K / 2) + 16 + fused <= 160 * 1024;

@@ -39,7 +39,7 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+using rq::v16f;
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kImage = 24, kStep = 64 * kImage, kChunkF6 = 2 * kStep;   // 1536 B per (row block, step); 3072 per stage
@@ -220,8 +220,8 @@ __device__ __forceinline__ void static_for6(F&& f)
 //    four codes make 16 bits; one exchange between the two half-wavefronts (v_permlane32_swap) pairs them to
 //    dwords of eight channels, a second one hands each half-wavefront the four dwords of its own 32 channels,
 //    which is the 16 bytes of canonical nibbles (stored if asked for) and the input of the register image.
-constexpr int kXPitch = 272;      // LDS row of 128 fp16 + 16 bytes: the 16-byte operand reads of 32 rows spread over all banks
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+using rq::kXPitch;
+using rq::v8h;
 
 // (at least four wavefronts per SIMD: with that bound the compiler keeps the accumulators in ordinary registers,
 // which the quantizer reads directly, instead of accumulation registers that cost a move per value)
@@ -339,11 +339,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
     });
 }
 
-// Rotation blocks of 4096 channels: H_4096 = H_32 x H_128, so a token's 128-channel blocks are first multiplied by H_128
-// on the matrix pipe, as above but with the 32 blocks of ONE token as the columns, and the five outer stages are fp32
-// butterflies between the lanes that hold the blocks.  With butterflies alone and a repack behind them the rotation of a
-// prepacked layer was two launches, bound by vector instructions and by launch latency (1111 x 4096: 9.8 + 5.5 us);
-// this is one launch that writes tiles, nibbles, or both (10.1 us).
+// Rotation blocks of 4096 channels (rq::rotate4096_quarter): one launch that writes tiles, nibbles, or both.  With butterflies
+// alone and a repack behind them the rotation of a prepacked layer was two launches, bound by vector instructions and by
+// launch latency (1111 x 4096: 9.8 + 5.5 -> 10.1 us).
 //
 // A workgroup of 16 wavefronts takes four tokens, four wavefronts each: wavefront n of a token computes the output
 // channels 32 n .. 32 n + 31 of every block (8 matrix instructions), so that a handful of tokens still keeps a CU busy.
@@ -379,45 +377,11 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __
         for (int p = 0; p < 2; ++p)
             *(__attribute__((address_space(3))) v4i*)(stg + (8 * n + 4 * p + (lane >> 4)) * kXPitch + (lane & 15) * 16) = raw[p];
     }
-    // ---- the H operand (see above): sign = parity of popcount(i & j), j = 32 n + l % 32, i = 16 s + 8 (l / 32) + 0..7
-    const int j = lane & 31, g = lane >> 5;
-    uint32_t hreg[2][4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t lo = __builtin_popcount((2 * d) & j & 7) & 1, hi = __builtin_popcount((2 * d + 1) & j & 7) & 1;
-        const uint32_t base = 0x3C003C00u ^ (lo << 15) ^ (hi << 31);
-        const uint32_t f0 = (uint32_t)(g & (j >> 3)) & 1u, f1 = f0 ^ ((uint32_t)(j >> 4) & 1u);
-        hreg[0][d] = base ^ (f0 * 0x80008000u);
-        hreg[1][d] = base ^ (f1 * 0x80008000u);
-    }
     __syncthreads();
-    // ---- blocks x H_128: lane l ends with block l % 32, channels 32 n + 8 (v / 4) + 4 (l / 32) + v % 4
-    v16f acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    static_for6<0, 8>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        const v4i xi = *(__attribute__((address_space(3))) const v4i*)(stg + j * kXPitch + 32 * s + 16 * g);
-        const uint32_t flip = (__builtin_popcount((s >> 1) & n) & 1) ? 0x80008000u : 0u;      // wavefront-uniform
-        const v4i hi4 = {(int)(hreg[s & 1][0] ^ flip), (int)(hreg[s & 1][1] ^ flip), (int)(hreg[s & 1][2] ^ flip), (int)(hreg[s & 1][3] ^ flip)};
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, hi4), __builtin_bit_cast(v8h, xi), acc, 0, 0, 0);
-    });
-    // ---- the outer stages: between blocks, i.e. between lanes
-    float v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = acc[i];
-    rq::lane_stage<0>(v, lane);
-    rq::lane_stage<1>(v, lane);
-    rq::lane_stage<2>(v, lane);
-    rq::lane_stage<3>(v, lane);
-    rq::lane_stage<4>(v, lane);
-    // ---- quantize; the half-wavefronts trade so that a lane has 16 consecutive channels (as in the kernel above)
-    const uint32_t w01 = rq::quant_pack8<false>(v, v, steps.mult, steps.step);
-    const uint32_t w23 = rq::quant_pack8<false>(v + 8, v + 8, steps.mult, steps.step);
-    const auto sw = __builtin_amdgcn_permlane32_swap(w01, w23, false, false);
-    const uint32_t mine = sw[0], theirs = sw[1];
-    const v2i two = {(int)__builtin_amdgcn_perm(theirs, mine, 0x05040100u), (int)__builtin_amdgcn_perm(theirs, mine, 0x07060302u)};
-    *(__attribute__((address_space(3))) v2i*)(codes_all + tok * (32 * kCodePitch) + j * kCodePitch + n * 16 + g * 8) = two;
+    uint32_t q[2];
+    rq::rotate4096_quarter(stg, n, lane, steps, q);
+    const v2i two = {(int)q[0], (int)q[1]};
+    *(__attribute__((address_space(3))) v2i*)(codes_all + tok * (32 * kCodePitch) + (lane & 31) * kCodePitch + n * 16 + (lane >> 5) * 8) = two;
     __syncthreads();
     // ---- out: 512 register images (four tokens side by side) by the first half of the workgroup, 512 pieces of 16 bytes of
     // nibbles by the other half (by all in turn if only one of the two is wanted, which leaves the rest idle)
@@ -928,8 +892,9 @@ int launch_rotate128_mfma(const void* x, int64_t R, int64_t K, float act_scale, 
     return hip_status(hipGetLastError());
 }
 
-// 4096-point blocks.  The choice depends on the row alone, so every call on the same input sees the same codes.  (The same
-// kernel with fewer outer stages is level with the butterflies at 2048 points and behind at 1024: 0.92-1.09 x.)
+// 4096-point blocks.  The fused launch of few tokens (k_decode) forms the same sums, so every call on the same input sees
+// the same codes.  (The same kernel with fewer outer stages is level with the butterflies at 2048 points and behind at
+// 1024: 0.92-1.09 x.)
 // out (tiles) or nibbles may be NULL, not both.
 bool rotate4096_mfma_supported(int64_t K, int32_t h) { return h == 4096 && (K % 4096) == 0 && K <= (1 << 24); }
 

@@ -443,5 +443,59 @@ __device__ __forceinline__ void rotate_quant_chunk(SRC x_row, int64_t K, int64_t
     rotate_quant_regs<G, EXACT>(raw, live, chunk0, log2h, mult, step, dst_row, xch, tid, active);
 }
 
+// ---- rotation blocks of 4096 channels on the matrix pipe: H_4096 = H_32 x H_128.  The 32 blocks of 128 channels are the
+// columns of a product with H_128, the five outer stages are fp32 butterflies between the lanes that hold the columns.
+// Every kernel that makes static 4-bit codes of such blocks calls this function, so a token has the same codes in
+// whichever call, form and batch it arrives (with sums in another order a code can differ at a rounding tie).
+constexpr int kXPitch = 272;      // LDS row of 128 fp16 + 16 bytes: the 16-byte operand reads of 32 rows spread over all banks
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// The output channels 32 n .. 32 n + 31 of all 32 blocks of 128, by one wavefront (n: uniform, 0..3).  stg: LDS, the fp16
+// input, one row of kXPitch bytes per block.  Lane l returns the codes of block l % 32, channels 32 n + 16 (l / 32) + 0..15:
+// two dwords of eight.
+template <typename STEPS>
+__device__ __forceinline__ void rotate4096_quarter(const uint8_t* stg, int n, int lane, const STEPS& steps, uint32_t (&codes)[2])
+{
+    // The H operand needs no memory: the sign is the parity of popcount(i & j), j = 32 n + l % 32, i = 16 s + 8 (l / 32) + 0..7
+    const int j = lane & 31, g = lane >> 5;
+    uint32_t hreg[2][4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t lo = __builtin_popcount((2 * d) & j & 7) & 1, hi = __builtin_popcount((2 * d + 1) & j & 7) & 1;
+        const uint32_t base = 0x3C003C00u ^ (lo << 15) ^ (hi << 31);
+        const uint32_t f0 = (uint32_t)(g & (j >> 3)) & 1u, f1 = f0 ^ ((uint32_t)(j >> 4) & 1u);
+        hreg[0][d] = base ^ (f0 * 0x80008000u);
+        hreg[1][d] = base ^ (f1 * 0x80008000u);
+    }
+    // blocks x H_128: lane l ends with block l % 32, channels 32 n + 8 (v / 4) + 4 (l / 32) + v % 4
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const v4i xi = *(lds_cv4_ptr)(stg + j * kXPitch + 32 * s + 16 * g);
+        const uint32_t flip = (__builtin_popcount((s >> 1) & n) & 1) ? 0x80008000u : 0u;      // wavefront-uniform
+        const v4i hi4 = {(int)(hreg[s & 1][0] ^ flip), (int)(hreg[s & 1][1] ^ flip), (int)(hreg[s & 1][2] ^ flip), (int)(hreg[s & 1][3] ^ flip)};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, hi4), __builtin_bit_cast(v8h, xi), acc, 0, 0, 0);
+    }
+    // the outer stages: between blocks, i.e. between lanes
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = acc[i];
+    lane_stage<0>(v, lane);
+    lane_stage<1>(v, lane);
+    lane_stage<2>(v, lane);
+    lane_stage<3>(v, lane);
+    lane_stage<4>(v, lane);
+    // quantize; the half-wavefronts trade so that a lane has 16 consecutive channels
+    const uint32_t w01 = quant_pack8<false>(v, v, steps.mult, steps.step, steps.zero_offset());
+    const uint32_t w23 = quant_pack8<false>(v + 8, v + 8, steps.mult, steps.step, steps.zero_offset());
+    const auto sw = __builtin_amdgcn_permlane32_swap(w01, w23, false, false);
+    const uint32_t mine = sw[0], theirs = sw[1];
+    codes[0] = __builtin_amdgcn_perm(theirs, mine, 0x05040100u);
+    codes[1] = __builtin_amdgcn_perm(theirs, mine, 0x07060302u);
+}
+
 }  // namespace rq
 }  // namespace pq
