@@ -339,10 +339,12 @@ int launch_rotate_quant(const void* x, int64_t M, int64_t K, int32_t h, float ac
     return launch_rq<4>(static_cast<const __half*>(x), M, K, h, static_step(act_scale, h), static_cast<uint32_t*>(xq), st);
 }
 
-// Eq. 1 with a zero-point: stored code = clamp(round(y / s) + z, 0, 15) - 8.
+// Eq. 1 with a zero-point: stored code = clamp(round(y / s) + z, 0, 15) - 8.  z = 8 is the symmetric quantizer, by the same
+// kernels (the sums of the matrix pipe's rotations are in another order than the butterflies').
 int launch_rotate_quant_zp(const void* x, int64_t M, int64_t K, int32_t h, float act_scale, int32_t zero_point, void* xq,
                            hipStream_t st)
 {
+    if (zero_point == 8) return launch_rotate_quant(x, M, K, h, act_scale, xq, st);
     const rq::StaticStep b = static_step(act_scale, h);
     return launch_rq<4>(static_cast<const __half*>(x), M, K, h, rq::StaticStepZp{b.mult, b.step, zero_point - 8},
                         static_cast<uint32_t*>(xq), st);

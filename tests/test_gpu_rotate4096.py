@@ -1,4 +1,5 @@
-"""Rotation blocks of 4096 channels: a token has the same codes in every call, form and batch.
+"""Rotations on the matrix pipe: a token has the same codes in every call, form and batch (blocks of 4096 channels), and
+the quantizer with a zero-point of 8 is the symmetric one.
 
 The inputs are made so that sums taken in another order give other codes: half of the channels hold one large value with
 the signs of a Hadamard row (every output but one cancels it), the others hold small ones, so the fp32 rounding of the
@@ -22,23 +23,23 @@ def pq():
     return b
 
 
-def order_sensitive(rows, K, seed):
+def order_sensitive(rows, K, seed, h=H):
     rng = np.random.default_rng(seed)
-    x = rng.normal(0.0, 0.06, size=(rows, K // H, H)).astype(np.float16)
-    sign = np.array([bin(i & 1234).count("1") & 1 for i in range(H)])
+    x = rng.normal(0.0, 0.06, size=(rows, K // h, h)).astype(np.float16)
+    sign = np.array([bin(i & 1234).count("1") & 1 for i in range(h)])
     x[:, :, 0::2] = np.where(sign[0::2], -2000.0, 2000.0).astype(np.float16)
     return x.reshape(rows, K), np.float32(1.2 / 64)
 
 
-def butterfly_codes(x, sx):
+def butterfly_codes(x, sx, h=H):
     """The codes of plain fp32 butterflies, one of the other orders."""
-    v = x.astype(np.float32).reshape(-1, H)
+    v = x.astype(np.float32).reshape(-1, h)
     d = 1
-    while d < H:
-        v = v.reshape(-1, H // (2 * d), 2, d)
-        v = np.stack([v[:, :, 0] + v[:, :, 1], v[:, :, 0] - v[:, :, 1]], axis=2).reshape(-1, H)
+    while d < h:
+        v = v.reshape(-1, h // (2 * d), 2, d)
+        v = np.stack([v[:, :, 0] + v[:, :, 1], v[:, :, 0] - v[:, :, 1]], axis=2).reshape(-1, h)
         d *= 2
-    return np.clip(np.rint(v * np.float32(1.0 / (np.float64(sx) * 64.0))), -8, 7).astype(np.int8).reshape(x.shape)
+    return np.clip(np.rint(v * np.float32(1.0 / (np.float64(sx) * np.sqrt(h)))), -8, 7).astype(np.int8).reshape(x.shape)
 
 
 # tokens of a call, channels, kernel variant: the shapes whose automatic choice is the fused launch (1 x 4096 .. 1 x 16384,
@@ -65,3 +66,12 @@ def test_few_tokens_have_the_codes_of_a_batch(pq, M, K, N, variant):
             assert np.array_equal(host(codes)[: M * K // 2].reshape(M, K // 2), batch[r:r + M])
         for got in (f6, a, b):
             assert np.array_equal(host(got).view(np.uint16), host(out).view(np.uint16))
+
+
+@pytest.mark.parametrize("M,K,h", [(70, 4096, 4096), (3, 8192, 4096), (600, 1152, 128)])
+def test_zero_point_eight_is_the_symmetric_quantizer(pq, M, K, h):
+    """Also for the blocks whose rotation runs on the matrix pipe."""
+    x, sx = order_sensitive(M, K, seed=M + K, h=h)
+    codes = host(pq.pq_rotate_quant(dev(x), h, float(sx)))
+    assert (O.unpack(codes) != butterfly_codes(x, sx, h)).any()
+    assert np.array_equal(host(pq.pq_rotate_quant_zp(dev(x), h, float(sx), 8)), codes)
