@@ -277,7 +277,7 @@ int pq_linear_prepacked(const void* x_f16, const void* wq_tiled, const float* w_
  * 16 (up to 32 in two launches where a cost estimate puts that ahead of the tiled kernel: outputs
  * of few tiles), tiled beyond; and with 4-bit activation codes the small tiles that split K over the
  * wavefronts of a workgroup in place of two streaming launches and of tiled where an estimate puts
- * them ahead.  No variant number forces these.  Every kernel gives the same accumulators and the same fp16 outputs
+ * them ahead (pq_gemm_small_tile tells).  No variant number forces these.  Every kernel gives the same accumulators and the same fp16 outputs
  * bit for bit.
  * Returns the previous value, or -1 if `variant` is unknown.  An atomic integer: safe to call from
  * any thread, but a product call running concurrently on another thread may see either value.
@@ -295,6 +295,12 @@ int pq_set_gemm_variant(int variant);
  */
 int pq_set_gemm_tile(int tile);
 int pq_set_gemm_f6_tile(int tile);
+
+/* Which small tile a product call would take (host only; for sweeps and tests): 10 * blocks of 32 tokens + blocks of 32
+ * channels, or 0 where another kernel serves.  N_b = 0: pq_w4a4_gemm_ws with plane_bytes of scratch memory for [N_a,K], or
+ * pq_w4a4_gemm_f6 (prepacked != 0); N_b > 0: the one launch for both products of pq_linear2 or pq_linear2_f6.
+ */
+int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t prepacked, size_t plane_bytes);
 
 /* ---- 4-bit weights, 8-bit static activations (the W4A8 rows of Table 3) -------------------
  * Same layer with the activation quantizer at 8 bits: q = clamp(round_half_even(y/act_scale),

@@ -41,6 +41,7 @@ SIGNATURES = {
     "pq_set_gemm_variant": (ctypes.c_int, [ctypes.c_int]),
     "pq_set_gemm_tile": (ctypes.c_int, [ctypes.c_int]),
     "pq_set_gemm_f6_tile": (ctypes.c_int, [ctypes.c_int]),
+    "pq_gemm_small_tile": (ctypes.c_int, [_i64, _i64, _i64, _i64, _i32, _sz]),
     "pq_probe_mfma_i8": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
     "pq_probe_stream_read": (ctypes.c_int, [_vp, _i64, _vp, _vp]),
     "pq_probe_mfma_f6": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
@@ -600,6 +601,10 @@ def pq_set_gemm_tile(tile: int) -> int:
 
 def pq_set_gemm_f6_tile(tile: int) -> int:
     return int(lib().pq_set_gemm_f6_tile(int(tile)))
+
+
+def pq_gemm_small_tile(M: int, N_a: int, N_b: int, K: int, prepacked: bool = False, plane_bytes: int = 0) -> int:
+    return int(lib().pq_gemm_small_tile(M, N_a, N_b, K, int(prepacked), plane_bytes))
 
 
 def pq_probe_mfma_i8(operands: torch.Tensor, iters: int, workgroups: int, sink: torch.Tensor) -> float:

@@ -106,6 +106,15 @@ bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes
     return pq::gemm_ksplit_i8_cost_us(M, N, K) < 0.97 * other;
 }
 
+// Both products of pq_linear2 on that kernel: one launch for the two.  Two launches of few tiles leave the chip half empty
+// twice and pay the launch and the reduction twice (32 tokens, 4096 -> 2 x 1024: 10.5 -> 6.8 us with the quantizer, 64 tokens,
+// 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).
+bool share_ksplit(int64_t M, int64_t N_a, int64_t N_b, int64_t K, size_t plane_bytes)
+{
+    auto small = [&](int64_t N) { return take_ksplit(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes); };
+    return small(N_a) && small(N_b) && pq::gemm_ksplit_i8_cost_us(M, N_a + N_b, K) < 1e9;
+}
+
 // Whether pq_linear takes the fused launch (every workgroup rotates and quantizes the few rows for itself)
 // when the shape allows it, rather than a quantizer launch and a product launch.  Measured with cold weights
 // on 8 to 117 MB matrices: without rotation the fused launch is level or ahead up to 32768 channels in all
@@ -280,12 +289,7 @@ int pq_linear2(const void* x_f16, const void* wq_a, const float* w_scale_a, int6
     if (rc != PQ_OK) return rc;
     const size_t codes = pq_linear_workspace_bytes(M, K);
     uint8_t* planes = static_cast<uint8_t*>(workspace) + codes;
-    const size_t plane_bytes = workspace_bytes - codes;
-    // Both products on the kernel that splits K over a workgroup's wavefronts: one launch for the two.  Two launches of
-    // few tiles leave the chip half empty twice and pay the launch and the reduction twice (32 tokens, 4096 -> 2 x 1024:
-    // 10.5 -> 6.8 us with the quantizer, 64 tokens, 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).
-    auto small = [&](int64_t N) { return take_ksplit(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes); };
-    if (small(N_a) && small(N_b) && pq::gemm_ksplit_i8_cost_us(M, N_a + N_b, K) < 1e9)
+    if (share_ksplit(M, N_a, N_b, K, workspace_bytes - codes))
         return pq::launch_gemm_ksplit_i8(workspace, wq_a, w_scale_a, act_scale, nullptr, nullptr, M, N_a, K, out_a_f16, nullptr,
                                          static_cast<hipStream_t>(stream), wq_b, w_scale_b, N_b, out_b_f16);
     rc = pq_w4a4_gemm_ws(workspace, wq_a, w_scale_a, act_scale, M, N_a, K, out_a_f16, nullptr, planes, workspace_bytes - codes, stream);
@@ -813,6 +817,21 @@ int pq_probe_stream_read(const void* src, int64_t bytes, int32_t* sink, void* st
 int pq_set_gemm_tile(int tile) { return pq::set_gemm_tile(tile); }
 
 int pq_set_gemm_f6_tile(int tile) { return pq::set_gemm_f6_tile(tile); }
+
+int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t prepacked, size_t plane_bytes)
+{
+    if (M <= 0 || N_a <= 0 || N_b < 0 || K <= 0 || (K % 128) != 0 || (N_a % 16) != 0 || (N_b % 16) != 0 || M > (1 << 30) ||
+        N_a > (1 << 30) || N_b > (1 << 30) || K > 262080)
+        return 0;
+    if (prepacked) {
+        if ((N_b != 0 && N_b != N_a) || !pq::gemm_f6_takes_ksplit(M, N_a, K, N_b != 0)) return 0;
+        return pq::gemm_ksplit_f6_tile(M, N_a + N_b, K);
+    }
+    if (N_b != 0 ? !share_ksplit(M, N_a, N_b, K, plane_bytes)
+                 : !take_ksplit(pick_with_planes(M, N_a, K, plane_bytes), M, N_a, K, plane_bytes))
+        return 0;
+    return pq::gemm_ksplit_i8_tile(M, N_a + N_b, K);
+}
 
 size_t pq_linear_noalloc_max_bytes(void) { return kScratchBytes; }
 

@@ -967,6 +967,23 @@ int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t
 }
 }  // namespace
 
+// Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
+// tiles was measured at 5 us + 0.33 us per 128-channel stage and round (0.5 with every CU busy) + its output; the
+// kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
+// 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).  Two
+// matrices count as one of twice the height on either side (two launches of few tiles -> one, with the quantizer:
+// 128 tokens, 4096 -> 2 x 4096: 15.6 -> 11.9 us, 512 tokens, 4096 -> 2 x 1024: 17.1 -> 13.4).
+bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two)
+{
+    if (forced_f6_tile() != -1) return false;
+    const int64_t mats = two ? 2 : 1;
+    const int64_t tiles = mats * ((M + 127) / 128) * ((N + 255) / 256);
+    const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
+    const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
+                                 (double)(mats * M) * N * 2 / 4.2e6;
+    return gemm_ksplit_f6_cost_us(M, mats * N, K) < 0.97 * persistent_us;
+}
+
 // Channels per tile: 512, 384 or 256 (CI = 4, 3, 2), or a mix of 512 and 384 in one launch where N = 512 a +
 // 384 b; the choice minimises the estimated time of the busiest CU (a tile costs a fixed part plus a part
 // proportional to its width).
@@ -979,20 +996,8 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     const int64_t mats = w6b ? 2 : 1;                                // matrices whose tiles follow one another
     const int64_t gm = (M + 127) / 128;
     const int forced_tile = forced_f6_tile();
-    // Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
-    // tiles was measured at 5 us + 0.33 us per 128-channel stage and round (0.5 with every CU busy) + its output; the
-    // kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
-    // 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).  Two
-    // matrices count as one of twice the height on either side (two launches of few tiles -> one, with the quantizer:
-    // 128 tokens, 4096 -> 2 x 4096: 15.6 -> 11.9 us, 512 tokens, 4096 -> 2 x 1024: 17.1 -> 13.4).
-    if (forced_tile == -1) {
-        const int64_t tiles = mats * gm * ((N + 255) / 256);
-        const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
-        const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
-                                     (double)(mats * M) * N * 2 / 4.2e6;
-        if (gemm_ksplit_f6_cost_us(M, mats * N, K) < 0.97 * persistent_us)
-            return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
-    }
+    if (gemm_f6_takes_ksplit(M, N, K, w6b != nullptr))
+        return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn

@@ -528,6 +528,18 @@ double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K)
     return plan_i8(M, N, K).us;
 }
 
+int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t K)
+{
+    const Plan p = plan_f6(M, N, K);
+    return p.ti * 10 + p.cj;
+}
+
+int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t K)
+{
+    const Plan p = plan_i8(M, N, K);
+    return p.ti * 10 + p.cj;
+}
+
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st, const void* w6b, const float* swb, int64_t Nb, void* outb)
 {

@@ -62,6 +62,18 @@ def test_host_only_calls(b):
     assert L.pq_set_gemm_variant(5) == 0
     assert wsb(100, 256, 2048) == 5 * 100 * 256 * 4 and wsb(100, 256, 384) == 0
     assert L.pq_set_gemm_variant(0) == 5
+    # which products take the small tiles that split K inside a workgroup, and which tile
+    small = b.pq_gemm_small_tile
+    assert small(64, 512, 0, 3200) == 11 and small(1, 16, 0, 128, prepacked=True) == 11
+    assert small(2048, 14336, 0, 4096) == 0 and small(2048, 14336, 14336, 4096, prepacked=True) == 0 and small(4, 4096, 0, 4096) == 0
+    assert small(64, 512, 0, 3200 + 32) == 0 and small(64, 500, 0, 3200) == 0 and small(0, 512, 0, 3200) == 0
+    assert small(64, 512, 256, 3200, prepacked=True) == 0 and small(64, 512, 256, 3200) > 0     # unequal heights: two launches
+    assert L.pq_set_gemm_variant(2) == 0
+    assert small(64, 512, 0, 3200) == 0
+    assert L.pq_set_gemm_variant(0) == 2
+    assert L.pq_set_gemm_f6_tile(2) == -1
+    assert small(1, 16, 0, 128, prepacked=True) == 0
+    assert L.pq_set_gemm_f6_tile(-1) == 2
     assert L.pq_linear_w4a8_workspace_bytes(3, 4096) == 12288
     assert L.pq_linear_dynamic_workspace_bytes(3, 4096, 4) == 6144 + 256
     assert L.pq_linear_dynamic_workspace_bytes(100, 128, 8) == 12800 + 512
