@@ -103,16 +103,18 @@ bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes
     } else {
         return false;
     }
-    return pq::gemm_ksplit_i8_cost_us(M, N, K) < 0.97 * other;
+    return pq::gemm_ksplit_i8_cost_us(M, N, 0, K) < 0.97 * other;
 }
 
 // Both products of pq_linear2 on that kernel: one launch for the two.  Two launches of few tiles leave the chip half empty
 // twice and pay the launch and the reduction twice (32 tokens, 4096 -> 2 x 1024: 10.5 -> 6.8 us with the quantizer, 64 tokens,
-// 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).
+// 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).  One tile serves both, so matrices that would each take
+// another, or a last round that both together leave nearly empty, can make two launches the cheaper way.
 bool share_ksplit(int64_t M, int64_t N_a, int64_t N_b, int64_t K, size_t plane_bytes)
 {
     auto small = [&](int64_t N) { return take_ksplit(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes); };
-    return small(N_a) && small(N_b) && pq::gemm_ksplit_i8_cost_us(M, N_a + N_b, K) < 1e9;
+    return small(N_a) && small(N_b) &&
+           pq::gemm_ksplit_i8_cost_us(M, N_a, N_b, K) < pq::gemm_ksplit_i8_cost_us(M, N_a, 0, K) + pq::gemm_ksplit_i8_cost_us(M, N_b, 0, K);
 }
 
 // Whether pq_linear takes the fused launch (every workgroup rotates and quantizes the few rows for itself)
@@ -825,12 +827,12 @@ int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t p
         return 0;
     if (prepacked) {
         if ((N_b != 0 && N_b != N_a) || !pq::gemm_f6_takes_ksplit(M, N_a, K, N_b != 0)) return 0;
-        return pq::gemm_ksplit_f6_tile(M, N_a + N_b, K);
+        return pq::gemm_ksplit_f6_tile(M, N_a, N_b, K);
     }
     if (N_b != 0 ? !share_ksplit(M, N_a, N_b, K, plane_bytes)
                  : !take_ksplit(pick_with_planes(M, N_a, K, plane_bytes), M, N_a, K, plane_bytes))
         return 0;
-    return pq::gemm_ksplit_i8_tile(M, N_a + N_b, K);
+    return pq::gemm_ksplit_i8_tile(M, N_a, N_b, K);
 }
 
 size_t pq_linear_noalloc_max_bytes(void) { return kScratchBytes; }

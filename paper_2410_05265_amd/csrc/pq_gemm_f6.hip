@@ -981,7 +981,7 @@ bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two)
     const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
     const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
                                  (double)(mats * M) * N * 2 / 4.2e6;
-    return gemm_ksplit_f6_cost_us(M, mats * N, K) < 0.97 * persistent_us;
+    return gemm_ksplit_f6_cost_us(M, N, two ? N : 0, K) < 0.97 * persistent_us;
 }
 
 // Channels per tile: 512, 384 or 256 (CI = 4, 3, 2), or a mix of 512 and 384 in one launch where N = 512 a +

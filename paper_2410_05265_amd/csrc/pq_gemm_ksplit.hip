@@ -476,17 +476,18 @@ struct TileShape {
     int ti, cj, resident;      // 32-row blocks of tokens and of channels; workgroups a CU holds at a time
 };
 
+// (two matrices: each ends in a tile of its own, so ragged heights can make one more column of tiles than their sum)
 template <int COUNT, typename COST>
-Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t K, double per_area, COST stage_us)
+Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t Nb, int64_t K, double per_area, COST stage_us)
 {
     Plan best{0, 0, 1e300};
     for (const TileShape& t : tiles) {
-        const int64_t count = ((M + 32 * t.ti - 1) / (32 * t.ti)) * ((N + 32 * t.cj - 1) / (32 * t.cj));
+        const int64_t tn = 32 * t.cj, count = ((M + 32 * t.ti - 1) / (32 * t.ti)) * ((N + tn - 1) / tn + (Nb + tn - 1) / tn);
         if (count > (1 << 20)) continue;
         const int64_t rounds = (count + 255) / 256;
         const double fill = count < 256 ? (double)count / 256 : 1.0;
         const double us = 1.5 + (double)rounds * (double)(K / 128) * stage_us(t, fill) +
-                          (double)((rounds + t.resident - 1) / t.resident) * (0.5 + per_area * t.ti * t.cj) + (double)M * N * 2 / 4.2e6;
+                          (double)((rounds + t.resident - 1) / t.resident) * (0.5 + per_area * t.ti * t.cj) + (double)M * (N + Nb) * 2 / 4.2e6;
         if (us < best.us) best = Plan{t.ti, t.cj, us};
     }
     return best;
@@ -496,47 +497,46 @@ constexpr TileShape kTilesF6[] = {{1, 1, 4}, {1, 2, 3}, {2, 2, 2}, {3, 2, 1}, {2
 constexpr TileShape kTilesI8[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {3, 2, 1}, {2, 3, 1}};
 
 // Prepacked: 0.035 us per stage and 32-row block of the tile (3 KiB at 85 KB/us).
-Plan plan_f6(int64_t M, int64_t N, int64_t K)
+Plan plan_f6(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    return best_plan(kTilesF6, M, N, K, 0.3, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
+    return best_plan(kTilesF6, M, N, Nb, K, 0.3, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
 }
 
 // Packed nibbles: the expansion and the INT8 instructions weigh in, 0.063 / 0.105 / 0.15 / 0.215 us per stage for tiles of
 // 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few; and no less than the weights' way from
 // memory (2.8 us + bytes at 6.3 TB/s).
-Plan plan_i8(int64_t M, int64_t N, int64_t K)
+Plan plan_i8(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    Plan p = best_plan(kTilesI8, M, N, K, 0.25, [](const TileShape& t, double fill) {
+    Plan p = best_plan(kTilesI8, M, N, Nb, K, 0.25, [](const TileShape& t, double fill) {
         const int area = t.ti * t.cj;
         return (area == 1 ? 0.063 : (area == 2 ? 0.105 : (area == 4 ? 0.15 : 0.215))) * (0.7 + 0.3 * fill);
     });
-    const double stream_us = 2.8 + (double)(N * (K / 2)) / 6.3e6;
+    const double stream_us = 2.8 + (double)((N + Nb) * (K / 2)) / 6.3e6;
     if (p.us < stream_us) p.us = stream_us;
     return p;
 }
 
 }  // namespace
 
-// Estimated microseconds; a large number where the kernel does not take the shape.  (Two matrices in one launch: N is the
-// sum of their heights.)
-double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K) { return plan_f6(M, N, K).us; }
+// Estimated microseconds; a large number where the kernel does not take the shape.
+double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K) { return plan_f6(M, N, Nb, K).us; }
 
-double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K)
+double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
     // (sums of 256 acc in int32, 32-bit byte offsets of the rows)
-    if (K % 128 != 0 || K >= 131072 || M * (K / 2) >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return 1e300;
-    return plan_i8(M, N, K).us;
+    if (K % 128 != 0 || K >= 131072 || M * (K / 2) >= ((int64_t)1 << 32) || (N + Nb) * (K / 2) >= ((int64_t)1 << 32)) return 1e300;
+    return plan_i8(M, N, Nb, K).us;
 }
 
-int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t K)
+int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    const Plan p = plan_f6(M, N, K);
+    const Plan p = plan_f6(M, N, Nb, K);
     return p.ti * 10 + p.cj;
 }
 
-int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t K)
+int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    const Plan p = plan_i8(M, N, K);
+    const Plan p = plan_i8(M, N, Nb, K);
     return p.ti * 10 + p.cj;
 }
 
@@ -545,7 +545,7 @@ int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float
 {
     const Epilogue ep{sw, sx, nullptr, nullptr, static_cast<__half*>(out), acc};
     const Second two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb), (int)Nb, 0};
-    const Plan p = plan_f6(M, N + Nb, K);
+    const Plan p = plan_f6(M, N, Nb, K);
     switch (p.ti * 10 + p.cj) {
         case 11: return launch_f6_tile<1, 1, 4, 2>(x6, w6, ep, M, N, K, two, st);
         case 12: return launch_f6_tile<1, 2, 4, 2>(x6, w6, ep, M, N, K, two, st);
@@ -564,7 +564,7 @@ int launch_gemm_ksplit_i8(const void* xq, const void* wq, const float* sw, float
 {
     const Epilogue ep{sw, sx, srow, zcorr, static_cast<__half*>(out), acc};
     const Second two{static_cast<const uint8_t*>(wqb), swb, static_cast<__half*>(outb), (int)Nb, 0};
-    const Plan p = plan_i8(M, N + Nb, K);
+    const Plan p = plan_i8(M, N, Nb, K);
     switch (p.ti * 10 + p.cj) {
         case 11: return launch_i8_tile<1, 1, 8, 2>(xq, wq, ep, M, N, K, two, st);
         case 12: return launch_i8_tile<1, 2, 4, 2>(xq, wq, ep, M, N, K, two, st);

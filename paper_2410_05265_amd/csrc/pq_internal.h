@@ -80,12 +80,12 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
 // number where the shape is not taken), the tile behind the estimate (10 * blocks of 32 tokens + blocks of 32 channels; 0 for
-// none) and the launches.  srow, zcorr as in the tiled kernel, or NULL.  wqb / w6b != NULL: a second matrix [Nb, K] on the same
-// tokens in the same launch, outputs without acc, srow and zcorr.
-double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t K);
-double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t K);
-int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t K);
-int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t K);
+// none) and the launches; Nb: rows of a second matrix on the same tokens in the same launch, or 0.  srow, zcorr as in the tiled kernel, or NULL.  wqb / w6b != NULL: that second matrix,
+// outputs without acc, srow and zcorr.
+double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
+double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
+int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
+int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
 // Whether launch_gemm_f6 takes them for one matrix [N, K], or for two of that size.
 bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two);
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,

@@ -83,6 +83,18 @@ def test_host_only_calls(b):
     assert L.pq_calibrate_zp_workspace_bytes(256, 64) == 256 * 66 * 4 and L.pq_calibrate_zp_workspace_bytes(256, 1) == 0
 
 
+@pytest.mark.parametrize("M,N_a,N_b,K,prepacked", [(134, 4080, 4080, 4096, False), (290, 2416, 2416, 4096, False), (264, 2704, 2704, 4096, False),
+                                                   (269, 2720, 2720, 4096, True), (187, 5424, 5424, 4096, True)])
+def test_shared_launch_counts_the_tiles_of_both_matrices(b, M, N_a, N_b, K, prepacked):
+    """Ragged heights: the tiles of each matrix are rounded up, which can be more than those of one matrix of both heights.
+    A plan that counts the latter puts two or three workgroups into a round of their own, twice the time."""
+    tile = b.pq_gemm_small_tile(M, N_a, N_b, K, prepacked)
+    tm, tn = tile // 10 * 32, tile % 10 * 32
+    assert tile > 0
+    workgroups = -(-M // tm) * (-(-N_a // tn) - (-N_b // tn))
+    assert not 256 < workgroups < 300, (tile, workgroups)
+
+
 def test_argument_errors_launch_nothing(b):
     L = b.lib()
     p = ctypes.c_void_p(0x1000)          # never dereferenced: each call fails validation first
