@@ -82,6 +82,17 @@ int pick_with_planes(int64_t M, int64_t N, int64_t K, size_t plane_bytes, int32_
     return kernel;
 }
 
+// Estimated microseconds of `kernel`; 0 where the small tiles do not stand in for it.
+double replaceable_cost_us(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes)
+{
+    if (g_variant != 0) return 0.0;
+    if (kernel == 2) return pq::gemm_tiled_cost_us(M, N, K, plane_bytes);
+    if (kernel != 1) return 0.0;
+    const int launches = pq::stream_mfma_launches(M, N, K, 4);
+    // (cold weights included: two launches 7.4-9 us on matrices up to 2 MB, 11-12 at 4-12 MB, 20 at 20 MB)
+    return launches < 2 ? 0.0 : launches * (4.0 + (double)(N * (K / 2)) / 4.0e6);
+}
+
 // Whether a 4-bit product goes to the kernel that splits K over the wavefronts of a workgroup (one launch, no planes)
 // instead of `kernel`, the choice above.  Against the tiled kernel (split with the planes of this call, or whole) and
 // against two or more streaming launches the estimates of both sides decide.  Measured before -> after, warm weights:
@@ -92,29 +103,26 @@ int pick_with_planes(int64_t M, int64_t N, int64_t K, size_t plane_bytes, int32_
 // 2048 -> 20480 10.8 against 12.1, 14336 -> 4096 product 9.6 against 10.9; 4096 -> 11008 alone 11.0 against 10.4).
 bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes)
 {
-    if (g_variant != 0) return false;
-    double other;
-    if (kernel == 2) {
-        other = pq::gemm_tiled_cost_us(M, N, K, plane_bytes);
-    } else if (kernel == 1) {
-        const int launches = pq::stream_mfma_launches(M, N, K, 4);
-        if (launches < 2) return false;
-        other = launches * (2.5 + (double)(N * (K / 2)) / 5.0e6);
-    } else {
-        return false;
-    }
-    return pq::gemm_ksplit_i8_cost_us(M, N, 0, K) < 0.97 * other;
+    return pq::gemm_ksplit_i8_cost_us(M, N, 0, K) < 0.97 * replaceable_cost_us(kernel, M, N, K, plane_bytes);
 }
 
-// Both products of pq_linear2 on that kernel: one launch for the two.  Two launches of few tiles leave the chip half empty
-// twice and pay the launch and the reduction twice (32 tokens, 4096 -> 2 x 1024: 10.5 -> 6.8 us with the quantizer, 64 tokens,
-// 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7).  One tile serves both, so matrices that would each take
-// another, or a last round that both together leave nearly empty, can make two launches the cheaper way.
+// Both products of pq_linear2 on that kernel, in one launch, where its estimate is below that of each product on its better
+// kernel alone.  Two launches of few tiles leave the chip half empty twice and pay the launch and the reduction twice (32 tokens,
+// 4096 -> 2 x 1024: 10.5 -> 6.8 us with the quantizer, 64 tokens, 4096 -> 2 x 11008: 20.9 -> 16.4, -> 2 x 14336: 21.9 -> 20.7; 30
+// tokens, 17280 -> 2 x 2944 with planes, where a split launch is the better kernel of one product: 30.5 -> 21.2).  One tile
+// serves both, so matrices that would each take another, or a last round that both together leave nearly empty, can make two
+// launches the cheaper way; where both would be small tiles in any case, one launch was the faster up to 5 % above their sum
+// (45 tokens, 6272 -> 2 x 16832 39.9 against 42.2, 917 tokens, 9856 -> 2 x 1664 64.8 against 71.5).
 bool share_ksplit(int64_t M, int64_t N_a, int64_t N_b, int64_t K, size_t plane_bytes)
 {
-    auto small = [&](int64_t N) { return take_ksplit(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes); };
-    return small(N_a) && small(N_b) &&
-           pq::gemm_ksplit_i8_cost_us(M, N_a, N_b, K) < pq::gemm_ksplit_i8_cost_us(M, N_a, 0, K) + pq::gemm_ksplit_i8_cost_us(M, N_b, 0, K);
+    double alone = 0.0;
+    for (const int64_t N : {N_a, N_b}) {
+        const double other = replaceable_cost_us(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes);
+        const double small = pq::gemm_ksplit_i8_cost_us(M, N, 0, K);
+        if (other <= 0.0) return false;
+        alone += small < 0.97 * other ? 1.05 * small : 0.97 * other;
+    }
+    return pq::gemm_ksplit_i8_cost_us(M, N_a, N_b, K) < alone;
 }
 
 // Whether pq_linear takes the fused launch (every workgroup rotates and quantizes the few rows for itself)

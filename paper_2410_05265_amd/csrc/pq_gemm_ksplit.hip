@@ -463,10 +463,9 @@ int launch_i8_tile(const void* xq, const void* wq, const Epilogue& ep, int64_t M
     return launch_tiles(k_gemm_i8_ksplit<TI, CJ, W, NS, false>, lds_ok[0], lds, 32 * TI, 32 * CJ, 64 * W, xq, wq, ep, M, N, K, two, st);
 }
 
-// Tile of a launch and its estimated time in microseconds.  Per 128-channel stage of K the operands' way into the CU,
-// and per tile the reduction and the epilogue (in proportion to the tile), which overlap another tile's stages where
-// several workgroups fit a CU; tiles go round 256 CUs.  Fitted to sweeps over 12 shapes (17 to 1111 tokens, K 4096 and
-// 14336), within about 10 % of what was measured.
+// Tile of a launch and its estimated time in microseconds: a fixed part, per 128-channel stage of K the operands' way into
+// the CU (and their expansion), and per tile the reduction and the epilogue (in proportion to the tile), which overlap another
+// tile's stages where several workgroups fit a CU; tiles go round 256 CUs.
 struct Plan {
     int ti, cj;
     double us;
@@ -476,9 +475,13 @@ struct TileShape {
     int ti, cj, resident;      // 32-row blocks of tokens and of channels; workgroups a CU holds at a time
 };
 
+struct PlanCosts {
+    double launch, tile, per_area;      // microseconds: once, per tile, per tile and 32 x 32 block
+};
+
 // (two matrices: each ends in a tile of its own, so ragged heights can make one more column of tiles than their sum)
 template <int COUNT, typename COST>
-Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t Nb, int64_t K, double per_area, COST stage_us)
+Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t Nb, int64_t K, PlanCosts c, COST stage_us)
 {
     Plan best{0, 0, 1e300};
     for (const TileShape& t : tiles) {
@@ -486,8 +489,8 @@ Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t Nb
         if (count > (1 << 20)) continue;
         const int64_t rounds = (count + 255) / 256;
         const double fill = count < 256 ? (double)count / 256 : 1.0;
-        const double us = 1.5 + (double)rounds * (double)(K / 128) * stage_us(t, fill) +
-                          (double)((rounds + t.resident - 1) / t.resident) * (0.5 + per_area * t.ti * t.cj) + (double)M * (N + Nb) * 2 / 4.2e6;
+        const double us = c.launch + (double)rounds * (double)(K / 128) * stage_us(t, fill) +
+                          (double)((rounds + t.resident - 1) / t.resident) * (c.tile + c.per_area * t.ti * t.cj) + (double)M * (N + Nb) * 2 / 4.2e6;
         if (us < best.us) best = Plan{t.ti, t.cj, us};
     }
     return best;
@@ -496,20 +499,30 @@ Plan best_plan(const TileShape (&tiles)[COUNT], int64_t M, int64_t N, int64_t Nb
 constexpr TileShape kTilesF6[] = {{1, 1, 4}, {1, 2, 3}, {2, 2, 2}, {3, 2, 1}, {2, 3, 1}, {4, 2, 1}, {2, 4, 1}};
 constexpr TileShape kTilesI8[] = {{1, 1, 1}, {1, 2, 1}, {2, 2, 1}, {3, 2, 1}, {2, 3, 1}};
 
-// Prepacked: 0.035 us per stage and 32-row block of the tile (3 KiB at 85 KB/us).
+// Prepacked: 0.035 us per stage and 32-row block of the tile (3 KiB at 85 KB/us).  Fitted to sweeps over 12 shapes (17 to 1111
+// tokens, K 4096 and 14336), within about 10 % of what was measured; on 1500 random shapes (17-2500 tokens, K 128-30000) no
+// product chosen by it was slower than the persistent launch.
 Plan plan_f6(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    return best_plan(kTilesF6, M, N, Nb, K, 0.3, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
+    return best_plan(kTilesF6, M, N, Nb, K, PlanCosts{1.5, 0.5, 0.3}, [](const TileShape& t, double) { return 0.035 * (t.ti + t.cj); });
 }
 
-// Packed nibbles: the expansion and the INT8 instructions weigh in, 0.063 / 0.105 / 0.15 / 0.215 us per stage for tiles of
-// 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, 30 % less with few; and no less than the weights' way from
-// memory (2.8 us + bytes at 6.3 TB/s).
+// Packed nibbles.  Fitted to 3300 random shapes (9-2500 tokens, K 128-28672, N 16-28672, weights from the memory-side cache and
+// from HBM), every tile measured on each, so that the choice against the other kernels' estimates errs least: of 4796 choices
+// (with and without planes) 45 are slower than the other kernel by more than 3 %, by 25 % at most.  A fit to warm weights and long
+// rows alone (1.5 + 0.5 + 0.25 per block) missed the launch's cost on short rows, 892 x 256 -> 1216 3.9 -> 5.4 us, and on
+// cold weights, 26 x 18816 -> 2352 13.0 -> 16.7 us: 111 of the same choices, by 38 % at most.  A stage takes 0.063 / 0.099 / 0.132 / 0.196 us
+// for tiles of 1 x 1, 1 x 2, 2 x 2 and 2 x 3 blocks with every CU busy, less with few; 11 % more where rows are an odd multiple of 64
+// bytes, so that a stage's 128 bytes of a row straddle two cache lines (40 % on long rows where one row of tiles leaves CUs idle:
+// every workgroup then streams weights of its own, 1.5 instead of 1.05 us per 2048 channels); and no less than the weights' way
+// from memory (2.8 us + bytes at 6.3 TB/s).
 Plan plan_i8(int64_t M, int64_t N, int64_t Nb, int64_t K)
 {
-    Plan p = best_plan(kTilesI8, M, N, Nb, K, 0.25, [](const TileShape& t, double fill) {
+    Plan p = best_plan(kTilesI8, M, N, Nb, K, PlanCosts{1.4, 1.05, 0.35}, [M, K](const TileShape& t, double fill) {
         const int area = t.ti * t.cj;
-        return (area == 1 ? 0.063 : (area == 2 ? 0.105 : (area == 4 ? 0.15 : 0.215))) * (0.7 + 0.3 * fill);
+        const double straddle = (K & 128) == 0 ? 1.0 : (M <= 32 && K >= 12800 && fill < 0.6 ? 1.4 : 1.11);
+        const double idle = area <= 2 ? 0.4 : 0.1;                      // share of a stage that goes with the CUs' crowding
+        return (area == 1 ? 0.063 : (area == 2 ? 0.099 : (area == 4 ? 0.132 : 0.196))) * (1.0 - idle + idle * fill) * straddle;
     });
     const double stream_us = 2.8 + (double)((N + Nb) * (K / 2)) / 6.3e6;
     if (p.us < stream_us) p.us = stream_us;

@@ -95,6 +95,27 @@ def test_shared_launch_counts_the_tiles_of_both_matrices(b, M, N_a, N_b, K, prep
     assert not 256 < workgroups < 300, (tile, workgroups)
 
 
+# tokens, channels out, channels in, with planes; measured us of the other kernel and of the best small tile
+@pytest.mark.parametrize("M,N,K,planes,other_us,small_us", [
+    (892, 1216, 256, False, 3.9, 5.4), (315, 3488, 128, False, 3.6, 4.9), (64, 23296, 384, False, 5.0, 6.3),           # short rows
+    (167, 7296, 512, False, 5.0, 6.0), (395, 10336, 5248, False, 32.7, 41.7),                                          # three rounds
+    (26, 2352, 18816, True, 13.0, 16.7), (28, 1472, 18304, True, 12.4, 16.6), (60, 2880, 23168, True, 17.4, 20.2),        # cold weights
+    (64, 4096, 14336, True, 14.6, 9.2), (200, 6144, 4096, False, 13.9, 11.0), (128, 4096, 4096, False, 12.5, 5.9),
+    (24, 14336, 4096, True, 12.8, 7.5), (32, 4096, 4096, False, 8.8, 4.1), (27, 144, 7424, False, 9.4, 5.5)])
+def test_small_tiles_where_they_were_measured_faster(b, M, N, K, planes, other_us, small_us):
+    tile = b.pq_gemm_small_tile(M, N, 0, K, plane_bytes=b.pq_w4a4_gemm_workspace_bytes(M, N, K) if planes else 0)
+    assert (tile > 0) == (small_us < other_us)
+
+
+# two matrices, with planes; measured us of one launch of small tiles and of the better way without it
+@pytest.mark.parametrize("M,N_a,N_b,K,shared_us,apart_us", [(30, 2944, 2944, 17280, 21.2, 30.5), (45, 16832, 16832, 6272, 39.9, 42.2),
+                                                             (32, 1024, 1024, 4096, 6.8, 10.5), (27, 208, 4000, 23168, 24.7, 31.4),
+                                                             (71, 6624, 10752, 384, 12.6, 11.7), (696, 2752, 1856, 256, 13.1, 11.5)])
+def test_shared_launch_where_it_was_measured_faster(b, M, N_a, N_b, K, shared_us, apart_us):
+    planes = max(b.pq_w4a4_gemm_workspace_bytes(M, n, K) for n in (N_a, N_b))
+    assert (b.pq_gemm_small_tile(M, N_a, N_b, K, plane_bytes=planes) > 0) == (shared_us < apart_us)
+
+
 def test_argument_errors_launch_nothing(b):
     L = b.lib()
     p = ctypes.c_void_p(0x1000)          # never dereferenced: each call fails validation first
