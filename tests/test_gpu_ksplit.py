@@ -1,16 +1,16 @@
 """GPU parity of the small-tile products that split K over a workgroup's wavefronts (outputs of few tiles).
 
 Accumulators are exact integers whatever the order of the partial sums, so they equal the oracle's, and the fp16
-outputs equal those of the large-tile kernels bit for bit.  Shapes: every tile size the rule picks, with ragged last
-tiles in both directions, fewer stages than wavefronts (most wavefronts then add zeros), stage counts the wavefronts do
-not share evenly (the prologue and the tails of the two-stage ring), rows that end in the middle of a stage, and the
-longest row.
+outputs equal those of the large-tile kernels bit for bit.  Shapes: every tile size the rule picks (small_tiles.py), among
+them fewer stages than wavefronts (most wavefronts then add zeros), stage counts the wavefronts do not share evenly (the
+prologue and the tails of the two-stage ring), rows that end in the middle of a stage, and the longest row.
 """
 
 import numpy as np
 import pytest
 
 import oracle as O
+import small_tiles as T
 from paper_2410_05265_amd import synth
 from pq_testlib import dev, host, ulp_diff
 
@@ -29,18 +29,9 @@ def operands(M, N, K):
             synth.random_scales(N, seed=N), np.float32(0.2173))
 
 
-# tokens, channels out, channels in; the tile the rule picks (32-row blocks of tokens x of channels)
-SHAPES_F6 = [(1, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (5, 80, 4224), (33, 4112, 128),  # 1 x 1
-             (40, 4240, 2304), (100, 8208, 128),                                                                                # 1 x 2
-             (100, 12304, 256), (500, 4080, 1024),                                                                              # 2 x 2
-             (100, 8208, 1152),                                                                                                 # 2 x 3
-             (190, 6032, 1280), (333, 4096, 1152),                                                                              # 3 x 2
-             (131, 8208, 2304),                                                                                                 # 2 x 4
-             (100, 12304, 2304)]                                                                                                # 4 x 2
-
-
-@pytest.mark.parametrize("M,N,K", SHAPES_F6)
-def test_prepacked_product(pq, M, N, K):
+@pytest.mark.parametrize("tile,M,N,K", T.ONE_PREPACKED)
+def test_prepacked_product(pq, tile, M, N, K):
+    assert pq.pq_gemm_small_tile(M, N, 0, K, prepacked=True) == tile
     xq, wq, sw, sx = operands(M, N, K)
     x6, w6 = pq.pq_repack_f6(dev(xq)), pq.pq_repack_f6(dev(wq))
     acc_ref = O.gemm_i64(O.unpack(xq), O.unpack(wq))
@@ -60,14 +51,6 @@ def test_prepacked_product(pq, M, N, K):
     assert none is None and np.array_equal(host(only), host(acc))
 
 
-# the same for packed nibbles; from 17 tokens on (fewer take a weight-streaming kernel)
-SHAPES_I8 = [(17, 16, 128), (17, 48, 640), (31, 1040, 1152), (33, 304, 2176), (64, 512, 3200), (20, 80, 4224),        # 1 x 1
-             (33, 4112, 128), (40, 4240, 2304),                                                                     # 1 x 2
-             (33, 8208, 384), (100, 4176, 1152),                                                                    # 2 x 2
-             (100, 8208, 384), (190, 6032, 1280),                                                                   # 2 x 3
-             (70, 12304, 384), (333, 4080, 1152)]                                                                   # 3 x 2
-
-
 def forced(pq, variant, fn, *a, **kw):
     prev = pq.pq_set_gemm_variant(variant)
     try:
@@ -76,8 +59,9 @@ def forced(pq, variant, fn, *a, **kw):
         pq.pq_set_gemm_variant(prev)
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES_I8)
-def test_packed_product_with_every_epilogue(pq, M, N, K):
+@pytest.mark.parametrize("tile,M,N,K", T.ONE_PACKED)
+def test_packed_product_with_every_epilogue(pq, tile, M, N, K):
+    assert pq.pq_gemm_small_tile(M, N, 0, K) == tile
     xq, wq, sw, sx = operands(M, N, K)
     x, w, s = dev(xq), dev(wq), dev(sw)
     acc_ref = O.gemm_i64(O.unpack(xq), O.unpack(wq))

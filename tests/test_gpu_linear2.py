@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+import small_tiles as T
 from paper_2410_05265_amd import synth
 from pq_testlib import check_end_to_end, dev, host
 
@@ -74,8 +75,9 @@ def test_two_matrices_prepacked(pq, M, K, Na, Nb, h):
 
 
 # equal heights: one launch for both (256-wide tiles in one and in several rounds, 384, 512, the mix of 512 and 384, a last
-# tile that is ragged in both directions), the small tiles among them
-@pytest.mark.parametrize("M,K,N", [(1030, 256, 4096), (2048, 128, 8208), (2048, 128, 6144), (4000, 256, 2064), (2000, 128, 14336), (40, 640, 272), (300, 384, 1040)])
+# tile that is ragged in both directions), every small tile among them
+@pytest.mark.parametrize("M,K,N", [(1030, 256, 4096), (2048, 128, 8208), (2048, 128, 6144), (4000, 256, 2064), (2000, 128, 14336), (40, 640, 272), (300, 384, 1040)] +
+                         [(M, K, N) for _, M, N, K in T.TWO_PREPACKED])
 def test_two_matrices_of_one_height_prepacked(pq, M, K, N):
     x = dev(synth.activations(M, K, seed=M + K))
     ws = [dev(synth.random_packed(N, K, seed=N + i, stream=7)) for i in (0, 1)]
@@ -95,6 +97,24 @@ def test_two_matrices_of_one_height_prepacked(pq, M, K, N):
             pq.pq_set_gemm_f6_tile(prev)
         assert np.array_equal(host(fa).view(np.uint16), host(a).view(np.uint16))
         assert np.array_equal(host(fb).view(np.uint16), host(b).view(np.uint16))
+
+
+@pytest.mark.parametrize("tile,M,Na,Nb,K", T.TWO_PACKED)
+def test_two_packed_products_of_every_small_tile(pq, tile, M, Na, Nb, K):
+    """One launch of small tiles against the tiled kernel's products of the same codes, bit for bit."""
+    assert pq.pq_gemm_small_tile(M, Na, Nb, K) == tile
+    x = dev(synth.activations(M, K, seed=M + K))
+    ws = [dev(synth.random_packed(N, K, seed=N + i, stream=7)) for i, N in enumerate((Na, Nb))]
+    steps = [dev(synth.random_scales(N, seed=N + i)) for i, N in enumerate((Na, Nb))]
+    a, b, _ = pq.pq_linear2(x, ws[0], steps[0], ws[1], steps[1], 0.21, 1)
+    xq = pq.pq_rotate_quant(x, 1, 0.21)
+    prev = pq.pq_set_gemm_variant(2)
+    try:
+        for got, w, s in ((a, ws[0], steps[0]), (b, ws[1], steps[1])):
+            want, _ = pq.pq_w4a4_gemm(xq, w, s, 0.21)
+            assert np.array_equal(host(got).view(np.uint16), host(want).view(np.uint16))
+    finally:
+        pq.pq_set_gemm_variant(prev)
 
 
 def test_argument_errors(pq):
