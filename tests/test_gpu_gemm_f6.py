@@ -236,7 +236,7 @@ def test_rotation_of_4096_point_blocks_on_the_matrix_pipe(pq, M, K, h):
     """4096-point blocks: 128-point products on the matrix pipe, the outer stages between lanes (2048-point blocks stay with
     the butterflies).  Against the oracle's fp64 rotation, codes differ only at rounding ties; the tiles of the prepacked
     layer are the same codes, rows past the end zero.  Token counts that are no multiple of 4 or 32, one to three blocks
-    per row; the last rows are one-hot and constant (their rotations are known in closed form, exact in fp32)."""
+    per row; the last rows are one-hot and constant (known in closed form: test_gpu_rotate4096.py)."""
     x = synth.activations(M, K, seed=3 * M + K)
     x[-1] = 0
     x[-1, K - h + 77] = np.float16(3.0)                       # +-3 / sqrt(h) in the last block

@@ -75,3 +75,31 @@ def test_zero_point_eight_is_the_symmetric_quantizer(pq, M, K, h):
     codes = host(pq.pq_rotate_quant(dev(x), h, float(sx)))
     assert (O.unpack(codes) != butterfly_codes(x, sx, h)).any()
     assert np.array_equal(host(pq.pq_rotate_quant_zp(dev(x), h, float(sx), 8)), codes)
+
+
+def test_one_hot_and_constant_rows(pq):
+    """Rows whose rotation is known in closed form.  A one-hot row of 3 becomes +-3 / 64 in its block, the signs a row of the
+    Hadamard matrix: codes +-7 there and 0 in the other blocks.  A constant row of 0.25 becomes 16 in the first channel of
+    every block."""
+    K, w = 3 * H, synth.random_packed(16, 3 * H, seed=1, stream=7)
+    at = [1 << b for b in range(12)] + [(77 * r + 13) % H for r in range(58)]          # every bit alone, then mixtures
+    x = np.zeros((len(at), K), dtype=np.float16)
+    want = np.zeros((len(at), K), dtype=np.int8)
+    j = np.arange(H)
+    for r, i in enumerate(at):
+        block = r % 3
+        x[r, block * H + i] = np.float16(3.0)
+        parity = np.array([bin(i & c).count("1") & 1 for c in j])
+        want[r, block * H:(block + 1) * H] = 7 - 14 * parity
+    sx = 3.0 / 64 / 7
+    assert np.array_equal(O.unpack(host(pq.pq_rotate_quant(dev(x), H, sx))), want)
+    dw, s = dev(w), dev(synth.random_scales(16))
+    _, ws = pq.pq_linear_f6(dev(x), pq.pq_repack_f6(dw), s, sx, H)
+    codes = host(ws)[(pq.pq_f6_tiles_bytes(len(at), K) + 255) // 256 * 256:][:len(at) * K // 2].reshape(len(at), K // 2)
+    assert np.array_equal(O.unpack(codes), want)
+    for r in (0, 1, 11, 12, 69):                                                       # the fused launch of one token
+        _, ws = pq.pq_linear(dev(x[r:r + 1]), dw, s, sx, H)
+        assert np.array_equal(O.unpack(host(ws)[:K // 2].reshape(1, K // 2)), want[r:r + 1])
+    const = np.full((5, K), 0.25, dtype=np.float16)
+    got = O.unpack(host(pq.pq_rotate_quant(dev(const), H, 16.0 / 7)))
+    assert (got[:, ::H] == 7).all() and np.count_nonzero(got) == 5 * 3
