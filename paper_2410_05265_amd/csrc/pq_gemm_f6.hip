@@ -339,7 +339,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
     });
 }
 
-// Rotation blocks of 4096 channels (rq::rotate4096_quarter): one launch that writes tiles, nibbles, or both.  With butterflies
+// Rotation blocks of 4096 channels (rq::rotate4096_quarter): one launch that writes nibbles, or nibbles and tiles.  With butterflies
 // alone and a repack behind them the rotation of a prepacked layer was two launches, bound by vector instructions and by
 // launch latency (1111 x 4096: 9.8 + 5.5 -> 10.1 us).
 //
@@ -383,8 +383,8 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __
     const v2i two = {(int)q[0], (int)q[1]};
     *(__attribute__((address_space(3))) v2i*)(codes_all + tok * (32 * kCodePitch) + (lane & 31) * kCodePitch + n * 16 + (lane >> 5) * 8) = two;
     __syncthreads();
-    // ---- out: 512 register images (four tokens side by side) by the first half of the workgroup, 512 pieces of 16 bytes of
-    // nibbles by the other half (by all in turn if only one of the two is wanted, which leaves the rest idle)
+    // ---- out: 512 register images (four tokens side by side) by the first half of the workgroup (idle where nibbles alone
+    // are wanted), 512 pieces of 16 bytes of nibbles by the other half
     const int half = tid >> 9, id = tid & 511;
     if (tiles && half == 0) {
         const int t = id & 3, part = id >> 2, b = part >> 2, st = (part >> 1) & 1, gg = part & 1;
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __
         image_of_nibbles(p, w);
         store_image<STREAM>(tiles + ((int64_t)(kt0 + b) * RB + (row >> 5)) * kChunkF6, (int)(row & 31) + 32 * gg, st, w);
     }
-    if (nibbles && half == 1) {
+    if (half == 1) {
         const int t = id >> 7, piece = id & 127, b = piece >> 2;
         if (row0 + t < M) {
             const v4i p = *(__attribute__((address_space(3))) const v4i*)(codes_all + t * (32 * kCodePitch) + b * kCodePitch + (piece & 3) * 16);
@@ -405,30 +405,8 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __
     }
 }
 
-__device__ __forceinline__ int xcd_run(int b, int total)   // each XCD takes a contiguous run of tiles
-{
-    const int x = b & 7, idx = b >> 3, q = total >> 3, rem = total & 7;
-    return x * q + (x < rem ? x : rem) + idx;
-}
-
 #define PQ6_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define PQ6_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
-
-// 16 bytes per lane from global memory straight into LDS (lane l lands at lds_addr + 16 l); base and
-// lds_addr are wavefront-uniform.  Issued as inline assembly on purpose: the compiler's bookkeeping of
-// outstanding loads treats a direct load to LDS as a memory operation of unknown kind and from then on
-// waits for *all* outstanding loads at the next register it needs, which would empty the ring of weight
-// loads every time.  Unknown to the compiler, these loads only make its waits for the weight registers
-// stricter than needed (more loads are in flight than it counts, and vmcnt waits for the oldest first);
-// the waits for the LDS data itself are placed by hand and count every load.
-__device__ __forceinline__ void lds_dma16(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_offset), "s"(base), "s"(lds_addr)
-                 : "memory");     // (m0 is written here and used by nothing else in these kernels: the compiler keeps
-                                  // no value in it and sets it itself right in front of the instructions that read it)
-}
 
 constexpr int kTokBlocks = 4;                       // 128 tokens per workgroup tile
 constexpr int kStageA = kTokBlocks * kChunkF6;      // their images for 128 channels: 12 KiB of LDS
@@ -894,8 +872,7 @@ int launch_rotate128_mfma(const void* x, int64_t R, int64_t K, float act_scale, 
 
 // 4096-point blocks.  The fused launch of few tokens (k_decode) forms the same sums, so every call on the same input sees
 // the same codes.  (The same kernel with fewer outer stages is level with the butterflies at 2048 points and behind at
-// 1024: 0.92-1.09 x.)
-// out (tiles) or nibbles may be NULL, not both.
+// 1024: 0.92-1.09 x.)  tiles may be NULL: nibbles alone.
 bool rotate4096_mfma_supported(int64_t K, int32_t h) { return h == 4096 && (K % 4096) == 0 && K <= (1 << 24); }
 
 int launch_rotate4096_mfma(const void* x, int64_t R, int64_t K, float act_scale, void* tiles, void* nibbles, hipStream_t st)

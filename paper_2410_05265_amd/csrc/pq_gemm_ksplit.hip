@@ -6,8 +6,10 @@
 // of 4 or 8 wavefronts owns one small tile of the output (32 to 128 tokens x 32 to 128 channels, chosen so that
 // the tiles go round the CUs once), every wavefront multiplies its own run of K for the whole tile, and the
 // partial tiles are added through LDS at the end: no planes in memory, no second launch, no barrier in the main
-// loop.  What bounds it is the rate at which a CU takes its operands in, (tokens + channels) x K codes per tile at
-// 80-100 KB/us, so the rule that picks the tile minimises that sum over the rounds.
+// loop.  What bounds the prepacked form is the rate at which a CU takes its operands in, (tokens + channels) x K codes per tile
+// at 85 KB/us; in the packed form the transfers through LDS, the expansion of the nibbles and the matrix instructions of a
+// SIMD follow one another (200 x 6144 x 4096: 328 KB of operands per CU in about 9 us).  The rule that picks the tile
+// minimises the estimated sum over the rounds.
 #include <hip/hip_fp16.h>
 
 #include <type_traits>
@@ -24,13 +26,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) uint8_t* lds_u8;
 
 constexpr int kMaxLds = 160 * 1024;
-
-// Each XCD takes a contiguous run of tiles, row tiles fastest: the tiles that share weights meet in one L2.
-__device__ __forceinline__ int xcd_run(int b, int total)
-{
-    const int x = b & 7, idx = b >> 3, q = total >> 3, rem = total & 7;
-    return x * q + (x < rem ? x : rem) + idx;
-}
 
 // What the epilogue multiplies by and adds: one static step or the tokens' own (srow), and the zero-point's
 // per-channel integers (zcorr), as in the tiled kernel.
@@ -51,7 +46,7 @@ struct Second {
     int N, first;
 };
 
-// This workgroup's tile within its matrix; w, ep and N become those of the second matrix where the tile is in that one.
+// This workgroup's tile within its matrix (row tiles fastest: the tiles that share weights meet in one L2); w, ep and N become those of the second matrix where the tile is in that one.
 template <bool TWO>
 __device__ __forceinline__ int own_tile(const Second& two, const uint8_t* __restrict__& w, Epilogue& ep, int& N)
 {
@@ -71,15 +66,13 @@ __device__ __forceinline__ int own_tile(const Second& two, const uint8_t* __rest
     return xcd_run(b, total);
 }
 
-// LDS bytes of the partial tiles: one copy per wavefront where that fits, else one per pair of wavefronts.
+// LDS bytes of the partial tiles, one copy per wavefront.
 template <int TI, int CJ, int W>
 struct Partial {
     static constexpr int kPitch = 128 * CJ + 16;              // a token's 32 CJ sums, padded (bank spread)
     static constexpr int kCopy = 32 * TI * kPitch;
     static constexpr int kSteps = 32 * CJ * 8 + 32 * TI * 4;  // channel steps, zero-point integers, token steps
-    static constexpr bool kPairs = W * kCopy + kSteps > kMaxLds;
-    static constexpr int kCopies = kPairs ? W / 2 : W;
-    static constexpr int kBytes = kCopies * kCopy;
+    static constexpr int kBytes = W * kCopy;
     static_assert(kBytes + kSteps <= kMaxLds, "partial tiles do not fit LDS");
 };
 
@@ -94,36 +87,14 @@ __device__ __forceinline__ void reduce_and_store(ACC (&acc)[CJ][TI], uint8_t* sm
     typedef __attribute__((address_space(3))) V4* lds4;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    auto at = [&](int copy, int i, int j, int q) {
-        return (lds4)(lds_u8)(smem + copy * P::kCopy + (32 * i + r) * P::kPitch + (32 * j + 8 * q + 4 * g) * 4);
-    };
-    auto put = [&](int copy) {
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < CJ; ++j)
+        for (int j = 0; j < CJ; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *at(copy, i, j, q) = (V4){acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
-    };
-    if constexpr (P::kPairs) {
-        if (wave >= W / 2) put(wave - W / 2);
-        __syncthreads();
-        if (wave < W / 2) {
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int j = 0; j < CJ; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const V4 t = *at(wave, i, j, q);
-                        *at(wave, i, j, q) = (V4){acc[j][i][4 * q] + t.x, acc[j][i][4 * q + 1] + t.y, acc[j][i][4 * q + 2] + t.z,
-                                                  acc[j][i][4 * q + 3] + t.w};
-                    }
-        }
-    } else {
-        put(wave);
-    }
+            for (int q = 0; q < 4; ++q)
+                *(lds4)(lds_u8)(smem + wave * P::kCopy + (32 * i + r) * P::kPitch + (32 * j + 8 * q + 4 * g) * 4) =
+                    (V4){acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
     __syncthreads();
     const float* steps = reinterpret_cast<const float*>(smem + steps_at);
     constexpr int UPR = 8 * CJ, ITEMS = 32 * TI * UPR;        // four channels of a token per item
@@ -134,7 +105,7 @@ __device__ __forceinline__ void reduce_and_store(ACC (&acc)[CJ][TI], uint8_t* sm
         const int row = it / UPR, u = it % UPR, m = m0 + row, n = n0 + 4 * u;
         V4 s = *(lds4)(lds_u8)(smem + row * P::kPitch + u * 16);
 #pragma unroll
-        for (int c = 1; c < P::kCopies; ++c) s += *(lds4)(lds_u8)(smem + c * P::kCopy + row * P::kPitch + u * 16);
+        for (int c = 1; c < W; ++c) s += *(lds4)(lds_u8)(smem + c * P::kCopy + row * P::kPitch + u * 16);
         if (m >= M || n >= N) continue;
         const int64_t o = (int64_t)m * N + n;
         if (ep.acc_out) {
@@ -142,10 +113,9 @@ __device__ __forceinline__ void reduce_and_store(ACC (&acc)[CJ][TI], uint8_t* sm
             *reinterpret_cast<v4i*>(ep.acc_out + o) = a;
         }
         if (ep.out) {
-            // the tiled kernels' two roundings: fp32(2^SHIFT' acc) * (sw * (step / 2^SHIFT')) with SHIFT' = 8 for 4-bit
-            // codes, 4 for 8-bit ones; the fp32 sums of the 6-bit instruction carry no factor, theirs goes to the step
-            constexpr int kFold = SHIFT == 0 ? 8 : SHIFT;
-            const float f = (ep.srow ? steps[64 * CJ + row] : ep.sx) * (1.0f / (float)(1 << kFold));
+            // the tiled kernel's two roundings: fp32(256 acc) * (sw * (step / 256)); the fp32 sums of the 6-bit instruction carry
+            // no factor, theirs goes to the step
+            const float f = (ep.srow ? steps[64 * CJ + row] : ep.sx) * (1.0f / 256.0f);
             const v4f c = *reinterpret_cast<const v4f*>(steps + 4 * u);
             float c0 = mul_rn(c.x, f), c1 = mul_rn(c.y, f), c2 = mul_rn(c.z, f), c3 = mul_rn(c.w, f);
             if constexpr (SHIFT == 0) { c0 *= 256.0f; c1 *= 256.0f; c2 *= 256.0f; c3 *= 256.0f; }
@@ -310,14 +280,6 @@ __global__ __launch_bounds__(64 * W) void k_gemm_f6_ksplit(const uint8_t* __rest
 // per row and stage (a whole cache line, eight lanes each), in a ring of NS stages that belongs to the wavefront alone (no
 // barrier); read back in the instruction's layout and expanded as in the tiled kernel.  Stages of 64 bytes a row, half
 // lines, measured 8-22 % slower at every size (64 x 4096 x 14336: 11.9 against 9.3 us, 333 x 4096 x 4096: 11.7 against 10.7).
-__device__ __forceinline__ void dma16(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
-{
-    // 16 bytes per lane from memory to LDS (lane l lands at lds_addr + 16 l); base and lds_addr are wavefront-uniform.
-    // Inline assembly so that the compiler places no waits of its own for it; the waits are counted by hand.
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_offset), "s"(base), "s"(lds_addr) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
 template <int TI, int CJ, int W, int NS, bool TWO>
 __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, Epilogue ep,
                                                           int M, int N, int K, int GM, Second two)
@@ -357,11 +319,11 @@ __global__ __launch_bounds__(64 * W) void k_gemm_i8_ksplit(const uint8_t* __rest
         if (s < whole) {
 #pragma unroll
             for (int p = 0; p < PIECES; ++p)
-                dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p], ring + slot * kStage + p * 1024);
+                lds_dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p], ring + slot * kStage + p * 1024);
         } else {
 #pragma unroll
             for (int p = 0; p < PIECES; ++p)
-                dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p] - back[p & 1], ring + slot * kStage + p * 1024);
+                lds_dma16((p < 4 * CJ ? wk : xk) + (size_t)s * 128, off[p] - back[p & 1], ring + slot * kStage + p * 1024);
         }
     };
     const int swr = (r >> 1) & 7;

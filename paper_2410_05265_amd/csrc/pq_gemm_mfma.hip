@@ -113,8 +113,6 @@ __device__ __forceinline__ void static_for(F&& f)
 #define PQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define PQ_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
 
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
 // One output tile [m0, m0 + BM) x [n0, n0 + BN) by the whole workgroup (the LDS ring is the
 // workgroup's dynamic shared memory).
 // SPLIT: the tile covers only the ring stages [kt0, kt0 + nk_part) of the K dimension and leaves

@@ -162,4 +162,30 @@ __device__ __forceinline__ void unpack16(const v4i p, v4i& even, v4i& odd)
     odd.x = p.x & m; odd.y = p.y & m; odd.z = p.z & m; odd.w = p.w & m;
 }
 
+// Each XCD takes a contiguous run of `total` tiles (workgroup b runs on XCD b % 8).
+__device__ __forceinline__ int xcd_run(int b, int total)
+{
+    const int x = b & 7, idx = b >> 3, q = total >> 3, rem = total & 7;
+    return x * q + (x < rem ? x : rem) + idx;
+}
+
+// 16 bytes per lane from global memory straight into LDS (lane l lands at lds_addr + 16 l); base and
+// lds_addr are wavefront-uniform.  Issued as inline assembly on purpose: the compiler's bookkeeping of
+// outstanding loads treats a direct load to LDS as a memory operation of unknown kind and from then on
+// waits for *all* outstanding loads at the next register it needs, which would empty the ring of weight
+// loads every time.  Unknown to the compiler, these loads only make its waits for the weight registers
+// stricter than needed (more loads are in flight than it counts, and vmcnt waits for the oldest first);
+// the waits for the LDS data itself are placed by hand and count every load.
+__device__ __forceinline__ void lds_dma16(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_offset), "s"(base), "s"(lds_addr)
+                 : "memory");     // (m0 is written here and used by nothing else in these kernels: the compiler keeps
+                                  // no value in it and sets it itself right in front of the instructions that read it)
+}
+
+// Until at most N memory operations of this wavefront are outstanding; they retire in order.
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
 }  // namespace pq
