@@ -241,7 +241,9 @@ int pq_rotate_quant_f6(const void* x_f16, int64_t M, int64_t K, int32_t had_bloc
  * pq_linear): pq_rotate_quant_f6, then pq_w4a4_gemm_f6, on one stream: two launches.  Rotation blocks
  * of 4096 channels take two launches as well (the quantizer writes tiles and nibbles together), other blocks
  * beyond 512 channels pq_rotate_quant, pq_repack_f6 and pq_w4a4_gemm_f6: three.  The codes behind
- * the tiles are those of pq_rotate_quant bit for bit, the outputs those of pq_linear.
+ * the tiles are those of pq_rotate_quant bit for bit, the outputs those of pq_linear (one exception: where pq_linear
+ * takes its fused launch, few tokens, rotation blocks of 128 channels are summed in another order there, and a code at a
+ * rounding tie can differ from pq_rotate_quant's).
  * workspace: device memory, 256-byte aligned, pq_linear_f6_workspace_bytes(M,K,had_block) bytes; on
  * return it holds the activations' tiles (pq_f6_tiles_bytes(M,K)), and behind them, rounded up to 256,
  * the canonical packed codes [M,K/2] if had_block > 512.  K % 128 == 0; limits as pq_repack_f6 and
@@ -254,7 +256,7 @@ int pq_linear_f6(const void* x_f16, const void* w_tiles, const float* w_scale,
 
 /* pq_linear2 on the prepacked path: two weight matrices as f6 tiles on the same tokens (gate_proj and up_proj),
  * X rotated, quantized and written as tiles once, two products (in one launch where N_a = N_b).  Outputs equal those of two pq_linear_f6 calls
- * (and of pq_linear2 on the canonical weights) bit for bit.  Arguments as for pq_linear_f6; workspace of
+ * (and, with pq_linear_f6's exception, of pq_linear2 on the canonical weights) bit for bit.  Arguments as for pq_linear_f6; workspace of
  * pq_linear_f6_workspace_bytes(M, K, had_block). */
 int pq_linear2_f6(const void* x_f16, const void* w_tiles_a, const float* w_scale_a, int64_t N_a, void* out_a_f16,
                   const void* w_tiles_b, const float* w_scale_b, int64_t N_b, void* out_b_f16, float act_scale,

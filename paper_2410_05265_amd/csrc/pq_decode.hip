@@ -201,7 +201,8 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
     if constexpr (MODE == 2) {
         // four wavefronts per block of 4096 channels, four blocks at a time (rows are contiguous: block u of all rows has
         // its codes at 2048 u).  Fused call with cold weights, butterflies by four of the wavefronts -> this: 1 x 4096 -> 4096
-        // 7.9 -> 4.8 us, 2 x 4096 -> 4096 12.3 -> 5.6, 1 x 16384 -> 4096 24.6 -> 10.8.
+        // 7.9 -> 4.8 us, 2 x 4096 -> 4096 12.3 -> 5.6, 1 x 16384 -> 4096 24.6 -> 10.8.  (Blocks of 128 in the same form are
+        // slower than their butterflies in registers: 1 x 14336 -> 4096 7.9 -> 13.1 us.)
         const int n = wave & 3, units = (M * K) >> 12;
         for (int u = wave >> 2; u < units; u += 4) {
             uint32_t q[2];
