@@ -103,7 +103,8 @@ double replaceable_cost_us(int kernel, int64_t M, int64_t N, int64_t K, size_t p
 // 2048 -> 20480 10.8 against 12.1, 14336 -> 4096 product 9.6 against 10.9; 4096 -> 11008 alone 11.0 against 10.4).
 bool take_ksplit(int kernel, int64_t M, int64_t N, int64_t K, size_t plane_bytes)
 {
-    return pq::gemm_ksplit_i8_cost_us(M, N, 0, K) < 0.97 * replaceable_cost_us(kernel, M, N, K, plane_bytes);
+    const double other = replaceable_cost_us(kernel, M, N, K, plane_bytes);
+    return other > 0.0 && pq::gemm_ksplit_i8_cost_us(M, N, 0, K) < 0.97 * other;      // (no plan is made for nothing)
 }
 
 // Both products of pq_linear2 on that kernel, in one launch, where its estimate is below that of each product on its better
@@ -118,8 +119,8 @@ bool share_ksplit(int64_t M, int64_t N_a, int64_t N_b, int64_t K, size_t plane_b
     double alone = 0.0;
     for (const int64_t N : {N_a, N_b}) {
         const double other = replaceable_cost_us(pick_with_planes(M, N, K, plane_bytes), M, N, K, plane_bytes);
-        const double small = pq::gemm_ksplit_i8_cost_us(M, N, 0, K);
         if (other <= 0.0) return false;
+        const double small = pq::gemm_ksplit_i8_cost_us(M, N, 0, K);
         alone += small < 0.97 * other ? 1.05 * small : 0.97 * other;
     }
     return pq::gemm_ksplit_i8_cost_us(M, N_a, N_b, K) < alone;
