@@ -343,22 +343,36 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
 // alone and a repack behind them the rotation of a prepacked layer was two launches, bound by vector instructions and by
 // launch latency (1111 x 4096: 9.8 + 5.5 -> 10.1 us).
 //
-// A workgroup of 16 wavefronts takes four tokens, four wavefronts each: wavefront n of a token computes the output
-// channels 32 n .. 32 n + 31 of every block (8 matrix instructions), so that a handful of tokens still keeps a CU busy.
+// A workgroup takes up to TOK tokens, four wavefronts each: wavefront n of a token computes the output channels 32 n ..
+// 32 n + 31 of every block (8 matrix instructions), so that a handful of tokens still keeps a CU busy.  What bounds it are the
+// vector instructions (640 a wavefront, half of them the outer stages), so what counts are the tokens of the busiest CU.
+// TOK = 1 (nibbles alone): at most one more than the average.  TOK = 4 (tiles): the first `fours` workgroups take four
+// tokens, the others one (their wavefronts 4 .. 15 end at once); see the launcher.
 // The codes meet in LDS (8 bytes per lane: lane (block b, half g) holds channels 32 n + 16 g ..), and one thread per register
 // image or per 16 bytes of nibbles writes them out; four tokens side by side make 64-byte runs of a tile's planes.
 constexpr int kCodePitch = 80;     // LDS bytes per 128-channel block of codes: 64 + 16 (bank spread, 16-byte aligned)
 
-template <bool STREAM>
-__global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __restrict__ x, int64_t row_base, int64_t M, int K,
-                                                                  rq::StaticStep steps, uint8_t* __restrict__ tiles,
+template <int TOK, bool STREAM>
+__global__ __launch_bounds__(256 * TOK) void k_rotate4096_quant_mfma(const __half* __restrict__ x, int64_t row_base, int64_t M, int K,
+                                                                  int fours, rq::StaticStep steps, uint8_t* __restrict__ tiles,
                                                                   uint8_t* __restrict__ nibbles)
 {
-    __shared__ __align__(16) uint8_t stage_all[4 * 32 * kXPitch];
-    __shared__ __align__(16) uint8_t codes_all[4 * 32 * kCodePitch];
+    __shared__ __align__(16) uint8_t stage_all[TOK * 32 * kXPitch];
+    __shared__ __align__(16) uint8_t codes_all[TOK * 32 * kCodePitch];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tok = wave >> 2, n = wave & 3;
-    const int64_t row0 = row_base + (int64_t)blockIdx.y * 4;
+    int group = blockIdx.y, tokens = TOK;
+    int64_t row0 = row_base + (int64_t)group * TOK;
+    if constexpr (TOK == 4) {
+        if (group >= fours) {
+            // single tokens: each XCD (workgroup i runs on XCD i % 8) takes a run of them, so that its L2 joins their 16-byte runs
+            const int singles = (int)gridDim.y - fours;       // a multiple of 8: whole row blocks
+            group -= fours;
+            tokens = 1;
+            row0 = row_base + (int64_t)fours * 4 + (group & 7) * (singles >> 3) + (group >> 3);
+            if (tok) return;
+        }
+    }
     const int kt0 = blockIdx.x * 32;                         // first 128-channel block of this rotation block
     uint8_t* stg = stage_all + tok * (32 * kXPitch);
     // ---- the token's 4096 channels into LDS, one row of 128 channels per block: this wavefront's quarter
@@ -383,11 +397,11 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_mfma(const __half* __
     const v2i two = {(int)q[0], (int)q[1]};
     *(__attribute__((address_space(3))) v2i*)(codes_all + tok * (32 * kCodePitch) + (lane & 31) * kCodePitch + n * 16 + (lane >> 5) * 8) = two;
     __syncthreads();
-    // ---- out: 512 register images (four tokens side by side) by the first half of the workgroup (idle where nibbles alone
-    // are wanted), 512 pieces of 16 bytes of nibbles by the other half
-    const int half = tid >> 9, id = tid & 511;
+    // ---- out: 128 register images a token (the tokens side by side) by the first half of the workgroup (idle where nibbles
+    // alone are wanted), 128 pieces of 16 bytes of nibbles a token by the other half
+    const int half = tid >= 128 * tokens, id = tid - half * (128 * tokens);
     if (tiles && half == 0) {
-        const int t = id & 3, part = id >> 2, b = part >> 2, st = (part >> 1) & 1, gg = part & 1;
+        const int t = tokens == 1 ? 0 : id % TOK, part = tokens == 1 ? id : id / TOK, b = part >> 2, st = (part >> 1) & 1, gg = part & 1;
         const v4i p = *(__attribute__((address_space(3))) const v4i*)(codes_all + t * (32 * kCodePitch) + b * kCodePitch + st * 32 + gg * 16);
         const int64_t row = row0 + t, RB = (M + 31) >> 5;    // (row < 32 RB: the grid covers whole row blocks)
         uint64_t w[3];
@@ -881,11 +895,21 @@ int launch_rotate4096_mfma(const void* x, int64_t R, int64_t K, float act_scale,
     const bool stream = (tiles ? (int64_t)f6_tiles_bytes(R, K) : R * (K / 2)) <= rq::kStreamBelow;   // (the larger output)
     uint8_t *tp = static_cast<uint8_t*>(tiles), *np = static_cast<uint8_t*>(nibbles);
     const int64_t rows = tiles ? (R + 31) / 32 * 32 : R;             // a tile's rows past the end are zero codes
-    for (int64_t r0 = 0; r0 < rows; r0 += 131072) {                  // grid.y is limited to 65535 per launch
-        const int64_t mm = rows - r0 < 131072 ? rows - r0 : 131072;
-        const dim3 grid((unsigned)(K / 4096), (unsigned)((mm + 3) / 4));
-        if (stream) hipLaunchKernelGGL((k_rotate4096_quant_mfma<true>), grid, dim3(1024), 0, st, static_cast<const __half*>(x), r0, R, (int)K, steps, tp, np);
-        else hipLaunchKernelGGL((k_rotate4096_quant_mfma<false>), grid, dim3(1024), 0, st, static_cast<const __half*>(x), r0, R, (int)K, steps, tp, np);
+    // Tiles: a single token stores runs of 16 bytes, which costs more than an even share gains where many do (8192 rows, all
+    // single: 43 -> 77 us), so only few rows are taken singly: all of up to 512 (256 rows 11.9 -> 8.3 us with a product of 16
+    // channels behind it, 512 12.4 -> 9.2; 777 would be 12.8 -> 14.2), and up to 256 behind the last 1024, which are four for
+    // every CU (1111 rows 15.5 -> 14.6; 476 behind them, 1500 rows, would be 16.0 -> 17.6).  Nibbles alone are stored as whole
+    // rows: always single (1111 rows 8.3 -> 6.1 us, 8192 29 -> 26.6).
+    const int64_t step = tiles ? 131072 : 32768;
+    for (int64_t r0 = 0; r0 < rows; r0 += step) {                    // grid.y is limited to 65535 per launch
+        const int64_t mm = rows - r0 < step ? rows - r0 : step, rest = mm % 1024;
+        const int64_t singles = tiles && rest <= (mm < 1024 ? 512 : 256) ? rest : 0, fours = (mm - singles + 3) / 4;
+        auto launch = [&](auto kern, int64_t groups, int tok) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)(K / 4096), (unsigned)groups), dim3((unsigned)(256 * tok)), 0, st, static_cast<const __half*>(x), r0, R,
+                               (int)K, (int)fours, steps, tp, np);
+        };
+        if (tiles) { if (stream) launch(k_rotate4096_quant_mfma<4, true>, fours + singles, 4); else launch(k_rotate4096_quant_mfma<4, false>, fours + singles, 4); }
+        else { if (stream) launch(k_rotate4096_quant_mfma<1, true>, mm, 1); else launch(k_rotate4096_quant_mfma<1, false>, mm, 1); }
         const int rc = hip_status(hipGetLastError());
         if (rc != PQ_OK) return rc;
     }

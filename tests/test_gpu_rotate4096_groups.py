@@ -1,0 +1,47 @@
+"""The 4096-point rotation where its launches change shape: rows of the prepacked layer in groups of four and singly (all of
+up to 512, up to 256 behind the last 1024), rows of nibbles always singly.
+
+A row's codes may depend on nothing but the row, so a long input repeats a few rows in an order of its own, and every copy
+has to equal the codes of a call of those few rows (which the oracle checks), byte for byte."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2410_05265_amd import synth
+from pq_testlib import dev, host
+from test_gpu_gemm_f6 import tiles_by_definition
+
+pytestmark = pytest.mark.gpu
+H = 4096
+
+
+@pytest.fixture(scope="module")
+def pq():
+    import paper_2410_05265_amd.binding as b
+    b.lib()
+    return b
+
+
+@pytest.mark.parametrize("M,K", [(1, 4096), (31, 8192), (511, 4096), (513, 4096), (544, 8192), (991, 4096), (1023, 4096), (1025, 4096),
+                                 (1279, 4096), (1281, 4096), (2300, 4096)])
+def test_rows_of_every_group_have_their_codes(pq, M, K):
+    few = synth.activations(48, K, seed=K)
+    order = np.random.default_rng(M).integers(0, 48, size=M)
+    y = O.rotate(few, H)
+    sx = np.float32(np.abs(y).max() / 7.0)
+    part = O.unpack(host(pq.pq_rotate_quant(dev(few), H, float(sx)))).astype(np.int32)
+    diff = part - O.quantize(y, sx).astype(np.int32)
+    at = np.nonzero(diff)
+    assert at[0].size <= 1e-3 * diff.size and np.all(np.abs(diff[at]) == 1)      # ties only
+    x = torch.from_numpy(few).cuda()[torch.from_numpy(order).cuda()].contiguous()
+    codes = host(pq.pq_rotate_quant(x, H, float(sx)))
+    assert np.array_equal(O.unpack(codes), part[order])
+    ws = torch.full((pq.pq_linear_f6_workspace_bytes(M, K, H),), 0x77, dtype=torch.uint8, device="cuda")
+    w6 = pq.pq_repack_f6(dev(synth.random_packed(16, K, seed=1, stream=7)))
+    pq.pq_linear_f6(x, w6, dev(synth.random_scales(16)), float(sx), H, workspace=ws)
+    tiles = pq.pq_f6_tiles_bytes(M, K)
+    assert np.array_equal(host(ws)[:tiles], tiles_by_definition(part[order]))
+    off = (tiles + 255) // 256 * 256
+    assert np.array_equal(host(ws)[off:off + M * K // 2].reshape(M, K // 2), codes)
