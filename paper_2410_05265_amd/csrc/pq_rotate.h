@@ -454,8 +454,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // The output channels 32 n .. 32 n + 31 of all 32 blocks of 128, by one wavefront (n: uniform, 0..3).  stg: LDS, the fp16
 // input, one row of kXPitch bytes per block.  Lane l returns the codes of block l % 32, channels 32 n + 16 (l / 32) + 0..15:
 // two dwords of eight.
-template <typename STEPS>
-__device__ __forceinline__ void rotate4096_quarter(const uint8_t* stg, int n, int lane, const STEPS& steps, uint32_t (&codes)[2])
+// (rotate4096_values leaves the sums: lane l ends with block l % 32, channels 32 n + 8 (i / 4) + 4 (l / 32) + i % 4 in v[i])
+__device__ __forceinline__ void rotate4096_values(const uint8_t* stg, int n, int lane, float (&v)[16])
 {
     // The H operand needs no memory: the sign is the parity of popcount(i & j), j = 32 n + l % 32, i = 16 s + 8 (l / 32) + 0..7
     const int j = lane & 31, g = lane >> 5;
@@ -480,7 +480,6 @@ __device__ __forceinline__ void rotate4096_quarter(const uint8_t* stg, int n, in
         acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, hi4), __builtin_bit_cast(v8h, xi), acc, 0, 0, 0);
     }
     // the outer stages: between blocks, i.e. between lanes
-    float v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = acc[i];
     lane_stage<0>(v, lane);
@@ -488,13 +487,25 @@ __device__ __forceinline__ void rotate4096_quarter(const uint8_t* stg, int n, in
     lane_stage<2>(v, lane);
     lane_stage<3>(v, lane);
     lane_stage<4>(v, lane);
-    // quantize; the half-wavefronts trade so that a lane has 16 consecutive channels
-    const uint32_t w01 = quant_pack8<false>(v, v, steps.mult, steps.step, steps.zero_offset());
-    const uint32_t w23 = quant_pack8<false>(v + 8, v + 8, steps.mult, steps.step, steps.zero_offset());
+}
+
+// The codes of those sums; the half-wavefronts trade so that a lane has 16 consecutive channels.
+__device__ __forceinline__ void rotate4096_codes(const float (&v)[16], float mult, float step, int zero_offset, uint32_t (&codes)[2])
+{
+    const uint32_t w01 = quant_pack8<false>(v, v, mult, step, zero_offset);
+    const uint32_t w23 = quant_pack8<false>(v + 8, v + 8, mult, step, zero_offset);
     const auto sw = __builtin_amdgcn_permlane32_swap(w01, w23, false, false);
     const uint32_t mine = sw[0], theirs = sw[1];
     codes[0] = __builtin_amdgcn_perm(theirs, mine, 0x05040100u);
     codes[1] = __builtin_amdgcn_perm(theirs, mine, 0x07060302u);
+}
+
+template <typename STEPS>
+__device__ __forceinline__ void rotate4096_quarter(const uint8_t* stg, int n, int lane, const STEPS& steps, uint32_t (&codes)[2])
+{
+    float v[16];
+    rotate4096_values(stg, n, lane, v);
+    rotate4096_codes(v, steps.mult, steps.step, steps.zero_offset(), codes);
 }
 
 }  // namespace rq

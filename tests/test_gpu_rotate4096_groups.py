@@ -1,5 +1,6 @@
 """The 4096-point rotation where its launches change shape: rows of the prepacked layer in groups of four and singly (all of
-up to 512, up to 256 behind the last 1024), rows of nibbles always singly.
+up to 512, up to 256 behind the last 1024), rows of nibbles always singly; and the per-token quantizer of one to four
+blocks a row, which rotates the same way.
 
 A row's codes may depend on nothing but the row, so a long input repeats a few rows in an order of its own, and every copy
 has to equal the codes of a call of those few rows (which the oracle checks), byte for byte."""
@@ -45,3 +46,23 @@ def test_rows_of_every_group_have_their_codes(pq, M, K):
     assert np.array_equal(host(ws)[:tiles], tiles_by_definition(part[order]))
     off = (tiles + 255) // 256 * 256
     assert np.array_equal(host(ws)[off:off + M * K // 2].reshape(M, K // 2), codes)
+
+
+@pytest.mark.parametrize("M,K", [(1, 4096), (3, 8192), (5, 12288), (70, 16384), (2, 20480)])
+def test_dynamic_steps_and_codes_of_4096_point_blocks(pq, M, K):
+    """(20480: past the longest row of that kernel, with the butterflies.)  The row maximum is a sum of 4096 terms in fp32:
+    within a few ulps of the oracle's; codes against those of the oracle differ only at ties."""
+    x = synth.activations(M, K, seed=M)
+    if M > 2:
+        x[1] = 0                                                    # step 1, codes 0
+        x[2, :K - H] = 0                                            # the maximum in the last block
+    y = O.rotate(x, H)
+    want_q, want_s = O.quantize_dynamic(y, 0.875, 4)
+    q, s = pq.pq_rotate_quant_dynamic(dev(x), H, 0.875, 4)
+    s, got = host(s), O.unpack(host(q)).astype(np.int32)
+    assert np.all(np.abs(s.view(np.int32).astype(np.int64) - np.asarray(want_s, np.float32).view(np.int32)) <= 8)
+    diff = got - want_q.astype(np.int32)
+    at = np.nonzero(diff)
+    assert at[0].size <= 1e-3 * diff.size and np.all(np.abs(diff[at]) == 1)
+    if M > 2:
+        assert s[1] == 1.0 and not got[1].any() and not got[2, :K - H].any()
