@@ -505,7 +505,7 @@ int launch_dma(const void* xq, const void* wq, const float* sw, float sx, int64_
 // runs of 128-channel stages and leaves an int32 plane of partial sums in the caller's workspace;
 // k_splitk_reduce adds the planes and applies the same epilogue arithmetic as the tiled kernel
 // (integer sums are exact in any order, so accumulators and outputs equal the unsplit ones).
-template <int BM, int BN, int WR, int WC, int NS, int ABITS, int ASHIFT>
+template <int BM, int BN, int WR, int WC, int NS, int ASHIFT>
 __global__ __launch_bounds__(WR * WC * 64) void k_gemm_splitk(const uint8_t* __restrict__ xq,
                                                              const uint8_t* __restrict__ wq, int M, int N, int K,
                                                              int GM, int tiles, int S, int32_t* __restrict__ part)
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(WR * WC * 64) void k_gemm_splitk(const uint8_t* __r
     const int tile = w % tiles, s = w / tiles;
     const int nk = K / 128;
     const int kt0 = (int)((int64_t)nk * s / S), kt1 = (int)((int64_t)nk * (s + 1) / S);
-    gemm_tile<BM, BN, WR, WC, NS, 1, ABITS, ASHIFT, true>(xq, wq, nullptr, 0.0f, M, N, K, (tile % GM) * BM, (tile / GM) * BN,
+    gemm_tile<BM, BN, WR, WC, NS, 1, 4, ASHIFT, true>(xq, wq, nullptr, 0.0f, M, N, K, (tile % GM) * BM, (tile / GM) * BN,
                                                           nullptr, part + (int64_t)s * M * N, nullptr, nullptr, kt0,
                                                           kt1 - kt0);
 }
@@ -563,26 +563,32 @@ struct SplitArgs {   // what the epilogue needs beyond the channel scales
     const int32_t* zcorr;
 };
 
-template <int BM, int ABITS>
+int launch_splitk_reduce(const int32_t* part, int S, const float* sw, SplitArgs ep, int64_t M, int64_t N, int shift, void* out,
+                         int32_t* acc, hipStream_t st)
+{
+    const int64_t plane = M * N;
+    hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((plane / 4 + 255) / 256)), dim3(256), 0, st, part, S, plane, sw,
+                       ep.sx, (int)N, shift, ep.srow, ep.zcorr, static_cast<__half*>(out), acc);
+    return hip_status(hipGetLastError());
+}
+
+template <int BM>
 int launch_splitk(const void* xq, const void* wq, const float* sw, SplitArgs ep, int64_t M, int64_t N, int64_t K, int S,
                   void* out, int32_t* acc, int32_t* part, hipStream_t st)
 {
     // (a ring of 4 or 6 stages measured the same as 3)
-    constexpr int BN = 128, NS = 3, ASHIFT = ABITS == 8 ? 4 : 8;
+    constexpr int BN = 128, NS = 3, ASHIFT = 8;
     const int GM = (int)((M + BM - 1) / BM), GN = (int)((N + BN - 1) / BN);
-    constexpr size_t lds = (size_t)NS * (BM * (ABITS == 8 ? 128 : 64) + BN * 64);
+    constexpr size_t lds = (size_t)NS * (BM + BN) * 64;
     static_assert(lds <= 160 * 1024, "LDS ring too large");
-    auto kern = k_gemm_splitk<BM, BN, 2, 2, NS, ABITS, ASHIFT>;
+    auto kern = k_gemm_splitk<BM, BN, 2, 2, NS, ASHIFT>;
     static std::atomic<uint64_t> lds_ok{0};
     if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_ok) != PQ_OK)
         return PQ_ERR_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(GM * GN * S)), dim3(256), lds, st, static_cast<const uint8_t*>(xq),
                        static_cast<const uint8_t*>(wq), (int)M, (int)N, (int)K, GM, GM * GN, S, part);
     if (hipGetLastError() != hipSuccess) return PQ_ERR_HIP;
-    const int64_t plane = M * N;
-    hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((plane / 4 + 255) / 256)), dim3(256), 0, st, part, S, plane, sw,
-                       ep.sx, (int)N, ASHIFT, ep.srow, ep.zcorr, static_cast<__half*>(out), acc);
-    return hip_status(hipGetLastError());
+    return launch_splitk_reduce(part, S, sw, ep, M, N, ASHIFT, out, acc, st);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -764,7 +770,7 @@ int pick_cfg(int64_t M, int64_t N)
 // Is a launch of n1 column panels of 256 and n2 of 192 (256 n1 + 192 n2 = N) cheaper than the best
 // single width?  Tiles go to the earliest free CU in index order; a tile's cost is its area over the
 // width's efficiency (the same model as pick_cfg).  PQ_GEMM_TILE switches the mixed launch off.
-bool pick_dual(int64_t M, int64_t N, int* n1_out, int* n2_out)
+bool pick_dual(int64_t M, int64_t N, int* n1_out, int* n2_out, double* cost_out = nullptr)
 {
     if (forced_tile() != -1 || (N % 64) != 0 || M < 256) return false;
     const int64_t GM = (M + 255) / 256;
@@ -801,7 +807,7 @@ bool pick_dual(int64_t M, int64_t N, int* n1_out, int* n2_out)
             finish = t_early > t_late ? t_early : t_late;
             if (finish < (ra + 1) * t1) finish = (ra + 1) * t1;
         }
-        if (finish < best) { best = finish; *n1_out = (int)n1; *n2_out = (int)n2; found = true; }
+        if (finish < best) { best = finish; *n1_out = (int)n1; *n2_out = (int)n2; found = true; if (cost_out) *cost_out = finish; }
     }
     return found;
 }
@@ -906,7 +912,6 @@ size_t gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force)
 
 namespace {
 // The split launch if the plan has one for this workspace; -1: the caller runs the unsplit kernel.
-template <int ABITS>
 int try_splitk(const void* xq, const void* wq, const float* sw, SplitArgs ep, int64_t M, int64_t N, int64_t K, void* out,
                int32_t* acc, void* ws, size_t ws_bytes, bool force, hipStream_t st)
 {
@@ -914,9 +919,9 @@ int try_splitk(const void* xq, const void* wq, const float* sw, SplitArgs ep, in
     if (ws) plan_splitk(M, N, K, ws_bytes, force, &bm, &S);
     if (S <= 1) return force ? PQ_ERR_UNSUPPORTED : -1;
     int32_t* part = static_cast<int32_t*>(ws);
-    if (bm == 64) return launch_splitk<64, ABITS>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
-    if (bm == 128) return launch_splitk<128, ABITS>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
-    return launch_splitk<256, ABITS>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
+    if (bm == 64) return launch_splitk<64>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
+    if (bm == 128) return launch_splitk<128>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
+    return launch_splitk<256>(xq, wq, sw, ep, M, N, K, S, out, acc, part, st);
 }
 }  // namespace
 
@@ -925,7 +930,7 @@ int launch_gemm_mfma_ws(const void* xq, const void* wq, const float* sw, float s
 {
     if (M <= (1 << 30) && N <= (1 << 30) && K < kMaxK4 && M * (K / 2) < ((int64_t)1 << 32) &&
         N * (K / 2) < ((int64_t)1 << 32)) {
-        const int rc = try_splitk<4>(xq, wq, sw, SplitArgs{sx, nullptr, nullptr}, M, N, K, out, acc, ws, ws_bytes, force, st);
+        const int rc = try_splitk(xq, wq, sw, SplitArgs{sx, nullptr, nullptr}, M, N, K, out, acc, ws, ws_bytes, force, st);
         if (rc >= 0) return rc;
     } else if (force) {
         return PQ_ERR_UNSUPPORTED;
@@ -935,23 +940,98 @@ int launch_gemm_mfma_ws(const void* xq, const void* wq, const float* sw, float s
 
 // 4-bit weights x 8-bit activations (codes in the even/odd-grouped byte order written by the
 // 8-bit quantizer): the same kernel with the activation operand taken from LDS as it stands.
+namespace {
+// What a product of int8 activations runs on: bm > 0: tiles of bm tokens (pq_gemm_bytes.hip), in S runs of K;
+// bm = 0: tiles of 32 x 32 results, 256 x bn, or with bn = 0 n1 panels of 256 and n2 of 192.
+struct BytesPlan { int bm, S, bn, n1, n2; };
+
+// The choice is the least of these estimates, in microseconds.  A stage of 128 channels of one tile takes `part` where few
+// CUs are busy (the walk over K and its loads bound it) and `full` where all are (power does), in between by the share that is
+// busy in a launch's rounds of 256 tiles.  Fitted to 140 shapes of 33 to 4096 tokens, 1024 to 28672 channels in and out: what it
+// takes is 0.3 % slower on average than the best of all kernels and splits, 9 % at most.  S runs add the planes, written and read
+// at 6.4 TB/s out of the caches, and the second launch.  Heights below 256 with the matrix instruction of 16 x 16 results
+// against the tiles that were there before: 64 x 4096 -> 4096 15.3 -> 11.1 us, 543 x 11776 -> 4160 49.0 -> 37.0, 2203 x 3456 ->
+// 2096 25.6 -> 21.2, with planes 915 x 28416 -> 1744 65.6 -> 52.9.  Outputs that fill the chip with 256-wide tiles keep them:
+// 4096 x 11008 -> 4096 151.7 against 213, 2048 x 14336 -> 4096 114 against 145 (each operand byte read serves twice the
+// products), 245 x 4736 -> 27200 33.5 against 40.6.
+struct BytesTile { int bm; double part_us, full_us; };
+constexpr BytesTile kBytesTiles[] = {{64, 0.25, 0.28}, {96, 0.30, 0.38}, {128, 0.34, 0.49}, {160, 0.40, 0.62}, {192, 0.45, 0.68}};
+constexpr BytesTile kBytesTall = {256, 0.38, 0.88};       // 256 x 128 of 32 x 32 results
+
+int64_t bytes_tiles(const BytesTile& t, int64_t M, int64_t N) { return (M + t.bm - 1) / t.bm * ((N + 127) / 128); }
+double bytes_stages_us(const BytesTile& t, int64_t tiles, int64_t stages)
+{
+    return (double)stages * (t.part_us * (double)((tiles + 255) >> 8) + (t.full_us - t.part_us) * (1.0 / 256.0) * (double)tiles);
+}
+
+BytesPlan plan_bytes(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool force)
+{
+    const int64_t nk = K / 128;
+    const size_t plane_bytes = (size_t)M * N * 4;
+    const bool planes = ws_bytes > 0 && M * N < ((int64_t)1 << 31);
+    BytesPlan p{0, 1, 256, 0, 0};
+    if (force) {   // (as in plan_splitk)
+        int S = planes ? 5 : 1;
+        while (S > 1 && ((int64_t)S * 2 > nk || (size_t)S * plane_bytes > ws_bytes)) --S;
+        p.bm = M > 128 ? 192 : (M > 64 ? 128 : 64);
+        p.S = S;
+        return p;
+    }
+    // 256 wide, in units of a full 256 x 256 tile's area; the busier the chip, the longer a stage (0.76 us + 0.94 at full use)
+    const int64_t GM = (M + 255) / 256;
+    double area = (double)((GM * ((N + 255) / 256) + 255) / 256);
+    const double narrow = (double)((GM * ((N + 191) / 192) + 255) / 256) * 0.75 / kCfgs[3].eff;
+    if (narrow < area) { area = narrow; p.bn = 192; }
+    double dual = 0.0;
+    if (pick_dual(M, N, &p.n1, &p.n2, &dual) && dual / 65536.0 < 0.97 * area) { area = dual / 65536.0; p.bn = 0; }
+    const double use = (double)M * N / (area * 256.0 * 65536.0);
+    double best = 3.8 + (double)nk * area * (0.76 + 0.94 * use) + (double)M * N * 2 / 4.2e6;
+    const double fixed = 3.3 + (double)M * N * 2 / 4.2e6, tall = fixed + bytes_stages_us(kBytesTall, bytes_tiles(kBytesTall, M, N), nk);
+    if (tall < best) { best = tall; p.bn = 128; }
+    for (const BytesTile& t : kBytesTiles) {
+        const int64_t tiles = bytes_tiles(t, M, N);
+        const double whole = fixed + bytes_stages_us(t, tiles, nk);
+        if (whole < best) { best = whole; p.bm = t.bm; p.S = 1; }
+        for (uint32_t S = 2; planes && S <= 32 && S * 2 <= nk && S * plane_bytes <= ws_bytes; ++S) {
+            const double pair = fixed + 3.2 + 0.11 * S + 2.0 * S * (double)plane_bytes / 6.4e6;     // (0.5 of it the margin to win by)
+            if (pair >= best) break;
+            const double us = pair + bytes_stages_us(t, tiles * S, ((uint32_t)nk + S - 1) / S);
+            if (us < best) { best = us; p.bm = t.bm; p.S = (int)S; }
+        }
+    }
+    if (const int tile = forced_tile(); tile >= 0 && p.S == 1) {
+        p.bm = tile == 0 || tile == 1 || tile == 3 ? 0 : (tile == 4 ? 64 : 128);
+        p.bn = tile == 3 ? 192 : (tile == 1 ? 128 : 256);
+    }
+    return p;
+}
+
+int launch_bytes(const void* xq8, const void* wq, const float* sw, SplitArgs ep, int64_t M, int64_t N, int64_t K, void* out, int32_t* acc,
+                 void* ws, size_t ws_bytes, bool force, hipStream_t st)
+{
+    const BytesPlan p = plan_bytes(M, N, K, ws ? ws_bytes : 0, force);
+    if (p.S > 1) {
+        int32_t* part = static_cast<int32_t*>(ws);
+        const int rc = launch_gemm_bytes(xq8, wq, sw, ep.sx, ep.srow, M, N, K, p.bm, p.S, nullptr, part, st);
+        return rc != PQ_OK ? rc : launch_splitk_reduce(part, p.S, sw, ep, M, N, 4, out, acc, st);
+    }
+    if (force) return PQ_ERR_UNSUPPORTED;
+    if (p.bm > 0) return launch_gemm_bytes(xq8, wq, sw, ep.sx, ep.srow, M, N, K, p.bm, 1, out, acc, st);
+    switch (p.bn) {
+        case 0: return launch_dual<256, 256, 192, 2, 2, 3, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, p.n1, p.n2, out, acc, st, ep.srow);
+        case 128: return launch_dma<256, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, out, acc, st, ep.srow);
+        case 192: return launch_dma<256, 192, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, out, acc, st, ep.srow);
+        default: return launch_dma<256, 256, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, out, acc, st, ep.srow);
+    }
+}
+}  // namespace
+
 int launch_gemm_w4a8(const void* xq8, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K,
                      void* out, int32_t* acc, hipStream_t st, void* ws, size_t ws_bytes, bool force)
 {
     if (M > (1 << 30) || N > (1 << 30) || K > 65536 || K % 128 != 0) return PQ_ERR_UNSUPPORTED;
     if (M * K >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return PQ_ERR_UNSUPPORTED;
-    const int rc = try_splitk<8>(xq8, wq, sw, SplitArgs{sx, nullptr, nullptr}, M, N, K, out, acc, ws, ws_bytes, force, st);
-    if (rc >= 0) return rc;
-    int n1 = 0, n2 = 0;
-    if (pick_dual(M, N, &n1, &n2))
-        return launch_dual<256, 256, 192, 2, 2, 3, 8, 4>(xq8, wq, sw, sx, M, N, K, n1, n2, out, acc, st);
-    switch (pick_cfg(M, N)) {
-        case 0: return launch_dma<256, 256, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, sx, M, N, K, out, acc, st);
-        case 1: return launch_dma<256, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, sx, M, N, K, out, acc, st);
-        case 3: return launch_dma<256, 192, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, sx, M, N, K, out, acc, st);
-        case 4: return launch_dma<64, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, sx, M, N, K, out, acc, st);
-        default: return launch_dma<128, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, sx, M, N, K, out, acc, st);
-    }
+    return launch_bytes(xq8, wq, sw, SplitArgs{sx, nullptr, nullptr}, M, N, K, out, acc, ws, ws_bytes, force, st);
 }
 
 // Per-token dynamic quantization (Table 1 row O1): out = acc * row_scale[m] * w_scale[n].  bits = 4
@@ -962,27 +1042,14 @@ int launch_gemm_dynamic(const void* xq, int32_t bits, const void* wq, const floa
 {
     if (M > (1 << 30) || N > (1 << 30) || K > 65536 || K % 128 != 0) return PQ_ERR_UNSUPPORTED;
     if (M * K >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return PQ_ERR_UNSUPPORTED;
-    {
-        const SplitArgs ep{1.0f, srow, nullptr};
-        const int rc = bits == 8 ? try_splitk<8>(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st)
-                                 : try_splitk<4>(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st);
-        if (rc >= 0) return rc;
-    }
-    const int cfg = pick_cfg(M, N);
+    const SplitArgs ep{1.0f, srow, nullptr};
+    if (bits == 8) return launch_bytes(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st);
+    const int rc = try_splitk(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st);
+    if (rc >= 0) return rc;
     int n1 = 0, n2 = 0;
-    const bool dual = pick_dual(M, N, &n1, &n2);
-    if (bits == 8) {
-        if (dual) return launch_dual<256, 256, 192, 2, 2, 3, 8, 4>(xq, wq, sw, 1.0f, M, N, K, n1, n2, out, acc, st, srow);
-        switch (cfg) {
-            case 0: return launch_dma<256, 256, 2, 2, 3, 1, 8, 4>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-            case 1: return launch_dma<256, 128, 2, 2, 3, 1, 8, 4>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-            case 3: return launch_dma<256, 192, 2, 2, 3, 1, 8, 4>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-            case 4: return launch_dma<64, 128, 2, 2, 3, 1, 8, 4>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-            default: return launch_dma<128, 128, 2, 2, 3, 1, 8, 4>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-        }
-    }
-    if (dual) return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, 1.0f, M, N, K, n1, n2, out, acc, st, srow);
-    switch (cfg) {
+    if (pick_dual(M, N, &n1, &n2))
+        return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, 1.0f, M, N, K, n1, n2, out, acc, st, srow);
+    switch (pick_cfg(M, N)) {
         case 0: return launch_dma<256, 256, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
         case 1: return launch_dma<256, 128, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
         case 3: return launch_dma<256, 192, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
@@ -997,7 +1064,7 @@ int launch_gemm_zp(const void* xq, const void* wq, const float* sw, float sx, co
 {
     if (M > (1 << 30) || N > (1 << 30) || K > 32768 || K % 128 != 0) return PQ_ERR_UNSUPPORTED;
     if (M * (K / 2) >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return PQ_ERR_UNSUPPORTED;
-    const int rc = try_splitk<4>(xq, wq, sw, SplitArgs{sx, nullptr, zcorr}, M, N, K, out, acc, ws, ws_bytes, force, st);
+    const int rc = try_splitk(xq, wq, sw, SplitArgs{sx, nullptr, zcorr}, M, N, K, out, acc, ws, ws_bytes, force, st);
     if (rc >= 0) return rc;
     int n1 = 0, n2 = 0;
     if (pick_dual(M, N, &n1, &n2))
