@@ -999,6 +999,10 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     const int forced_tile = forced_f6_tile();
     if (gemm_f6_takes_ksplit(M, N, K, w6b != nullptr))
         return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
+    // Weights of half the memory-side cache and more come from HBM again on each call of a program that has others as well: there
+    // square tiles, which take in a fifth less, win where they fill the chip (2048 x 28672 -> 8192, product 245 -> 224 us); below,
+    // or with a last round part empty, the kernels are level or the 128-row tiles ahead.
+    if (forced_tile == -1 && !w6b && gemm_f6_square_supported(M, N, K)) return launch_gemm_f6_square(x6, w6, sw, sx, M, N, K, out, acc, st);
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn

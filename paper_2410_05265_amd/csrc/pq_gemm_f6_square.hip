@@ -1,0 +1,380 @@
+// The product of f6 tiles (layout and exactness: pq_gemm_f6.hip) on tiles of 256 tokens x 256 channels, for weights that come
+// from HBM.
+//
+// What bounds it: the operands' way into the CU and the chip's power limit.  A CU keeps about 32 KiB of lines in flight,
+// whatever the depth of the ring in front of it, so it takes in 113 KiB/us of what the L2 holds, 80 of what the memory-side
+// cache holds and 60-65 of a stream from HBM.  The 128 x 512 tiles of k_gemm_f6 ask for 60 KiB per 1024 clocks of matrix work
+// and are bound by that (2048 x 28672 -> 8192 without the matrix instructions: 228 of 243 us); a square tile of the same area
+// asks for 48 (173 us).  Both operands then pass through LDS (144 KiB of reads and writes per 1024 clocks of matrix work),
+// which 128 bytes per clock still cover.  With that the kernel reaches the power limit: its clock falls from 2.0 to 1.75 GHz.
+// So the matrix instruction is the 16 x 16 x 128 one: on the same operands, alone, it is 25 % above the 32 x 32 x 64 one at
+// that limit (6.9 against 5.5 POP/s), and neighbouring instructions share an operand.  2048 x 28672 -> 8192, three copies of
+// the weights in turn: 245 -> 224 us.  Where the operands come from the caches the two kernels are level.
+//
+// A workgroup of four wavefronts, a wavefront 128 tokens x 128 channels: 64 accumulators of four registers.  One half stage =
+// 128 channels of the product: step s of the two blocks 2 p and 2 p + 1 of 128 channels.  Lane l of an operand holds row l % 16
+// and the image of half-wavefront (l / 16) % 2 of block 2 p + l / 32, which is 32 channels, the same ones for both operands; an
+// image's two planes are two LDS reads.  A direct load fills 1 KiB: 512 bytes of a step of block 2 p, then the same 512 bytes
+// of block 2 p + 1.  Operands are read a half stage ahead into a second register set, so a ring slot is free as soon as its
+// half stage begins and three slots give the loads two half stages (1.3 us) of lead.
+#include <hip/hip_fp16.h>
+
+#include <atomic>
+#include <type_traits>
+
+#include "pq_internal.h"
+
+namespace pq {
+namespace {
+
+typedef int v6i __attribute__((ext_vector_type(6)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+#define PQ_INLINE __attribute__((always_inline))      // lambdas: one left to the late inliner keeps its captures in scratch memory
+#define PQS_LDS(p) ((__attribute__((address_space(3))) void*)(p))
+
+constexpr int kBlock = 3072, kStep = 1536;          // 32 rows x 128 channels of the tiles; one of its two steps
+constexpr int kRing = 3;
+constexpr int kWorkgroups = 256;                    // persistent, one per CU
+constexpr int TM = 8, TN = 8;                       // operands of 16 tokens and of 16 channels per wavefront
+constexpr int BM = 32 * TM, BN = 32 * TN;
+constexpr int L = (TM + TN) * 3 / 4;                // direct loads per wavefront and half stage
+constexpr int STAGE = L * 4096, SCALES = kRing * STAGE;
+constexpr size_t kLds = (size_t)SCALES + 2 * 1024;
+static_assert(kLds <= 160 * 1024, "LDS");
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for_s(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for_s<I + 1, N>(f);
+    }
+}
+
+// (instructions the compiler knows, so that its own counting of outstanding operations starts from these)
+template <int N> __device__ __forceinline__ void wait_loads()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
+
+// The accumulator is tied to the result (the compiler's own form of the instruction may write another register and copy:
+// 3.4 times the clocks), and operands are six registers, not the builtin's eight.  Formats 3, 3: E3M2.
+// The compiler places no wait states around it: two are needed between a vector instruction that writes an operand and this
+// one, eighteen between it and a read of its result (operands come from LDS alone).
+__device__ __forceinline__ void mfma_e3m2(v4f& c, const v6i& a, const v6i& b)
+{
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:3 blgp:3" : "+a"(c) : "v"(a), "v"(b));
+}
+template <bool RESULTS> __device__ __forceinline__ void settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (RESULTS) asm volatile("s_nop 15\n\ts_nop 3");
+    else asm volatile("s_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// 64 x 16 bytes to LDS address lds_addr + T
+template <int T>
+__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_offset), "s"(base), "s"(lds_addr), "n"(T)
+                 : "memory", "scc");
+}
+
+// (workgroup-uniform by construction: kept in scalar registers)
+__device__ __forceinline__ const uint8_t* uniform(const uint8_t* p)
+{
+    const uint64_t a = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return reinterpret_cast<const uint8_t*>((uintptr_t)((uint64_t)hi << 32 | lo));
+}
+
+// Persistent workgroups walk a list of GM x GN tiles, row tiles fastest; in a round of 256 each XCD takes a
+// contiguous run (8 row tiles x 4 panels where the list divides so).
+__global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6,
+                                                       const float* __restrict__ sw, float sx, int M, int N, int K, int GM,
+                                                       int GN, __half* __restrict__ out, int32_t* __restrict__ acc_out)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int H = K >> 7, np = H >> 1;                         // half stages (as many as blocks of 128 channels), pairs of blocks
+    const int RBX = (M + 31) >> 5, RBW = (N + 31) >> 5;
+    const uint32_t stride_x = (uint32_t)RBX * kBlock, stride_w = (uint32_t)RBW * kBlock;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)PQS_LDS(smem);
+    const int G = gridDim.x, bid = blockIdx.x;
+    const int total = GM * GN;
+    // XCDs that read the same panels start an eighth of K apart (integer sums do not care about the order)
+    const int p_first = (int)(((int64_t)(bid & 7) * np) >> 3);
+
+    auto tile_of = [&](int seq) PQ_INLINE {                              // seq-th tile of this workgroup, -1 past the end
+        const int base = seq * G;
+        if (base >= total) return -1;
+        const int cnt = total - base < G ? total - base : G;
+        return bid < cnt ? base + xcd_run(bid, cnt) : -1;
+    };
+    int m0 = 0, n0 = 0;                                        // the tile whose loads are in flight or whose main loop runs
+    auto move_to = [&](int t) PQ_INLINE {
+        int mt, nt;
+        if ((GM & 7) == 0 && (GN & 3) == 0 && G == kWorkgroups) {
+            const int blk = t >> 5, in = t & 31, rows = GM >> 3;
+            mt = (blk % rows) * 8 + (in & 7);
+            nt = (blk / rows) * 4 + (in >> 3);
+        } else {
+            mt = t % GM;
+            nt = t / GM;
+        }
+        m0 = __builtin_amdgcn_readfirstlane(mt * BM);
+        n0 = __builtin_amdgcn_readfirstlane(nt * BN);
+    };
+    auto pair_of = [&](int h) PQ_INLINE {                                // past the end: the last pair again (harmless re-reads)
+        const int q = (h < H ? h >> 1 : np - 1) + p_first;
+        return q >= np ? q - np : q;
+    };
+
+    uint32_t voff[L];                                          // lane offsets of the direct loads
+    v6i tok[2][TM], wgt[2][TN];
+    v4f acc[TN][TM];
+
+    // piece q of a half stage: third q % 3 of row block q / 3 (tokens first); its upper lanes fetch from block 2 p + 1
+    auto addresses = [&]() PQ_INLINE {
+        // (copies: a choice between captured variables would put them in memory)
+        const int rx = m0 >> 5, rw = n0 >> 5, last_x = RBX - 1, last_w = RBW - 1;
+        const uint32_t next_x = lane < 32 ? 0u : stride_x, next_w = lane < 32 ? 0u : stride_w;
+        const uint32_t at = (uint32_t)(lane & 31) * 16;
+        static_for_s<0, L>([&](auto tc) PQ_INLINE {
+            constexpr int t = decltype(tc)::value;
+            const int q = wave + 4 * t, b = q / 3, part = q % 3;
+            int rb = rx + b;
+            rb = rb < last_x ? rb : last_x;
+            const uint32_t off_x = (uint32_t)rb * kBlock + next_x;
+            rb = rw + b - TM;
+            rb = rb < last_w ? rb : last_w;
+            const uint32_t off_w = (uint32_t)rb * kBlock + next_w;
+            voff[t] = (t < L / 2 ? off_x : off_w) + part * 512 + at;
+        });
+    };
+    auto dma = [&](auto tc, const uint8_t* xk, const uint8_t* wk, uint32_t fill) PQ_INLINE {
+        constexpr int t = decltype(tc)::value;
+        static_assert(TM == TN, "half of the loads are the tokens'");
+        if constexpr (t < L / 2) lds_dma16_at<t * 4096>(xk, voff[t], fill);
+        else lds_dma16_at<t * 4096>(wk, voff[t], fill);
+    };
+    // where this lane's images lie (an operand of odd number is the other half of the same block)
+    const int g = (lane >> 4) & 1, b = lane >> 5, r = lane & 15;
+    const uint32_t wide = (uint32_t)(g * 1024 + b * 512 + r * 16), narrow = (uint32_t)(b * 512 + g * 256 + r * 8);
+    static_assert(TM % 2 == 0 && TN % 2 == 0, "whole blocks per wavefront");
+    const uint32_t xw = (uint32_t)(wm * TM / 2) * kBlock + wide, xn = (uint32_t)(wm * TM / 2) * kBlock + narrow;
+    const uint32_t ww = (uint32_t)(TM + wn * TN / 2) * kBlock + wide, wnr = (uint32_t)(TM + wn * TN / 2) * kBlock + narrow;
+    // LDS read n of the 2 (TM + TN) of a half stage: even n the 16-byte plane of an operand's image, odd n the 8-byte one
+    auto read = [&](auto stc, uint32_t slot, auto nc) PQ_INLINE {
+        constexpr int st = decltype(stc)::value, n = decltype(nc)::value, f = n / 2, j = f < TM ? f : f - TM;
+        v6i& d = f < TM ? tok[st][j] : wgt[st][j];
+        if constexpr ((n & 1) == 0) {
+            constexpr int off = (j >> 1) * kBlock + (j & 1) * 256 + (st == 0 ? 0 : 1024);
+            uint32_t at;
+            if constexpr (f < TM) at = xw; else at = ww;
+            const v4i t = *(__attribute__((address_space(3))) const v4i*)(smem + slot + at + off);
+            if constexpr (st == 0) { d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w; }
+            else { d[2] = t.x; d[3] = t.y; d[4] = t.z; d[5] = t.w; }
+        } else {
+            constexpr int off = (j >> 1) * kBlock + (j & 1) * 128 + (st == 0 ? 2048 : 0);
+            uint32_t at;
+            if constexpr (f < TM) at = xn; else at = wnr;
+            const v2i u = *(__attribute__((address_space(3))) const v2i*)(smem + slot + at + off);
+            if constexpr (st == 0) { d[4] = u.x; d[5] = u.y; }
+            else { d[0] = u.x; d[1] = u.y; }
+        }
+    };
+    constexpr int READS = 2 * (TM + TN);
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+
+    // The first loads of a tile: its channel steps (256 of them at most, one load of the first wavefront; read back in the
+    // epilogue, two regions in turn) and the whole ring.
+    auto prefetch = [&](int parity) PQ_INLINE {
+        addresses();
+        if (out && wave == 0) {
+            int n = n0 + 4 * lane;
+            n = n + 4 <= N ? n : N - 4;
+            lds_dma16_at<0>(reinterpret_cast<const uint8_t*>(sw), (uint32_t)n * 4u, lds0 + SCALES + parity * 1024);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        static_for_s<0, kRing>([&](auto rc) PQ_INLINE {
+            constexpr int s = decltype(rc)::value;
+            const size_t at = (size_t)pair_of(s) * 2;
+            const uint8_t *xk = uniform(x6 + at * stride_x + (s & 1) * kStep), *wk = uniform(w6 + at * stride_w + (s & 1) * kStep);
+            const uint32_t fill = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024 + s * STAGE);
+            static_for_s<0, L>([&](auto tc) PQ_INLINE { dma(tc, xk, wk, fill); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    // stores of a full tile's output per wavefront, issued behind the next tile's first loads
+    constexpr int STORES = TM * TN / 2;
+    static_assert((kRing - 1) * L + STORES < 64, "vmcnt has six bits");
+
+    // stores_behind: a full tile's stores were issued since this tile's first loads; they are not waited for
+    auto compute = [&](bool stores_behind) PQ_INLINE {
+        static_for_s<0, TN>([&](auto ic) PQ_INLINE { static_for_s<0, TM>([&](auto jc) PQ_INLINE { 
+            v4f& a = acc[decltype(ic)::value][decltype(jc)::value];
+            a = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            asm volatile("" : "+a"(a));                        // (written here, not moved down to the first use)
+        }); });
+        // all matrix instructions of a half stage: channel operand i with every token operand, there and back
+        auto multiply = [&](auto stc, auto&& between) PQ_INLINE {
+            constexpr int st = decltype(stc)::value;
+            static_for_s<0, TN * TM>([&](auto nc) PQ_INLINE {
+                constexpr int n = decltype(nc)::value, i = n / TM, jj = n % TM, j = (i & 1) ? TM - 1 - jj : jj;
+                mfma_e3m2(acc[i][j], wgt[st][i], tok[st][j]);
+                between(nc);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        auto half_stage = [&](auto stc, int h, int slot, int next) PQ_INLINE {
+            constexpr int st = decltype(stc)::value;
+            const size_t at = (size_t)pair_of(h + kRing) * 2;
+            constexpr int fill_step = (st + kRing) & 1;
+            const uint8_t *xk = uniform(x6 + at * stride_x + fill_step * kStep), *wk = uniform(w6 + at * stride_w + fill_step * kStep);
+            const uint32_t fill = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024 + slot * STAGE);
+            // half stage h + 1 has landed: behind its loads lie those of h + 2 (and, for h < 2, the stores)
+            if (stores_behind && h < 2) wait_loads<L + STORES>();
+            else wait_loads<L>();
+            asm volatile("s_barrier" ::: "memory");            // for everyone, and everyone has read half stage h
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(stc, [&](auto nc) PQ_INLINE {
+                constexpr int n = decltype(nc)::value;
+                if constexpr (n < READS) read(std::integral_constant<int, st ^ 1>{}, next * STAGE, nc);
+                if constexpr ((n & 1) == 0 && n / 2 < L) dma(std::integral_constant<int, n / 2>{}, xk, wk, fill);
+            });
+            wait_lds();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        static_assert(READS <= TM * TN && 2 * L <= TM * TN, "a read per instruction, a load per two");
+        if (stores_behind) wait_loads<(kRing - 1) * L + STORES>();
+        else wait_loads<(kRing - 1) * L>();
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        static_for_s<0, READS>([&](auto nc) PQ_INLINE { read(S0{}, 0u, nc); });
+        wait_lds();
+        settle<false>();                                       // (the zeroed accumulators)
+        int slot = 0;
+        for (int h = 0; h < H; h += 2) {
+            const int s1 = slot + 1 == kRing ? 0 : slot + 1, s2 = s1 + 1 == kRing ? 0 : s1 + 1;
+            half_stage(S0{}, h, slot, s1);
+            half_stage(S1{}, h + 1, s1, s2);
+            slot = s2;
+        }
+        wait_loads<0>();                                       // none may still be writing LDS
+        settle<true>();
+        asm volatile("s_barrier" ::: "memory");                // nobody reads the ring any more
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // out = fp16(fp32(acc * factor)), factor = 256 fl(sw * (sx / 256)): the same real product, hence the same rounding, as the
+    // INT8 tiled kernel's (256 acc) * fl(sw * (sx / 256)).  A lane has four channels of one token per operand pair; 16 tokens
+    // are turned at a time through a padded region of the wavefront's own and stored as rows (non-temporal: the output is
+    // not read here again and leaves the caches to the operands).
+    auto epilogue = [&](int m0, int n0, int parity) PQ_INLINE {
+        // (the lane number is taken afresh: what derives from it would otherwise be held, or spilled, across the main loop)
+        int lane;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        const int g4 = lane >> 4, r = lane & 15;
+        const float* scl = reinterpret_cast<const float*>(smem + SCALES + parity * 1024) + wn * (16 * TN);
+        const int mb = m0 + wm * (16 * TM), nb = n0 + wn * (16 * TN);
+        const float f = sx * (1.0f / 256.0f);
+        v4f sc[TN];
+        if (out) {
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                v4f s = *(__attribute__((address_space(3))) const v4f*)(scl + i * 16 + 4 * g4);
+                s.x = mul_rn(s.x, f) * 256.0f; s.y = mul_rn(s.y, f) * 256.0f; s.z = mul_rn(s.z, f) * 256.0f; s.w = mul_rn(s.w, f) * 256.0f;
+                sc[i] = s;
+            }
+        }
+        static_for_s<0, TM>([&](auto jc) PQ_INLINE {
+            constexpr int j = decltype(jc)::value;
+            const int m16 = mb + j * 16;
+            if (acc_out) {
+#pragma unroll
+                for (int i = 0; i < TN; ++i) {
+                    const int m = m16 + r, n = nb + i * 16 + 4 * g4;
+                    const v4i iv = {(int)acc[i][j].x, (int)acc[i][j].y, (int)acc[i][j].z, (int)acc[i][j].w};
+                    if (m < M && n + 4 <= N) *reinterpret_cast<v4i*>(acc_out + (int64_t)m * N + n) = iv;
+                }
+            }
+            if (out) {
+                const int m = m16 + r;
+                __half* const row = out + (int64_t)m * N;
+                static_for_s<0, TN / 2>([&](auto pc) PQ_INLINE {
+                    constexpr int i = 2 * decltype(pc)::value;
+                    auto pack = [&](const v4f& a, const v4f& s) PQ_INLINE {
+                        const __half2 lo = __floats2half2_rn(mul_rn(a.x, s.x), mul_rn(a.y, s.y));
+                        const __half2 hi = __floats2half2_rn(mul_rn(a.z, s.z), mul_rn(a.w, s.w));
+                        v2i val;
+                        val.x = *reinterpret_cast<const int*>(&lo);
+                        val.y = *reinterpret_cast<const int*>(&hi);
+                        return val;
+                    };
+                    const v2i even = pack(acc[i][j], sc[i]);
+                    // rows 0 .. 3 of 16 lanes hold channels 0-3, 4-7, 8-11, 12-15 of either operand; after the swap rows 0
+                    // and 2 hold 0-7 and 8-15 of the even one, rows 1 and 3 of the odd one
+                    const v2i odd = pack(acc[i + 1][j], sc[i + 1]);
+                    const auto s0 = __builtin_amdgcn_permlane16_swap(even.x, odd.x, false, false);
+                    const auto s1 = __builtin_amdgcn_permlane16_swap(even.y, odd.y, false, false);
+                    const v4i val = {(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
+                    const int n = nb + i * 16 + (g4 & 1) * 16 + (g4 >> 1) * 8;
+                    if (m < M && n + 8 <= N) *reinterpret_cast<v4i*>(row + n) = val;
+                });
+            }
+        });
+    };
+
+    int t = tile_of(0);
+    if (t < 0) return;
+    move_to(t);
+    prefetch(0);
+    bool stores_behind = false;
+    for (int seq = 1, parity = 0;; ++seq, parity ^= 1) {
+        compute(stores_behind);
+        const int m_done = m0, n_done = n0;
+        t = tile_of(seq);
+        if (t >= 0) {
+            move_to(t);
+            prefetch(parity ^ 1);
+        }
+        epilogue(m_done, n_done, parity);
+        if (t < 0) break;
+        stores_behind = out && m_done + BM <= M && n_done + BN <= N;
+    }
+}
+
+}  // namespace
+
+bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN), rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
+    return K % 256 == 0 && K >= 8192 && N * K / 4 * 3 >= ((int64_t)128 << 20) && tiles < (1 << 24) && M * N * 16 >= rounds * kWorkgroups * BM * BN * 15;
+}
+
+int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st)
+{
+    const int GM = (int)((M + BM - 1) / BM), GN = (int)((N + BN - 1) / BN);
+    static std::atomic<uint64_t> lds_ok{0};
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(k_gemm_f6_square), kLds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
+    const int64_t tiles = (int64_t)GM * GN;
+    hipLaunchKernelGGL(k_gemm_f6_square, dim3((unsigned)(tiles < kWorkgroups ? tiles : kWorkgroups)), dim3(256), kLds, st,
+                       static_cast<const uint8_t*>(x6), static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, GN,
+                       static_cast<__half*>(out), acc);
+    return hip_status(hipGetLastError());
+}
+
+}  // namespace pq

@@ -79,6 +79,10 @@ int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_sc
 int launch_repack_f6(const void* codes, int64_t R, int64_t K, void* out, hipStream_t st);
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                    int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
+// 256 x 256 tiles for large weights (pq_gemm_f6_square.hip)
+bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K);
+int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
 // number where the shape is not taken), the tile behind the estimate (10 * blocks of 32 tokens + blocks of 32 channels; 0 for
