@@ -999,9 +999,12 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     const int forced_tile = forced_f6_tile();
     if (gemm_f6_takes_ksplit(M, N, K, w6b != nullptr))
         return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
-    // Weights of half the memory-side cache and more come from HBM again on each call of a program that has others as well: there
-    // square tiles, which take in a fifth less, win where they fill the chip (2048 x 28672 -> 8192, product 245 -> 224 us); below,
-    // or with a last round part empty, the kernels are level or the 128-row tiles ahead.
+    // Square tiles take in a fifth less.  They win on rows of 6144 channels and more where they fill 9/10 of the chip's rounds
+    // (product, three copies in turn / one: 4096 x 14336 -> 4096 1.08 / 1.05 x, 2048 x 8192 -> 8192 1.07 / 1.06, 3604 x 14848 ->
+    // 4192 1.17 / 1.16, 1523 x 6912 -> 20176 1.24 / 1.09; 8192 x 4096 -> 14336 0.95 / 0.98), and from 3/4 on where the operands are half
+    // the memory-side cache and more, so that they come from HBM in a program that has others as well (512 x 8192 -> 28672 1.29 /
+    // 1.03, 4445 x 28416 -> 2816 1.23 / 0.99, 2048 x 8192 -> 28672 1.10 / 0.94; 2824 x 7424 -> 13312, 86 MB, 0.94 / 0.89); below that
+    // the narrower tiles of this kernel leave fewer CUs idle (1285 x 24832 -> 8400, 0.64 of the rounds, 0.99 / 0.88).
     if (forced_tile == -1 && !w6b && gemm_f6_square_supported(M, N, K)) return launch_gemm_f6_square(x6, w6, sw, sx, M, N, K, out, acc, st);
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {

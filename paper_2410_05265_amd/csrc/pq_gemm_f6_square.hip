@@ -1,5 +1,5 @@
-// The product of f6 tiles (layout and exactness: pq_gemm_f6.hip) on tiles of 256 tokens x 256 channels, for weights that come
-// from HBM.
+// The product of f6 tiles (layout and exactness: pq_gemm_f6.hip) on tiles of 256 tokens x 256 channels, for long rows and
+// for operands that come from HBM.
 //
 // What bounds it: the operands' way into the CU and the chip's power limit.  A CU keeps about 32 KiB of lines in flight,
 // whatever the depth of the ring in front of it, so it takes in 113 KiB/us of what the L2 holds, 80 of what the memory-side
@@ -9,7 +9,7 @@
 // which 128 bytes per clock still cover.  With that the kernel reaches the power limit: its clock falls from 2.0 to 1.75 GHz.
 // So the matrix instruction is the 16 x 16 x 128 one: on the same operands, alone, it is 25 % above the 32 x 32 x 64 one at
 // that limit (6.9 against 5.5 POP/s), and neighbouring instructions share an operand.  2048 x 28672 -> 8192, three copies of
-// the weights in turn: 245 -> 224 us.  Where the operands come from the caches the two kernels are level.
+// the weights in turn: layer 277 -> 233 us.
 //
 // A workgroup of four wavefronts, a wavefront 128 tokens x 128 channels: 64 accumulators of four registers.  One half stage =
 // 128 channels of the product: step s of the two blocks 2 p and 2 p + 1 of 128 channels.  Lane l of an operand holds row l % 16
@@ -358,10 +358,13 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 
 }  // namespace
 
+// Where these tiles are the faster ones.  `use` is the share of the chip's rounds of 256 tiles that the output fills.
 bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN), rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
-    return K % 256 == 0 && K >= 8192 && N * K / 4 * 3 >= ((int64_t)128 << 20) && tiles < (1 << 24) && M * N * 16 >= rounds * kWorkgroups * BM * BN * 15;
+    if (K % 256 != 0 || tiles >= (1 << 24)) return false;
+    const double use = (double)M * (double)N / ((double)rounds * kWorkgroups * BM * BN);
+    return use >= 0.9 ? K >= 6144 : use >= 0.74 && (M + N) * K / 4 * 3 >= ((int64_t)128 << 20);
 }
 
 int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,

@@ -79,7 +79,7 @@ int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_sc
 int launch_repack_f6(const void* codes, int64_t R, int64_t K, void* out, hipStream_t st);
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                    int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
-// 256 x 256 tiles for large weights (pq_gemm_f6_square.hip)
+// 256 x 256 tiles (pq_gemm_f6_square.hip) and where they are the faster ones
 bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K);
 int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st);

@@ -1,4 +1,4 @@
-"""The 256 x 256 tiles that the prepacked product takes for large weights: the automatic choice against a forced width of the other
+"""The 256 x 256 tiles that the prepacked product takes for long rows and large operands: the automatic choice against a forced width of the other
 kernel, whole outputs bit for bit, and sampled rows and channels against the oracle's integer sums.  Rows and channels end
 inside a tile and inside a 32-row image, with an odd count of 256-channel pairs, and with two rounds of tiles."""
 
@@ -12,7 +12,7 @@ from pq_testlib import host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(2017, 8112, 22016), (2048, 8192, 22272), (500, 65040, 8192)])
+@pytest.mark.parametrize("M,N,K", [(2017, 8112, 22016), (2048, 8192, 22272), (500, 65040, 8192), (2048, 8176, 6144), (4439, 2800, 28672)])
 def test_square_tiles_match_the_other_kernel_and_the_oracle(M, N, K):
     import paper_2410_05265_amd.binding as pq
     gen = torch.Generator(device="cuda")
