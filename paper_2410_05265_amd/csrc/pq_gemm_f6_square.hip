@@ -274,6 +274,10 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         }
         wait_loads<0>();                                       // none may still be writing LDS
         settle<true>();
+        static_for_s<0, TN>([&](auto ic) PQ_INLINE { static_for_s<0, TM>([&](auto jc) PQ_INLINE {
+            v4f& a = acc[decltype(ic)::value][decltype(jc)::value];
+            asm volatile("" : "+a"(a));                        // (read behind the wait states above)
+        }); });
         asm volatile("s_barrier" ::: "memory");                // nobody reads the ring any more
         __builtin_amdgcn_sched_barrier(0);
     };
