@@ -87,6 +87,15 @@ __device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t lane_
                  : "memory", "scc");
 }
 
+// The lane number, taken afresh: what derives from threadIdx would be held, or spilled, across the main loop, and a reload
+// behind direct loads waits for all of them.
+__device__ __forceinline__ int fresh_lane()
+{
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
 // (workgroup-uniform by construction: kept in scalar registers)
 __device__ __forceinline__ const uint8_t* uniform(const uint8_t* p)
 {
@@ -145,6 +154,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 
     // piece q of a half stage: third q % 3 of row block q / 3 (tokens first); its upper lanes fetch from block 2 p + 1
     auto addresses = [&]() PQ_INLINE {
+        const int lane = fresh_lane();
         // (copies: a choice between captured variables would put them in memory)
         const int rx = m0 >> 5, rw = n0 >> 5, last_x = RBX - 1, last_w = RBW - 1;
         const uint32_t next_x = lane < 32 ? 0u : stride_x, next_w = lane < 32 ? 0u : stride_w;
@@ -202,7 +212,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     auto prefetch = [&](int parity) PQ_INLINE {
         addresses();
         if (out && wave == 0) {
-            int n = n0 + 4 * lane;
+            int n = n0 + 4 * fresh_lane();
             n = n + 4 <= N ? n : N - 4;
             lds_dma16_at<0>(reinterpret_cast<const uint8_t*>(sw), (uint32_t)n * 4u, lds0 + SCALES + parity * 1024);
         }
@@ -262,10 +272,11 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         else wait_loads<(kRing - 1) * L>();
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        static_for_s<0, READS>([&](auto nc) PQ_INLINE { read(S0{}, 0u, nc); });
+        int slot = 0;
+        asm volatile("" : "+s"(slot));                         // (addresses formed here, as for sx below)
+        static_for_s<0, READS>([&](auto nc) PQ_INLINE { read(S0{}, slot * STAGE, nc); });
         wait_lds();
         settle<false>();                                       // (the zeroed accumulators)
-        int slot = 0;
         for (int h = 0; h < H; h += 2) {
             const int s1 = slot + 1 == kRing ? 0 : slot + 1, s2 = s1 + 1 == kRing ? 0 : s1 + 1;
             half_stage(S0{}, h, slot, s1);
@@ -287,13 +298,13 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     // are turned at a time through a padded region of the wavefront's own and stored as rows (non-temporal: the output is
     // not read here again and leaves the caches to the operands).
     auto epilogue = [&](int m0, int n0, int parity) PQ_INLINE {
-        // (the lane number is taken afresh: what derives from it would otherwise be held, or spilled, across the main loop)
-        int lane;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        const int lane = fresh_lane();
         const int g4 = lane >> 4, r = lane & 15;
         const float* scl = reinterpret_cast<const float*>(smem + SCALES + parity * 1024) + wn * (16 * TN);
         const int mb = m0 + wm * (16 * TM), nb = n0 + wn * (16 * TN);
-        const float f = sx * (1.0f / 256.0f);
+        float step = sx;
+        asm volatile("" : "+s"(step));                         // (the product is formed here, not held across the main loop)
+        const float f = step * (1.0f / 256.0f);
         v4f sc[TN];
         if (out) {
 #pragma unroll

@@ -146,6 +146,14 @@ def test_results_and_operands_are_waited_for(compiled, source):
     assert found                                    # (the parser still finds the instructions it is there for)
 
 
+@pytest.mark.parametrize("source", SOURCES)
+def test_nothing_is_spilled(compiled, source):
+    """Memory operations of a wavefront retire in order: the reload of a spilled register behind direct loads to LDS waits for
+    all of them, and with that for the operands of a tile whose loads were issued early to overlap the last one's epilogue."""
+    sizes = [int(n) for n in re.findall(r"\.private_segment_fixed_size: (\d+)", compiled[source])]
+    assert sizes and not any(sizes), sizes
+
+
 @pytest.mark.parametrize("lines,bad", [
     (["v_mfma_x a[0:3], v[0:3], v[4:7], a[0:3]", "v_accvgpr_read_b32 v9, a3"], 1),
     (["v_mfma_x a[0:3], v[0:3], v[4:7], a[0:3]", "s_nop 15", "s_nop 1", "v_accvgpr_read_b32 v9, a3"], 0),
