@@ -104,8 +104,11 @@ __device__ __forceinline__ const uint8_t* uniform(const uint8_t* p)
     return reinterpret_cast<const uint8_t*>((uintptr_t)((uint64_t)hi << 32 | lo));
 }
 
-// Persistent workgroups walk a list of GM x GN tiles, row tiles fastest; in a round of 256 each XCD takes a
-// contiguous run (8 row tiles x 4 panels where the list divides so).
+// Persistent workgroups walk a list of GM x GN tiles; in a round of 256 each XCD takes a contiguous run of 32.  The list goes
+// through four panels at a time, and in those through strips of eight row tiles (fewer at the ends), row tiles fastest, so that a
+// run is 8 row tiles x 4 panels and needs the least operand bytes.  With plain columns where GM is no multiple of 8 a run of 30000
+// rows was 32 row tiles x one panel (30000 x 6144 -> 16384 1795 -> 1490 us, 20000 x 28672 -> 2048 755 -> 629, 7000 x 5120 -> 28000 583 ->
+// 539; up to 16 row tiles level).
 __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6,
                                                        const float* __restrict__ sw, float sx, int M, int N, int K, int GM,
                                                        int GN, __half* __restrict__ out, int32_t* __restrict__ acc_out)
@@ -131,15 +134,9 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     };
     int m0 = 0, n0 = 0;                                        // the tile whose loads are in flight or whose main loop runs
     auto move_to = [&](int t) PQ_INLINE {
-        int mt, nt;
-        if ((GM & 7) == 0 && (GN & 3) == 0 && G == kWorkgroups) {
-            const int blk = t >> 5, in = t & 31, rows = GM >> 3;
-            mt = (blk % rows) * 8 + (in & 7);
-            nt = (blk / rows) * 4 + (in >> 3);
-        } else {
-            mt = t % GM;
-            nt = t / GM;
-        }
+        const int group = t / (4 * GM), in = t - group * 4 * GM, wide = GN - 4 * group < 4 ? GN - 4 * group : 4;
+        const int strip = in / (8 * wide), at = in - strip * 8 * wide, high = GM - 8 * strip < 8 ? GM - 8 * strip : 8;
+        const int mt = 8 * strip + at % high, nt = 4 * group + at / high;
         m0 = __builtin_amdgcn_readfirstlane(mt * BM);
         n0 = __builtin_amdgcn_readfirstlane(nt * BN);
     };

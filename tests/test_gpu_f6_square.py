@@ -12,7 +12,8 @@ from pq_testlib import host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(2017, 8112, 22016), (2048, 8192, 22272), (500, 65040, 8192), (2048, 8176, 6144), (4439, 2800, 28672)])
+@pytest.mark.parametrize("M,N,K", [(2017, 8112, 22016), (2048, 8192, 22272), (500, 65040, 8192), (2048, 8176, 6144), (4439, 2800, 28672),
+                                   (4850, 9968, 6144)])          # (19 row tiles x 39 panels: strips and panels that do not divide)
 def test_square_tiles_match_the_other_kernel_and_the_oracle(M, N, K):
     import paper_2410_05265_amd.binding as pq
     gen = torch.Generator(device="cuda")
