@@ -42,6 +42,7 @@ SIGNATURES = {
     "pq_set_gemm_tile": (ctypes.c_int, [ctypes.c_int]),
     "pq_set_gemm_f6_tile": (ctypes.c_int, [ctypes.c_int]),
     "pq_gemm_small_tile": (ctypes.c_int, [_i64, _i64, _i64, _i64, _i32, _sz]),
+    "pq_gemm_square_tiles": (ctypes.c_int, [_i64, _i64, _i64]),
     "pq_probe_mfma_i8": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
     "pq_probe_stream_read": (ctypes.c_int, [_vp, _i64, _vp, _vp]),
     "pq_probe_mfma_f6": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
@@ -605,6 +606,10 @@ def pq_set_gemm_f6_tile(tile: int) -> int:
 
 def pq_gemm_small_tile(M: int, N_a: int, N_b: int, K: int, prepacked: bool = False, plane_bytes: int = 0) -> int:
     return int(lib().pq_gemm_small_tile(M, N_a, N_b, K, int(prepacked), plane_bytes))
+
+
+def pq_gemm_square_tiles(M: int, N: int, K: int) -> bool:
+    return bool(lib().pq_gemm_square_tiles(M, N, K))
 
 
 def pq_probe_mfma_i8(operands: torch.Tensor, iters: int, workgroups: int, sink: torch.Tensor) -> float:

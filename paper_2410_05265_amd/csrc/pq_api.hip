@@ -844,6 +844,12 @@ int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t p
     return pq::gemm_ksplit_i8_tile(M, N_a, N_b, K);
 }
 
+int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || (K % 128) != 0 || (N % 16) != 0 || M > (1 << 30) || N > (1 << 30) || K > 262080) return 0;
+    return pq::gemm_f6_takes_square(M, N, K, false) ? 1 : 0;
+}
+
 size_t pq_linear_noalloc_max_bytes(void) { return kScratchBytes; }
 
 int pq_linear_noalloc(const void* x_f16, const void* wq_packed, const float* w_scale, float act_scale,

@@ -985,6 +985,12 @@ bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two)
     return gemm_ksplit_f6_cost_us(M, N, two ? N : 0, K) < 0.97 * persistent_us;
 }
 
+// Square tiles take in a fifth less; their rule is beside them.
+bool gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two)
+{
+    return !two && forced_f6_tile() == -1 && !gemm_f6_takes_ksplit(M, N, K, false) && gemm_f6_square_supported(M, N, K);
+}
+
 // Channels per tile: 512, 384 or 256 (CI = 4, 3, 2), or a mix of 512 and 384 in one launch where N = 512 a +
 // 384 b; the choice minimises the estimated time of the busiest CU (a tile costs a fixed part plus a part
 // proportional to its width).
@@ -999,13 +1005,7 @@ int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, in
     const int forced_tile = forced_f6_tile();
     if (gemm_f6_takes_ksplit(M, N, K, w6b != nullptr))
         return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
-    // Square tiles take in a fifth less.  They win on rows of 6144 channels and more where they fill 9/10 of the chip's rounds
-    // (product, three copies in turn / one: 4096 x 14336 -> 4096 1.08 / 1.05 x, 2048 x 8192 -> 8192 1.07 / 1.06, 3604 x 14848 ->
-    // 4192 1.17 / 1.16, 1523 x 6912 -> 20176 1.24 / 1.09; 8192 x 4096 -> 14336 0.95 / 0.98), and from 3/4 on where the operands are half
-    // the memory-side cache and more, so that they come from HBM in a program that has others as well (512 x 8192 -> 28672 1.29 /
-    // 1.03, 4445 x 28416 -> 2816 1.23 / 0.99, 2048 x 8192 -> 28672 1.10 / 0.94; 2824 x 7424 -> 13312, 86 MB, 0.94 / 0.89); below that
-    // the narrower tiles of this kernel leave fewer CUs idle (1285 x 24832 -> 8400, 0.64 of the rounds, 0.99 / 0.88).
-    if (forced_tile == -1 && !w6b && gemm_f6_square_supported(M, N, K)) return launch_gemm_f6_square(x6, w6, sw, sx, M, N, K, out, acc, st);
+    if (gemm_f6_takes_square(M, N, K, w6b != nullptr)) return launch_gemm_f6_square(x6, w6, sw, sx, M, N, K, out, acc, st);
     auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn

@@ -370,13 +370,27 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 
 }  // namespace
 
-// Where these tiles are the faster ones.  `use` is the share of the chip's rounds of 256 tiles that the output fills.
+// Where these tiles are the faster ones.  `use` is the share of the chip's rounds of 256 tiles that the output fills, `big`: the
+// operands are half the memory-side cache and more, so that they come from HBM in a program that has others as well.  Products, 128-row
+// tiles -> these, three copies of the operands in turn / one copy, us:
+//   rows of 6144 channels and more, the rounds 9/10 full: 4096 x 14336 -> 4096 114 -> 110 / 118 -> 112, 2048 x 8192 -> 8192 69.4 -> 66.4,
+//     3604 x 14848 -> 4192 134 -> 112, 1523 x 6912 -> 20176 138 -> 112;
+//   from 0.74 on where the operands are big: 512 x 8192 -> 28672 83.6 -> 68.7, 4445 x 28416 -> 2816 236 -> 192 / 186 -> 180, 2048 x 8192 ->
+//     28672 273 -> 248 / 241 -> 243; below that the narrower tiles of the other kernel leave fewer CUs idle (1285 x 24832 -> 8400, 0.64);
+//   shorter rows, from 2048 channels on, where the operands are big and the rounds two and more, since a round's fixed cost weighs
+//     more: 450 x 2048 -> 128256 121 -> 98, 900 x 4096 -> 49152 131 -> 114, 2048 x 4096 -> 128256 723 -> 579, 12000 x 4096 -> 49152 1539 ->
+//     1299 (one copy 148 -> 157 at 1024 x 4096 -> 65536, 370 -> 304 at -> 128256).  One round: 256 x 4096 -> 49152 41.8 -> 44.7 / 32.2 -> 37.3;
+//     shorter still: 450 x 512 -> 400000 183 -> 171 / 151 -> 169, 8192 x 2048 -> 8192, not big, 98 -> 101.
+// Many short rows onto output rows 128 KiB apart stay with the other kernel: a round of 16 row tiles then writes to the same few
+// memory channels (4096 x 3072 -> 65536 543 -> 581, -> 65552 646 -> 511; 1024 x 3072 -> 65536 153 -> 124).
 bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K)
 {
-    const int64_t tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN), rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
+    const int64_t gm = (M + BM - 1) / BM, tiles = gm * ((N + BN - 1) / BN), rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
     if (K % 256 != 0 || tiles >= (1 << 24)) return false;
     const double use = (double)M * (double)N / ((double)rounds * kWorkgroups * BM * BN);
-    return use >= 0.9 ? K >= 6144 : use >= 0.74 && (M + N) * K / 4 * 3 >= ((int64_t)128 << 20);
+    const bool big = (M + N) * K / 4 * 3 >= ((int64_t)128 << 20);
+    if (K >= 6144) return use >= (big ? 0.74 : 0.9);
+    return K >= 2048 && big && use >= 0.74 && rounds >= 2 && !(gm >= 16 && N % 65536 == 0);
 }
 
 int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,

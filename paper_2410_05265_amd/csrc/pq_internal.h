@@ -92,8 +92,9 @@ double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
 double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
 int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
 int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
-// Whether launch_gemm_f6 takes them for one matrix [N, K], or for two of that size.
+// Whether launch_gemm_f6 takes them, or the 256 x 256 tiles, for one matrix [N, K], or for two of that size.
 bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two);
+bool gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two);
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, int64_t Nb = 0,
                           void* outb = nullptr);

@@ -8,12 +8,12 @@ import torch
 
 import oracle as O
 from pq_testlib import host
+from tile_plans import SQUARE
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(2017, 8112, 22016), (2048, 8192, 22272), (500, 65040, 8192), (2048, 8176, 6144), (4439, 2800, 28672),
-                                   (4850, 9968, 6144)])          # (19 row tiles x 39 panels: strips and panels that do not divide)
+@pytest.mark.parametrize("M,N,K", SQUARE)            # (which take them: test_tile_plans.py)
 def test_square_tiles_match_the_other_kernel_and_the_oracle(M, N, K):
     import paper_2410_05265_amd.binding as pq
     gen = torch.Generator(device="cuda")
