@@ -307,6 +307,10 @@ int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t p
 /* Whether pq_w4a4_gemm_f6 would take tiles of 256 tokens x 256 channels (host only; for sweeps and tests): 1 or 0. */
 int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K);
 
+/* How many of the last rows (M rounded up to 32) pq_linear_f6 rotates singly, the others four to a workgroup, in blocks of 4096
+ * channels (host only; for sweeps and tests; up to 131072 rows). */
+int64_t pq_rotate4096_single_rows(int64_t M, int64_t K);
+
 /* ---- 4-bit weights, 8-bit static activations (the W4A8 rows of Table 3) -------------------
  * Same layer with the activation quantizer at 8 bits: q = clamp(round_half_even(y/act_scale),
  * -128, 127), one int8 per code.  The three calls below mirror pq_rotate_quant, pq_w4a4_gemm and

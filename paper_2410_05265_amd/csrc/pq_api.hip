@@ -850,6 +850,12 @@ int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K)
     return pq::gemm_f6_takes_square(M, N, K, false) ? 1 : 0;
 }
 
+int64_t pq_rotate4096_single_rows(int64_t M, int64_t K)
+{
+    if (M <= 0 || M > 131072 || K > (1 << 24) || !pq::rotate4096_mfma_supported(K, 4096)) return 0;
+    return pq::rotate4096_single_rows((M + 31) / 32 * 32, K);
+}
+
 size_t pq_linear_noalloc_max_bytes(void) { return kScratchBytes; }
 
 int pq_linear_noalloc(const void* x_f16, const void* wq_packed, const float* w_scale, float act_scale,

@@ -365,7 +365,8 @@ __global__ __launch_bounds__(256 * TOK) void k_rotate4096_quant_mfma(const __hal
     int64_t row0 = row_base + (int64_t)group * TOK;
     if constexpr (TOK == 4) {
         if (group >= fours) {
-            // single tokens: each XCD (workgroup i runs on XCD i % 8) takes a run of them, so that its L2 joins their 16-byte runs
+            // single tokens: workgroup i runs on XCD i % 8, so those of one x whose y agree mod 8 share an XCD, and take a run of
+            // tokens: its L2 joins their 16-byte runs
             const int singles = (int)gridDim.y - fours;       // a multiple of 8: whole row blocks
             group -= fours;
             tokens = 1;
@@ -889,21 +890,32 @@ int launch_rotate128_mfma(const void* x, int64_t R, int64_t K, float act_scale, 
 // 1024: 0.92-1.09 x.)  tiles may be NULL: nibbles alone.
 bool rotate4096_mfma_supported(int64_t K, int32_t h) { return h == 4096 && (K % 4096) == 0 && K <= (1 << 24); }
 
+// The last rows of a launch with tiles that are taken singly (rows: whole row blocks, singles: a multiple of 32).  A single
+// token stores runs of 16 bytes, which costs more than an even share gains where many do (8192 x 4096, all single: 43 -> 77 us).  What
+// counts are blocks of 4096 channels, each of them a workgroup if single and a quarter of one if not: all are single up to 768
+// (layer with 16 output channels, fours -> single, us: 256 x 4096 11.5 -> 7.8, 512 12.1 -> 8.9, 320 x 8192 15.3 -> 14.7, 192 x 16384 22.0 -> 21.6, 96 x
+// 28672 31.5 -> 32.5, 256 x 12288 18.6 -> 19.0; 448 x 8192 would be 15.9 -> 17.3, 512 x 16384 27.2 -> 30.2), and up to 256 behind the last 1024, which are four for every CU
+// (1120 x 4096 15.1 -> 14.4, 640 x 8192 18.6 -> 17.6, 384 x 12288 21.6 -> 20.6, 320 x 16384 25.1 -> 23.9, 160 x 28672 34.1 -> 33.3; 512 behind
+// them, 1280 x 8192, would be 24.0 -> 24.6).
+int64_t rotate4096_single_rows(int64_t rows, int64_t K)
+{
+    const int64_t blocks = K / 4096;
+    if (rows * blocks <= 768) return rows;
+    const int64_t behind = rows - rows * blocks / 1024 * 1024 / blocks / 32 * 32;
+    return behind * blocks <= 256 ? behind : 0;
+}
+
 int launch_rotate4096_mfma(const void* x, int64_t R, int64_t K, float act_scale, void* tiles, void* nibbles, hipStream_t st)
 {
     const rq::StaticStep steps{(float)(1.0 / ((double)act_scale * 64.0)), act_scale};
     const bool stream = (tiles ? (int64_t)f6_tiles_bytes(R, K) : R * (K / 2)) <= rq::kStreamBelow;   // (the larger output)
     uint8_t *tp = static_cast<uint8_t*>(tiles), *np = static_cast<uint8_t*>(nibbles);
     const int64_t rows = tiles ? (R + 31) / 32 * 32 : R;             // a tile's rows past the end are zero codes
-    // Tiles: a single token stores runs of 16 bytes, which costs more than an even share gains where many do (8192 rows, all
-    // single: 43 -> 77 us), so only few rows are taken singly: all of up to 512 (256 rows 11.9 -> 8.3 us with a product of 16
-    // channels behind it, 512 12.4 -> 9.2; 777 would be 12.8 -> 14.2), and up to 256 behind the last 1024, which are four for
-    // every CU (1111 rows 15.5 -> 14.6; 476 behind them, 1500 rows, would be 16.0 -> 17.6).  Nibbles alone are stored as whole
-    // rows: always single (1111 rows 8.3 -> 6.1 us, 8192 29 -> 26.6).
+    // Nibbles alone are stored as whole rows: always single (1111 x 4096 8.3 -> 6.1 us, 8192 29 -> 26.6, 1024 x 8192 9.1 -> 9.2).
     const int64_t step = tiles ? 131072 : 32768;
     for (int64_t r0 = 0; r0 < rows; r0 += step) {                    // grid.y is limited to 65535 per launch
-        const int64_t mm = rows - r0 < step ? rows - r0 : step, rest = mm % 1024;
-        const int64_t singles = tiles && rest <= (mm < 1024 ? 512 : 256) ? rest : 0, fours = (mm - singles + 3) / 4;
+        const int64_t mm = rows - r0 < step ? rows - r0 : step;
+        const int64_t singles = tiles ? rotate4096_single_rows(mm, K) : 0, fours = (mm - singles + 3) / 4;
         auto launch = [&](auto kern, int64_t groups, int tok) {
             hipLaunchKernelGGL(kern, dim3((unsigned)(K / 4096), (unsigned)groups), dim3((unsigned)(256 * tok)), 0, st, static_cast<const __half*>(x), r0, R,
                                (int)K, (int)fours, steps, tp, np);

@@ -73,6 +73,7 @@ size_t f6_tiles_bytes(int64_t R, int64_t K);
 bool rotate128_mfma_supported(int64_t R, int64_t K, int32_t h);
 int launch_rotate128_mfma(const void* x, int64_t R, int64_t K, float act_scale, void* tiles, void* nibbles, hipStream_t st);
 bool rotate4096_mfma_supported(int64_t K, int32_t h);
+int64_t rotate4096_single_rows(int64_t rows, int64_t K);
 int launch_rotate4096_mfma(const void* x, int64_t R, int64_t K, float act_scale, void* tiles, void* nibbles, hipStream_t st);
 bool quant_f6_supported(int64_t R, int64_t K, int32_t h);
 int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_scale, void* out, void* nibbles, hipStream_t st);

@@ -1,5 +1,5 @@
 """The 4096-point rotation where its launches change shape: rows of the prepacked layer in groups of four and singly (all of
-up to 512, up to 256 behind the last 1024), rows of nibbles always singly; and the per-token quantizer of one to four
+up to 768 blocks of 4096 channels, up to 256 behind the last 1024), rows of nibbles always singly; and the per-token quantizer of one to four
 blocks a row, which rotates the same way.
 
 A row's codes may depend on nothing but the row, so a long input repeats a few rows in an order of its own, and every copy
@@ -26,7 +26,7 @@ def pq():
 
 
 @pytest.mark.parametrize("M,K", [(1, 4096), (31, 8192), (511, 4096), (513, 4096), (544, 8192), (991, 4096), (1023, 4096), (1025, 4096),
-                                 (1279, 4096), (1281, 4096), (2300, 4096)])
+                                 (1279, 4096), (1281, 4096), (2300, 4096), (630, 8192), (383, 12288), (160, 28672)])
 def test_rows_of_every_group_have_their_codes(pq, M, K):
     few = synth.activations(48, K, seed=K)
     order = np.random.default_rng(M).integers(0, 48, size=M)

@@ -35,3 +35,14 @@ def test_square_tiles_are_for_one_matrix_and_whole_pairs(b):
         assert not b.pq_gemm_square_tiles(2048, 8192, 22272)
     finally:
         assert b.pq_set_gemm_f6_tile(-1) == 4
+
+
+# tokens, channels; measured us of the prepacked layer with 16 output channels, all rows in fours and the last `singly` single
+@pytest.mark.parametrize("M,K,fours_us,single_us,singly", [
+    (512, 4096, 12.1, 8.9, 512), (1120, 4096, 15.1, 14.4, 96), (1280, 4096, 15.3, 14.1, 256), (1408, 4096, 15.5, 16.9, 384),
+    (320, 8192, 15.3, 14.7, 320), (448, 8192, 15.9, 17.3, 448), (512, 8192, 16.4, 18.2, 512), (640, 8192, 18.6, 17.6, 128),
+    (1280, 8192, 24.0, 24.6, 256), (384, 12288, 21.6, 20.6, 64), (1280, 12288, 31.9, 35.5, 256), (192, 16384, 22.0, 21.6, 192),
+    (512, 16384, 27.2, 30.2, 512), (320, 16384, 25.1, 23.9, 64), (1280, 16384, 40.0, 44.3, 256), (160, 28672, 34.1, 33.3, 32),
+    (512, 28672, 43.8, 53.5, 512)])
+def test_rows_are_rotated_singly_where_it_was_measured_faster(b, M, K, fours_us, single_us, singly):
+    assert b.pq_rotate4096_single_rows(M, K) == (singly if single_us < fours_us else 0)
