@@ -428,9 +428,15 @@ int launch_rotate_quant_dynamic(const void* x, int64_t M, int64_t K, int32_t h, 
     if (bits == 8)
         return launch_dyn<8>(static_cast<const __half*>(x), M, K, h, clip, static_cast<uint32_t*>(xq), row_scale, st);
     if (rotate4096_mfma_supported(K, h) && K <= 16384 && M <= 0x7fffffff) {
-        hipLaunchKernelGGL(k_rotate4096_quant_dyn, dim3((unsigned)M), dim3((unsigned)(K >> 4)), (size_t)(K >> 12) * 32 * rq::kXPitch, st,
-                           static_cast<const __half*>(x), (int)K, clip, static_cast<uint8_t*>(xq), row_scale);
-        return hip_status(hipGetLastError());
+        for (int64_t m0 = 0; m0 < M; m0 += 1 << 20) {             // (a launch has fewer than 2^32 threads)
+            const int64_t mm = M - m0 < (1 << 20) ? M - m0 : 1 << 20;
+            hipLaunchKernelGGL(k_rotate4096_quant_dyn, dim3((unsigned)mm), dim3((unsigned)(K >> 4)), (size_t)(K >> 12) * 32 * rq::kXPitch, st,
+                               static_cast<const __half*>(x) + m0 * K, (int)K, clip, static_cast<uint8_t*>(xq) + m0 * (K >> 1),
+                               row_scale + m0);
+            const int rc = hip_status(hipGetLastError());
+            if (rc != PQ_OK) return rc;
+        }
+        return PQ_OK;
     }
     return launch_dyn<4>(static_cast<const __half*>(x), M, K, h, clip, static_cast<uint32_t*>(xq), row_scale, st);
 }

@@ -66,3 +66,22 @@ def test_dynamic_steps_and_codes_of_4096_point_blocks(pq, M, K):
     assert at[0].size <= 1e-3 * diff.size and np.all(np.abs(diff[at]) == 1)
     if M > 2:
         assert s[1] == 1.0 and not got[1].any() and not got[2, :K - H].any()
+
+
+def test_dynamic_rows_past_the_threads_of_one_launch(pq):
+    """2^22 rows of 16384 channels are 2^32 threads, one launch's limit (137 GB of input; the last rows and the ones around the
+    borders of the launches are looked at)."""
+    M, K = (1 << 22) + 3, 16384
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < M * K * 5 // 2 + (8 << 30):
+        pytest.skip("needs 172 GB of free device memory")
+    few = synth.activations(8, K, seed=22)
+    part, steps = pq.pq_rotate_quant_dynamic(dev(few), H, 0.875, 4)
+    x = torch.empty((M, K), dtype=torch.float16, device="cuda")
+    at = torch.tensor([0, (1 << 20) - 1, 1 << 20, (1 << 21) + 1, 3 << 20, (1 << 22) - 1, 1 << 22, M - 1], device="cuda")
+    for i, row in enumerate(at.tolist()):
+        x[row] = torch.from_numpy(few[i])
+    codes, got = pq.pq_rotate_quant_dynamic(x, H, 0.875, 4)
+    assert torch.equal(codes[at], part) and torch.equal(got[at], steps)
+    del x, codes
+    torch.cuda.empty_cache()
