@@ -307,6 +307,11 @@ int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t p
 /* Whether pq_w4a4_gemm_f6 would take tiles of 256 tokens x 256 channels (host only; for sweeps and tests): 1 or 0. */
 int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K);
 
+/* Which tile pq_w4a8_gemm_ws (and pq_gemm_dynamic_ws with 8 bits) would take with plane_bytes of scratch memory (host only; for
+ * sweeps and tests): 100 * runs of K + blocks of 32 tokens (2 to 6, of 128 channels), 1 for 128 x 128 of the 4-bit
+ * products' kernel, or 0 for its 256-wide ones and where a streaming kernel serves. */
+int pq_gemm_w4a8_tile(int64_t M, int64_t N, int64_t K, size_t plane_bytes);
+
 /* How many of the last rows (M rounded up to 32) pq_linear_f6 rotates singly, the others four to a workgroup, in blocks of 4096
  * channels (host only; for sweeps and tests; up to 131072 rows). */
 int64_t pq_rotate4096_single_rows(int64_t M, int64_t K);

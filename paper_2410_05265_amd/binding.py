@@ -43,6 +43,7 @@ SIGNATURES = {
     "pq_set_gemm_f6_tile": (ctypes.c_int, [ctypes.c_int]),
     "pq_gemm_small_tile": (ctypes.c_int, [_i64, _i64, _i64, _i64, _i32, _sz]),
     "pq_gemm_square_tiles": (ctypes.c_int, [_i64, _i64, _i64]),
+    "pq_gemm_w4a8_tile": (ctypes.c_int, [_i64, _i64, _i64, _sz]),
     "pq_rotate4096_single_rows": (_i64, [_i64, _i64]),
     "pq_probe_mfma_i8": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
     "pq_probe_stream_read": (ctypes.c_int, [_vp, _i64, _vp, _vp]),
@@ -611,6 +612,10 @@ def pq_gemm_small_tile(M: int, N_a: int, N_b: int, K: int, prepacked: bool = Fal
 
 def pq_gemm_square_tiles(M: int, N: int, K: int) -> bool:
     return bool(lib().pq_gemm_square_tiles(M, N, K))
+
+
+def pq_gemm_w4a8_tile(M: int, N: int, K: int, plane_bytes: int = 0) -> int:
+    return int(lib().pq_gemm_w4a8_tile(M, N, K, plane_bytes))
 
 
 def pq_rotate4096_single_rows(M: int, K: int) -> int:

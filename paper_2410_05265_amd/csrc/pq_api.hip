@@ -45,7 +45,11 @@ std::atomic<int> g_variant{0};  // 0 auto, 1 streaming MFMA (M <= 32), 2 MFMA ti
 // weights): 4-bit codes from 5 tokens on (9 on small matrices), int8 codes from 3, 5 and 7.
 // 17 to 32 tokens are two launches of the matrix kernel where a cost estimate puts that ahead of
 // the tiled kernel (8B shapes: everything but gate/up; 70B: not gate/up either, 224 tiles).
-int pick_few_tokens(int64_t M, int64_t N, int64_t K, int32_t abits)
+// With int8 activations that estimate includes a split with the call's planes.  A streaming launch was measured, weights from HBM, at
+// 3.9 us + 0.28 per 1024 channels or at 3 us + the bytes at 5.6 TB/s, whichever is more, and the tiles then at 1.1 x their estimate (17
+// to 32 tokens, 119 sizes, streaming against tiles: 17 x 1024 -> 4096 8.9 against 5.4 us, 24 x 2048 -> 8192 10.1 against 8.4, 17 x 8192 ->
+// 1024 with planes 12.0 against 8.7; 17 x 4096 -> 4096 without 10.0 against 12.7, 32 x 8192 -> 8192 20.5 against 23.7).
+int pick_few_tokens(int64_t M, int64_t N, int64_t K, int32_t abits, size_t plane_bytes)
 {
     const bool dot = M <= 8 && pq::decode_supported(M, N, K, -1, abits);
     const bool mat = M <= 32 && pq::stream_mfma_supported(M, N, K, abits);
@@ -62,20 +66,24 @@ int pick_few_tokens(int64_t M, int64_t N, int64_t K, int32_t abits)
         // kernel, whose time there is a walk over K by however many tiles the output has
         const int launches = pq::stream_mfma_launches(M, N, K, abits);
         if (launches == 1) return 1;
+        if (abits == 8) {
+            const double fixed = 3.9 + 0.000275 * (double)K, stream = 3.0 + (double)weight_bytes / 5.6e6;
+            return launches * (fixed > stream ? fixed : stream) < 1.1 * pq::gemm_bytes_cost_us(M, N, K, plane_bytes) ? 1 : 2;
+        }
         const double stream_us = launches * (2.5 + (double)weight_bytes / 5.0e6);
         if (stream_us < pq::gemm_unsplit_cost_us(M, N, K)) return 1;
     }
     return 2;
 }
 
-// The same choice when the call brings scratch memory for partial-sum planes (timings: 4-bit codes).
+// The same choice when the call brings scratch memory for partial-sum planes (4-bit codes; those of 8 bits see it above).
 // Where the matrix streaming kernel needs two or more launches (17 to 32 tokens, or rows too long
 // for 16 tokens' codes in LDS), the split tiled launch with its planes in place beats them on
 // matrices of 8 MB and more (8B shapes at 24 tokens: 8-13 us against 9-16; not measured below 8 MB).
 int pick_with_planes(int64_t M, int64_t N, int64_t K, size_t plane_bytes, int32_t abits = 4)
 {
-    const int kernel = pick_few_tokens(M, N, K, abits);
-    if (g_variant == 0 && kernel == 1 && N * (K / 2) >= 8000000 && pq::stream_mfma_launches(M, N, K, abits) > 1) {
+    const int kernel = pick_few_tokens(M, N, K, abits, plane_bytes);
+    if (g_variant == 0 && abits == 4 && kernel == 1 && N * (K / 2) >= 8000000 && pq::stream_mfma_launches(M, N, K, abits) > 1) {
         const size_t want = pq::gemm_splitk_workspace_bytes(M, N, K);
         if (want > 0 && plane_bytes >= want) return 2;
     }
@@ -223,7 +231,7 @@ size_t pq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int32_t act_bits
 {
     if (M <= 0 || N <= 0 || K <= 0 || (K % 32) != 0 || (N % 16) != 0 || (act_bits != 4 && act_bits != 8)) return 0;
     if (g_variant == 3 || pick_with_planes(M, N, K, ~(size_t)0, act_bits) != 2) return 0;
-    return pq::gemm_splitk_workspace_bytes(M, N, K, g_variant == 5);
+    return act_bits == 8 ? pq::gemm_bytes_workspace_bytes(M, N, K, g_variant == 5) : pq::gemm_splitk_workspace_bytes(M, N, K, g_variant == 5);
 }
 
 size_t pq_w4a4_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return pq_gemm_workspace_bytes(M, N, K, 4); }
@@ -848,6 +856,14 @@ int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0 || (K % 128) != 0 || (N % 16) != 0 || M > (1 << 30) || N > (1 << 30) || K > 262080) return 0;
     return pq::gemm_f6_takes_square(M, N, K, false) ? 1 : 0;
+}
+
+int pq_gemm_w4a8_tile(int64_t M, int64_t N, int64_t K, size_t plane_bytes)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || (K % 128) != 0 || (N % 16) != 0 || M > (1 << 30) || N > (1 << 30) || K > 65536 ||
+        pick_with_planes(M, N, K, plane_bytes, 8) != 2)
+        return 0;
+    return pq::gemm_bytes_tile(M, N, K, plane_bytes);
 }
 
 int64_t pq_rotate4096_single_rows(int64_t M, int64_t K)

@@ -938,27 +938,28 @@ int launch_gemm_mfma_ws(const void* xq, const void* wq, const float* sw, float s
     return launch_gemm_mfma(xq, wq, sw, sx, M, N, K, out, acc, st);
 }
 
-// 4-bit weights x 8-bit activations (codes in the even/odd-grouped byte order written by the
-// 8-bit quantizer): the same kernel with the activation operand taken from LDS as it stands.
 namespace {
 // What a product of int8 activations runs on: bm > 0: tiles of bm tokens (pq_gemm_bytes.hip), in S runs of K;
-// bm = 0: tiles of 32 x 32 results, 256 x bn, or with bn = 0 n1 panels of 256 and n2 of 192.
-struct BytesPlan { int bm, S, bn, n1, n2; };
+// bm = 0: tiles of 32 x 32 results, rows x bn, or with bn = 0 n1 panels of 256 and n2 of 192.  us: the estimate.
+struct BytesPlan { int bm, S, rows, bn, n1, n2; double us; };
 
 // The choice is the least of these estimates, in microseconds.  A stage of 128 channels of one tile takes `part` where few
 // CUs are busy (the walk over K and its loads bound it) and `full` where all are (power does), in between by the share that is
-// busy in a launch's rounds of 256 tiles.  Fitted to 140 shapes of 33 to 4096 tokens, 1024 to 28672 channels in and out: what it
-// takes is 0.3 % slower on average than the best of all kernels and splits, 9 % at most.  S runs add the planes, written and read
-// at 6.4 TB/s out of the caches, and the second launch.  Heights below 256 with the matrix instruction of 16 x 16 results
-// against the tiles that were there before: 64 x 4096 -> 4096 15.3 -> 11.1 us, 543 x 11776 -> 4160 49.0 -> 37.0, 2203 x 3456 ->
-// 2096 25.6 -> 21.2, with planes 915 x 28416 -> 1744 65.6 -> 52.9.  Outputs that fill the chip with 256-wide tiles keep them:
-// 4096 x 11008 -> 4096 151.7 against 213, 2048 x 14336 -> 4096 114 against 145 (each operand byte read serves twice the
-// products), 245 x 4736 -> 27200 33.5 against 40.6.
-struct BytesTile { int bm; double part_us, full_us; };
+// busy in a launch's rounds of 256 tiles.  S runs add a launch and the planes, written and read at 5 TB/s; runs in fours are level
+// over the XCDs, others cost 0.3 us more.  The tiles are fitted to 140 shapes of 33 to 4096 tokens, 1024 to 28672 channels in and
+// out, the launches of a split and the 128 x 128 tiles to 439 (512 channels and more, all heights and splits, weights cached and from
+// HBM): what the plan takes there is 0.8 % slower on average than the best with planes, 0.4 % without, 18 % at most.
+// Heights below 256 with the matrix instruction of 16 x 16 results against the tiles of 32 x 32: 64 x 4096 -> 4096 15.3 -> 11.1 us,
+// 543 x 11776 -> 4160 49.0 -> 37.0, 2203 x 3456 -> 2096 25.6 -> 21.2, with planes 915 x 28416 -> 1744 65.6 -> 52.9.  The latter stay
+// where they are better: 256 wide on outputs that fill the chip with them (4096 x 11008 -> 4096 151.7 against 213, 2048 x 14336 ->
+// 4096 114 against 145, 245 x 4736 -> 27200 33.5 against 40.6: each operand byte read serves twice the products), and 128 x 128, whose
+// two workgroups a CU hide one another's first loads and stores, on short rows from the second round on (1363 x 1280 -> 11024 29.8
+// against 32.4, 1900 x 1280 -> 27696 84.7 against 93.4, 539 x 3840 -> 11680 33.1 against 35.6).
+struct BytesTile { int rows; double part_us, full_us; };
 constexpr BytesTile kBytesTiles[] = {{64, 0.25, 0.28}, {96, 0.30, 0.38}, {128, 0.34, 0.49}, {160, 0.40, 0.62}, {192, 0.45, 0.68}};
-constexpr BytesTile kBytesTall = {256, 0.38, 0.88};       // 256 x 128 of 32 x 32 results
+constexpr BytesTile kBytesTall = {256, 0.38, 0.88}, kBytesPair = {128, 0.30, 0.46};       // x 128, of 32 x 32 results
 
-int64_t bytes_tiles(const BytesTile& t, int64_t M, int64_t N) { return (M + t.bm - 1) / t.bm * ((N + 127) / 128); }
+int64_t bytes_tiles(const BytesTile& t, int64_t M, int64_t N) { return (M + t.rows - 1) / t.rows * ((N + 127) / 128); }
 double bytes_stages_us(const BytesTile& t, int64_t tiles, int64_t stages)
 {
     return (double)stages * (t.part_us * (double)((tiles + 255) >> 8) + (t.full_us - t.part_us) * (1.0 / 256.0) * (double)tiles);
@@ -969,7 +970,7 @@ BytesPlan plan_bytes(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool forc
     const int64_t nk = K / 128;
     const size_t plane_bytes = (size_t)M * N * 4;
     const bool planes = ws_bytes > 0 && M * N < ((int64_t)1 << 31);
-    BytesPlan p{0, 1, 256, 0, 0};
+    BytesPlan p{0, 1, 256, 256, 0, 0, 0.0};
     if (force) {   // (as in plan_splitk)
         int S = planes ? 5 : 1;
         while (S > 1 && ((int64_t)S * 2 > nk || (size_t)S * plane_bytes > ws_bytes)) --S;
@@ -984,23 +985,27 @@ BytesPlan plan_bytes(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool forc
     if (narrow < area) { area = narrow; p.bn = 192; }
     double dual = 0.0;
     if (pick_dual(M, N, &p.n1, &p.n2, &dual) && dual / 65536.0 < 0.97 * area) { area = dual / 65536.0; p.bn = 0; }
-    const double use = (double)M * N / (area * 256.0 * 65536.0);
-    double best = 3.8 + (double)nk * area * (0.76 + 0.94 * use) + (double)M * N * 2 / 4.2e6;
-    const double fixed = 3.3 + (double)M * N * 2 / 4.2e6, tall = fixed + bytes_stages_us(kBytesTall, bytes_tiles(kBytesTall, M, N), nk);
+    const double use = (double)M * N / (area * 256.0 * 65536.0), store = (double)M * N * 2 / 4.2e6, fixed = 3.3 + store;
+    double best = 3.8 + store + (double)nk * area * (0.76 + 0.94 * use);
+    const double tall = fixed + bytes_stages_us(kBytesTall, bytes_tiles(kBytesTall, M, N), nk);
     if (tall < best) { best = tall; p.bn = 128; }
+    const double pairs = fixed + bytes_stages_us(kBytesPair, bytes_tiles(kBytesPair, M, N), nk);
+    if (bytes_tiles(kBytesPair, M, N) > 256 && pairs < best) { best = pairs; p.rows = p.bn = 128; }
     for (const BytesTile& t : kBytesTiles) {
         const int64_t tiles = bytes_tiles(t, M, N);
         const double whole = fixed + bytes_stages_us(t, tiles, nk);
-        if (whole < best) { best = whole; p.bm = t.bm; p.S = 1; }
+        if (whole < best) { best = whole; p.bm = t.rows; p.S = 1; }
         for (uint32_t S = 2; planes && S <= 32 && S * 2 <= nk && S * plane_bytes <= ws_bytes; ++S) {
-            const double pair = fixed + 3.2 + 0.11 * S + 2.0 * S * (double)plane_bytes / 6.4e6;     // (0.5 of it the margin to win by)
-            if (pair >= best) break;
-            const double us = pair + bytes_stages_us(t, tiles * S, ((uint32_t)nk + S - 1) / S);
-            if (us < best) { best = us; p.bm = t.bm; p.S = (int)S; }
+            const double added = fixed + 2.2 + 0.07 * S + 2.0 * S * (double)plane_bytes / 5.0e6;
+            if (added >= best) break;
+            const double us = added + (S % 4 ? 0.3 : 0.0) + bytes_stages_us(t, tiles * S, ((uint32_t)nk + S - 1) / S);
+            if (us < best) { best = us; p.bm = t.rows; p.S = (int)S; }
         }
     }
+    p.us = best;
     if (const int tile = forced_tile(); tile >= 0 && p.S == 1) {
         p.bm = tile == 0 || tile == 1 || tile == 3 ? 0 : (tile == 4 ? 64 : 128);
+        p.rows = 256;
         p.bn = tile == 3 ? 192 : (tile == 1 ? 128 : 256);
     }
     return p;
@@ -1017,6 +1022,7 @@ int launch_bytes(const void* xq8, const void* wq, const float* sw, SplitArgs ep,
     }
     if (force) return PQ_ERR_UNSUPPORTED;
     if (p.bm > 0) return launch_gemm_bytes(xq8, wq, sw, ep.sx, ep.srow, M, N, K, p.bm, 1, out, acc, st);
+    if (p.rows == 128) return launch_dma<128, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, out, acc, st, ep.srow);
     switch (p.bn) {
         case 0: return launch_dual<256, 256, 192, 2, 2, 3, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, p.n1, p.n2, out, acc, st, ep.srow);
         case 128: return launch_dma<256, 128, 2, 2, 3, 1, 8, 4>(xq8, wq, sw, ep.sx, M, N, K, out, acc, st, ep.srow);
@@ -1026,6 +1032,22 @@ int launch_bytes(const void* xq8, const void* wq, const float* sw, SplitArgs ep,
 }
 }  // namespace
 
+size_t gemm_bytes_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force)
+{
+    if (K % 128 != 0) return 0;
+    const BytesPlan p = plan_bytes(M, N, K, ~(size_t)0, force);
+    return p.S > 1 ? (size_t)p.S * (size_t)M * (size_t)N * 4 : 0;
+}
+
+double gemm_bytes_cost_us(int64_t M, int64_t N, int64_t K, size_t ws_bytes) { return K % 128 == 0 ? plan_bytes(M, N, K, ws_bytes, false).us : 1e9; }
+
+int gemm_bytes_tile(int64_t M, int64_t N, int64_t K, size_t ws_bytes)
+{
+    const BytesPlan p = plan_bytes(M, N, K, ws_bytes, false);
+    return p.bm > 0 ? 100 * p.S + p.bm / 32 : (p.rows == 128 ? 1 : 0);
+}
+
+// 4-bit weights x 8-bit activations (codes in the even/odd-grouped byte order written by the 8-bit quantizer).
 int launch_gemm_w4a8(const void* xq8, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K,
                      void* out, int32_t* acc, hipStream_t st, void* ws, size_t ws_bytes, bool force)
 {

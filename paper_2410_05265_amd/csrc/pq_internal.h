@@ -24,6 +24,11 @@ int launch_gemm_w4a8(const void* xq8, const void* wq, const float* sw, float sx,
                      size_t ws_bytes = 0, bool force = false);
 int launch_gemm_bytes(const void* xq8, const void* wq, const float* sw, float sx, const float* srow, int64_t M, int64_t N,
                       int64_t K, int bm, int S, void* out, int32_t* acc, hipStream_t st);
+// What its plan asks for, its estimate in microseconds with that scratch memory, and its tile (100 * runs of K + blocks of
+// 32 tokens; 1: 128 x 128 of 32 x 32 results, 0: 256 wide, both of launch_gemm_mfma's kernel)
+size_t gemm_bytes_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force = false);
+double gemm_bytes_cost_us(int64_t M, int64_t N, int64_t K, size_t ws_bytes);
+int gemm_bytes_tile(int64_t M, int64_t N, int64_t K, size_t ws_bytes);
 int launch_rotate_quant_dynamic(const void* x, int64_t M, int64_t K, int32_t h, float clip, int32_t bits,
                                 void* xq, float* row_scale, hipStream_t st);
 int launch_gemm_dynamic(const void* xq, int32_t bits, const void* wq, const float* sw, const float* srow,

@@ -43,7 +43,7 @@ int main(void)
                 total += pq_linear_w4a8_workspace_bytes(M, K) + pq_linear_w4a8_workspace_bytes_split(M, N, K);
                 total += pq_linear_dynamic_workspace_bytes(M, K, 4) + pq_linear_dynamic_workspace_bytes_split(M, N, K, 8);
                 total += pq_gemm_small_tile(M, N, 0, K, 0, 0) + pq_gemm_small_tile(M, N, N, K, 0, 1 << 24) + pq_gemm_small_tile(M, N, N, K, 1, 0);
-                total += pq_gemm_square_tiles(M, N, K) + (size_t)pq_rotate4096_single_rows(M, K);
+                total += pq_gemm_square_tiles(M, N, K) + (size_t)pq_rotate4096_single_rows(M, K) + pq_gemm_w4a8_tile(M, N, K, 1 << 24);
                 total += pq_f6_tiles_bytes(M, K) + pq_linear_f6_workspace_bytes(M, K, 128) + pq_linear_f6_workspace_bytes(M, K, 4096);
             }
     EXPECT(total > 0, 1);

@@ -1,6 +1,6 @@
 """The product of int8 activations on tiles of 64, 96, 128, 160 and 192 tokens x 128 channels: last tiles with one row and one
-group of 16 channels, one stage, odd and even counts of them, more tiles than the chip has CUs, and runs of K in planes (an
-automatic split gets scratch memory for 16 planes).  Integer sums are exact; both epilogues are within an fp16 ulp."""
+group of 16 channels, one stage, odd and even counts of them, more tiles than the chip has CUs, runs of K in planes (an
+automatic split gets scratch memory for 16 planes), and the tiles of 32 x 32 results that the plan still takes.  Integer sums are exact; both epilogues are within an fp16 ulp."""
 
 import numpy as np
 import pytest
@@ -9,6 +9,7 @@ import torch
 import oracle as O
 from paper_2410_05265_amd import synth
 from pq_testlib import dev, host, ulp_diff
+from tile_plans import BYTES
 
 pytestmark = pytest.mark.gpu
 
@@ -20,13 +21,8 @@ def pq():
     return b
 
 
-# (the height that the estimates choose is given beside each shape; 64 also where everything fits one tile)
-@pytest.mark.parametrize("M,N,K,planes", [(33, 16, 128, 0), (65, 144, 256, 0), (129, 272, 1152, 0),               # 64
-                                          (1441, 2032, 384, 0),                                                # 96
-                                          (897, 4016, 128, 0), (1000, 4080, 256, 0),                           # 128
-                                          (2081, 2064, 384, 0),                                                # 160
-                                          (1345, 4016, 640, 0), (1475, 4080, 128, 0),                          # 192
-                                          (70, 272, 4096, 16), (135, 3600, 6400, 16), (390, 2576, 12288, 16)])  # 64, 96, 128, split
+# (which tile each of these takes: test_tile_plans.py)
+@pytest.mark.parametrize("M,N,K,planes", [c[1:] for c in BYTES])
 def test_tile_heights_edges_and_runs(pq, M, N, K, planes):
     q = synth.random_codes(M, K, seed=M, stream=9, lo=-128, hi=127)
     q[0], q[-1] = -128, 127                                       # the largest sums
