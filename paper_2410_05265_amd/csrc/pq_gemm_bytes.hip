@@ -33,38 +33,12 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 
 constexpr int kBN = 128, kWR = 2, kWC = 4, kNW = kWR * kWC, kRing = 4, kShift = 4;
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for_b(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for_b<I + 1, N>(f);
-    }
-}
-
 // The accumulator is tied to the result: the builtin may write other registers and copy.  The compiler places no wait states
 // around it: two are needed between a vector instruction that writes an operand and this one, eighteen between it and a read of
 // its result.
 __device__ __forceinline__ void mfma_i8(v4i& c, const v4i& a, const v4i& b)
 {
     asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
-}
-
-// 64 x 16 bytes to LDS address lds_addr + T
-template <int T>
-__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
-{
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_offset), "s"(base), "s"(lds_addr), "n"(T)
-                 : "memory", "scc");
-}
-
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
-template <int N> __device__ __forceinline__ void wait_loads()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 constexpr int stage_bytes(int bm) { return bm * 128 + kBN * 64; }
@@ -96,7 +70,7 @@ __global__ __launch_bounds__(kNW * 64) void k_gemm_bytes(const uint8_t* __restri
     constexpr bool AGAIN = BLK % kNW != 0;
     const bool again = AGAIN && wave + kNW * (LW - 1) >= BLK;
     uint32_t goff[LW];
-    static_for_b<0, LW>([&](auto ic) {
+    static_for<0, LW>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         const int blk = i == LW - 1 && again ? wave + kNW * (i - 1) : wave + kNW * i;
         const int lrow8 = lane >> 3, lrow16 = lane >> 2;
@@ -147,13 +121,13 @@ __global__ __launch_bounds__(kNW * 64) void k_gemm_bytes(const uint8_t* __restri
         wait_loads<(kRing - 2) * LW>();
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        static_for_b<0, NM>([&](auto nc) {
+        static_for<0, NM>([&](auto nc) {
             constexpr int n = decltype(nc)::value, i = n / (2 * TN), ph = (n / TN) & 1, jj = n % TN, j = ph ? TN - 1 - jj : jj;
             mfma_i8(acc[i][j], xb[par][ph][j], xa[ph][i]);
             if constexpr (n < TN) packed[n] = from_lds(next + rd_b + n * 1024);
             if constexpr (n >= EXPAND) {
                 constexpr int e0 = (n - EXPAND) * TN / (NM - EXPAND), e1 = (n + 1 - EXPAND) * TN / (NM - EXPAND);
-                static_for_b<e0, e1>([&](auto ec) { expand(par ^ 1, decltype(ec)::value); });
+                static_for<e0, e1>([&](auto ec) { expand(par ^ 1, decltype(ec)::value); });
             }
             if constexpr (jj == TN - 1) xa[ph][i] = from_lds(next + rd_a[ph] + i * 2048);
             if constexpr (n < LW) dma(std::integral_constant<int, n>{}, kt, fill);
@@ -164,21 +138,21 @@ __global__ __launch_bounds__(kNW * 64) void k_gemm_bytes(const uint8_t* __restri
         asm volatile("s_nop 1");
     };
 
-    static_for_b<0, kRing>([&](auto sc) {
+    static_for<0, kRing>([&](auto sc) {
         constexpr int s = decltype(sc)::value;
         const uint32_t fill = __builtin_amdgcn_readfirstlane(lds0 + s * STAGE);
-        static_for_b<0, LW>([&](auto ic) { dma(ic, s < nk ? s : nk - 1, fill); });
+        static_for<0, LW>([&](auto ic) { dma(ic, s < nk ? s : nk - 1, fill); });
     });
     wait_loads<(kRing - 1) * LW>();
     asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    static_for_b<0, TN>([&](auto jc) { packed[decltype(jc)::value] = from_lds(rd_b + decltype(jc)::value * 1024); });
-    static_for_b<0, TM>([&](auto ic) {
+    static_for<0, TN>([&](auto jc) { packed[decltype(jc)::value] = from_lds(rd_b + decltype(jc)::value * 1024); });
+    static_for<0, TM>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         xa[0][i] = from_lds(rd_a[0] + i * 2048);
         xa[1][i] = from_lds(rd_a[1] + i * 2048);
     });
-    static_for_b<0, TN>([&](auto jc) { expand(0, decltype(jc)::value); });
+    static_for<0, TN>([&](auto jc) { expand(0, decltype(jc)::value); });
     wait_lds();
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 1");

@@ -193,15 +193,6 @@ __global__ __launch_bounds__(256) void k_rotate_quant_f6(const __half* __restric
     }
 }
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for6(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for6<I + 1, N>(f);
-    }
-}
-
 // The 128-point block rotation as a product on the matrix pipe, fused with the quantizer (App. B "Online
 // Rotation" + Eq. 1).  Butterflies cost about 25 vector instructions per element with conversion and
 // quantizer, which bounds the kernel above (2048 x 14336: 23.6 us for 81 MB); here Y^T = H X^T runs on
@@ -272,7 +263,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
             hreg[1][1][d] = hreg[1][0][d] ^ 0x80008000u;
         }
     }
-    static_for6<0, TILES>([&](auto bc) {
+    static_for<0, TILES>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
         const int kt = kt0 + b;
         if (kt >= nk) return;
@@ -300,11 +291,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
         for (int n = 0; n < 4; ++n)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[n][v] = 0.0f;
-        static_for6<0, 8>([&](auto sc) {
+        static_for<0, 8>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             const v4i xi = *(__attribute__((address_space(3))) const v4i*)(stg + t * kXPitch + 32 * s + 16 * g);
             const v8h xop = __builtin_bit_cast(v8h, xi);
-            static_for6<0, 4>([&](auto nc) {
+            static_for<0, 4>([&](auto nc) {
                 constexpr int n = decltype(nc)::value;
                 constexpr int flip = __builtin_popcount((s >> 1) & n) & 1;     // input bits 5, 6 against output bits 5, 6
                 const v4i hi4 = {(int)hreg[s & 1][flip][0], (int)hreg[s & 1][flip][1], (int)hreg[s & 1][flip][2], (int)hreg[s & 1][flip][3]};
@@ -313,7 +304,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
         });
         // ---- quantize, pair, exchange
         uint32_t lo2[4], hi2[4];                        // per 32 channels: dwords of channels 8 q .. for q = 2 g, 2 g + 1
-        static_for6<0, 4>([&](auto nc) {
+        static_for<0, 4>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
             float v01[8], v23[8];
 #pragma unroll
@@ -327,7 +318,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 8
             lo2[n] = __builtin_amdgcn_perm(theirs, mine, 0x05040100u);   // group 2 g:     mine.lo16 | theirs.lo16 << 16
             hi2[n] = __builtin_amdgcn_perm(theirs, mine, 0x07060302u);   // group 2 g + 1: mine.hi16 | theirs.hi16 << 16
         });
-        static_for6<0, 2>([&](auto stc) {
+        static_for<0, 2>([&](auto stc) {
             constexpr int st = decltype(stc)::value;
             // tiles 2 st (for the lower half-wavefront) and 2 st + 1 (for the upper): the lower half gives its dwords of
             // the odd tile and takes the upper half's dwords of the even one
@@ -426,16 +417,6 @@ __global__ __launch_bounds__(256 * TOK) void k_rotate4096_quant_mfma(const __hal
 constexpr int kTokBlocks = 4;                       // 128 tokens per workgroup tile
 constexpr int kStageA = kTokBlocks * kChunkF6;      // their images for 128 channels: 12 KiB of LDS
 constexpr int kLoadsA = kStageA / 1024 / 4;         // direct loads to LDS per wavefront and stage: 3
-
-// Waits as instructions the compiler knows (not inline asm): its own bookkeeping of outstanding loads,
-// which places the waits for the weight registers, then counts from these.  gfx9 encoding of s_waitcnt:
-// vmcnt in bits 3:0 and 15:14, expcnt in 6:4, lgkmcnt in 11:8; all ones = no wait on that counter.
-template <int N> __device__ __forceinline__ void wait_vm6()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lds6() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
 
 // One workgroup's share of the product: the tiles b, b + G, b + 2 G ... of a list of GM x GN tiles of 128 CI
 // channels that starts at channel n_base (row tiles fastest; inside a round of G tiles each XCD takes a
@@ -569,11 +550,11 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
         }
         if (out) request_scales(n0, parity);
         __builtin_amdgcn_sched_barrier(0);
-        static_for6<0, R>([&](auto rc) {
+        static_for<0, R>([&](auto rc) {
             constexpr int r = decltype(rc)::value;
 #pragma unroll
             for (int t = 0; t < kLoadsA; ++t) load_a(t, r, r);
-            static_for6<0, CI>([&](auto ic) {
+            static_for<0, CI>([&](auto ic) {
                 load_b(std::integral_constant<int, r>{}, std::integral_constant<int, 0>{}, ic, r);
                 load_b(std::integral_constant<int, r>{}, std::integral_constant<int, 1>{}, ic, r);
             });
@@ -599,7 +580,7 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
         auto step = [&](auto slotc, auto stepc, int kt) {
             constexpr int slot = decltype(slotc)::value, st = decltype(stepc)::value;
             constexpr int rslot = st == 0 ? slot : (slot + 1) % R;      // where the other step's token images lie
-            static_for6<0, CI * kTokBlocks>([&](auto nc) {
+            static_for<0, CI * kTokBlocks>([&](auto nc) {
                 constexpr int n = decltype(nc)::value, i = n / kTokBlocks, j = n % kTokBlocks;
                 // formats 3, 3: E3M2 both; scale bytes 127 = 2^0
                 if constexpr (st == 0)
@@ -623,12 +604,12 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
             // them this wavefront has issued the second-step weights of that stage (2 CI), R - 2 whole stages
             // and the first-step weights of this one (2 CI).  (In the first R - 1 stages more lies behind
             // them, the previous tile's output stores included, so there the count is only stricter than needed.)
-            wait_lds6();
-            wait_vm6<4 * CI + (R - 2) * V>();
+            wait_lds();
+            wait_loads<4 * CI + (R - 2) * V>();
             asm volatile("s_barrier" ::: "memory");          // all have read stage kt; all of stage kt + 1 is in LDS
             __builtin_amdgcn_sched_barrier(0);
             step(std::integral_constant<int, slot>{}, std::integral_constant<int, 1>{}, kt);
-            wait_lds6();
+            wait_lds();
             __builtin_amdgcn_sched_barrier(0);
         };
         // Stage 0 has landed when all but the (R - 1) V newest operations are complete: behind its own V
@@ -636,7 +617,7 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
         // output stores (then more than stage 0 is waited for, but never a store: there are at most 8 CI <
         // (R - 1) V of them).
         static_assert(8 * CI <= (R - 1) * V, "the first wait of a tile would wait for output stores");
-        wait_vm6<(R - 1) * V>();
+        wait_loads<(R - 1) * V>();
         asm volatile("s_barrier" ::: "memory");
         if (out && lane < 8 * CI) {
             // The channel steps have landed (they were requested ahead of stage 0).  Turn them, in place, into
@@ -651,18 +632,18 @@ __device__ __forceinline__ void f6_persistent(const uint8_t* __restrict__ x6, co
         }
 #pragma unroll
         for (int p = 0; p < 2 * kTokBlocks; ++p) read_a(0, 0, p >> 1, p & 1, a0);
-        wait_lds6();
+        wait_lds();
         __builtin_amdgcn_sched_barrier(0);
         // the ring slot of a stage is a compile-time constant (its weights live in registers): the loop body
         // is R stages, the remaining nk % R stages follow one by one
         int kt = 0;
         for (; kt + R <= nk; kt += R)
-            static_for6<0, R>([&](auto uc) { stage(uc, kt + decltype(uc)::value); });
+            static_for<0, R>([&](auto uc) { stage(uc, kt + decltype(uc)::value); });
         const int rem = nk - kt;
-        static_for6<0, R - 1>([&](auto uc) {
+        static_for<0, R - 1>([&](auto uc) {
             if (decltype(uc)::value < rem) stage(uc, kt + decltype(uc)::value);
         });
-        wait_vm6<0>();      // the loads past the last stage: none may still be writing LDS or registers
+        wait_loads<0>();      // the loads past the last stage: none may still be writing LDS or registers
     };
 
     // ---- epilogue: out = fp16(fp32(acc * factor)) with the factors prepared in LDS: the same real product,

@@ -44,23 +44,6 @@ constexpr int STAGE = L * 4096, SCALES = kRing * STAGE;
 constexpr size_t kLds = (size_t)SCALES + 2 * 1024;
 static_assert(kLds <= 160 * 1024, "LDS");
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for_s(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for_s<I + 1, N>(f);
-    }
-}
-
-// (instructions the compiler knows, so that its own counting of outstanding operations starts from these)
-template <int N> __device__ __forceinline__ void wait_loads()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
-
 // The accumulator is tied to the result (the compiler's own form of the instruction may write another register and copy:
 // 3.4 times the clocks), and operands are six registers, not the builtin's eight.  Formats 3, 3: E3M2.
 // The compiler places no wait states around it: two are needed between a vector instruction that writes an operand and this
@@ -75,16 +58,6 @@ template <bool RESULTS> __device__ __forceinline__ void settle()
     if constexpr (RESULTS) asm volatile("s_nop 15\n\ts_nop 3");
     else asm volatile("s_nop 1");
     __builtin_amdgcn_sched_barrier(0);
-}
-
-// 64 x 16 bytes to LDS address lds_addr + T
-template <int T>
-__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
-{
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_offset), "s"(base), "s"(lds_addr), "n"(T)
-                 : "memory", "scc");
 }
 
 // The lane number, taken afresh: what derives from threadIdx would be held, or spilled, across the main loop, and a reload
@@ -156,7 +129,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         const int rx = m0 >> 5, rw = n0 >> 5, last_x = RBX - 1, last_w = RBW - 1;
         const uint32_t next_x = lane < 32 ? 0u : stride_x, next_w = lane < 32 ? 0u : stride_w;
         const uint32_t at = (uint32_t)(lane & 31) * 16;
-        static_for_s<0, L>([&](auto tc) PQ_INLINE {
+        static_for<0, L>([&](auto tc) PQ_INLINE {
             constexpr int t = decltype(tc)::value;
             const int q = wave + 4 * t, b = q / 3, part = q % 3;
             int rb = rx + b;
@@ -214,12 +187,12 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
             lds_dma16_at<0>(reinterpret_cast<const uint8_t*>(sw), (uint32_t)n * 4u, lds0 + SCALES + parity * 1024);
         }
         __builtin_amdgcn_sched_barrier(0);
-        static_for_s<0, kRing>([&](auto rc) PQ_INLINE {
+        static_for<0, kRing>([&](auto rc) PQ_INLINE {
             constexpr int s = decltype(rc)::value;
             const size_t at = (size_t)pair_of(s) * 2;
             const uint8_t *xk = uniform(x6 + at * stride_x + (s & 1) * kStep), *wk = uniform(w6 + at * stride_w + (s & 1) * kStep);
             const uint32_t fill = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024 + s * STAGE);
-            static_for_s<0, L>([&](auto tc) PQ_INLINE { dma(tc, xk, wk, fill); });
+            static_for<0, L>([&](auto tc) PQ_INLINE { dma(tc, xk, wk, fill); });
             __builtin_amdgcn_sched_barrier(0);
         });
     };
@@ -230,7 +203,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 
     // stores_behind: a full tile's stores were issued since this tile's first loads; they are not waited for
     auto compute = [&](bool stores_behind) PQ_INLINE {
-        static_for_s<0, TN>([&](auto ic) PQ_INLINE { static_for_s<0, TM>([&](auto jc) PQ_INLINE { 
+        static_for<0, TN>([&](auto ic) PQ_INLINE { static_for<0, TM>([&](auto jc) PQ_INLINE { 
             v4f& a = acc[decltype(ic)::value][decltype(jc)::value];
             a = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
             asm volatile("" : "+a"(a));                        // (written here, not moved down to the first use)
@@ -238,7 +211,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         // all matrix instructions of a half stage: channel operand i with every token operand, there and back
         auto multiply = [&](auto stc, auto&& between) PQ_INLINE {
             constexpr int st = decltype(stc)::value;
-            static_for_s<0, TN * TM>([&](auto nc) PQ_INLINE {
+            static_for<0, TN * TM>([&](auto nc) PQ_INLINE {
                 constexpr int n = decltype(nc)::value, i = n / TM, jj = n % TM, j = (i & 1) ? TM - 1 - jj : jj;
                 mfma_e3m2(acc[i][j], wgt[st][i], tok[st][j]);
                 between(nc);
@@ -271,7 +244,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         __builtin_amdgcn_sched_barrier(0);
         int slot = 0;
         asm volatile("" : "+s"(slot));                         // (addresses formed here, as for sx below)
-        static_for_s<0, READS>([&](auto nc) PQ_INLINE { read(S0{}, slot * STAGE, nc); });
+        static_for<0, READS>([&](auto nc) PQ_INLINE { read(S0{}, slot * STAGE, nc); });
         wait_lds();
         settle<false>();                                       // (the zeroed accumulators)
         for (int h = 0; h < H; h += 2) {
@@ -282,7 +255,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         }
         wait_loads<0>();                                       // none may still be writing LDS
         settle<true>();
-        static_for_s<0, TN>([&](auto ic) PQ_INLINE { static_for_s<0, TM>([&](auto jc) PQ_INLINE {
+        static_for<0, TN>([&](auto ic) PQ_INLINE { static_for<0, TM>([&](auto jc) PQ_INLINE {
             v4f& a = acc[decltype(ic)::value][decltype(jc)::value];
             asm volatile("" : "+a"(a));                        // (read behind the wait states above)
         }); });
@@ -311,7 +284,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
                 sc[i] = s;
             }
         }
-        static_for_s<0, TM>([&](auto jc) PQ_INLINE {
+        static_for<0, TM>([&](auto jc) PQ_INLINE {
             constexpr int j = decltype(jc)::value;
             const int m16 = mb + j * 16;
             if (acc_out) {
@@ -325,7 +298,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
             if (out) {
                 const int m = m16 + r;
                 __half* const row = out + (int64_t)m * N;
-                static_for_s<0, TN / 2>([&](auto pc) PQ_INLINE {
+                static_for<0, TN / 2>([&](auto pc) PQ_INLINE {
                     constexpr int i = 2 * decltype(pc)::value;
                     auto pack = [&](const v4f& a, const v4f& s) PQ_INLINE {
                         const __half2 lo = __floats2half2_rn(mul_rn(a.x, s.x), mul_rn(a.y, s.y));

@@ -101,15 +101,6 @@ struct MmaSched {
 };
 template <int TM, int TN, bool A8> inline constexpr MmaSched<TM, TN, A8> kSched{};
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 #define PQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 #define PQ_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
 

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "../../include/pq.h"
 
@@ -196,6 +197,35 @@ __device__ __forceinline__ void lds_dma16(const uint8_t* base, uint32_t lane_off
                  : "v"(lane_offset), "s"(base), "s"(lds_addr)
                  : "memory");     // (m0 is written here and used by nothing else in these kernels: the compiler keeps
                                   // no value in it and sets it itself right in front of the instructions that read it)
+}
+
+// The same to LDS address lds_addr + T.
+template <int T>
+__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t lane_offset, uint32_t lds_addr)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_offset), "s"(base), "s"(lds_addr), "n"(T)
+                 : "memory", "scc");
+}
+
+// Waits as instructions the compiler knows (not inline asm): its own bookkeeping of outstanding loads, which places the waits for
+// registers that it loads itself, then counts from these.  gfx9 encoding of s_waitcnt: vmcnt in bits 3:0 and 15:14, expcnt in 6:4,
+// lgkmcnt in 11:8; all ones = no wait on that counter.
+template <int N> __device__ __forceinline__ void wait_loads()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8)); }
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
 }
 
 // Until at most N memory operations of this wavefront are outstanding; they retire in order.
