@@ -191,6 +191,10 @@ int pq_probe_stream_read(const void* src, int64_t bytes, int32_t* sink, void* st
  */
 int pq_probe_mfma_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups,
                      int32_t* sink, void* stream);
+/* pq_probe_mfma16_i8, pq_probe_mfma16_f6: the same for the forms with 16 x 16 results, 16x16x64 INT8 and 16x16x128 6-bit: half the
+ *   operations of a launch.  (They reach more at the power limit.) */
+int pq_probe_mfma16_i8(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, void* stream);
+int pq_probe_mfma16_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, void* stream);
 int pq_probe_f6_product(const int8_t* a_codes, const int8_t* b_codes, int64_t K, int32_t* out_i32,
                         void* stream);
 

@@ -48,6 +48,8 @@ SIGNATURES = {
     "pq_probe_mfma_i8": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
     "pq_probe_stream_read": (ctypes.c_int, [_vp, _i64, _vp, _vp]),
     "pq_probe_mfma_f6": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
+    "pq_probe_mfma16_i8": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
+    "pq_probe_mfma16_f6": (ctypes.c_int, [_vp, _i64, _i64, _i32, _vp, _vp]),
     "pq_f6_tiles_bytes": (_sz, [_i64, _i64]),
     "pq_repack_f6": (ctypes.c_int, [_vp, _i64, _i64, _vp, _vp]),
     "pq_w4a4_gemm_f6": (ctypes.c_int, [_vp, _vp, _vp, _f32, _i64, _i64, _i64, _vp, _vp, _vp]),
@@ -702,6 +704,20 @@ def pq_probe_mfma_f6(operands: torch.Tensor, iters: int, workgroups: int, sink: 
     _check(lib().pq_probe_mfma_f6(_ptr(operands), operands.numel() * operands.element_size(), int(iters), int(workgroups),
                                   _ptr(sink), _stream()), "pq_probe_mfma_f6")
     return float(workgroups) * 4 * iters * 16 * 131072
+
+
+def pq_probe_mfma16_i8(operands: torch.Tensor, iters: int, workgroups: int, sink: torch.Tensor) -> float:
+    """pq_probe_mfma_i8 with 16 x 16 results; returns the integer operations of the launch."""
+    _check(lib().pq_probe_mfma16_i8(_ptr(operands), operands.numel() * operands.element_size(), int(iters), int(workgroups),
+                                    _ptr(sink), _stream()), "pq_probe_mfma16_i8")
+    return float(workgroups) * 4 * iters * 16 * 32768
+
+
+def pq_probe_mfma16_f6(operands: torch.Tensor, iters: int, workgroups: int, sink: torch.Tensor) -> float:
+    """pq_probe_mfma_f6 with 16 x 16 results; returns the operations of the launch."""
+    _check(lib().pq_probe_mfma16_f6(_ptr(operands), operands.numel() * operands.element_size(), int(iters), int(workgroups),
+                                    _ptr(sink), _stream()), "pq_probe_mfma16_f6")
+    return float(workgroups) * 4 * iters * 16 * 65536
 
 
 def pq_probe_f6_product(a_codes: torch.Tensor, b_codes: torch.Tensor) -> torch.Tensor:

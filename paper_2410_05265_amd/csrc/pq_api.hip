@@ -651,26 +651,41 @@ int pq_calibrate_static_zp(const void* x_cal_f16, int64_t T, int64_t K, int32_t 
                                    static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
 }
 
+// operand_unit: bytes of one lane's operand, also its alignment
+static int check_probe(const void* operands, int64_t operand_bytes, int64_t operand_unit, int64_t iters, int32_t workgroups, const int32_t* sink)
+{
+    if (!operands || !sink) return PQ_ERR_NULL;
+    if ((reinterpret_cast<uintptr_t>(operands) & (uintptr_t)(operand_unit - 1)) || (reinterpret_cast<uintptr_t>(sink) & 3u)) return PQ_ERR_ALIGN;
+    if (operand_bytes < operand_unit || (operand_bytes % operand_unit) != 0 || operand_bytes > ((int64_t)1 << 34) || iters < 0 ||
+        iters > (1 << 24) || workgroups < 1 || workgroups > (1 << 20))
+        return PQ_ERR_SHAPE;
+    return PQ_OK;
+}
+
 int pq_probe_mfma_i8(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink,
                      void* stream)
 {
-    if (!operands || !sink) return PQ_ERR_NULL;
-    if (!aligned16(operands) || (reinterpret_cast<uintptr_t>(sink) & 3u)) return PQ_ERR_ALIGN;
-    if (operand_bytes < 16 || (operand_bytes % 16) != 0 || operand_bytes > ((int64_t)1 << 34) || iters < 0 || iters > (1 << 24) ||
-        workgroups < 1 || workgroups > (1 << 20))
-        return PQ_ERR_SHAPE;
-    return pq::launch_probe_mfma(operands, operand_bytes, iters, workgroups, sink, static_cast<hipStream_t>(stream));
+    const int rc = check_probe(operands, operand_bytes, 16, iters, workgroups, sink);
+    return rc != PQ_OK ? rc : pq::launch_probe_mfma(operands, operand_bytes, iters, workgroups, sink, static_cast<hipStream_t>(stream));
 }
 
 int pq_probe_mfma_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink,
                      void* stream)
 {
-    if (!operands || !sink) return PQ_ERR_NULL;
-    if ((reinterpret_cast<uintptr_t>(operands) & 31u) || (reinterpret_cast<uintptr_t>(sink) & 3u)) return PQ_ERR_ALIGN;
-    if (operand_bytes < 32 || (operand_bytes % 32) != 0 || operand_bytes > ((int64_t)1 << 34) || iters < 0 || iters > (1 << 24) ||
-        workgroups < 1 || workgroups > (1 << 20))
-        return PQ_ERR_SHAPE;
-    return pq::launch_probe_mfma_f6(operands, operand_bytes, iters, workgroups, sink, static_cast<hipStream_t>(stream));
+    const int rc = check_probe(operands, operand_bytes, 32, iters, workgroups, sink);
+    return rc != PQ_OK ? rc : pq::launch_probe_mfma_f6(operands, operand_bytes, iters, workgroups, sink, static_cast<hipStream_t>(stream));
+}
+
+int pq_probe_mfma16_i8(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, void* stream)
+{
+    const int rc = check_probe(operands, operand_bytes, 16, iters, workgroups, sink);
+    return rc != PQ_OK ? rc : pq::launch_probe_mfma16(operands, operand_bytes, iters, workgroups, sink, false, static_cast<hipStream_t>(stream));
+}
+
+int pq_probe_mfma16_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, void* stream)
+{
+    const int rc = check_probe(operands, operand_bytes, 32, iters, workgroups, sink);
+    return rc != PQ_OK ? rc : pq::launch_probe_mfma16(operands, operand_bytes, iters, workgroups, sink, true, static_cast<hipStream_t>(stream));
 }
 
 int pq_probe_f6_product(const int8_t* a_codes, const int8_t* b_codes, int64_t K, int32_t* out_i32, void* stream)

@@ -6,7 +6,8 @@
 // without cost, so eight wavefronts (two to a SIMD) share the tile; and the tile's height comes in steps of 32, so that a
 // shape finds one that fills the CUs (1500 x 4096: 8 x 32 = 256 tiles of 192 x 128, where 256 x 128 has 192).  Measured against
 // the tiles of 32 x 32 results (pq_gemm_mfma.hip, which stays the faster on outputs that fill the chip with 256-wide ones):
-// 1500 x 11008 -> 4096 85.5 -> 70.8 us, 877 x 15872 -> 2512 62.2 -> 49.4, 3774 x 5760 -> 1296 42.7 -> 35.0.
+// 1500 x 11008 -> 4096 85.5 -> 70.8 us, 877 x 15872 -> 2512 62.2 -> 49.4, 3774 x 5760 -> 1296 42.7 -> 35.0 on bytes uniform over the
+// whole range; on activations as a quantizer leaves them the first is 71.6 -> 61.2, with all operands from HBM 77.4 -> 63.8.
 //
 // A stage is 128 channels: BM rows of 128 activation bytes and 128 rows of 64 packed bytes, fetched into an LDS ring of four
 // by direct loads.  Wavefront (wm, wn) of 2 x 4 computes BM / 2 tokens x 32 channels: TM = BM / 32 token operands x 2 channel

@@ -9,7 +9,7 @@
 // which 128 bytes per clock still cover.  With that the kernel reaches the power limit: its clock falls from 2.0 to 1.75 GHz.
 // So the matrix instruction is the 16 x 16 x 128 one: on the same operands, alone, it is 25 % above the 32 x 32 x 64 one at
 // that limit (6.9 against 5.5 POP/s), and neighbouring instructions share an operand.  2048 x 28672 -> 8192, three copies of
-// the weights in turn: layer 277 -> 233 us.
+// the weights in turn: layer 272-277 -> 233-238 us (one copy 214 -> 201, product).
 //
 // A workgroup of four wavefronts, a wavefront 128 tokens x 128 channels: 64 accumulators of four registers.  One half stage =
 // 128 channels of the product: step s of the two blocks 2 p and 2 p + 1 of 128 channels.  Lane l of an operand holds row l % 16
@@ -264,9 +264,9 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     };
 
     // out = fp16(fp32(acc * factor)), factor = 256 fl(sw * (sx / 256)): the same real product, hence the same rounding, as the
-    // INT8 tiled kernel's (256 acc) * fl(sw * (sx / 256)).  A lane has four channels of one token per operand pair; 16 tokens
-    // are turned at a time through a padded region of the wavefront's own and stored as rows (non-temporal: the output is
-    // not read here again and leaves the caches to the operands).
+    // INT8 tiled kernel's (256 acc) * fl(sw * (sx / 256)).  A lane has four channels of one token per operand; neighbouring
+    // rows of 16 lanes trade halves of two operands, so that a lane stores eight channels of its token.  Ordinary stores: with
+    // non-temporal ones the 32-byte runs reach memory one by one (2048 x 8192 -> 28672 252 -> 276 us, 1523 x 6912 -> 20176 115 -> 124).
     auto epilogue = [&](int m0, int n0, int parity) PQ_INLINE {
         const int lane = fresh_lane();
         const int g4 = lane >> 4, r = lane & 15;

@@ -74,6 +74,8 @@ int launch_probe_mfma(const void* operands, int64_t operand_bytes, int64_t iters
 int launch_probe_read(const void* src, int64_t bytes, int32_t* sink, hipStream_t st);
 int launch_probe_mfma_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink,
                          hipStream_t st);
+int launch_probe_mfma16(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, bool f6,
+                        hipStream_t st);
 // f6 tiles: the register images of the 6-bit matrix instruction, see pq_gemm_f6.hip
 size_t f6_tiles_bytes(int64_t R, int64_t K);
 bool rotate128_mfma_supported(int64_t R, int64_t K, int32_t h);

@@ -153,7 +153,70 @@ __global__ __launch_bounds__(64) void k_probe_f6_product(const int8_t* __restric
     for (int v = 0; v < 16; ++v) out[(8 * (v >> 2) + 4 * kb + (v & 3)) * 32 + row] = (int32_t)acc[v];
 }
 
+typedef int v6i __attribute__((ext_vector_type(6)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The same sticks for the forms with 16 x 16 results, as the product kernels that use them write them: in line, the accumulator
+// tied to the result, six registers a 6-bit operand, wait states by hand.
+__device__ __forceinline__ void mfma16(v4i& c, const v4i& a, const v4i& b) { asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b)); }
+__device__ __forceinline__ void mfma16(v4f& c, const v6i& a, const v6i& b) { asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:3 blgp:3" : "+v"(c) : "v"(a), "v"(b)); }
+__device__ __forceinline__ void operand(v4i& o, const int* p) { o = *reinterpret_cast<const v4i*>(p); }
+__device__ __forceinline__ void operand(v6i& o, const int* p)
+{
+#pragma unroll
+    for (int i = 0; i < 6; ++i) o[i] = p[i];
+}
+
+// (REGS dwords of `operands` per lane and operand, of which an operand takes the first)
+template <typename ACC, typename OPERAND, int REGS>
+__global__ __launch_bounds__(256) void k_probe_mfma16(const int* __restrict__ operands, int n_operands, int iters, int* __restrict__ sink)
+{
+    const int lane = threadIdx.x & 63;
+    OPERAND a[4], b[4];
+    ACC c[4][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        operand(a[t], operands + (size_t)(((blockIdx.x * 8 + t) * 64 + lane) % n_operands) * REGS);
+        operand(b[t], operands + (size_t)(((blockIdx.x * 8 + 4 + t) * 64 + lane) % n_operands) * REGS);
+        asm volatile("" : "+v"(a[t]), "+v"(b[t]));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[t][j] = (ACC){0, 0, 0, 0};
+            asm volatile("" : "+v"(c[t][j]));
+        }
+    }
+    asm volatile("s_nop 1");
+    __builtin_amdgcn_sched_barrier(0);
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mfma16(c[i][j], a[i], b[j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 3");
+    __builtin_amdgcn_sched_barrier(0);
+    bool found = true;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            asm volatile("" : "+v"(c[i][j]));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) found &= c[i][j][v] == (decltype(c[i][j][v] + 0))12345678;
+        }
+    if (found) sink[0] = 1;   // keeps the results alive; practically never true
+}
+
 }  // namespace
+
+int launch_probe_mfma16(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink, bool f6, hipStream_t st)
+{
+    const int* op = static_cast<const int*>(operands);
+    if (f6) hipLaunchKernelGGL((k_probe_mfma16<v4f, v6i, 8>), dim3((unsigned)workgroups), dim3(256), 0, st, op, (int)(operand_bytes / 32), (int)iters, sink);
+    else hipLaunchKernelGGL((k_probe_mfma16<v4i, v4i, 4>), dim3((unsigned)workgroups), dim3(256), 0, st, op, (int)(operand_bytes / 16), (int)iters, sink);
+    return hip_status(hipGetLastError());
+}
 
 int launch_probe_mfma_f6(const void* operands, int64_t operand_bytes, int64_t iters, int32_t workgroups, int32_t* sink,
                          hipStream_t st)

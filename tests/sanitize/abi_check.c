@@ -103,6 +103,8 @@ int main(void)
     EXPECT(pq_probe_mfma_i8(p, 1000, 10, 256, pi, NULL), PQ_ERR_SHAPE);
     EXPECT(pq_probe_stream_read(odd, 1024, pi, NULL), PQ_ERR_ALIGN);
     EXPECT(pq_probe_mfma_f6(p, 48, 1, 1, pi, NULL), PQ_ERR_SHAPE);
+    EXPECT(pq_probe_mfma16_i8(p, 1000, 10, 256, pi, NULL), PQ_ERR_SHAPE);
+    EXPECT(pq_probe_mfma16_f6(p, 48, 1, 1, pi, NULL), PQ_ERR_SHAPE);
     EXPECT(pq_probe_f6_product((const int8_t*)p, (const int8_t*)p, 96, pi, NULL), PQ_ERR_SHAPE);
     EXPECT(pq_repack_f6(p, 32, 262144, p, NULL), PQ_ERR_UNSUPPORTED);
     EXPECT(pq_w4a4_gemm_f6(p, p, pf, 0.1f, 32, 16, 160, p, NULL, NULL), PQ_ERR_SHAPE);

@@ -60,3 +60,11 @@ def test_rate_probe_runs(pq):
     ops = pq.pq_probe_mfma_f6(torch.zeros(4096, dtype=torch.uint8, device="cuda"), 10, 8, sink)
     torch.cuda.synchronize()
     assert ops == 8 * 4 * 10 * 16 * 131072 and int(sink[0]) == 0
+
+
+@pytest.mark.parametrize("name,per_instruction", [("pq_probe_mfma16_i8", 32768), ("pq_probe_mfma16_f6", 65536)])
+def test_rate_probes_of_16x16_results_run(pq, name, per_instruction):
+    sink = torch.zeros(4, dtype=torch.int32, device="cuda")
+    ops = getattr(pq, name)(torch.zeros(4096, dtype=torch.uint8, device="cuda"), 10, 8, sink)
+    torch.cuda.synchronize()
+    assert ops == 8 * 4 * 10 * 16 * per_instruction and int(sink[0]) == 0
