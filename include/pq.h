@@ -292,7 +292,8 @@ int pq_set_gemm_variant(int variant);
 
 /* Force the tiled kernel's tile (sweeps and tests; host, process-wide, atomic): -1 = by shape, 0 256x256,
  * 1 256x128, 2 128x128, 3 256x192, 4 64x128, 5-8 variants of these with more wavefronts or a deeper
- * ring; any forced tile also switches the mixed-width launch off.  Before the first call the value
+ * ring (8-bit codes: 0, 1 and 3 the same, 4 tiles of 64 x 128, others of 128 x 128, in their own kernel); any forced
+ * tile also switches the mixed-width launch off.  Before the first call the value
  * is that of the environment variable PQ_GEMM_TILE, read once at the first product of the process.
  * pq_set_gemm_f6_tile: the same for pq_w4a4_gemm_f6 (tiles of 128 tokens): -1 = by shape, 2 = 256 channels per
  * tile, 3 = the mix of 512 and 384 in one launch where N allows it, else 384, 4 = 512 (environment variable

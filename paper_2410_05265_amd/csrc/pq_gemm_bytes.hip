@@ -1,8 +1,8 @@
 // The product of int8 activations (grouped byte order) and packed 4-bit weights on tiles of 64 to 192 tokens x 128 channels.
 //
 // What bounds it: with random bytes the INT8 matrix instructions alone bring the chip to its power limit, and the form with
-// 16 x 16 results needs a quarter less energy than the 32 x 32 one (all CUs, operands in registers: 3.71 against 2.72 POP/s;
-// codes times 16: 4.21 against 3.33), so this kernel uses v_mfma_i32_16x16x64_i8.  Beside it only two other instructions fit
+// 16 x 16 results needs less energy than the 32 x 32 one (all CUs, operands in registers: 3.71 against 2.72 POP/s, codes times
+// 16 4.21 against 3.33; on another machine 3.94 against 3.38 and 4.58 against 4.07), so this kernel uses v_mfma_i32_16x16x64_i8.  Beside it only two other instructions fit
 // without cost, so eight wavefronts (two to a SIMD) share the tile; and the tile's height comes in steps of 32, so that a
 // shape finds one that fills the CUs (1500 x 4096: 8 x 32 = 256 tiles of 192 x 128, where 256 x 128 has 192).  Measured against
 // the tiles of 32 x 32 results (pq_gemm_mfma.hip, which stays the faster on outputs that fill the chip with 256-wide ones):

@@ -8,7 +8,7 @@
 // asks for 48 (173 us).  Both operands then pass through LDS (144 KiB of reads and writes per 1024 clocks of matrix work),
 // which 128 bytes per clock still cover.  With that the kernel reaches the power limit: its clock falls from 2.0 to 1.75 GHz.
 // So the matrix instruction is the 16 x 16 x 128 one: on the same operands, alone, it is 25 % above the 32 x 32 x 64 one at
-// that limit (6.9 against 5.5 POP/s), and neighbouring instructions share an operand.  2048 x 28672 -> 8192, three copies of
+// that limit (6.9 against 5.5 POP/s; on another machine 6.98 against 6.47), and neighbouring instructions share an operand.  2048 x 28672 -> 8192, three copies of
 // the weights in turn: layer 272-277 -> 233-238 us (one copy 214 -> 201, product).
 //
 // A workgroup of four wavefronts, a wavefront 128 tokens x 128 channels: 64 accumulators of four registers.  One half stage =
