@@ -273,6 +273,8 @@ int pq_linear(const void* x_f16, const void* wq_packed, const float* w_scale, fl
         pq::decode_supported(M, N, K, had_block))
         return pq::launch_decode(x_f16, nullptr, wq_packed, w_scale, act_scale, had_block, M, N, K, out_f16, nullptr,
                                  workspace, static_cast<hipStream_t>(stream));
+    if (g_variant == 0 && had_block <= 1 && pq::take_stream_fused(M, N, K, false))
+        return pq::launch_stream_fused(x_f16, wq_packed, w_scale, act_scale, M, N, K, out_f16, workspace, static_cast<hipStream_t>(stream));
     rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, workspace, stream);
     if (rc != PQ_OK) return rc;
     // whatever the workspace holds beyond the codes serves the product's split launch
@@ -298,12 +300,14 @@ int pq_linear2(const void* x_f16, const void* wq_a, const float* w_scale_a, int6
         return PQ_ERR_SHAPE;
     if (!aligned16(x_f16)) return PQ_ERR_ALIGN;
     // few tokens: one launch streams both matrices (the rule of pq_linear, on the rows of both)
+    const pq::DecodeSecond second{static_cast<const uint8_t*>(wq_b), w_scale_b, static_cast<__half*>(out_b_f16), (int)N_a};
     if (((g_variant == 0 && fused_few_tokens(M, K, had_block)) || g_variant == 4) &&
-        N_a + N_b <= (1 << 30) && pq::decode_supported(M, N_a + N_b, K, had_block)) {
-        const pq::DecodeSecond second{static_cast<const uint8_t*>(wq_b), w_scale_b, static_cast<__half*>(out_b_f16), (int)N_a};
+        N_a + N_b <= (1 << 30) && pq::decode_supported(M, N_a + N_b, K, had_block))
         return pq::launch_decode(x_f16, nullptr, wq_a, w_scale_a, act_scale, had_block, M, N_a + N_b, K, out_a_f16, nullptr,
                                  workspace, static_cast<hipStream_t>(stream), nullptr, 4, nullptr, &second);
-    }
+    if (g_variant == 0 && had_block <= 1 && pq::take_stream_fused(M, N_a + N_b, K, true))
+        return pq::launch_stream_fused(x_f16, wq_a, w_scale_a, act_scale, M, N_a + N_b, K, out_a_f16, workspace,
+                                       static_cast<hipStream_t>(stream), &second);
     rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, workspace, stream);
     if (rc != PQ_OK) return rc;
     const size_t codes = pq_linear_workspace_bytes(M, K);

@@ -137,6 +137,11 @@ int launch_decode(const void* x_f16, const void* xq_in, const void* wq, const fl
                   const float* srow = nullptr, int32_t abits = 4, const int32_t* zcorr = nullptr,
                   const DecodeSecond* second = nullptr);
 
+// Quantizer (no rotation) and product of up to 16 tokens in one launch; codes to xq_out as well, if it is not NULL
+bool take_stream_fused(int64_t M, int64_t N, int64_t K, bool two);
+int launch_stream_fused(const void* x, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                        void* xq_out, hipStream_t st, const DecodeSecond* second = nullptr);
+
 inline int hip_status(hipError_t e) { return e == hipSuccess ? PQ_OK : PQ_ERR_HIP; }
 
 // A kernel may use more than the default amount of dynamic LDS only after the runtime has been told,

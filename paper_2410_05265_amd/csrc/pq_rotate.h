@@ -127,6 +127,42 @@ __device__ __forceinline__ uint32_t quant_pack8(const float* v, const float* raw
     return (s - kMagicSum) ^ 0x88888888u;   // offset-binary nibbles -> two's complement
 }
 
+// The same codes for eight fp16 values as they were loaded, in half the instructions (34 against 65): the value times the
+// reciprocal step is added to 200.5 + 2^-16 in one fused multiply-add, whose result has 16 fractional bits, clamped to the ends of the
+// range, and its upper half is 0x4340 + 8 + floor(t + 1/2).  The sum is within 2^-17 + 2^-20 of the quotient's, so the floor is that of
+// the exact quotient unless the lower half is 0, 1 or 2; then the group takes the path above.
+__device__ __forceinline__ uint32_t quant_pack8_f16(const v4i raw, float mult, float step)
+{
+    constexpr float kMid = 200.5f + 0x1.0p-16f;
+    typedef uint16_t v2u16 __attribute__((ext_vector_type(2)));
+    float v[8];
+    uint32_t bits[8];
+    const __half2* h2 = reinterpret_cast<const __half2*>(&raw);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float2 f = __half22float2(h2[i]);
+        v[2 * i] = f.x;
+        v[2 * i + 1] = f.y;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) bits[i] = __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(v[i], mult, kMid), kMid - 8.0f, kMid + 7.0f));
+    uint32_t low[4], high[4];                              // values i and i + 4 in the halves
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        low[i] = __builtin_amdgcn_perm(bits[i + 4], bits[i], 0x05040100u);
+        high[i] = __builtin_amdgcn_perm(bits[i + 4], bits[i], 0x07060302u);
+    }
+    v2u16 least = __builtin_bit_cast(v2u16, low[0]);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) least = __builtin_elementwise_min(least, __builtin_bit_cast(v2u16, low[i]));
+    least = __builtin_elementwise_min(least, (v2u16){3, 3});
+    if (__builtin_amdgcn_ballot_w64(__builtin_bit_cast(uint32_t, least) != 0x00030003u) != 0) return quant_pack8<true>(v, v, mult, step);
+    uint32_t s = high[3];
+#pragma unroll
+    for (int i = 2; i >= 0; --i) s = (s << 4) + high[i];
+    return (s - 0x4340u * 0x1111u * 0x10001u) ^ 0x88888888u;
+}
+
 // 8-bit variant: codes in [-128, 127], one byte each.  The four even-channel bytes and the four
 // odd-channel bytes of the thread's eight channels are returned as two dwords.
 constexpr float kMagic8 = 12582912.0f;   // 1.5 * 2^23, bit pattern 0x4B400000: low byte = code

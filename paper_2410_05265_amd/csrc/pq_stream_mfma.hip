@@ -40,6 +40,7 @@
 // v_mfma_i32_16x16x64_i8 layout used (lane l, r = l % 16, g = l / 16):
 //   A: row r, bytes k = 16 g .. 16 g + 15;  B: column r, same bytes;  D: register v holds D[4 g + v][r].
 #include "pq_internal.h"
+#include "pq_rotate.h"
 
 #include <hip/hip_fp16.h>
 
@@ -72,6 +73,38 @@ __device__ __forceinline__ V pick4(const V s0, const V s1, const V s2, const V s
     r.z = g & 2 ? (g & 1 ? s3.z : s2.z) : (g & 1 ? s1.z : s0.z);
     r.w = g & 2 ? (g & 1 ? s3.w : s2.w) : (g & 1 ? s1.w : s0.w);
     return r;
+}
+
+// The products of one unit: a, b its two loads, src the lane (in bytes) that an operand's piece comes from, x this lane's
+// codes of the unit's first 64-byte block.
+template <int ABITS>
+__device__ __forceinline__ void multiply_unit(const v4i a, const v4i b, int src, const uint8_t* x, v4i& acc)
+{
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        v4i u, t, we, wo, xe, xo;
+        if (kb == 0) {
+            u.x = low_blocks(a.x, b.x); u.y = low_blocks(a.y, b.y);
+            u.z = low_blocks(a.z, b.z); u.w = low_blocks(a.w, b.w);
+        } else {
+            u.x = high_blocks(a.x, b.x); u.y = high_blocks(a.y, b.y);
+            u.z = high_blocks(a.z, b.z); u.w = high_blocks(a.w, b.w);
+        }
+        t.x = __builtin_amdgcn_ds_bpermute(src, u.x);
+        t.y = __builtin_amdgcn_ds_bpermute(src, u.y);
+        t.z = __builtin_amdgcn_ds_bpermute(src, u.z);
+        t.w = __builtin_amdgcn_ds_bpermute(src, u.w);
+        unpack16(t, we, wo);
+        if constexpr (ABITS == 8) {
+            xe = *(lds_cv4)(x + kb * 128);
+            xo = *(lds_cv4)(x + kb * 128 + 16);
+        } else {
+            const v4i xv = *(lds_cv4)(x + kb * 64);
+            unpack16(xv, xe, xo);
+        }
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(we, xe, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wo, xo, acc, 0, 0, 0);
+    }
 }
 
 // DEPTH: units (2 x 16 bytes per lane) a lane keeps in flight; the launcher picks the smallest
@@ -188,32 +221,7 @@ __global__ __launch_bounds__(1024) void k_stream_mfma(const uint8_t* __restrict_
         const int rg = ((int)blockIdx.x + ct * (int)gridDim.x) * RG + q;
         const v4i a = w[d][0], b = w[d][1];
         if (live && rg < R && p0 + cb < p1) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                v4i u, t, we, wo, xe, xo;
-                if (kb == 0) {
-                    u.x = low_blocks(a.x, b.x); u.y = low_blocks(a.y, b.y);
-                    u.z = low_blocks(a.z, b.z); u.w = low_blocks(a.w, b.w);
-                } else {
-                    u.x = high_blocks(a.x, b.x); u.y = high_blocks(a.y, b.y);
-                    u.z = high_blocks(a.z, b.z); u.w = high_blocks(a.w, b.w);
-                }
-                t.x = __builtin_amdgcn_ds_bpermute(src, u.x);
-                t.y = __builtin_amdgcn_ds_bpermute(src, u.y);
-                t.z = __builtin_amdgcn_ds_bpermute(src, u.z);
-                t.w = __builtin_amdgcn_ds_bpermute(src, u.w);
-                unpack16(t, we, wo);
-                const int p = p0 + cb;
-                if constexpr (ABITS == 8) {
-                    xe = *(lds_cv4)(xlane + p * 256 + kb * 128);
-                    xo = *(lds_cv4)(xlane + p * 256 + kb * 128 + 16);
-                } else {
-                    const v4i xv = *(lds_cv4)(xlane + p * 128 + kb * 64);
-                    unpack16(xv, xe, xo);
-                }
-                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(we, xe, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wo, xo, acc, 0, 0, 0);
-            }
+            multiply_unit<ABITS>(a, b, src, xlane + (p0 + cb) * (ABITS == 8 ? 256 : 128), acc);
         }
         if (live && ++cb == upt) {
             if (rg < R) {
@@ -282,6 +290,163 @@ __global__ __launch_bounds__(1024) void k_stream_mfma(const uint8_t* __restrict_
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) consume(d);
     }
+}
+
+constexpr int kEpoch = 4;                       // tasks whose partial tiles are in LDS at a time: 16 KiB each
+// The whole layer for up to 16 tokens without rotation in one launch: every workgroup quantizes all tokens for itself, and streams its rows
+// of one or two matrices as k_stream_mfma does.  What bounds it is the weight stream, and the vector instructions of the quantizer (13 x
+// 4096 -> 14336: 1.7 of 9.5 us).  So a wavefront quantizes its own slice of K alone, which needs no barrier in front of the products
+// (rows of up to eight units: the wavefronts of a slice share it, and one barrier), and leaves a partial tile per task in LDS with a plain
+// store; up to four tasks later one barrier and a sum over the slices, a value per thread, end them (atomic adds and a counter per
+// tile, as in k_stream_mfma, keep a wavefront waiting at the end of every task: with 16 slices 9.5 against 8.3 us with four).
+template <int DEPTH, int XB>
+__global__ __launch_bounds__(1024) void k_stream_fused(const __half* __restrict__ x, const uint8_t* __restrict__ wq,
+                                                     const float* __restrict__ sw, float sx, float mult, int M, int N, int K,
+                                                     int log2S, __half* __restrict__ out, uint8_t* __restrict__ xq_out, DecodeSecond two)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Kb = K >> 1, S = 1 << log2S, RG = 16 >> log2S;
+    const int P = Kb >> 7, upt = (P + S - 1) >> log2S;
+    const int q = wave >> log2S, s = wave & (S - 1);
+    const int p0 = s * upt;
+    const int p1 = p0 + upt < P ? p0 + upt : P;
+    const int R = N >> 4, T = (R + RG - 1) / RG;
+    const int my_tasks = (T - 1 - (int)blockIdx.x) / (int)gridDim.x + 1;      // (the grid is no larger than T)
+    const int r = lane & 15, g = lane >> 4;
+    const int xstride = Kb + 16;
+    uint8_t* const xs = smem + kEpoch * 16384;
+
+    // ---- this wavefront's channels of all tokens, two tokens of one unit per load: requested ahead of any weight
+    const int pairs = (M + 1) >> 1, half = lane >> 5, l32 = lane & 31;
+    const int own = q < pairs ? (pairs - 1 - q) >> (4 - log2S) : -1;             // pairs q, q + RG, .. of the slice are this wavefront's
+    const int pieces = p0 < p1 ? (own + 1) * (p1 - p0) : 0;
+    v4i xr[XB];
+    {
+        int p = p0, pair = q;
+#pragma unroll
+        for (int i = 0; i < XB; ++i) {
+            if (i < pieces) {
+                const int row = 2 * pair + half < M ? 2 * pair + half : M - 1;
+                xr[i] = *reinterpret_cast<const v4i*>(x + (uint32_t)row * (uint32_t)K + p * 256 + l32 * 8);
+                if ((pair += RG) >= pairs) { pair = q; ++p; }
+            }
+        }
+    }
+    // channel step of the output that this thread will own after the first epoch
+    auto step_at = [&](int first_task) {
+        const int t = tid >> 8, rg = ((int)blockIdx.x + (first_task + (t >> (4 - log2S))) * (int)gridDim.x) * RG + (t & (RG - 1));
+        int n = rg * 16 + ((tid >> 6) & 3) * 4 + (tid & 3);
+        n = n < N ? n : N - 1;
+        return *(n >= two.n1 ? two.sw + (n - two.n1) : sw + n);
+    };
+    float step = step_at(0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- ring of weight loads
+    v4i w[DEPTH][2];
+    auto row_group = [&](int rg) {                         // (the matrices behind one another: n1 % 16 == 0)
+        return rg * 16 < two.n1 ? wq + (int64_t)rg * 16 * Kb : two.wq + (int64_t)(rg * 16 - two.n1) * Kb;
+    };
+    const uint32_t wlane = (uint32_t)(lane >> 3) * (uint32_t)Kb + (lane & 7) * 16;
+    const int rg_first = (int)blockIdx.x * RG + q;
+    const uint8_t* const idle = rg_first < R && p0 < p1 ? row_group(rg_first) + p0 * 128 : wq;      // (in bounds, and its own lines)
+    auto issue = [&](int d, int task, int b) {
+        const int rg = ((int)blockIdx.x + task * (int)gridDim.x) * RG + q;
+        const bool valid = task < my_tasks && rg < R && p0 + b < p1;
+        const uint8_t* base = valid ? row_group(rg) + (p0 + b) * 128 : idle;
+        w[d][0] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(base + wlane));
+        w[d][1] = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(base + 8 * (int64_t)Kb + wlane));
+    };
+    int it = 0, ib = 0;
+    auto issue_next = [&](int d) {
+        __builtin_amdgcn_sched_barrier(0);
+        issue(d, it, ib);
+        if (++ib == upt) { ib = 0; ++it; }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    issue_next(0);
+
+    // ---- codes into LDS, for this wavefront alone, or for the RG wavefronts that share a slice.  The ring's other loads
+    // go out between the pieces: a CU has about 32 KiB on their way at a time, and a wavefront whose load is not accepted yet does not
+    // go on to its codes.
+    {
+        const bool copy = blockIdx.x == 0 && xq_out != nullptr;
+        int p = p0, pair = q;
+        static_for<0, XB>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, every = XB / 4;
+            if (i < pieces) {
+                const uint32_t code = rq::quant_pack8_f16(xr[i], mult, sx);
+                const int row = 2 * pair + half < M ? 2 * pair + half : M - 1;
+                *(rq::lds_u32_ptr)(xs + row * xstride + p * 128 + l32 * 4) = code;
+                if (copy) *reinterpret_cast<uint32_t*>(xq_out + (int64_t)row * Kb + p * 128 + l32 * 4) = code;
+                if ((pair += RG) >= pairs) { pair = q; ++p; }
+            }
+            if constexpr ((i + 1) % every == 0 && (i + 1) / every < DEPTH) issue_next((i + 1) / every);
+        });
+    }
+    if (RG > 1) lds_sync();
+    else asm volatile("" ::: "memory");                    // (its own codes: a wavefront's LDS operations execute in order)
+
+    // ---- units in order; a task ends with this wavefront's partial tile in LDS
+    const int src = (8 * (r & 7) + 4 * (r >> 3) + g) * 4;
+    const uint8_t* xlane = xs + (r < M ? r : M - 1) * xstride + g * 16;
+    v4i acc = {0, 0, 0, 0};
+    int ct = 0, cb = 0, open = 0;                          // task, its unit, tasks whose tiles are in LDS
+    auto consume = [&](int d) {
+        if (ct >= my_tasks) return;
+        const int rg = ((int)blockIdx.x + ct * (int)gridDim.x) * RG + q;
+        const v4i a = w[d][0], b = w[d][1];
+        if (rg < R && p0 + cb < p1) multiply_unit<4>(a, b, src, xlane + (p0 + cb) * 128, acc);
+        if (++cb < upt) return;
+        *(lds_v4)(smem + open * 16384 + wave * 1024 + lane * 16) = acc;
+        acc = (v4i){0, 0, 0, 0};
+        cb = 0;
+        ++ct;
+        ++open;
+    };
+    const int per_round = (DEPTH + upt - 1) / upt;         // tasks that may end in a round
+    // the open tiles, summed over the slices: a value per thread
+    auto finish = [&](bool last) {
+        if (!last && open + per_round <= kEpoch) return;
+        lds_sync();
+        const int first = ct - open;
+        for (int o = tid; o < open * RG * 256; o += 1024) {
+            const int t = o >> 8, e = t >> (4 - log2S), qq = t & (RG - 1);
+            const int rg = ((int)blockIdx.x + (first + e) * (int)gridDim.x) * RG + qq;
+            const uint8_t* at = smem + e * 16384 + qq * S * 1024 + (o & 255) * 4;
+            int sum = 0;
+            for (int i = 0; i < S; i += 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum += *(__attribute__((address_space(3))) const int*)(at + (i + j) * 1024);
+            const int tok = (o >> 2) & 15, n = rg * 16 + ((o >> 6) & 3) * 4 + (o & 3);
+            if (tok < M && rg < R) {
+                const bool b = n >= two.n1;
+                __half* dst = b ? two.out + (int64_t)tok * (N - two.n1) + (n - two.n1) : out + (int64_t)tok * two.n1 + n;
+                if (o != tid) step = *(b ? two.sw + (n - two.n1) : sw + n);
+                *dst = __float2half_rn(mul_rn((float)(sum >> 8), sx * step));
+            }
+        }
+        open = 0;
+        if (!last) {
+            step = step_at(ct);
+            lds_sync();
+        }
+    };
+    const int rounds = (my_tasks * upt + DEPTH - 1) / DEPTH;
+    for (int rnd = 1; rnd < rounds; ++rnd) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            consume(d);
+            issue(d, it, ib);
+            if (++ib == upt) { ib = 0; ++it; }
+        }
+        finish(false);
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) consume(d);
+    finish(true);
 }
 
 }  // namespace
@@ -380,6 +545,64 @@ int launch_stream_mfma(const void* xq, const void* wq, const float* sw, float sx
     return launch_stream_mfma(static_cast<const uint8_t*>(xq) + m1 * ka, wq, sw, sx, M - m1, N, K,
                               out ? static_cast<__half*>(out) + m1 * N : nullptr, acc ? acc + m1 * N : nullptr, st,
                               srow ? srow + m1 : nullptr, abits, zcorr);
+}
+
+// ---- the fused launch
+namespace {
+struct FusedPlan { int log2S, upt, pieces; size_t lds; };
+// slices of K: a wavefront each where the row has more than eight units, else as few as leave none without one
+FusedPlan fused_plan(int64_t M, int64_t K)
+{
+    FusedPlan p;
+    const int P = (int)(K / 256), pairs = (int)((M + 1) / 2);
+    p.log2S = P > 8 ? 4 : (P > 4 ? 3 : 2);
+    p.upt = (P + (1 << p.log2S) - 1) >> p.log2S;
+    p.pieces = ((pairs + (16 >> p.log2S) - 1) >> (4 - p.log2S)) * p.upt;
+    p.lds = (size_t)kEpoch * 16384 + (size_t)M * (K / 2 + 16);
+    return p;
+}
+bool fused_shape(int64_t M, int64_t N, int64_t K)
+{
+    return M >= 1 && M <= 16 && N >= 16 && (N % 16) == 0 && N <= (1 << 30) && K >= 256 && (K % 256) == 0 && K <= 65536 &&
+           fused_plan(M, K).pieces <= 16;
+}
+}  // namespace
+
+// Where one launch beats the quantizer's and the products'.  A piece (2 tokens x 256 channels a wavefront) costs a CU 0.2-0.4 us, the
+// quantizer launch 2.5-3.  One matrix, 5 to 16 tokens, before -> now, us, with up to eight pieces: 13 x 4096 -> 14336 10.1 -> 9.5, 8 x 4096
+// -> 14336 10.1 -> 8.1, 5 x 4096 -> 4096 6.0 -> 5.1, 7 x 1024 -> 13696 8.4 -> 4.6, 9 x 3072 -> 23136 14.1 -> 11.9 from HBM.  With several units
+// a wavefront the codes wait for more of the row, and a small matrix has arrived by then: 9 x 7680 -> 1760 7.5 -> 7.8, 9 x 7680 -> 2784 8.7 ->
+// 9.3, 16 x 8192 -> 8192 11.4 -> 13.9 stay.  Up to 4 tokens the dot products of pq_decode.hip are ahead (4 x 4096 -> 14336 7.6 against 7.7,
+// 2 x 4096 -> 4096 3.7 against 4.3).  Two matrices save a launch more: every one of 62 random shapes beyond what pq_decode.hip fuses gains,
+// 1.07 to 2.5 x (16 x 4096 -> 2 x 11008 19.3 -> 13.8, 12 x 2048 -> 2 x 4096 10.5 -> 6.5).
+bool take_stream_fused(int64_t M, int64_t N, int64_t K, bool two)
+{
+    if (!fused_shape(M, N, K)) return false;
+    if (two) return M >= 2;
+    const FusedPlan p = fused_plan(M, K);
+    return M >= 5 && p.pieces <= 8 && (p.upt == 1 || p.pieces <= 5 || N * (K / 2) >= 8000000);
+}
+
+int launch_stream_fused(const void* x, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                        void* xq_out, hipStream_t st, const DecodeSecond* second)
+{
+    if (!fused_shape(M, N, K)) return PQ_ERR_UNSUPPORTED;
+    const DecodeSecond two = second ? *second : DecodeSecond{nullptr, nullptr, nullptr, (int)N};
+    const FusedPlan p = fused_plan(M, K);
+    const int RG = 16 >> p.log2S;
+    const int64_t T = (N / 16 + RG - 1) / RG;
+    const unsigned grid = (unsigned)(T < 256 ? T : 256);
+    const int64_t units = ((T + grid - 1) / grid) * p.upt;
+    auto launch = [&](auto kern) {
+        static std::atomic<uint64_t> lds_ok{0};
+        if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), p.lds, st, static_cast<const __half*>(x), static_cast<const uint8_t*>(wq), sw,
+                           sx, (float)(1.0 / (double)sx), (int)M, (int)N, (int)K, p.log2S, static_cast<__half*>(out),
+                           static_cast<uint8_t*>(xq_out), two);
+        return hip_status(hipGetLastError());
+    };
+    if (p.pieces <= 8) return units <= 2 ? launch(k_stream_fused<2, 8>) : launch(k_stream_fused<4, 8>);
+    return units <= 2 ? launch(k_stream_fused<2, 16>) : launch(k_stream_fused<4, 16>);
 }
 
 }  // namespace pq
