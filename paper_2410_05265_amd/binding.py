@@ -1,4 +1,4 @@
-"""ctypes binding of libpq.so: argument marshalling only.
+"""Binding of libpq.so (ctypes, and native code for the calls that take least): argument marshalling only.
 
 Every step of the layer runs in the HIP kernels behind the C ABI declared in
 include/pq.h; torch is used here for device memory and the current stream, nothing else.
@@ -8,12 +8,14 @@ There is no CPU fallback: if the library has not been built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpq.so")
+CALL_PATH = os.path.join(_HERE, "_pq_call.so")
 
 PQ_OK, PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_ALIGN, PQ_ERR_SCALE, PQ_ERR_WORKSPACE, PQ_ERR_HIP, PQ_ERR_UNSUPPORTED = range(8)
 
@@ -86,6 +88,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_call = None          # the native call path of pq_linear and pq_linear2 (csrc/pq_call.cpp)
 
 
 class PQError(RuntimeError):
@@ -95,17 +98,22 @@ class PQError(RuntimeError):
 
 
 def lib() -> ctypes.CDLL:
-    """The loaded library; raises if libpq.so is missing (build it with build.build_lib())."""
-    global _lib
+    """The loaded library; raises if libpq.so or the native call path is missing (build them with build.build_lib())."""
+    global _lib, _call
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                "%s not found: the HIP library is not built (python -m paper_2410_05265_amd.build)" % LIB_PATH)
+        for path in (LIB_PATH, CALL_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    "%s not found: the HIP library is not built (python -m paper_2410_05265_amd.build)" % path)
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = res, args
-        _lib = L
+        spec = importlib.util.spec_from_file_location("_pq_call", CALL_PATH)
+        call = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(call)
+        call.bind(*(ctypes.cast(getattr(L, f), _vp).value for f in ("pq_linear", "pq_linear2")))
+        _call, _lib = call, L
     return _lib
 
 
@@ -204,6 +212,14 @@ def pq_linear_workspace_bytes(M: int, K: int) -> int:
 
 def pq_linear(x, wq, w_scale, act_scale, had_block, out=None, workspace=None):
     """The whole layer.  Returns (out fp16 [M,N], workspace uint8 holding the packed codes)."""
+    if out is not None and workspace is not None:
+        if _lib is None:
+            lib()
+        rc = _call.linear(x, wq, w_scale, act_scale, had_block, out, workspace)
+        if rc == PQ_OK:
+            return out, workspace
+        if rc > 0:
+            raise PQError(rc, "pq_linear")
     _dev(x, torch.float16, "x")
     _dev(wq, torch.uint8, "wq")
     _dev(w_scale, torch.float32, "w_scale")
@@ -222,6 +238,14 @@ def pq_linear(x, wq, w_scale, act_scale, had_block, out=None, workspace=None):
 
 def pq_linear2(x, wq_a, w_scale_a, wq_b, w_scale_b, act_scale, had_block, out_a=None, out_b=None, workspace=None):
     """Two layers on the same tokens (gate and up).  Returns (out_a, out_b, workspace)."""
+    if out_a is not None and out_b is not None and workspace is not None:
+        if _lib is None:
+            lib()
+        rc = _call.linear2(x, wq_a, w_scale_a, wq_b, w_scale_b, act_scale, had_block, out_a, out_b, workspace)
+        if rc == PQ_OK:
+            return out_a, out_b, workspace
+        if rc > 0:
+            raise PQError(rc, "pq_linear2")
     _dev(x, torch.float16, "x")
     M, K = x.shape
     for w, s in ((wq_a, w_scale_a), (wq_b, w_scale_b)):
