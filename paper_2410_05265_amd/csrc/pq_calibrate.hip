@@ -44,6 +44,7 @@ __device__ __forceinline__ float wave_sum(float a)
 // A step provider that quantizes nothing: it hands the rotated values back to the kernel (the
 // shared routine is then run in its store-nothing mode, BITS = 0).
 struct Capture {
+    static constexpr bool kMagnitudes = false;
     float* dst;   // G * 8 floats of the calling thread
     template <int NV>
     __device__ __forceinline__ void prepare(const float (&v)[NV])

@@ -85,6 +85,7 @@ __global__ __launch_bounds__(kThreads) void k_silu_mul_rotate_quant(const __half
 // its own rotated values; the steps go to scale_row[channel / gs] of the token's row.
 template <int G>
 struct GroupDynStep {
+    static constexpr bool kMagnitudes = true;
     double inv_sqrt_h;
     float clip;
     int log2gs;
@@ -212,6 +213,7 @@ __device__ __forceinline__ float lane_max(float amax)
 
 template <int BITS>
 struct DynamicStep {
+    static constexpr bool kMagnitudes = true;
     double inv_sqrt_h;
     float clip;
     float* red;        // 4 floats of LDS
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_dyn(const __half* __r
     const float step = dynamic_step<4>(amax, clip, inv_sqrt_h);
     if (tid == 0) row_scale[row] = step;
     uint32_t q[2];
-    rq::rotate4096_codes(v, (float)(inv_sqrt_h / (double)step), step, 0, q);
+    rq::rotate4096_codes(v, lane, (float)(inv_sqrt_h / (double)step), step, 0, q);
     // lane (block b, half g) has channels 32 n + 16 g of row b of 128 channels: 8 bytes
     const uint2 two = {q[0], q[1]};
     *reinterpret_cast<uint2*>(xq + row * (K >> 1) + blk * 2048 + (lane & 31) * 64 + n * 16 + (lane >> 5) * 8) = two;
@@ -306,6 +308,7 @@ __global__ __launch_bounds__(1024) void k_rotate4096_quant_dyn(const __half* __r
 // linear, as rotation absorption requires) followed by the static quantizer.  The step of the
 // normalised row is static; what the row supplies is 1 / rms.
 struct NormStep {
+    static constexpr bool kMagnitudes = false;
     double inv_step;   // 1 / s
     double inv_k;      // 1 / K
     float eps, step;
