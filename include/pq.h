@@ -309,7 +309,7 @@ int pq_set_gemm_f6_tile(int tile);
  */
 int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t prepacked, size_t plane_bytes);
 
-/* Whether pq_w4a4_gemm_f6 would take tiles of 256 tokens x 256 channels (host only; for sweeps and tests): 1 or 0. */
+/* Whether pq_w4a4_gemm_f6 would take near-square tiles, of up to 256 tokens x 256 channels (host only; for sweeps and tests): 1 or 0. */
 int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K);
 
 /* Which tile pq_w4a8_gemm_ws (and pq_gemm_dynamic_ws with 8 bits) would take with plane_bytes of scratch memory (host only; for

@@ -874,7 +874,7 @@ int pq_gemm_small_tile(int64_t M, int64_t N_a, int64_t N_b, int64_t K, int32_t p
 int pq_gemm_square_tiles(int64_t M, int64_t N, int64_t K)
 {
     if (M <= 0 || N <= 0 || K <= 0 || (K % 128) != 0 || (N % 16) != 0 || M > (1 << 30) || N > (1 << 30) || K > 262080) return 0;
-    return pq::gemm_f6_takes_square(M, N, K, false) ? 1 : 0;
+    return pq::gemm_f6_takes_square(M, N, K, false) != 0 ? 1 : 0;
 }
 
 int pq_gemm_w4a8_tile(int64_t M, int64_t N, int64_t K, size_t plane_bytes)

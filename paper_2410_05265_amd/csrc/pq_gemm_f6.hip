@@ -961,73 +961,114 @@ int launch_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t
 }
 }  // namespace
 
-// Outputs of few tiles leave most CUs without one and the others alone with K.  The persistent launch on 128 x 256
-// tiles was measured at 5 us + 0.33 us per 128-channel stage and round (0.5 with every CU busy) + its output; the
-// kernel that splits K over a workgroup's wavefronts takes over where its own estimate is lower (333 x 4096 x 4096:
-// 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6 us, 1024 x 4096 x 4096: 20 against 24 us, which stays here).  Two
-// matrices count as one of twice the height on either side (two launches of few tiles -> one, with the quantizer:
-// 128 tokens, 4096 -> 2 x 4096: 15.6 -> 11.9 us, 512 tokens, 4096 -> 2 x 1024: 17.1 -> 13.4).
-bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two)
-{
-    if (forced_f6_tile() != -1) return false;
-    const int64_t mats = two ? 2 : 1;
-    const int64_t tiles = mats * ((M + 127) / 128) * ((N + 255) / 256);
-    const double fill = tiles < kPersistentWorkgroups ? (double)tiles / kPersistentWorkgroups : 1.0;
-    const double persistent_us = 5.0 + (double)((tiles + kPersistentWorkgroups - 1) / kPersistentWorkgroups) * (double)(K / 128) * (0.33 + 0.17 * fill) +
-                                 (double)(mats * M) * N * 2 / 4.2e6;
-    return gemm_ksplit_f6_cost_us(M, N, two ? N : 0, K) < 0.97 * persistent_us;
-}
+namespace {
+// Channels per tile of the persistent launch: 512, 384 or 256 (CI = 4, 3, 2), or a mix of 512 and 384 in one launch where N = 512 a +
+// 384 b (a, b: tiles across, then a > 0); the choice minimises the estimated time of the busiest CU, `rounds` (a tile costs a fixed
+// part plus a part proportional to its width, 512 channels = 1).
+struct PersistentPlan {
+    int ci, a, b;
+    double rounds;
+};
 
-// Square tiles take in a fifth less; their rule is beside them.
-bool gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two)
+PersistentPlan persistent_plan(int64_t M, int64_t N, int64_t mats, int forced_tile)
 {
-    return !two && forced_f6_tile() == -1 && !gemm_f6_takes_ksplit(M, N, K, false) && gemm_f6_square_supported(M, N, K);
-}
-
-// Channels per tile: 512, 384 or 256 (CI = 4, 3, 2), or a mix of 512 and 384 in one launch where N = 512 a +
-// 384 b; the choice minimises the estimated time of the busiest CU (a tile costs a fixed part plus a part
-// proportional to its width).
-// pq_set_gemm_f6_tile: 2, 4 force one width, 3 the mix where N allows one (else 384 wide).
-// w6b != NULL: a second [N, K] matrix on the same tokens, in the same launch.
-int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                   int32_t* acc, hipStream_t st, const void* w6b, const float* swb, void* outb)
-{
-    const SecondF6 two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb)};
-    const int64_t mats = w6b ? 2 : 1;                                // matrices whose tiles follow one another
     const int64_t gm = (M + 127) / 128;
-    const int forced_tile = forced_f6_tile();
-    if (gemm_f6_takes_ksplit(M, N, K, w6b != nullptr))
-        return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
-    if (gemm_f6_takes_square(M, N, K, w6b != nullptr)) return launch_gemm_f6_square(x6, w6, sw, sx, M, N, K, out, acc, st);
-    auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };      // relative to a 512-wide tile = 1
+    auto cost_of = [](int ci) { return 0.35 + 0.1625 * ci; };
     auto makespan = [&](int64_t tiles_a, double ca, int64_t tiles_b, double cb) {
         // each list is dealt round-robin to its (up to) 256 workgroups; a CU hosts one workgroup of each list in turn
         const int64_t G = kPersistentWorkgroups;
         return (double)((mats * tiles_a + G - 1) / G) * ca + (double)((mats * tiles_b + G - 1) / G) * cb;
     };
-    int best_ci = 4, best_a = 0, best_b = 0;
-    double best = 1e300;
+    PersistentPlan p{4, 0, 0, 1e300};
     for (int ci = 2; ci <= 4; ++ci) {
         if (forced_tile != -1 && forced_tile != 3 && forced_tile != ci) continue;
         const int64_t gn = (N + 128 * ci - 1) / (128 * ci);
         if (gm * gn > (1 << 24)) continue;
         const double c = makespan(gm * gn, cost_of(ci), 0, 0.0);
-        if (c < best) { best = c; best_ci = ci; }
+        if (c < p.rounds) { p.rounds = c; p.ci = ci; }
     }
     if (forced_tile == -1 || forced_tile == 3) {
-        double bar = forced_tile == 3 ? 1e300 : best * 0.97;       // the mixed launch has to win by a margin
+        double bar = forced_tile == 3 ? 1e300 : p.rounds * 0.97;   // the mixed launch has to win by a margin
         for (int64_t b = 1; 384 * b < N; ++b) {
             if ((N - 384 * b) % 512 != 0) continue;
             const int64_t a = (N - 384 * b) / 512;
             if (a < 1 || gm * (a + b) > (1 << 24)) continue;
             const double c = makespan(gm * a, cost_of(4), gm * b, cost_of(3));
-            if (c < bar) { bar = c; best_a = (int)a; best_b = (int)b; }
+            if (c < bar) { bar = c; p.rounds = c; p.a = (int)a; p.b = (int)b; }
         }
     }
-    if (best_a > 0) return launch_f6<4, true>(x6, w6, sw, sx, M, N, K, best_a, best_b, out, acc, two, st);
-    const int gn = (int)((N + 128 * best_ci - 1) / (128 * best_ci));
-    if (best_ci == 2) return launch_f6<2, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
-    if (best_ci == 3) return launch_f6<3, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
+    return p;
+}
+
+// Which kernel a product takes: the one of least estimated time.  Two matrices count as one of twice the height.
+struct ProductPlan {
+    bool ksplit;
+    int square;                  // the tile of pq_gemm_f6_square.hip, or 0
+    PersistentPlan persistent;
+};
+
+// The estimates of the persistent launch and of the near-square tiles are fits to 191 measured shapes (24 to 9000 tokens, K 1024 to
+// 28672, N 512 to 30000, one matrix and two; three copies of the operands in turn; 7 % rms near the choice).  Near-square tiles against
+// the rule that knew only 256 x 256 ones of one matrix: geometric mean 1.08 over those; over 121 further shapes whose kernel
+// changed 1.17 (682 x 13568 -> 11024 135 -> 69 us, 2048 x 4096 -> 2 x 14336 150.5 -> 147.7, 963 x 6400 -> 2 x 10368 104.5 -> 87.8, 1557 x 28672
+// -> 1296 and like it, formerly K split, up to 2.7).  Where operands of 70 to 90 MB take turns by threes, so that they just fit the
+// memory-side cache, the persistent launch stays ahead (471 x 8960 -> 12336 36 -> 47, 2048 x 8192 -> 10240 92 -> 102): its outputs bypass
+// that cache.  With one copy (38.1 -> 37.5, 91.9 -> 90.8) or six (49.3 -> 49.4, 122 -> 103) it does not, so the rule ignores it.
+//
+// Rows under 6144 channels: the two lie close, and a round's fixed part counts for more.
+// - onto 8192 channels and more, of operands that the memory-side cache holds, near-square tiles need 7 % on paper (2048 x 4096 ->
+//   14336 66.5 -> 69.7, 1505 x 4864 -> 22784 101 -> 107; from HBM 900 x 4096 -> 49152 131 -> 114, 450 x 2048 -> 128256 121 -> 98);
+// - many of them onto output rows a multiple of 32 KiB apart stay: a round of 16 row tiles then writes to the same few memory
+//   channels (4096 x 3072 -> 65536 543 -> 581, -> 32768 237 -> 279, -> 16384 120 -> 135 (one copy 122 -> 108); -> 65552 646 -> 511);
+// - and those under 2048 channels with 64 MB of output: 4889 x 1280 -> 2 x 6496 74 -> 88 (one copy 75.2 -> 73.8).
+//
+// K split over the wavefronts of a workgroup is for outputs of few tiles, which leave most CUs without one and the others
+// alone with K (333 x 4096 x 4096: 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6; two launches of few tiles -> one, with the quantizer: 128
+// tokens, 4096 -> 2 x 4096 15.6 -> 11.9).  It has to be ahead of a second, older estimate of the persistent launch too, on tiles of
+// 128 x 256, which is the better one of outputs under 1200 channels (4948 x 2944 -> 576 15.2 against 19.5 us split).
+ProductPlan product_plan(int64_t M, int64_t N, int64_t K, bool two)
+{
+    const int forced_tile = forced_f6_tile();
+    const int64_t mats = two ? 2 : 1, G = kPersistentWorkgroups;
+    ProductPlan p{false, 0, persistent_plan(M, N, mats, forced_tile)};
+    if (forced_tile != -1) return p;
+    const double H = (double)(K / 128), out_mb = (double)(mats * M) * N * 2e-6;
+    const double rounds = p.persistent.rounds, area = (double)(mats * M) * N / (128.0 * 512 * G), idle = area < rounds ? 1.0 - area / rounds : 0.0;
+    double us = rounds * (10.657 + H * 0.9673 * (1.0 - 0.476 * idle)) - 0.01 * out_mb - 1.075, square_us;
+    const int tile = gemm_f6_square_tile(M, N, K, two, &square_us);
+    const bool shorter = K < 6144, wide = shorter && N >= 8192 && (M + N) * K / 4 * 3 < ((int64_t)128 << 20);
+    const bool stays = (shorter && M > 15 * 256 && N % 16384 == 0) || (K < 2048 && out_mb >= 64);
+    if (tile != 0 && !stays && us >= (wide ? 1.067 : 0.97) * square_us) {
+        p.square = tile;
+        us = square_us;
+    }
+    const int64_t tiles = mats * ((M + 127) / 128) * ((N + 255) / 256);
+    const double fill = tiles < G ? (double)tiles / G : 1.0;
+    const double narrow_us = 5.0 + (double)((tiles + G - 1) / G) * H * (0.33 + 0.17 * fill) + out_mb / 4.2;
+    const double split_us = gemm_ksplit_f6_cost_us(M, N, two ? N : 0, K);
+    p.ksplit = split_us < us && split_us < 0.97 * narrow_us;
+    if (p.ksplit) p.square = 0;
+    return p;
+}
+}  // namespace
+
+bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two) { return product_plan(M, N, K, two).ksplit; }
+int gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two) { return product_plan(M, N, K, two).square; }
+
+// pq_set_gemm_f6_tile: 2, 4 force one width of the persistent launch, 3 the mix where N allows one (else 384 wide).
+// w6b != NULL: a second [N, K] matrix on the same tokens, in the same launch.
+int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                   int32_t* acc, hipStream_t st, const void* w6b, const float* swb, void* outb)
+{
+    const ProductPlan plan = product_plan(M, N, K, w6b != nullptr);
+    if (plan.ksplit) return launch_gemm_ksplit_f6(x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, w6b ? N : 0, outb);
+    if (plan.square) return launch_gemm_f6_square(plan.square, x6, w6, sw, sx, M, N, K, out, acc, st, w6b, swb, outb);
+    const SecondF6 two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb)};
+    const int ci = plan.persistent.ci, a = plan.persistent.a, b = plan.persistent.b;
+    if (a > 0) return launch_f6<4, true>(x6, w6, sw, sx, M, N, K, a, b, out, acc, two, st);
+    const int gn = (int)((N + 128 * ci - 1) / (128 * ci));
+    if (ci == 2) return launch_f6<2, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
+    if (ci == 3) return launch_f6<3, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
     return launch_f6<4, false>(x6, w6, sw, sx, M, N, K, gn, 0, out, acc, two, st);
 }
 

@@ -1,5 +1,5 @@
-// The product of f6 tiles (layout and exactness: pq_gemm_f6.hip) on tiles of 256 tokens x 256 channels, for long rows and
-// for operands that come from HBM.
+// The product of f6 tiles (layout and exactness: pq_gemm_f6.hip) on near-square tiles, 256 tokens x 256 channels and smaller ones, of one
+// matrix or of two of one size for the same tokens.
 //
 // What bounds it: the operands' way into the CU and the chip's power limit.  A CU keeps about 32 KiB of lines in flight,
 // whatever the depth of the ring in front of it, so it takes in 113 KiB/us of what the L2 holds, 80 of what the memory-side
@@ -37,12 +37,15 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kBlock = 3072, kStep = 1536;          // 32 rows x 128 channels of the tiles; one of its two steps
 constexpr int kRing = 3;
 constexpr int kWorkgroups = 256;                    // persistent, one per CU
-constexpr int TM = 8, TN = 8;                       // operands of 16 tokens and of 16 channels per wavefront
-constexpr int BM = 32 * TM, BN = 32 * TN;
-constexpr int L = (TM + TN) * 3 / 4;                // direct loads per wavefront and half stage
-constexpr int STAGE = L * 4096, SCALES = kRing * STAGE;
-constexpr size_t kLds = (size_t)SCALES + 2 * 1024;
-static_assert(kLds <= 160 * 1024, "LDS");
+// TM, TN: operands of 16 tokens and of 16 channels per wavefront
+template <int TM_, int TN_> struct Tile {
+    static constexpr int TM = TM_, TN = TN_, BM = 32 * TM, BN = 32 * TN;
+    static constexpr int PIECES = 3 * (TM + TN);            // KiB of a half stage
+    static constexpr int L = (PIECES + 3) / 4;              // direct loads per wavefront and half stage (past the last piece: that again, into the pad)
+    static constexpr int STAGE = L * 4096, SCALES = kRing * STAGE, STEPS = (BN + 255) / 256 * 1024;
+    static constexpr size_t kLds = (size_t)SCALES + 2 * STEPS;
+    static_assert(kLds <= 160 * 1024, "LDS");
+};
 
 // The accumulator is tied to the result (the compiler's own form of the instruction may write another register and copy:
 // 3.4 times the clocks), and operands are six registers, not the builtin's eight.  Formats 3, 3: E3M2.
@@ -82,10 +85,20 @@ __device__ __forceinline__ const uint8_t* uniform(const uint8_t* p)
 // run is 8 row tiles x 4 panels and needs the least operand bytes.  With plain columns where GM is no multiple of 8 a run of 30000
 // rows was 32 row tiles x one panel (30000 x 6144 -> 16384 1795 -> 1490 us, 20000 x 28672 -> 2048 755 -> 629, 7000 x 5120 -> 28000 583 ->
 // 539; up to 16 row tiles level).
-__global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6,
-                                                       const float* __restrict__ sw, float sx, int M, int N, int K, int GM,
-                                                       int GN, __half* __restrict__ out, int32_t* __restrict__ acc_out)
+// A second matrix of the same size for the same tokens (w6 NULL: none); its tiles follow the first one's in the list.
+struct Second {
+    const uint8_t* w6;
+    const float* sw;
+    __half* out;
+};
+
+template <int TM, int TN, bool TWO>
+__global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6a,
+                                                       const float* __restrict__ swa, float sx, int M, int N, int K, int GM,
+                                                       int GN, __half* __restrict__ outa, int32_t* __restrict__ acc_out, Second two)
 {
+    using T = Tile<TM, TN>;
+    constexpr int BM = T::BM, BN = T::BN, L = T::L, STAGE = T::STAGE, SCALES = T::SCALES;
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -95,7 +108,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     const uint32_t stride_x = (uint32_t)RBX * kBlock, stride_w = (uint32_t)RBW * kBlock;
     const uint32_t lds0 = (uint32_t)(uintptr_t)PQS_LDS(smem);
     const int G = gridDim.x, bid = blockIdx.x;
-    const int total = GM * GN;
+    const int total = (TWO ? 2 : 1) * GM * GN;
     // XCDs that read the same panels start an eighth of K apart (integer sums do not care about the order)
     const int p_first = (int)(((int64_t)(bid & 7) * np) >> 3);
 
@@ -106,7 +119,17 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         return bid < cnt ? base + xcd_run(bid, cnt) : -1;
     };
     int m0 = 0, n0 = 0;                                        // the tile whose loads are in flight or whose main loop runs
+    const uint8_t* w6 = w6a;                                   // its matrix
+    const float* sw = swa;
+    __half* out = outa;
     auto move_to = [&](int t) PQ_INLINE {
+        if constexpr (TWO) {
+            const bool b = t >= GM * GN;
+            w6 = b ? two.w6 : w6a;
+            sw = b ? two.sw : swa;
+            out = b ? two.out : outa;
+            t = b ? t - GM * GN : t;
+        }
         const int group = t / (4 * GM), in = t - group * 4 * GM, wide = GN - 4 * group < 4 ? GN - 4 * group : 4;
         const int strip = in / (8 * wide), at = in - strip * 8 * wide, high = GM - 8 * strip < 8 ? GM - 8 * strip : 8;
         const int mt = 8 * strip + at % high, nt = 4 * group + at / high;
@@ -131,43 +154,45 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         const uint32_t at = (uint32_t)(lane & 31) * 16;
         static_for<0, L>([&](auto tc) PQ_INLINE {
             constexpr int t = decltype(tc)::value;
-            const int q = wave + 4 * t, b = q / 3, part = q % 3;
+            const int q = wave + 4 * t < T::PIECES ? wave + 4 * t : T::PIECES - 1, b = q / 3, part = q % 3;
             int rb = rx + b;
             rb = rb < last_x ? rb : last_x;
             const uint32_t off_x = (uint32_t)rb * kBlock + next_x;
             rb = rw + b - TM;
             rb = rb < last_w ? rb : last_w;
             const uint32_t off_w = (uint32_t)rb * kBlock + next_w;
-            voff[t] = (t < L / 2 ? off_x : off_w) + part * 512 + at;
+            voff[t] = (b < TM ? off_x : off_w) + part * 512 + at;
         });
     };
     auto dma = [&](auto tc, const uint8_t* xk, const uint8_t* wk, uint32_t fill) PQ_INLINE {
         constexpr int t = decltype(tc)::value;
-        static_assert(TM == TN, "half of the loads are the tokens'");
-        if constexpr (t < L / 2) lds_dma16_at<t * 4096>(xk, voff[t], fill);
-        else lds_dma16_at<t * 4096>(wk, voff[t], fill);
+        if constexpr (4 * t + 3 < 3 * TM) lds_dma16_at<t * 4096>(xk, voff[t], fill);
+        else if constexpr (4 * t >= 3 * TM) lds_dma16_at<t * 4096>(wk, voff[t], fill);
+        else lds_dma16_at<t * 4096>(wave + 4 * t < 3 * TM ? xk : wk, voff[t], fill);
     };
     // where this lane's images lie (an operand of odd number is the other half of the same block)
     const int g = (lane >> 4) & 1, b = lane >> 5, r = lane & 15;
     const uint32_t wide = (uint32_t)(g * 1024 + b * 512 + r * 16), narrow = (uint32_t)(b * 512 + g * 256 + r * 8);
-    static_assert(TM % 2 == 0 && TN % 2 == 0, "whole blocks per wavefront");
-    const uint32_t xw = (uint32_t)(wm * TM / 2) * kBlock + wide, xn = (uint32_t)(wm * TM / 2) * kBlock + narrow;
-    const uint32_t ww = (uint32_t)(TM + wn * TN / 2) * kBlock + wide, wnr = (uint32_t)(TM + wn * TN / 2) * kBlock + narrow;
+    // operands of even and of odd number from their own start: with an odd count the second wavefront starts inside a block
+    auto start = [&](int o, uint32_t plane, uint32_t halfstep) PQ_INLINE { return (uint32_t)(o >> 1) * kBlock + (uint32_t)(o & 1) * halfstep + plane; };
+    const uint32_t xw[2] = {start(wm * TM, wide, 256), start(wm * TM + 1, wide, 256)}, xn[2] = {start(wm * TM, narrow, 128), start(wm * TM + 1, narrow, 128)};
+    const uint32_t ww[2] = {start(2 * TM + wn * TN, wide, 256), start(2 * TM + wn * TN + 1, wide, 256)};
+    const uint32_t wnr[2] = {start(2 * TM + wn * TN, narrow, 128), start(2 * TM + wn * TN + 1, narrow, 128)};
     // LDS read n of the 2 (TM + TN) of a half stage: even n the 16-byte plane of an operand's image, odd n the 8-byte one
     auto read = [&](auto stc, uint32_t slot, auto nc) PQ_INLINE {
         constexpr int st = decltype(stc)::value, n = decltype(nc)::value, f = n / 2, j = f < TM ? f : f - TM;
         v6i& d = f < TM ? tok[st][j] : wgt[st][j];
         if constexpr ((n & 1) == 0) {
-            constexpr int off = (j >> 1) * kBlock + (j & 1) * 256 + (st == 0 ? 0 : 1024);
+            constexpr int off = (j >> 1) * kBlock + (st == 0 ? 0 : 1024);
             uint32_t at;
-            if constexpr (f < TM) at = xw; else at = ww;
+            if constexpr (f < TM) at = xw[j & 1]; else at = ww[j & 1];
             const v4i t = *(__attribute__((address_space(3))) const v4i*)(smem + slot + at + off);
             if constexpr (st == 0) { d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w; }
             else { d[2] = t.x; d[3] = t.y; d[4] = t.z; d[5] = t.w; }
         } else {
-            constexpr int off = (j >> 1) * kBlock + (j & 1) * 128 + (st == 0 ? 2048 : 0);
+            constexpr int off = (j >> 1) * kBlock + (st == 0 ? 2048 : 0);
             uint32_t at;
-            if constexpr (f < TM) at = xn; else at = wnr;
+            if constexpr (f < TM) at = xn[j & 1]; else at = wnr[j & 1];
             const v2i u = *(__attribute__((address_space(3))) const v2i*)(smem + slot + at + off);
             if constexpr (st == 0) { d[4] = u.x; d[5] = u.y; }
             else { d[0] = u.x; d[1] = u.y; }
@@ -177,14 +202,14 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
 
-    // The first loads of a tile: its channel steps (256 of them at most, one load of the first wavefront; read back in the
+    // The first loads of a tile: its channel steps (256 a load, one of the first wavefront; read back in the
     // epilogue, two regions in turn) and the whole ring.
     auto prefetch = [&](int parity) PQ_INLINE {
         addresses();
-        if (out && wave == 0) {
-            int n = n0 + 4 * fresh_lane();
+        if (out && wave < T::STEPS / 1024) {
+            int n = n0 + 256 * wave + 4 * fresh_lane();
             n = n + 4 <= N ? n : N - 4;
-            lds_dma16_at<0>(reinterpret_cast<const uint8_t*>(sw), (uint32_t)n * 4u, lds0 + SCALES + parity * 1024);
+            lds_dma16_at<0>(reinterpret_cast<const uint8_t*>(sw), (uint32_t)n * 4u, lds0 + SCALES + parity * T::STEPS + wave * 1024);
         }
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, kRing>([&](auto rc) PQ_INLINE {
@@ -198,7 +223,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     };
 
     // stores of a full tile's output per wavefront, issued behind the next tile's first loads
-    constexpr int STORES = TM * TN / 2;
+    constexpr int STORES = TM * ((TN + 1) / 2);
     static_assert((kRing - 1) * L + STORES < 64, "vmcnt has six bits");
 
     // stores_behind: a full tile's stores were issued since this tile's first loads; they are not waited for
@@ -267,10 +292,10 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     // INT8 tiled kernel's (256 acc) * fl(sw * (sx / 256)).  A lane has four channels of one token per operand; neighbouring
     // rows of 16 lanes trade halves of two operands, so that a lane stores eight channels of its token.  Ordinary stores: with
     // non-temporal ones the 32-byte runs reach memory one by one (2048 x 8192 -> 28672 252 -> 276 us, 1523 x 6912 -> 20176 115 -> 124).
-    auto epilogue = [&](int m0, int n0, int parity) PQ_INLINE {
+    auto epilogue = [&](int m0, int n0, __half* out, int parity) PQ_INLINE {
         const int lane = fresh_lane();
         const int g4 = lane >> 4, r = lane & 15;
-        const float* scl = reinterpret_cast<const float*>(smem + SCALES + parity * 1024) + wn * (16 * TN);
+        const float* scl = reinterpret_cast<const float*>(smem + SCALES + parity * T::STEPS) + wn * (16 * TN);
         const int mb = m0 + wm * (16 * TM), nb = n0 + wn * (16 * TN);
         float step = sx;
         asm volatile("" : "+s"(step));                         // (the product is formed here, not held across the main loop)
@@ -298,16 +323,21 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
             if (out) {
                 const int m = m16 + r;
                 __half* const row = out + (int64_t)m * N;
+                auto pack = [&](const v4f& a, const v4f& s) PQ_INLINE {
+                    const __half2 lo = __floats2half2_rn(mul_rn(a.x, s.x), mul_rn(a.y, s.y));
+                    const __half2 hi = __floats2half2_rn(mul_rn(a.z, s.z), mul_rn(a.w, s.w));
+                    v2i val;
+                    val.x = *reinterpret_cast<const int*>(&lo);
+                    val.y = *reinterpret_cast<const int*>(&hi);
+                    return val;
+                };
+                if constexpr (TN & 1) {                        // the last operand alone: four channels a lane
+                    const int n = nb + (TN - 1) * 16 + 4 * g4;
+                    const v2i val = pack(acc[TN - 1][j], sc[TN - 1]);
+                    if (m < M && n + 4 <= N) *reinterpret_cast<v2i*>(row + n) = val;
+                }
                 static_for<0, TN / 2>([&](auto pc) PQ_INLINE {
                     constexpr int i = 2 * decltype(pc)::value;
-                    auto pack = [&](const v4f& a, const v4f& s) PQ_INLINE {
-                        const __half2 lo = __floats2half2_rn(mul_rn(a.x, s.x), mul_rn(a.y, s.y));
-                        const __half2 hi = __floats2half2_rn(mul_rn(a.z, s.z), mul_rn(a.w, s.w));
-                        v2i val;
-                        val.x = *reinterpret_cast<const int*>(&lo);
-                        val.y = *reinterpret_cast<const int*>(&hi);
-                        return val;
-                    };
                     const v2i even = pack(acc[i][j], sc[i]);
                     // rows 0 .. 3 of 16 lanes hold channels 0-3, 4-7, 8-11, 12-15 of either operand; after the swap rows 0
                     // and 2 hold 0-7 and 8-15 of the even one, rows 1 and 3 of the odd one
@@ -330,53 +360,82 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     for (int seq = 1, parity = 0;; ++seq, parity ^= 1) {
         compute(stores_behind);
         const int m_done = m0, n_done = n0;
+        __half* const out_done = out;
         t = tile_of(seq);
         if (t >= 0) {
             move_to(t);
             prefetch(parity ^ 1);
         }
-        epilogue(m_done, n_done, parity);
+        epilogue(m_done, n_done, out_done, parity);
         if (t < 0) break;
-        stores_behind = out && m_done + BM <= M && n_done + BN <= N;
+        stores_behind = out_done && m_done + BM <= M && n_done + BN <= N;
     }
+}
+
+// The tiles that are built, 10 * TM + TN.  (Of fifteen swept, those that were the fastest somewhere; the first one on equal estimates.)
+constexpr int kTiles[] = {88, 78, 68, 58, 48, 87, 66, 46, 44, 64};
+
+template <int TM, int TN>
+int launch_tile(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out, int32_t* acc,
+                hipStream_t st, const Second& two)
+{
+    using T = Tile<TM, TN>;
+    const int GM = (int)((M + T::BM - 1) / T::BM), GN = (int)((N + T::BN - 1) / T::BN);
+    const int64_t tiles = (two.w6 ? 2 : 1) * (int64_t)GM * GN;
+    auto launch = [&](auto twoc) {
+        auto kern = k_gemm_f6_square<TM, TN, decltype(twoc)::value>;
+        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per tile and count)
+        if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), T::kLds, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tiles < kWorkgroups ? tiles : kWorkgroups)), dim3(256), T::kLds, st,
+                           static_cast<const uint8_t*>(x6), static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, GN,
+                           static_cast<__half*>(out), acc, two);
+        return hip_status(hipGetLastError());
+    };
+    return two.w6 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 }  // namespace
 
-// Where these tiles are the faster ones.  `use` is the share of the chip's rounds of 256 tiles that the output fills, `big`: the
-// operands are half the memory-side cache and more, so that they come from HBM in a program that has others as well.  Products, 128-row
-// tiles -> these, three copies of the operands in turn / one copy, us:
-//   rows of 6144 channels and more, the rounds 9/10 full: 4096 x 14336 -> 4096 114 -> 110 / 118 -> 112, 2048 x 8192 -> 8192 69.4 -> 66.4,
-//     3604 x 14848 -> 4192 134 -> 112, 1523 x 6912 -> 20176 138 -> 112;
-//   from 0.74 on where the operands are big: 512 x 8192 -> 28672 83.6 -> 68.7, 4445 x 28416 -> 2816 236 -> 192 / 186 -> 180, 2048 x 8192 ->
-//     28672 273 -> 248 / 241 -> 243; below that the narrower tiles of the other kernel leave fewer CUs idle (1285 x 24832 -> 8400, 0.64);
-//   shorter rows, from 2048 channels on, where the operands are big and the rounds two and more, since a round's fixed cost weighs
-//     more: 450 x 2048 -> 128256 121 -> 98, 900 x 4096 -> 49152 131 -> 114, 2048 x 4096 -> 128256 723 -> 579, 12000 x 4096 -> 49152 1539 ->
-//     1299 (one copy 148 -> 157 at 1024 x 4096 -> 65536, 370 -> 304 at -> 128256).  One round: 256 x 4096 -> 49152 41.8 -> 44.7 / 32.2 -> 37.3;
-//     shorter still: 450 x 512 -> 400000 183 -> 171 / 151 -> 169, 8192 x 2048 -> 8192, not big, 98 -> 101.
-// Many short rows onto output rows 128 KiB apart stay with the other kernel: a round of 16 row tiles then writes to the same few
-// memory channels (4096 x 3072 -> 65536 543 -> 581, -> 65552 646 -> 511; 1024 x 3072 -> 65536 153 -> 124).
-bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K)
+// The least estimate: the fits of the header, plus the output (0.08 us per MB beside the main loops), and a half stage takes up to a third
+// less the fewer CUs share the memory side.  Rows under 1024 channels were not swept and stay with the other kernel (450 x 512 ->
+// 400000 on 256 x 256 151 -> 169 us).
+int gemm_f6_square_tile(int64_t M, int64_t N, int64_t K, bool two, double* us)
 {
-    const int64_t gm = (M + BM - 1) / BM, tiles = gm * ((N + BN - 1) / BN), rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
-    if (K % 256 != 0 || tiles >= (1 << 24)) return false;
-    const double use = (double)M * (double)N / ((double)rounds * kWorkgroups * BM * BN);
-    const bool big = (M + N) * K / 4 * 3 >= ((int64_t)128 << 20);
-    if (K >= 6144) return use >= (big ? 0.74 : 0.9);
-    return K >= 2048 && big && use >= 0.74 && rounds >= 2 && !(gm >= 16 && N % 65536 == 0);
+    *us = 1e30;
+    if (K % 256 != 0 || K < 1024) return 0;
+    const int64_t mats = two ? 2 : 1;
+    const double H = (double)(K / 128), out_mb = (double)(mats * M) * N * 2e-6;
+    int best = 0;
+    for (const int tile : kTiles) {
+        const int tm = tile / 10, tn = tile % 10;
+        const int64_t gm = (M + 32 * tm - 1) / (32 * tm), gn = (N + 32 * tn - 1) / (32 * tn), tiles = mats * gm * gn;
+        const int64_t rounds = (tiles + kWorkgroups - 1) / kWorkgroups;
+        if (tiles >= (1 << 24)) continue;
+        const double fill = (double)tiles / (double)(rounds * kWorkgroups);
+        const double half_stage = (0.00798 * tm * tn + 0.02276 * (tm + tn)) * (1.0 - 0.33118 * (1.0 - fill));
+        const double t = 1.74267 + 0.08083 * out_mb + (double)rounds * (1.05165 + 0.08898 * tm * tn + H * half_stage);
+        if (t < *us) { *us = t; best = tile; }
+    }
+    return best;
 }
 
-int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                          int32_t* acc, hipStream_t st)
+int launch_gemm_f6_square(int tile, const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st, const void* w6b, const float* swb, void* outb)
 {
-    const int GM = (int)((M + BM - 1) / BM), GN = (int)((N + BN - 1) / BN);
-    static std::atomic<uint64_t> lds_ok{0};
-    if (allow_dynamic_lds(reinterpret_cast<const void*>(k_gemm_f6_square), kLds, lds_ok) != PQ_OK) return PQ_ERR_HIP;
-    const int64_t tiles = (int64_t)GM * GN;
-    hipLaunchKernelGGL(k_gemm_f6_square, dim3((unsigned)(tiles < kWorkgroups ? tiles : kWorkgroups)), dim3(256), kLds, st,
-                       static_cast<const uint8_t*>(x6), static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, GN,
-                       static_cast<__half*>(out), acc);
-    return hip_status(hipGetLastError());
+    const Second two{static_cast<const uint8_t*>(w6b), swb, static_cast<__half*>(outb)};
+    switch (tile) {
+    case 88: return launch_tile<8, 8>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 78: return launch_tile<7, 8>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 68: return launch_tile<6, 8>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 58: return launch_tile<5, 8>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 48: return launch_tile<4, 8>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 87: return launch_tile<8, 7>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 66: return launch_tile<6, 6>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 46: return launch_tile<4, 6>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 44: return launch_tile<4, 4>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    case 64: return launch_tile<6, 4>(x6, w6, sw, sx, M, N, K, out, acc, st, two);
+    }
+    return PQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace pq

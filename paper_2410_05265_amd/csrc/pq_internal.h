@@ -88,10 +88,11 @@ int launch_quant_f6(const void* x, int64_t R, int64_t K, int32_t h, float act_sc
 int launch_repack_f6(const void* codes, int64_t R, int64_t K, void* out, hipStream_t st);
 int launch_gemm_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                    int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
-// 256 x 256 tiles (pq_gemm_f6_square.hip) and where they are the faster ones
-bool gemm_f6_square_supported(int64_t M, int64_t N, int64_t K);
-int launch_gemm_f6_square(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
-                          int32_t* acc, hipStream_t st);
+// Near-square tiles (pq_gemm_f6_square.hip): the one of least estimated time, 10 * operands of 16 tokens + of 16 channels per wavefront (a
+// tile is 32 x 32 times that), its estimate in microseconds, 0 for none; and its launch.
+int gemm_f6_square_tile(int64_t M, int64_t N, int64_t K, bool two, double* us);
+int launch_gemm_f6_square(int tile, const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
+                          int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, void* outb = nullptr);
 int launch_probe_f6_product(const int8_t* a, const int8_t* b, int64_t K, int32_t* out, hipStream_t st);
 // Small tiles with K split over the wavefronts of a workgroup (pq_gemm_ksplit.hip): estimated microseconds (a large
 // number where the shape is not taken), the tile behind the estimate (10 * blocks of 32 tokens + blocks of 32 channels; 0 for
@@ -101,9 +102,9 @@ double gemm_ksplit_f6_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
 double gemm_ksplit_i8_cost_us(int64_t M, int64_t N, int64_t Nb, int64_t K);
 int gemm_ksplit_f6_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
 int gemm_ksplit_i8_tile(int64_t M, int64_t N, int64_t Nb, int64_t K);
-// Whether launch_gemm_f6 takes them, or the 256 x 256 tiles, for one matrix [N, K], or for two of that size.
+// Whether launch_gemm_f6 takes them, or which of the near-square tiles (0: none), for one matrix [N, K], or for two of that size.
 bool gemm_f6_takes_ksplit(int64_t M, int64_t N, int64_t K, bool two);
-bool gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two);
+int gemm_f6_takes_square(int64_t M, int64_t N, int64_t K, bool two);
 int launch_gemm_ksplit_f6(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out,
                           int32_t* acc, hipStream_t st, const void* w6b = nullptr, const float* swb = nullptr, int64_t Nb = 0,
                           void* outb = nullptr);
