@@ -803,6 +803,52 @@ bool pick_dual(int64_t M, int64_t N, int* n1_out, int* n2_out, double* cost_out 
     return found;
 }
 
+// Sizes of one launch's tiles and their estimate in microseconds: fixed + output MB * out + rounds of 256 tiles * round + stages of 128
+// channels * (rounds * part + tiles / 256 * full): a stage costs `part` however few CUs are busy (its loads and barriers) and up to
+// `full` more where all are (power).  Fitted to 104 shapes, 65 to 8000 tokens, three copies of the operands in turn, 3 to 6 % rms.
+struct PackedTile { int bm, bn; double fixed, out, round, part, full; };
+constexpr PackedTile kPackedTiles[] = {
+    {128, 128, 3.610, 0.212, 0.000, 0.309, 0.108}, {256, 192, 1.289, 0.145, 5.258, 0.694, 0.328}, {192, 128, 1.864, 0.145, 2.178, 0.387, 0.238},
+    {320, 192, 1.155, 0.143, 5.825, 0.861, 0.349}, {192, 192, 2.063, 0.184, 2.898, 0.527, 0.270}, {128, 192, 1.366, 0.020, 4.041, 0.402, 0.224},
+    {192, 256, 1.506, 0.135, 5.265, 0.701, 0.319}, {64, 128, 3.430, 0.159, 0.000, 0.196, 0.091},  {256, 256, 0.638, 0.110, 7.163, 0.918, 0.369},
+    {256, 128, 1.328, 0.137, 3.433, 0.518, 0.262}, {320, 128, 1.683, 0.202, 3.150, 0.624, 0.267}, {192, 320, 0.561, 0.093, 7.671, 0.830, 0.393},
+    {128, 320, 1.380, 0.071, 5.771, 0.552, 0.352}};
+
+double packed_us(const PackedTile& t, int64_t M, int64_t N, int64_t K)
+{
+    const int64_t tiles = (M + t.bm - 1) / t.bm * ((N + t.bn - 1) / t.bn), rounds = (tiles + 255) / 256;
+    return t.fixed + (double)M * N * 2e-6 * t.out + (double)rounds * t.round +
+           (double)(K / 128) * ((double)rounds * t.part + (double)tiles / 256.0 * t.full);
+}
+
+// What a packed product runs on: cfg >= 0: that configuration (of kCfgs; forced, or the area model's); n1 > 0: n1 panels of 256 and n2 of
+// 192; else tiles of bm x bn.  A size of its own is taken where its estimate is 2 % under that of the five the area model knows, or of the
+// mixed launch: 1.11 x, geometric mean, over 110 further shapes where it is, the slowest 0.98 x.  300 x 4096 -> 28672 45.6 -> 33.9 us, 359 x 4096 ->
+// 12160 27.5 -> 22.3, 1308 x 11520 -> 6896 94.5 -> 78.9, 777 x 4096 -> 11008 37.4 -> 34.8, 1500 x 11008 -> 4096 65.3 -> 57.8.
+struct PackedPlan { int cfg, n1, n2, bm, bn; };
+
+PackedPlan plan_packed(int64_t M, int64_t N, int64_t K)
+{
+    PackedPlan p{-1, 0, 0, 0, 0};
+    if (forced_tile() >= 0) { p.cfg = forced_tile(); return p; }
+    double us, dual;
+    if (pick_dual(M, N, &p.n1, &p.n2, &dual)) {
+        const double area = dual / 65536.0;                      // in 256 x 256 tiles of the busiest CU
+        us = 0.638 + (double)M * N * 2e-6 * 0.110 + area * 7.163 + (double)(K / 128) * (area * 0.918 + (double)M * N / (256.0 * 65536.0) * 0.369);
+    } else {
+        const TileCfg& c = kCfgs[pick_cfg(M, N)];
+        p.bm = c.bm;
+        p.bn = c.bn;
+        us = 1e300;
+        for (const PackedTile& t : kPackedTiles)
+            if (t.bm == c.bm && t.bn == c.bn) us = packed_us(t, M, N, K);
+    }
+    us *= 0.98;
+    for (const PackedTile& t : kPackedTiles)
+        if (const double v = packed_us(t, M, N, K); v < us) { us = v; p.n1 = p.n2 = 0; p.bm = t.bm; p.bn = t.bn; }
+    return p;
+}
+
 // Tile height and number of K runs of the split launch, from a cost model in microseconds
 // (per 128-channel stage: 0.27-0.33 for a 64 x 128 tile, 0.42 for 128 x 128, 0.77 for 256 x 128, 1.35
 // for 256 x 256; 3.5 fixed for the unsplit launch, 5.8 for the split pair; partial planes written
@@ -835,6 +881,41 @@ void plan_splitk(int64_t M, int64_t N, int64_t K, size_t ws_bytes, bool force, i
     }
 }
 
+// srow, zcorr: as in k_gemm_dma.  Two 128-channel sub-stages per ring stage, i.e. one barrier per 256 channels with a 2-deep
+// ring, measured 3-10 % slower than a 3-deep ring of single sub-stages; 256 x 128 and 128 x 256 as two 128 x 128 wavefront tiles on either
+// half of K, a third less expansion and LDS reads per matrix instruction, level to 10 % slower (2048 x 14336 -> 4096 93 -> 95-97 us).
+int launch_packed(const void* xq, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out, int32_t* acc,
+                  hipStream_t st, const float* srow, const int32_t* zcorr)
+{
+    const PackedPlan p = plan_packed(M, N, K);
+    if (p.n1 > 0) return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, sx, M, N, K, p.n1, p.n2, out, acc, st, srow, zcorr);
+#define PQ_TILE(BM, BN, WR, WC, NS) launch_dma<BM, BN, WR, WC, NS, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, srow, zcorr)
+    switch (p.cfg) {                               // (forced)
+        case 5: return PQ_TILE(256, 256, 2, 4, 3);
+        case 6: return PQ_TILE(256, 256, 2, 2, 4);
+        case 7: return PQ_TILE(256, 128, 4, 2, 3);
+        case 8: return PQ_TILE(256, 128, 2, 4, 3);
+    }
+    const int bm = p.cfg >= 0 ? kCfgs[p.cfg].bm : p.bm, bn = p.cfg >= 0 ? kCfgs[p.cfg].bn : p.bn;
+    switch (1000 * bm + bn) {
+        case 64128: return PQ_TILE(64, 128, 2, 2, 3);
+        case 128128: return PQ_TILE(128, 128, 2, 2, 3);
+        case 128192: return PQ_TILE(128, 192, 2, 2, 3);
+        case 128320: return PQ_TILE(128, 320, 2, 2, 3);
+        case 192128: return PQ_TILE(192, 128, 2, 2, 3);
+        case 192192: return PQ_TILE(192, 192, 2, 2, 3);
+        case 192256: return PQ_TILE(192, 256, 2, 2, 3);
+        case 192320: return PQ_TILE(192, 320, 2, 2, 3);
+        case 256128: return PQ_TILE(256, 128, 2, 2, 3);
+        case 256192: return PQ_TILE(256, 192, 2, 2, 3);
+        case 256256: return PQ_TILE(256, 256, 2, 2, 3);
+        case 320128: return PQ_TILE(320, 128, 2, 2, 3);
+        case 320192: return PQ_TILE(320, 192, 2, 2, 3);
+    }
+#undef PQ_TILE
+    return PQ_ERR_UNSUPPORTED;
+}
+
 }  // namespace
 
 int launch_gemm_mfma(const void* xq, const void* wq, const float* sw, float sx, int64_t M, int64_t N, int64_t K,
@@ -844,21 +925,13 @@ int launch_gemm_mfma(const void* xq, const void* wq, const float* sw, float sx, 
     if (M > (1 << 30) || N > (1 << 30) || K >= kMaxK4) return PQ_ERR_UNSUPPORTED;
     if (M * (K / 2) >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return PQ_ERR_UNSUPPORTED;
     if (K % 128 != 0) return launch_ragged(xq, wq, sw, sx, M, N, K, out, acc, st);
-    // (two 128-channel sub-stages per ring stage, i.e. one barrier per 256 channels with a 2-deep
-    // ring, measured 3-10 % slower than a 3-deep ring of single sub-stages: depth wins)
-    int n1 = 0, n2 = 0;
-    if (pick_dual(M, N, &n1, &n2)) return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, sx, M, N, K, n1, n2, out, acc, st);
-    switch (pick_cfg(M, N)) {
-        case 0: return launch_dma<256, 256, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 1: return launch_dma<256, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 2: return launch_dma<128, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 3: return launch_dma<256, 192, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 4: return launch_dma<64, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 5: return launch_dma<256, 256, 2, 4, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 7: return launch_dma<256, 128, 4, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        case 8: return launch_dma<256, 128, 2, 4, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-        default: return launch_dma<256, 256, 2, 2, 4, 1>(xq, wq, sw, sx, M, N, K, out, acc, st);
-    }
+    return launch_packed(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, nullptr);
+}
+
+int gemm_packed_tile(int64_t M, int64_t N, int64_t K)
+{
+    const PackedPlan p = plan_packed(M, N, K);
+    return p.cfg >= 0 || p.n1 > 0 ? 0 : 1000 * p.bm + p.bn;
 }
 
 int set_gemm_tile(int tile)
@@ -1059,16 +1132,7 @@ int launch_gemm_dynamic(const void* xq, int32_t bits, const void* wq, const floa
     if (bits == 8) return launch_bytes(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st);
     const int rc = try_splitk(xq, wq, sw, ep, M, N, K, out, acc, ws, ws_bytes, force, st);
     if (rc >= 0) return rc;
-    int n1 = 0, n2 = 0;
-    if (pick_dual(M, N, &n1, &n2))
-        return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, 1.0f, M, N, K, n1, n2, out, acc, st, srow);
-    switch (pick_cfg(M, N)) {
-        case 0: return launch_dma<256, 256, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-        case 1: return launch_dma<256, 128, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-        case 3: return launch_dma<256, 192, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-        case 4: return launch_dma<64, 128, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-        default: return launch_dma<128, 128, 2, 2, 3, 1>(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow);
-    }
+    return launch_packed(xq, wq, sw, 1.0f, M, N, K, out, acc, st, srow, nullptr);
 }
 
 // Static steps with a zero-point (Eq. 1): out = (acc + zcorr[n]) * s_x * s_w[n].
@@ -1079,16 +1143,7 @@ int launch_gemm_zp(const void* xq, const void* wq, const float* sw, float sx, co
     if (M * (K / 2) >= ((int64_t)1 << 32) || N * (K / 2) >= ((int64_t)1 << 32)) return PQ_ERR_UNSUPPORTED;
     const int rc = try_splitk(xq, wq, sw, SplitArgs{sx, nullptr, zcorr}, M, N, K, out, acc, ws, ws_bytes, force, st);
     if (rc >= 0) return rc;
-    int n1 = 0, n2 = 0;
-    if (pick_dual(M, N, &n1, &n2))
-        return launch_dual<256, 256, 192, 2, 2, 3>(xq, wq, sw, sx, M, N, K, n1, n2, out, acc, st, nullptr, zcorr);
-    switch (pick_cfg(M, N)) {
-        case 0: return launch_dma<256, 256, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
-        case 1: return launch_dma<256, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
-        case 3: return launch_dma<256, 192, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
-        case 4: return launch_dma<64, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
-        default: return launch_dma<128, 128, 2, 2, 3, 1>(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
-    }
+    return launch_packed(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, zcorr);
 }
 
 }  // namespace pq
