@@ -173,26 +173,27 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
     // where this lane's images lie (an operand of odd number is the other half of the same block)
     const int g = (lane >> 4) & 1, b = lane >> 5, r = lane & 15;
     const uint32_t wide = (uint32_t)(g * 1024 + b * 512 + r * 16), narrow = (uint32_t)(b * 512 + g * 256 + r * 8);
-    // operands of even and of odd number from their own start: with an odd count the second wavefront starts inside a block
-    auto start = [&](int o, uint32_t plane, uint32_t halfstep) PQ_INLINE { return (uint32_t)(o >> 1) * kBlock + (uint32_t)(o & 1) * halfstep + plane; };
-    const uint32_t xw[2] = {start(wm * TM, wide, 256), start(wm * TM + 1, wide, 256)}, xn[2] = {start(wm * TM, narrow, 128), start(wm * TM + 1, narrow, 128)};
-    const uint32_t ww[2] = {start(2 * TM + wn * TN, wide, 256), start(2 * TM + wn * TN + 1, wide, 256)};
-    const uint32_t wnr[2] = {start(2 * TM + wn * TN, narrow, 128), start(2 * TM + wn * TN + 1, narrow, 128)};
+    // With an odd count of operands the second wavefront starts inside a block: odd numbers then have a start of their own ([1]).
+    auto start = [&](int o, uint32_t plane, uint32_t half) PQ_INLINE { return (uint32_t)(o >> 1) * kBlock + (uint32_t)(o & 1) * half + plane; };
+    constexpr int XO = TM & 1, WO = TN & 1;
+    const uint32_t xw[2] = {start(wm * TM, wide, 256), start(wm * TM + XO, wide, 256)}, xn[2] = {start(wm * TM, narrow, 128), start(wm * TM + XO, narrow, 128)};
+    const uint32_t ww[2] = {start(2 * TM + wn * TN, wide, 256), start(2 * TM + wn * TN + WO, wide, 256)};
+    const uint32_t wnr[2] = {start(2 * TM + wn * TN, narrow, 128), start(2 * TM + wn * TN + WO, narrow, 128)};
     // LDS read n of the 2 (TM + TN) of a half stage: even n the 16-byte plane of an operand's image, odd n the 8-byte one
     auto read = [&](auto stc, uint32_t slot, auto nc) PQ_INLINE {
-        constexpr int st = decltype(stc)::value, n = decltype(nc)::value, f = n / 2, j = f < TM ? f : f - TM;
+        constexpr int st = decltype(stc)::value, n = decltype(nc)::value, f = n / 2, j = f < TM ? f : f - TM, own = (j & 1) & (f < TM ? XO : WO);
         v6i& d = f < TM ? tok[st][j] : wgt[st][j];
         if constexpr ((n & 1) == 0) {
-            constexpr int off = (j >> 1) * kBlock + (st == 0 ? 0 : 1024);
+            constexpr int off = (j >> 1) * kBlock + (own ? 0 : (j & 1) * 256) + (st == 0 ? 0 : 1024);
             uint32_t at;
-            if constexpr (f < TM) at = xw[j & 1]; else at = ww[j & 1];
+            if constexpr (f < TM) at = xw[own]; else at = ww[own];
             const v4i t = *(__attribute__((address_space(3))) const v4i*)(smem + slot + at + off);
             if constexpr (st == 0) { d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w; }
             else { d[2] = t.x; d[3] = t.y; d[4] = t.z; d[5] = t.w; }
         } else {
-            constexpr int off = (j >> 1) * kBlock + (st == 0 ? 2048 : 0);
+            constexpr int off = (j >> 1) * kBlock + (own ? 0 : (j & 1) * 128) + (st == 0 ? 2048 : 0);
             uint32_t at;
-            if constexpr (f < TM) at = xn[j & 1]; else at = wnr[j & 1];
+            if constexpr (f < TM) at = xn[own]; else at = wnr[own];
             const v2i u = *(__attribute__((address_space(3))) const v2i*)(smem + slot + at + off);
             if constexpr (st == 0) { d[4] = u.x; d[5] = u.y; }
             else { d[0] = u.x; d[1] = u.y; }
