@@ -821,7 +821,7 @@ double packed_us(const PackedTile& t, int64_t M, int64_t N, int64_t K)
            (double)(K / 128) * ((double)rounds * t.part + (double)tiles / 256.0 * t.full);
 }
 
-// What a packed product runs on: cfg >= 0: that configuration (of kCfgs; forced, or the area model's); n1 > 0: n1 panels of 256 and n2 of
+// What a packed product runs on: cfg >= 0: the forced configuration (of kCfgs); n1 > 0: n1 panels of 256 and n2 of
 // 192; else tiles of bm x bn.  A size of its own is taken where its estimate is 2 % under that of the five the area model knows, or of the
 // mixed launch: 1.11 x, geometric mean, over 110 further shapes where it is, the slowest 0.98 x.  300 x 4096 -> 28672 45.6 -> 33.9 us, 359 x 4096 ->
 // 12160 27.5 -> 22.3, 1308 x 11520 -> 6896 94.5 -> 78.9, 777 x 4096 -> 11008 37.4 -> 34.8, 1500 x 11008 -> 4096 65.3 -> 57.8.
