@@ -119,9 +119,10 @@ size_t pq_linear_workspace_bytes(int64_t M, int64_t K);
 size_t pq_linear_workspace_bytes_split(int64_t M, int64_t N, int64_t K);
 
 /* The whole layer: pq_rotate_quant into `workspace`, then pq_w4a4_gemm (same stream).
- * For M <= 4 and M*K <= 8192 (16384 for a single token, 32768 without rotation) the two steps run in
- * one fused launch (every workgroup rotates and quantizes the few rows for itself while its first
- * weight loads are in flight).
+ * For M <= 4 and M*K <= 8192 (16384 for a single token, 32768 without rotation), and without rotation for most
+ * calls of 5 to 16 tokens, the two steps run in one fused launch (every workgroup rotates and quantizes the few
+ * rows for itself while its first weight loads are in flight).
+ * out_f16 may lie over x_f16 (in place): the codes are then complete before any output is stored.
  * workspace: device memory, 256-byte aligned, at least pq_linear_workspace_bytes(M,K);
  * its first M*K/2 bytes on return are the packed activation codes (canonical layout).
  */

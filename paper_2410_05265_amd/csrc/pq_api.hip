@@ -147,6 +147,14 @@ inline bool fused_few_tokens(int64_t M, int64_t K, int32_t had_block)
     return total <= 8192 || (M == 1 && total <= 16384);
 }
 
+// Whether an output of out_bytes lies over the tokens: workgroups of a fused launch read the tokens while others store already, so such a
+// call takes a launch for the codes and another for the product.
+inline bool over_tokens(const void* x, int64_t M, int64_t K, const void* out, int64_t N)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(out);
+    return a < b + (uintptr_t)(2 * M * N) && b < a + (uintptr_t)(2 * M * K);
+}
+
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline bool good_scale(float s) { return isfinite(s) && s > 0.0f; }
 
@@ -269,11 +277,12 @@ int pq_linear(const void* x_f16, const void* wq_packed, const float* w_scale, fl
         return PQ_ERR_SHAPE;
     if (!aligned16(x_f16)) return PQ_ERR_ALIGN;
     // decode: one fused launch (rotate + quantize per workgroup, weights streamed once)
-    if (((g_variant == 0 && fused_few_tokens(M, K, had_block)) || g_variant == 4) &&
+    const bool apart = over_tokens(x_f16, M, K, out_f16, N);
+    if (((g_variant == 0 && fused_few_tokens(M, K, had_block)) || g_variant == 4) && !apart &&
         pq::decode_supported(M, N, K, had_block))
         return pq::launch_decode(x_f16, nullptr, wq_packed, w_scale, act_scale, had_block, M, N, K, out_f16, nullptr,
                                  workspace, static_cast<hipStream_t>(stream));
-    if (g_variant == 0 && had_block <= 1 && pq::take_stream_fused(M, N, K, false))
+    if (g_variant == 0 && had_block <= 1 && !apart && pq::take_stream_fused(M, N, K, false))
         return pq::launch_stream_fused(x_f16, wq_packed, w_scale, act_scale, M, N, K, out_f16, workspace, static_cast<hipStream_t>(stream));
     rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, workspace, stream);
     if (rc != PQ_OK) return rc;
@@ -301,11 +310,12 @@ int pq_linear2(const void* x_f16, const void* wq_a, const float* w_scale_a, int6
     if (!aligned16(x_f16)) return PQ_ERR_ALIGN;
     // few tokens: one launch streams both matrices (the rule of pq_linear, on the rows of both)
     const pq::DecodeSecond second{static_cast<const uint8_t*>(wq_b), w_scale_b, static_cast<__half*>(out_b_f16), (int)N_a};
-    if (((g_variant == 0 && fused_few_tokens(M, K, had_block)) || g_variant == 4) &&
+    const bool apart = over_tokens(x_f16, M, K, out_a_f16, N_a) || over_tokens(x_f16, M, K, out_b_f16, N_b);
+    if (((g_variant == 0 && fused_few_tokens(M, K, had_block)) || g_variant == 4) && !apart &&
         N_a + N_b <= (1 << 30) && pq::decode_supported(M, N_a + N_b, K, had_block))
         return pq::launch_decode(x_f16, nullptr, wq_a, w_scale_a, act_scale, had_block, M, N_a + N_b, K, out_a_f16, nullptr,
                                  workspace, static_cast<hipStream_t>(stream), nullptr, 4, nullptr, &second);
-    if (g_variant == 0 && had_block <= 1 && pq::take_stream_fused(M, N_a + N_b, K, true))
+    if (g_variant == 0 && had_block <= 1 && !apart && pq::take_stream_fused(M, N_a + N_b, K, true))
         return pq::launch_stream_fused(x_f16, wq_a, w_scale_a, act_scale, M, N_a + N_b, K, out_a_f16, workspace,
                                        static_cast<hipStream_t>(stream), &second);
     rc = pq_rotate_quant(x_f16, M, K, had_block, act_scale, workspace, stream);

@@ -8,6 +8,7 @@ a task.  Inputs: values on rounding ties of the step and one fp16 step beside th
 
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 from paper_2410_05265_amd import synth
@@ -95,3 +96,20 @@ def test_against_the_oracle(pq, M, K, N):
     codes = host(ws)[: M * K // 2].reshape(M, K // 2)
     assert np.array_equal(codes, O.linear(x, w, sw, sx, 1, return_all=True)["xq"])
     check_end_to_end(x, w, sw, sx, 1, host(out), codes)
+
+
+@pytest.mark.parametrize("M,K", [(1, 4096), (4, 4096), (5, 4096), (16, 4096), (8, 2048)])
+def test_output_over_the_tokens(pq, M, K):
+    """In place: the codes are complete before any output is stored."""
+    step, x = 0.3719, dev(inputs(M, K, 0.3719, M))
+    w, sw = dev(synth.random_packed(K, K, seed=K, stream=7)), dev(synth.random_scales(K, seed=K))
+    want, _ = pq.pq_linear(x, w, sw, step, 1)
+    for second in (False, True):
+        y, other = x.clone(), torch.empty_like(x)
+        ws = torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+        if second:
+            pq.pq_linear2(y, w, sw, w, sw, step, 1, out_a=other, out_b=y, workspace=ws)
+            assert np.array_equal(bits(other), bits(want))
+        else:
+            pq.pq_linear(y, w, sw, step, 1, out=y, workspace=ws)
+        assert np.array_equal(bits(y), bits(want))
