@@ -492,22 +492,21 @@ int launch_tokens(const void* xq, const void* wq, const float* sw, float sx, int
     const unsigned grid = (unsigned)(T < 256 ? T : 256);
     // units a wavefront has at most: the ring is as deep as that, up to 4
     const int64_t units = ((T + grid - 1) / grid) * upt;
-    auto launch = [&](auto kern) {
-        static std::atomic<uint64_t> lds_ok{0};
+    auto launch = [&](auto bits, auto depth) {
+        auto kern = k_stream_mfma<decltype(bits)::value, decltype(depth)::value>;
+        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per width and depth)
         if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), lds, st, static_cast<const uint8_t*>(xq),
                            static_cast<const uint8_t*>(wq), sw, sx, (int)M, (int)N, (int)K, log2S,
                            static_cast<__half*>(out), acc, srow, zcorr);
         return hip_status(hipGetLastError());
     };
-    if (abits == 8) {
-        if (units <= 1) return launch(k_stream_mfma<8, 1>);
-        if (units <= 2) return launch(k_stream_mfma<8, 2>);
-        return launch(k_stream_mfma<8, 4>);
-    }
-    if (units <= 1) return launch(k_stream_mfma<4, 1>);
-    if (units <= 2) return launch(k_stream_mfma<4, 2>);
-    return launch(k_stream_mfma<4, 4>);
+    auto of_depth = [&](auto bits) {
+        if (units <= 1) return launch(bits, std::integral_constant<int, 1>{});
+        if (units <= 2) return launch(bits, std::integral_constant<int, 2>{});
+        return launch(bits, std::integral_constant<int, 4>{});
+    };
+    return abits == 8 ? of_depth(std::integral_constant<int, 8>{}) : of_depth(std::integral_constant<int, 4>{});
 }
 }  // namespace
 
@@ -593,16 +592,19 @@ int launch_stream_fused(const void* x, const void* wq, const float* sw, float sx
     const int64_t T = (N / 16 + RG - 1) / RG;
     const unsigned grid = (unsigned)(T < 256 ? T : 256);
     const int64_t units = ((T + grid - 1) / grid) * p.upt;
-    auto launch = [&](auto kern) {
-        static std::atomic<uint64_t> lds_ok{0};
+    auto launch = [&](auto depth, auto pieces) {
+        auto kern = k_stream_fused<decltype(depth)::value, decltype(pieces)::value>;
+        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per depth and pieces)
         if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), p.lds, st, static_cast<const __half*>(x), static_cast<const uint8_t*>(wq), sw,
                            sx, (float)(1.0 / (double)sx), (int)M, (int)N, (int)K, p.log2S, static_cast<__half*>(out),
                            static_cast<uint8_t*>(xq_out), two);
         return hip_status(hipGetLastError());
     };
-    if (p.pieces <= 8) return units <= 2 ? launch(k_stream_fused<2, 8>) : launch(k_stream_fused<4, 8>);
-    return units <= 2 ? launch(k_stream_fused<2, 16>) : launch(k_stream_fused<4, 16>);
+    auto of_depth = [&](auto pieces) {
+        return units <= 2 ? launch(std::integral_constant<int, 2>{}, pieces) : launch(std::integral_constant<int, 4>{}, pieces);
+    };
+    return p.pieces <= 8 ? of_depth(std::integral_constant<int, 8>{}) : of_depth(std::integral_constant<int, 16>{});
 }
 
 }  // namespace pq

@@ -22,3 +22,29 @@ def test_output_over_the_tokens_keeps_the_launches_apart(call):
         first, *products = kernels(events)
         assert rc == 0 and first.startswith(("k_rotate_quant<", "k_rotate128")) and products
         assert not any(k.startswith(("k_rotate", "k_stream_fused")) for k in products)
+
+
+def allowed_before_launched(events):
+    """Kernels launched with more than 64 KiB of dynamic LDS and not allowed as much before."""
+    limit, late = {}, []
+    for what, kernel, _, lds in events:
+        if what == "allow":
+            limit[kernel] = lds
+        elif lds > 65536 and limit.get(kernel, 0) < lds:
+            late.append(kernel)
+    return late
+
+
+def test_every_kernel_is_allowed_its_dynamic_lds():
+    """The runtime is told per kernel.  One process, as a program's: what one kernel was told must not count for another."""
+    calls = [dict(fn="linear", M=M, K=K, N=N, variant=v) for v in (0, 1, 2, 4, 5) for M in (1, 3, 5, 8, 13, 16, 24, 40, 96, 300, 777, 2048)
+             for K, N in ((256, 16), (1024, 4096), (4096, 528), (4096, 14336), (8192, 8192), (14336, 4096), (8192, 528), (65536, 16))]
+    calls += [dict(fn="linear2", M=M, K=K, N=N) for M in (2, 4, 9, 16, 100) for K, N in ((1024, 272), (8192, 528), (8192, 11008), (12288, 14336))]
+    calls += [dict(fn=f, M=M, K=K, N=N) for f in ("f6", "f6_two") for M in (40, 333, 700, 1111, 2048, 5000) for K in (1024, 4096, 11008)
+              for N in (1024, 4096, 12288, 28672)]
+    done = launches(calls)
+    events = [e for rc, ev in done if rc == 0 for e in ev]
+    used = {e[1] for e in events if e[0] == "launch"}
+    assert not allowed_before_launched(events)
+    for family, count in (("k_stream_fused<", 4), ("k_stream_mfma<4", 3), ("k_gemm_f6_square<", 10), ("k_decode<", 6)):
+        assert sum(k.startswith(family) for k in used) >= count, (family, used)
