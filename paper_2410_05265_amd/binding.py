@@ -150,6 +150,20 @@ def _dev(t: torch.Tensor, dtype, what: str):
         raise TypeError("%s must be a contiguous %s tensor on the GPU" % (what, dtype))
 
 
+def _reachable(t: torch.Tensor, what: str):
+    """A buffer of the caller's that kernels write: contiguous, on the GPU or in pinned memory."""
+    if not (t.is_cuda or t.is_pinned()) or not t.is_contiguous():
+        raise TypeError("%s must be a contiguous tensor on the GPU" % what)
+
+
+def _result(t: torch.Tensor, count: int, what: str):
+    _reachable(t, what)
+    if t.dtype != torch.float16:
+        raise TypeError("%s must be a %s tensor" % (what, torch.float16))
+    if t.numel() < count:
+        raise ValueError("%s has room for %d of %d values" % (what, t.numel(), count))
+
+
 def pq_rotate_quant(x: torch.Tensor, had_block: int, act_scale: float, out: torch.Tensor | None = None):
     """x fp16 [M,K] -> packed codes uint8 [M,K/2]."""
     _dev(x, torch.float16, "x")
@@ -229,8 +243,12 @@ def pq_linear(x, wq, w_scale, act_scale, had_block, out=None, workspace=None):
         raise ValueError("shape mismatch")
     if workspace is None:
         workspace = torch.empty((max(pq_linear_workspace_bytes(M, K), 256),), dtype=torch.uint8, device=x.device)
+    else:
+        _reachable(workspace, "workspace")
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=x.device)
+    else:
+        _result(out, M * N, "out")
     _check(lib().pq_linear(_ptr(x), _ptr(wq), _ptr(w_scale), float(act_scale), int(had_block), M, N, K, _ptr(out),
                            _ptr(workspace), workspace.numel(), _stream()), "pq_linear")
     return out, workspace
@@ -256,10 +274,16 @@ def pq_linear2(x, wq_a, w_scale_a, wq_b, w_scale_b, act_scale, had_block, out_a=
     Na, Nb = wq_a.shape[0], wq_b.shape[0]
     if workspace is None:
         workspace = torch.empty((max(pq_linear_workspace_bytes(M, K), 256),), dtype=torch.uint8, device=x.device)
+    else:
+        _reachable(workspace, "workspace")
     if out_a is None:
         out_a = torch.empty((M, Na), dtype=torch.float16, device=x.device)
+    else:
+        _result(out_a, M * Na, "out_a")
     if out_b is None:
         out_b = torch.empty((M, Nb), dtype=torch.float16, device=x.device)
+    else:
+        _result(out_b, M * Nb, "out_b")
     _check(lib().pq_linear2(_ptr(x), _ptr(wq_a), _ptr(w_scale_a), Na, _ptr(out_a), _ptr(wq_b), _ptr(w_scale_b), Nb,
                             _ptr(out_b), float(act_scale), int(had_block), M, K, _ptr(workspace), workspace.numel(),
                             _stream()), "pq_linear2")

@@ -28,12 +28,15 @@ bool operand(PyObject* o, at::ScalarType type, const at::Tensor** t)
     return (*t)->is_cuda() && (*t)->scalar_type() == type && (*t)->is_contiguous();
 }
 
-// a tensor of the caller's that is passed on as it is
-bool buffer(PyObject* o, const at::Tensor** t)
+// the caller's fp16 output, with room for M x N values
+bool result(PyObject* o, int64_t M, int64_t N, const at::Tensor** t) { return operand(o, at::kHalf, t) && (*t)->numel() >= M * N; }
+
+// the caller's workspace, of any type (the library compares its elements, taken as bytes, with what it needs)
+bool workspace(PyObject* o, const at::Tensor** t)
 {
     if (!THPVariable_CheckExact(o)) return false;
     *t = &THPVariable_Unpack(o);
-    return true;
+    return (*t)->is_cuda() && (*t)->is_contiguous();
 }
 
 bool number(PyObject* step, PyObject* block, double* s, long* h)
@@ -65,7 +68,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n)
         double step;
         long h;
         if (n == 7 && g_linear && operand(a[0], at::kHalf, &x) && x->dim() == 2 && matrix(a[1], a[2], x->size(1), &w, &s) &&
-            number(a[3], a[4], &step, &h) && buffer(a[5], &out) && buffer(a[6], &ws)) {
+            number(a[3], a[4], &step, &h) && result(a[5], x->size(0), w->size(0), &out) && workspace(a[6], &ws)) {
             const void *xp = x->data_ptr(), *wp = w->data_ptr();
             const float* sp = static_cast<const float*>(s->data_ptr());
             void *op = out->data_ptr(), *wsp = ws->data_ptr(), *st = stream();
@@ -90,8 +93,8 @@ PyObject* linear2(PyObject*, PyObject* const* a, Py_ssize_t n)
         double step;
         long h;
         if (n == 10 && g_linear2 && operand(a[0], at::kHalf, &x) && x->dim() == 2 && matrix(a[1], a[2], x->size(1), &wa, &sa) &&
-            matrix(a[3], a[4], x->size(1), &wb, &sb) && number(a[5], a[6], &step, &h) && buffer(a[7], &oa) && buffer(a[8], &ob) &&
-            buffer(a[9], &ws)) {
+            matrix(a[3], a[4], x->size(1), &wb, &sb) && number(a[5], a[6], &step, &h) &&
+            result(a[7], x->size(0), wa->size(0), &oa) && result(a[8], x->size(0), wb->size(0), &ob) && workspace(a[9], &ws)) {
             const void *xp = x->data_ptr(), *wap = wa->data_ptr(), *wbp = wb->data_ptr();
             const float *sap = static_cast<const float*>(sa->data_ptr()), *sbp = static_cast<const float*>(sb->data_ptr());
             void *oap = oa->data_ptr(), *obp = ob->data_ptr(), *wsp = ws->data_ptr(), *st = stream();

@@ -30,6 +30,28 @@ def test_declines_what_is_not_plain():
         b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=out, out_b=out, workspace=ws)
 
 
+def test_python_path_checks_the_callers_buffers(monkeypatch):
+    """On the CPU, with the checks of the operands taken out of the way: the output's and the workspace's own checks."""
+    b.lib()
+    monkeypatch.setattr(b, "_dev", lambda *a: None)
+    monkeypatch.setattr(torch.Tensor, "is_pinned", lambda t: True)
+    launched = []
+    monkeypatch.setattr(b, "lib", lambda: type("L", (), {"pq_linear": staticmethod(lambda *a: launched.append(a) or 0),
+                                                         "pq_linear2": staticmethod(lambda *a: launched.append(a) or 0)}))
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    x, w, s = tensors("cpu")
+    out, ws = torch.empty(3, 64).half(), torch.empty(4096, dtype=torch.uint8)
+    for o, k in ((out[:2], ws), (out.float(), ws), (torch.empty(64, 3).half().t(), ws), (out, torch.empty(8192, dtype=torch.uint8)[::2])):
+        with pytest.raises((TypeError, ValueError)):
+            b.pq_linear(x, w, s, 0.5, 1, out=o, workspace=k)
+        for oa, ob in ((o, out), (out, o)):
+            with pytest.raises((TypeError, ValueError)):
+                b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=oa, out_b=ob, workspace=k)
+    assert not launched
+    b.pq_linear(x, w, s, 0.5, 1, out=torch.empty(5, 64).half(), workspace=ws)
+    assert len(launched) == 1
+
+
 @pytest.mark.gpu
 def test_same_refusals_as_the_python_path():
     b.lib()
@@ -103,3 +125,49 @@ def test_runs_on_the_current_stream():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("two", [False, True])
+def test_outputs_and_workspaces_that_kernels_must_not_write(two):
+    """Too small, of another type, not contiguous, not on the GPU: refused before anything is launched, on either path; a larger
+    output, a workspace of another type and pinned memory are accepted as before."""
+    b.lib()
+    x, w, s = tensors("cuda")
+    M, N = 3, 64
+    ws, good = torch.empty(4096, dtype=torch.uint8, device="cuda"), torch.empty((M, N), dtype=torch.float16, device="cuda")
+    ref, _ = b.pq_linear(x, w, s, 0.5, 1)
+    half = dict(dtype=torch.float16, device="cuda")
+
+    def call(out, workspace, native):
+        saved, b._call = b._call, b._call if native else Declines()
+        try:
+            if two:
+                b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=out, out_b=good, workspace=workspace)
+                b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=good, out_b=out, workspace=workspace)
+            else:
+                b.pq_linear(x, w, s, 0.5, 1, out=out, workspace=workspace)
+        finally:
+            b._call = saved
+
+    bad = [(torch.empty((M - 1, N), **half), ws), (torch.empty((M, N), device="cuda"), ws), (torch.empty((N, M), **half).t(), ws),
+           (torch.empty((M, 2 * N), **half)[:, ::2], ws), (torch.empty((M, N), dtype=torch.float16), ws),
+           (good, torch.empty(8192, dtype=torch.uint8, device="cuda")[::2]), (good, torch.empty(4096, dtype=torch.uint8))]
+    for native in (True, False):
+        for out, workspace in bad:
+            with pytest.raises((TypeError, ValueError)):
+                call(out, workspace, native)
+        for out, workspace in ((torch.zeros((M + 2, N), **half), ws), (torch.zeros(M * N, **half), torch.empty(4096, device="cuda")),
+                               (torch.zeros((M, N), dtype=torch.float16).pin_memory(), ws)):
+            call(out, workspace, native)
+            torch.cuda.synchronize()
+            assert torch.equal(out.reshape(-1)[:M * N].cuda(), ref.reshape(-1))
+
+
+class Declines:
+    """The native call path that takes nothing."""
+
+    @staticmethod
+    def linear(*a):
+        return -1
+
+    linear2 = linear
