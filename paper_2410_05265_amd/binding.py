@@ -10,12 +10,15 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpq.so")
-CALL_PATH = os.path.join(_HERE, "_pq_call.so")
+# (the module is of one Python and one torch, and is not looked for under another)
+CALL_PATH = os.path.join(_HERE, "_pq_call.%s.torch-%s.so" % (sys.implementation.cache_tag, torch.__version__))
 
 PQ_OK, PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_ALIGN, PQ_ERR_SCALE, PQ_ERR_WORKSPACE, PQ_ERR_HIP, PQ_ERR_UNSUPPORTED = range(8)
 
@@ -87,8 +90,20 @@ SIGNATURES = {
     "pq_calibrate_static": (ctypes.c_int, [_vp, _i64, _i64, _i32, _i32, _i32, _f32, _vp, _vp, _sz, _vp]),
 }
 
+
+
+class _Declines:
+    """In the place of the native call path where it is not built: it takes no call."""
+
+    @staticmethod
+    def linear(*args):
+        return -1
+
+    linear2 = linear
+
+
 _lib = None
-_call = None          # the native call path of pq_linear and pq_linear2 (csrc/pq_call.cpp)
+_call = _Declines     # the native call path of pq_linear and pq_linear2 (csrc/pq_call.cpp)
 
 
 class PQError(RuntimeError):
@@ -97,23 +112,31 @@ class PQError(RuntimeError):
         super().__init__("%s failed: %s" % (where, status_str(status)))
 
 
+def _load_call(L):
+    """The native call path, bound to this library; without it every call goes through ctypes."""
+    try:
+        spec = importlib.util.spec_from_file_location("_pq_call", CALL_PATH)
+        call = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(call)
+    except (ImportError, OSError) as e:
+        warnings.warn("the native call path is not there (python -m paper_2410_05265_amd.build makes it); calls go through ctypes: %s" % e)
+        return _Declines
+    call.bind(*(ctypes.cast(getattr(L, f), _vp).value for f in ("pq_linear", "pq_linear2")))
+    return call
+
+
 def lib() -> ctypes.CDLL:
-    """The loaded library; raises if libpq.so or the native call path is missing (build them with build.build_lib())."""
+    """The loaded library; raises if libpq.so is missing (build it with build.build_lib())."""
     global _lib, _call
     if _lib is None:
-        for path in (LIB_PATH, CALL_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(
-                    "%s not found: the HIP library is not built (python -m paper_2410_05265_amd.build)" % path)
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                "%s not found: the HIP library is not built (python -m paper_2410_05265_amd.build)" % LIB_PATH)
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = res, args
-        spec = importlib.util.spec_from_file_location("_pq_call", CALL_PATH)
-        call = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(call)
-        call.bind(*(ctypes.cast(getattr(L, f), _vp).value for f in ("pq_linear", "pq_linear2")))
-        _call, _lib = call, L
+        _call, _lib = _load_call(L), L
     return _lib
 
 

@@ -1,6 +1,9 @@
 """The native call path of pq_linear and pq_linear2: what it declines (the Python path then words the error), and on the GPU that it
 passes on what the ctypes path does, on the current stream, from several threads."""
 
+import os
+import subprocess
+import sys
 import threading
 
 import numpy as np
@@ -8,6 +11,9 @@ import pytest
 import torch
 
 import paper_2410_05265_amd.binding as b
+from paper_2410_05265_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def tensors(device, M=3, K=512, N=64):
@@ -28,6 +34,40 @@ def test_declines_what_is_not_plain():
         b.pq_linear(x, w, s, 0.5, 1, out=out, workspace=ws)
     with pytest.raises(TypeError):
         b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=out, out_b=out, workspace=ws)
+
+
+SCRIPT = """
+import sys, warnings
+from paper_2410_05265_amd import binding as b, build
+%s
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    assert b.lib().pq_version() >= 100 and b._call is b._Declines and b._call.linear(1) == b._call.linear2(1) == -1
+    assert any("native call path" in str(x.message) for x in w)
+import torch
+x, k, s = torch.zeros(3, 512).half(), torch.zeros(64, 256, dtype=torch.uint8), torch.ones(64)
+try:
+    b.pq_linear(x, k, s, 0.5, 1, out=torch.empty(3, 64).half(), workspace=torch.empty(4096, dtype=torch.uint8))
+except TypeError:
+    print("declined by the Python path")
+"""
+
+
+@pytest.mark.parametrize("how", ["absent", "of another torch", "unreadable"])
+def test_library_loads_without_the_native_call_path(how, tmp_path):
+    broken = tmp_path / "broken.so"
+    broken.write_bytes(b"not a library")
+    setup = {"absent": "b.CALL_PATH = %r" % str(tmp_path / "none.so"), "unreadable": "b.CALL_PATH = %r" % str(broken),
+             "of another torch": "import importlib, torch; torch.__version__ = '0.0'; importlib.reload(b); assert build._call_is_stale()"}[how]
+    r = subprocess.run([sys.executable, "-c", SCRIPT % setup], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "declined by the Python path" in r.stdout, r.stderr[-2000:]
+
+
+def test_build_goes_on_without_a_host_compiler(monkeypatch, capfd):
+    monkeypatch.setenv("PATH", "/nonexistent")
+    before = os.path.getmtime(b.CALL_PATH)
+    assert not build._build_call() and "ctypes" in capfd.readouterr().err
+    assert os.path.getmtime(b.CALL_PATH) == before and not build._call_is_stale()
 
 
 def test_python_path_checks_the_callers_buffers(monkeypatch):
@@ -139,7 +179,7 @@ def test_outputs_and_workspaces_that_kernels_must_not_write(two):
     half = dict(dtype=torch.float16, device="cuda")
 
     def call(out, workspace, native):
-        saved, b._call = b._call, b._call if native else Declines()
+        saved, b._call = b._call, b._call if native else b._Declines
         try:
             if two:
                 b.pq_linear2(x, w, s, w, s, 0.5, 1, out_a=out, out_b=good, workspace=workspace)
@@ -162,12 +202,3 @@ def test_outputs_and_workspaces_that_kernels_must_not_write(two):
             torch.cuda.synchronize()
             assert torch.equal(out.reshape(-1)[:M * N].cuda(), ref.reshape(-1))
 
-
-class Declines:
-    """The native call path that takes nothing."""
-
-    @staticmethod
-    def linear(*a):
-        return -1
-
-    linear2 = linear
