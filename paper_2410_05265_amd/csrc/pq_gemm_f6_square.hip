@@ -43,7 +43,9 @@ template <int TM_, int TN_> struct Tile {
     static constexpr int PIECES = 3 * (TM + TN);            // KiB of a half stage
     static constexpr int L = (PIECES + 3) / 4;              // direct loads per wavefront and half stage (past the last piece: that again, into the pad)
     static constexpr int STAGE = L * 4096, SCALES = kRing * STAGE, STEPS = (BN + 255) / 256 * 1024;
-    static constexpr size_t kLds = (size_t)SCALES + 2 * STEPS;
+    // STREAM: per wavefront 16 tokens x 64 channels (an odd count: x all channels) between accumulators and memory, PITCH bytes a token
+    static constexpr int TURN = SCALES + 2 * STEPS, PITCH = TN & 1 ? 32 * TN : 144;
+    static constexpr size_t kLds = (size_t)TURN + 4 * 16 * PITCH;
     static_assert(kLds <= 160 * 1024, "LDS");
 };
 
@@ -92,7 +94,7 @@ struct Second {
     __half* out;
 };
 
-template <int TM, int TN, bool TWO>
+template <int TM, int TN, bool TWO, bool STREAM>
 __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restrict__ x6, const uint8_t* __restrict__ w6a,
                                                        const float* __restrict__ swa, float sx, int M, int N, int K, int GM,
                                                        int GN, __half* __restrict__ outa, int32_t* __restrict__ acc_out, Second two)
@@ -223,7 +225,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
         });
     };
 
-    // stores of a full tile's output per wavefront, issued behind the next tile's first loads
+    // stores of a full tile's output per wavefront, issued behind the next tile's first loads (STREAM: two per four operands, one per two or one)
     constexpr int STORES = TM * ((TN + 1) / 2);
     static_assert((kRing - 1) * L + STORES < 64, "vmcnt has six bits");
 
@@ -291,8 +293,11 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 
     // out = fp16(fp32(acc * factor)), factor = 256 fl(sw * (sx / 256)): the same real product, hence the same rounding, as the
     // INT8 tiled kernel's (256 acc) * fl(sw * (sx / 256)).  A lane has four channels of one token per operand; neighbouring
-    // rows of 16 lanes trade halves of two operands, so that a lane stores eight channels of its token.  Ordinary stores: with
-    // non-temporal ones the 32-byte runs reach memory one by one (2048 x 8192 -> 28672 252 -> 276 us, 1523 x 6912 -> 20176 115 -> 124).
+    // rows of 16 lanes trade halves of two operands, so that a lane stores eight channels of its token: 16 bytes of 16 rows at a
+    // time, in ordinary stores that wait in the L2 and the memory-side cache (non-temporal ones reach memory one by one: 2048 x 8192 ->
+    // 28672 252 -> 276 us).  STREAM: 16 tokens x 64 channels turn through LDS instead, a wavefront's own part of it, and eight
+    // neighbouring lanes store 128 bytes of a row non-temporally, past that cache; where it lies: streams_output.
+    // (LDS reads and writes of a turn without bank conflicts: rows 144 bytes apart, or 224 with the pieces of the upper eight rows swapped.)
     auto epilogue = [&](int m0, int n0, __half* out, int parity) PQ_INLINE {
         const int lane = fresh_lane();
         const int g4 = lane >> 4, r = lane & 15;
@@ -310,6 +315,7 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
                 sc[i] = s;
             }
         }
+        uint8_t* const turn = smem + T::TURN + wave * (16 * T::PITCH);
         static_for<0, TM>([&](auto jc) PQ_INLINE {
             constexpr int j = decltype(jc)::value;
             const int m16 = mb + j * 16;
@@ -322,8 +328,6 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
                 }
             }
             if (out) {
-                const int m = m16 + r;
-                __half* const row = out + (int64_t)m * N;
                 auto pack = [&](const v4f& a, const v4f& s) PQ_INLINE {
                     const __half2 lo = __floats2half2_rn(mul_rn(a.x, s.x), mul_rn(a.y, s.y));
                     const __half2 hi = __floats2half2_rn(mul_rn(a.z, s.z), mul_rn(a.w, s.w));
@@ -332,23 +336,61 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
                     val.y = *reinterpret_cast<const int*>(&hi);
                     return val;
                 };
-                if constexpr (TN & 1) {                        // the last operand alone: four channels a lane
-                    const int n = nb + (TN - 1) * 16 + 4 * g4;
-                    const v2i val = pack(acc[TN - 1][j], sc[TN - 1]);
-                    if (m < M && n + 4 <= N) *reinterpret_cast<v2i*>(row + n) = val;
+                if constexpr (STREAM) {
+                    // CNT operands: from columns (of 8 channels) `at` on of the turned rows to the wavefront's columns `col` on
+                    auto store = [&](auto cntc, int at, int col, auto nontemporal) PQ_INLINE {
+                        constexpr int CNT = decltype(cntc)::value, LANES = 2 * CNT, ROWS = 64 / LANES < 16 ? 64 / LANES : 16;
+                        const int c = lane % LANES, k = lane / LANES % ROWS;
+                        static_for<0, 16 / ROWS>([&](auto pc) PQ_INLINE {
+                            const int row = decltype(pc)::value * ROWS + k, m = m16 + row, n = nb + (col + c) * 8;
+                            const int swapped = (at + c) ^ (TN & 1 ? row >> 3 : 0);
+                            const v4i val = *(__attribute__((address_space(3))) const v4i*)(turn + row * T::PITCH + swapped * 16);
+                            v4i* const to = reinterpret_cast<v4i*>(out + (int64_t)m * N + n);
+                            if (lane < ROWS * LANES && m < M && n + 8 <= N) {
+                                if constexpr (decltype(nontemporal)::value) __builtin_nontemporal_store(val, to);
+                                else *to = val;
+                            }
+                        });
+                    };
+                    auto turned = [&](auto ic, int at) PQ_INLINE {
+                        constexpr int i = decltype(ic)::value;
+                        const int piece = g4 ^ (TN & 1 ? (r >> 3) << 1 : 0);
+                        *(__attribute__((address_space(3))) v2i*)(turn + r * T::PITCH + at * 32 + piece * 8) = pack(acc[i][j], sc[i]);
+                    };
+                    if constexpr (TN & 1) {                    // the operand beside the other wavefront's shares its 64 bytes: ordinary
+                        static_assert(TN == 7, "a chunk of four, of two and of one");
+                        static_for<0, TN>([&](auto ic) PQ_INLINE { turned(ic, decltype(ic)::value); });
+                        store(std::integral_constant<int, 4>{}, 2 * wn, 2 * wn, std::true_type{});
+                        store(std::integral_constant<int, 2>{}, 2 * wn + 8, 2 * wn + 8, std::true_type{});
+                        store(std::integral_constant<int, 1>{}, wn ? 0 : 12, wn ? 0 : 12, std::false_type{});
+                    } else {
+                        static_for<0, (TN + 2) / 4>([&](auto cc) PQ_INLINE {
+                            constexpr int first = 4 * decltype(cc)::value, CNT = TN - first < 4 ? TN - first : 4;
+                            static_for<0, CNT>([&](auto ic) PQ_INLINE { turned(std::integral_constant<int, first + decltype(ic)::value>{}, decltype(ic)::value); });
+                            store(std::integral_constant<int, CNT>{}, 0, 2 * first, std::true_type{});
+                        });
+                    }
+                } else {
+                    const int m = m16 + r;
+                    __half* const row = out + (int64_t)m * N;
+                    if constexpr (TN & 1) {                        // the last operand alone: four channels a lane
+                        const int n = nb + (TN - 1) * 16 + 4 * g4;
+                        const v2i val = pack(acc[TN - 1][j], sc[TN - 1]);
+                        if (m < M && n + 4 <= N) *reinterpret_cast<v2i*>(row + n) = val;
+                    }
+                    static_for<0, TN / 2>([&](auto pc) PQ_INLINE {
+                        constexpr int i = 2 * decltype(pc)::value;
+                        const v2i even = pack(acc[i][j], sc[i]);
+                        // rows 0 .. 3 of 16 lanes hold channels 0-3, 4-7, 8-11, 12-15 of either operand; after the swap rows 0
+                        // and 2 hold 0-7 and 8-15 of the even one, rows 1 and 3 of the odd one
+                        const v2i odd = pack(acc[i + 1][j], sc[i + 1]);
+                        const auto s0 = __builtin_amdgcn_permlane16_swap(even.x, odd.x, false, false);
+                        const auto s1 = __builtin_amdgcn_permlane16_swap(even.y, odd.y, false, false);
+                        const v4i val = {(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
+                        const int n = nb + i * 16 + (g4 & 1) * 16 + (g4 >> 1) * 8;
+                        if (m < M && n + 8 <= N) *reinterpret_cast<v4i*>(row + n) = val;
+                    });
                 }
-                static_for<0, TN / 2>([&](auto pc) PQ_INLINE {
-                    constexpr int i = 2 * decltype(pc)::value;
-                    const v2i even = pack(acc[i][j], sc[i]);
-                    // rows 0 .. 3 of 16 lanes hold channels 0-3, 4-7, 8-11, 12-15 of either operand; after the swap rows 0
-                    // and 2 hold 0-7 and 8-15 of the even one, rows 1 and 3 of the odd one
-                    const v2i odd = pack(acc[i + 1][j], sc[i + 1]);
-                    const auto s0 = __builtin_amdgcn_permlane16_swap(even.x, odd.x, false, false);
-                    const auto s1 = __builtin_amdgcn_permlane16_swap(even.y, odd.y, false, false);
-                    const v4i val = {(int)s0[0], (int)s1[0], (int)s0[1], (int)s1[1]};
-                    const int n = nb + i * 16 + (g4 & 1) * 16 + (g4 >> 1) * 8;
-                    if (m < M && n + 8 <= N) *reinterpret_cast<v4i*>(row + n) = val;
-                });
             }
         });
     };
@@ -376,6 +418,24 @@ __global__ __launch_bounds__(256) void k_gemm_f6_square(const uint8_t* __restric
 // The tiles that are built, 10 * TM + TN.  (Of fifteen swept, those that were the fastest somewhere; the first one on equal estimates.)
 constexpr int kTiles[] = {88, 78, 68, 58, 48, 87, 66, 46, 44, 64};
 
+// Whether the output goes past the memory-side cache.  An output that stays there takes the place of operands that the next calls read again
+// (471 x 8960 -> 12336, three copies in turn 47.3 -> 36.4 us, 1500 x 4096 -> 2 x 11008 100 -> 83.6, 2048 x 8192 -> 10240 102 -> 93, 4735 x
+// 15360 -> 2288 96.2 -> 87); pieces that are no whole lines cost a non-temporal store more.  By the pieces of a wavefront's rows:
+// - whole lines of 128 bytes (112 runs 0.964 x, geometric mean, 0.835 to 1.02), unless the operands alone fill the cache (2048 x 4096 -> 128256, one
+//   copy 589 -> 615);
+// - halves, up to half the cache (2048 x 8192 -> 28672 241 -> 259, 2867 x 7680 -> 14368, six copies, 166 -> 180; 259 x 3328 -> 2 x 24736, two
+//   copies 51.0 -> 41.7);
+// - 32 bytes, on long rows, whose outputs are few beside the operands (1724 x 1024 -> 15440 28.9 -> 37.5, 2195 x 4608 -> 3824 25.7 -> 28.2; 618 x
+//   10496 -> 9904, three copies 52.0 -> 40.7).
+bool streams_output(int TN, int64_t M, int64_t N, int64_t K, const void* out, const Second& two)
+{
+    const int64_t operands = (M + (two.w6 ? 2 : 1) * N) * K / 4 * 3, mib = 1 << 20;
+    const uintptr_t start = (uintptr_t)out | (uintptr_t)two.out | (uintptr_t)(2 * N);
+    if (start % 128 == 0 && TN % 4 == 0) return operands < 256 * mib;
+    if (start % 64 == 0) return operands < 128 * mib;
+    return TN % 2 == 0 && K >= 6144 && operands < 96 * mib;
+}
+
 template <int TM, int TN>
 int launch_tile(const void* x6, const void* w6, const float* sw, float sx, int64_t M, int64_t N, int64_t K, void* out, int32_t* acc,
                 hipStream_t st, const Second& two)
@@ -383,16 +443,19 @@ int launch_tile(const void* x6, const void* w6, const float* sw, float sx, int64
     using T = Tile<TM, TN>;
     const int GM = (int)((M + T::BM - 1) / T::BM), GN = (int)((N + T::BN - 1) / T::BN);
     const int64_t tiles = (two.w6 ? 2 : 1) * (int64_t)GM * GN;
-    auto launch = [&](auto twoc) {
-        auto kern = k_gemm_f6_square<TM, TN, decltype(twoc)::value>;
-        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per tile and count)
+    auto launch = [&](auto twoc, auto streamc) {
+        auto kern = k_gemm_f6_square<TM, TN, decltype(twoc)::value, decltype(streamc)::value>;
+        static std::atomic<uint64_t> lds_ok{0};      // (of this kernel: the lambda is instantiated per tile, count and kind of store)
         if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), T::kLds, lds_ok) != PQ_OK) return (int)PQ_ERR_HIP;
         hipLaunchKernelGGL(kern, dim3((unsigned)(tiles < kWorkgroups ? tiles : kWorkgroups)), dim3(256), T::kLds, st,
                            static_cast<const uint8_t*>(x6), static_cast<const uint8_t*>(w6), sw, sx, (int)M, (int)N, (int)K, GM, GN,
                            static_cast<__half*>(out), acc, two);
         return hip_status(hipGetLastError());
     };
-    return two.w6 ? launch(std::true_type{}) : launch(std::false_type{});
+    const std::true_type yes;
+    const std::false_type no;
+    if (out && streams_output(TN, M, N, K, out, two)) return two.w6 ? launch(yes, yes) : launch(no, yes);
+    return two.w6 ? launch(yes, no) : launch(no, no);
 }
 
 }  // namespace

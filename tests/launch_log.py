@@ -1,7 +1,7 @@
 """What library calls would launch, read without a GPU: the calls run in a process of their own on a stand-in for the runtime's
 launch entries (launch_log.cpp).  `launches(calls)`: one entry per call, its status and its ("launch" or "allow", kernel, workgroups,
 bytes of dynamic LDS) in order.  A call is a dict: fn ("linear", "linear2", "f6", "f6_two"), M, K, N (N2: of the second matrix), h, variant
-(pq_set_gemm_variant), over ("out": the output lies over the tokens, "out_b": the second one does)."""
+(pq_set_gemm_variant), over ("out": the output lies over the tokens, "out_b": the second one does), start (bytes that the outputs start behind a line)."""
 
 import ctypes
 import functools
@@ -44,7 +44,7 @@ def _main():
     for c in json.load(sys.stdin):
         M, K, N, N2, h, room = i64(c["M"]), i64(c["K"]), i64(c["N"]), i64(c.get("N2", c["N"])), i32(c.get("h", 1)), size(1 << 36)
         over = c.get("over")
-        a, b = x if over == "out" else oa, x if over == "out_b" else ob
+        a, b = (x if over == o else p(t.value + c.get("start", 0)) for o, t in (("out", oa), ("out_b", ob)))
         pq.pq_set_gemm_variant(c.get("variant", 0))
         log.launch_log_clear()
         fn = c["fn"]

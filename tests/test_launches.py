@@ -5,6 +5,7 @@ import os
 import pytest
 
 from launch_log import kernels, launches
+from square_tiles import LARGE, ONE, STREAM_ONE, STREAM_TWO, TWO
 
 pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"), reason="no HIP headers")
 
@@ -48,3 +49,18 @@ def test_every_kernel_is_allowed_its_dynamic_lds():
     assert not allowed_before_launched(events)
     for family, count in (("k_stream_fused<", 4), ("k_stream_mfma<4", 3), ("k_gemm_f6_square<", 10), ("k_decode<", 6)):
         assert sum(k.startswith(family) for k in used) >= count, (family, used)
+
+
+@pytest.mark.parametrize("cases,fn,streamed", [(ONE, "f6", 0), (TWO, "f6_two", 0), (STREAM_ONE, "f6", 1), (STREAM_TWO, "f6_two", 1), (LARGE, "f6", 0)])
+def test_near_square_tiles_and_how_they_store(cases, fn, streamed):
+    done = launches([dict(fn=fn, M=M, K=K, N=N) for _, M, N, K in cases])
+    want = ["k_gemm_f6_square<%d, %d, %s, %s>" % (t // 10, t % 10, ("false", "true")[fn == "f6_two"], ("false", "true")[streamed])
+            for t, _, _, _ in cases]
+    assert [kernels(events)[-1] for _, events in done] == want
+
+
+@pytest.mark.parametrize("fn,M,K,N", [("f6", 2319, 1024, 10048), ("f6_two", 772, 1024, 9920)])
+def test_outputs_that_start_within_a_line(fn, M, K, N):
+    """The start of the output counts as the length of its rows does: whole lines from 128 bytes on, halves from 64."""
+    done = launches([dict(fn=fn, M=M, K=K, N=N, start=s) for s in (0, 128, 64, 32, 16)])
+    assert [kernels(events)[-1].endswith("true>") for _, events in done] == [True, True, True, False, False]
