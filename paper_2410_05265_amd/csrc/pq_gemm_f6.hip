@@ -1000,7 +1000,7 @@ PersistentPlan persistent_plan(int64_t M, int64_t N, int64_t mats, int forced_ti
     return p;
 }
 
-// Which kernel a product takes: the one of least estimated time.  Two matrices count as one of twice the height.
+// Which kernel a product takes, by estimated times.  Two matrices count as one of twice the height.
 struct ProductPlan {
     bool ksplit;
     int square;                  // the tile of pq_gemm_f6_square.hip, or 0
@@ -1008,19 +1008,22 @@ struct ProductPlan {
 };
 
 // The estimates of the persistent launch and of the near-square tiles are fits to 191 measured shapes (24 to 9000 tokens, K 1024 to
-// 28672, N 512 to 30000, one matrix and two; three copies of the operands in turn; 7 % rms near the choice).  Near-square tiles against
-// the rule that knew only 256 x 256 ones of one matrix: geometric mean 1.08 over those; over 121 further shapes whose kernel
-// changed 1.17 (682 x 13568 -> 11024 135 -> 69 us, 2048 x 4096 -> 2 x 14336 150.5 -> 147.7, 963 x 6400 -> 2 x 10368 104.5 -> 87.8, 1557 x 28672
-// -> 1296 and like it, formerly K split, up to 2.7).  Where operands of 70 to 90 MB take turns by threes, so that they just fit the
-// memory-side cache, the persistent launch stays ahead (471 x 8960 -> 12336 36 -> 47, 2048 x 8192 -> 10240 92 -> 102): its outputs bypass
-// that cache.  With one copy (38.1 -> 37.5, 91.9 -> 90.8) or six (49.3 -> 49.4, 122 -> 103) it does not, so the rule ignores it.
+// 28672, N 512 to 30000, one matrix and two; three copies of the operands in turn; 7 % rms near the choice).  They were fitted before the
+// near-square tiles' outputs went past the memory-side cache, which made those 1 to 20 % faster, so near-square tiles are taken up to 3 %
+// above the other estimate: 0.87 x, geometric mean, of the time of the rule that knew only 256 x 256 tiles of one matrix over 603 runs
+// whose kernel changed with it (one to six copies; 682 x 13568 -> 11024 135 -> 69 us, 963 x 6400 -> 2 x 10368 104.5 -> 87.8, 1557 x 28672 -> 1296 and like it,
+// formerly K split, up to 2.7 x), 12 of them more than 2 % above it, the worst 8 %.
 //
-// Rows under 6144 channels: the two lie close, and a round's fixed part counts for more.
-// - onto 8192 channels and more, of operands that the memory-side cache holds, near-square tiles need 7 % on paper (2048 x 4096 ->
-//   14336 66.5 -> 69.7, 1505 x 4864 -> 22784 101 -> 107; from HBM 900 x 4096 -> 49152 131 -> 114, 450 x 2048 -> 128256 121 -> 98);
-// - many of them onto output rows a multiple of 32 KiB apart stay: a round of 16 row tiles then writes to the same few memory
-//   channels (4096 x 3072 -> 65536 543 -> 581, -> 32768 237 -> 279, -> 16384 120 -> 135 (one copy 122 -> 108); -> 65552 646 -> 511);
-// - and those under 2048 channels with 64 MB of output: 4889 x 1280 -> 2 x 6496 74 -> 88 (one copy 75.2 -> 73.8).
+// Rows under 6144 channels, where the two lie close: exceptions for outputs that are not stored as whole lines (rows of N no multiple of
+// 64, or tiles with other than 4 or 8 operands of channels a wavefront), which stay in the cache or cost a store more.  With whole lines
+// the same exceptions would hold back 230 runs that near-square tiles do in 0.925 x (1024 x 4096 -> 2 x 22016 130 -> 108 us, 8192 x 4096 ->
+// 16384 302 -> 284, 4096 x 3072 -> 16384 126 -> 118; three over 1.02 besides the last one here).
+// - onto 8192 channels and more, of operands that are under half the cache, they need 7 % on paper (2048 x 4096 -> 14336 66.7 -> 67.5,
+//   3403 x 3840 -> 14976 121 -> 126, 1488 x 3328 -> 16896 59 -> 62.5, 1004 x 2816 -> 22672 47 -> 52; 1024 x 4096 -> 2 x 14336, 7 % below on paper,
+//   76 -> 69);
+// - those under 2048 channels with 64 MB of output: 4889 x 1280 -> 2 x 6496 77 -> 81, 1979 x 1280 -> 2 x 8800 45.8 -> 47.6;
+// - and with whole lines too, many rows 128 KiB apart: a round of 16 row tiles then writes to the same few memory channels (4096 x 3072 ->
+//   65536, three copies 551 -> 571; -> 65552 646 -> 511).
 //
 // K split over the wavefronts of a workgroup is for outputs of few tiles, which leave most CUs without one and the others
 // alone with K (333 x 4096 x 4096: 17.8 -> 10.0 us, 64 x 4096 x 14336: 44 -> 10.6; two launches of few tiles -> one, with the quantizer: 128
@@ -1036,8 +1039,9 @@ ProductPlan product_plan(int64_t M, int64_t N, int64_t K, bool two)
     const double rounds = p.persistent.rounds, area = (double)(mats * M) * N / (128.0 * 512 * G), idle = area < rounds ? 1.0 - area / rounds : 0.0;
     double us = rounds * (10.657 + H * 0.9673 * (1.0 - 0.476 * idle)) - 0.01 * out_mb - 1.075, square_us;
     const int tile = gemm_f6_square_tile(M, N, K, two, &square_us);
-    const bool shorter = K < 6144, wide = shorter && N >= 8192 && (M + N) * K / 4 * 3 < ((int64_t)128 << 20);
-    const bool stays = (shorter && M > 15 * 256 && N % 16384 == 0) || (K < 2048 && out_mb >= 64);
+    const bool shorter = K < 6144, lines = N % 64 == 0 && (tile % 10) % 4 == 0;
+    const bool wide = shorter && !lines && N >= 8192 && (M + mats * N) * K / 4 * 3 < ((int64_t)128 << 20);
+    const bool stays = (shorter && M > 15 * 256 && N % 65536 == 0) || (K < 2048 && !lines && out_mb >= 64);
     if (tile != 0 && !stays && us >= (wide ? 1.067 : 0.97) * square_us) {
         p.square = tile;
         us = square_us;

@@ -64,3 +64,15 @@ def test_outputs_that_start_within_a_line(fn, M, K, N):
     """The start of the output counts as the length of its rows does: whole lines from 128 bytes on, halves from 64."""
     done = launches([dict(fn=fn, M=M, K=K, N=N, start=s) for s in (0, 128, 64, 32, 16)])
     assert [kernels(events)[-1].endswith("true>") for _, events in done] == [True, True, True, False, False]
+
+
+# channels in under 6144: tokens, channels in, channels out; measured us of the other kernel and of near-square tiles, three sets of operands
+@pytest.mark.parametrize("fn,M,K,N,other_us,square_us", [
+    ("f6_two", 1024, 4096, 22016, 129.5, 108.2), ("f6_two", 2048, 4096, 22016, 236.5, 212.0), ("f6_two", 3000, 4096, 22016, 364.4, 347.4),
+    ("f6_two", 4889, 1280, 6496, 77.3, 81.4), ("f6_two", 1979, 1280, 8800, 45.8, 47.6), ("f6", 2048, 4096, 14336, 66.7, 67.6),
+    ("f6", 4096, 3072, 16384, 126.8, 119.3), ("f6", 4096, 3072, 32768, 253.9, 249.9), ("f6", 4096, 3072, 65536, 550.8, 571.3),
+    ("f6", 8192, 4096, 16384, 301.4, 285.6), ("f6", 3403, 3840, 14976, 121.4, 125.9), ("f6", 1004, 2816, 22672, 47.1, 51.6),
+    ("f6", 641, 3072, 17920, 28.2, 25.3), ("f6", 1505, 4864, 22784, 102.1, 94.3), ("f6", 5024, 1280, 17344, 110.8, 97.2)])
+def test_near_square_tiles_of_short_rows_where_they_were_measured_faster(fn, M, K, N, other_us, square_us):
+    (_, events), = launches([dict(fn=fn, M=M, K=K, N=N)])
+    assert kernels(events)[-1].startswith("k_gemm_f6_square<") == (square_us < other_us)
