@@ -60,8 +60,12 @@ __device__ __forceinline__ int bitrev(int x, int bits)
     return r;
 }
 
-// MODE 0: packed codes are given (xq_in); 1: rows are fp16, quantized with exact ties (log2h == 0)
-// or rotated with blocks of 2^log2h <= 2048 first; 2: rotated with blocks of 4096 (on the matrix pipe).
+constexpr int kRegChannels = 32768;         // rows that the threads of a workgroup hold in registers, e.g. one token of 28672
+
+// MODE 0: packed codes are given (xq_in); 1: rows are fp16, rotated with blocks of 2^log2h <= 2048 first, or, where they are more than the
+// registers hold, quantized with exact ties (log2h == 0); 2: rotated with blocks of 4096 (on the matrix pipe); 3: quantized with
+// exact ties, up to kRegChannels channels in all.  (3 as a branch of 1 is at the mercy of what the rotation's code does to its place in
+// the instruction cache, which every launch fills anew: 1 x 896 -> 560 2.92 us, 2.97 with the rotation's one-instruction stages beside it, 2.69 alone.)
 // One workgroup of 16 wavefronts per CU; a wavefront owns RPW weight rows at a time and has
 // RPW * CB 16-byte loads in flight; MP = padded M.
 // ABITS = 8 (given codes only): the activation codes are int8 in the grouped order (16 even
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
 
     // ---- 1. first pieces of the activation rows (ordinary loads, issued before the weights:
     // loads complete in order, so waiting for these leaves the weight loads in flight)
-    constexpr int XB = 4;   // enough for 32768 channels in all (e.g. one token of 28672); more pieces wait behind the weights
+    constexpr int XB = kRegChannels / 8192;   // (more pieces, if any, wait behind the weights)
     const uint8_t* xsrc = MODE == 0 ? xq_in : reinterpret_cast<const uint8_t*>(x);
     const int pieces = (MODE == 0 ? M * Ka : M * K * 2) >> 4;   // 16-byte pieces
     uint8_t* xdst = MODE == 0 ? xs : smem + xraw_off;
@@ -157,9 +161,9 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
     // wavefront holds channels 8 l .. 8 l + 7 of 512 consecutive ones, which is what the register form of
     // the quantizer expects), and writes the packed dword: no staging of the fp16 rows, one barrier.
     // Otherwise: rows into LDS (later pieces, if any, wait behind the weights), then chunk by chunk.
-    const bool in_registers = MODE == 1 && log2h <= 9 && pieces <= 1024 * XB;
+    const bool in_registers = MODE == 3 || (MODE == 1 && log2h >= 1 && log2h <= 9 && pieces <= 1024 * XB);
     if (in_registers) {
-        if constexpr (MODE == 1) {
+        if constexpr (MODE == 1 || MODE == 3) {
 #pragma unroll
             for (int u = 0; u < XB; ++u) {
                 const int i = tid + 1024 * u;
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(1024) void k_decode(const __half* __restrict__ x, c
                     const v4i raw1[1] = {xr[u]};
                     const bool live1[1] = {i < pieces};
                     auto dst = (rq::lds_u32_ptr)xs;           // piece i -> dword i: rows are contiguous, K / 8 dwords each
-                    if (log2h == 0)
+                    if constexpr (MODE == 3)
                         rq::rotate_quant_regs_with<1, true, 4>(raw1, live1, 0, 0, rq::StaticStep{mult, sx}, dst,
                                                                (rq::lds_f32_ptr) nullptr, i, live1[0]);
                     else
@@ -330,7 +334,7 @@ int launch_one(const __half* x, const uint8_t* xq_in, const uint8_t* wq, const f
                const float* srow, const int32_t* zcorr, const DecodeSecond& two)
 {
     const size_t lds = (((size_t)MP * (ABITS == 8 ? K : K / 2) + 15) & ~(size_t)15) +
-                       (MODE == 0 ? 16 : (MODE == 1 ? (size_t)kChunk * 4 + (size_t)M * K * 2 : 16 + (size_t)M * (K / 128) * rq::kXPitch));
+                       (MODE == 0 || MODE == 3 ? 16 : (MODE == 1 ? (size_t)kChunk * 4 + (size_t)M * K * 2 : 16 + (size_t)M * (K / 128) * rq::kXPitch));
     auto kern = k_decode<RPW, CB, MP, MODE, ABITS>;
     static std::atomic<uint64_t> lds_ok{0};
     if (lds > 48 * 1024 && allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_ok) != PQ_OK)
@@ -358,6 +362,8 @@ int launch_mode(const __half* x, const uint8_t* xq_in, const uint8_t* wq, const 
     if constexpr (MP > 4) return PQ_ERR_UNSUPPORTED;   // more than 4 tokens: codes only, no fused quantizer
     else if (h <= 1) {
         const float inv = (float)(1.0 / (double)sx);
+        if ((int64_t)M * K <= kRegChannels)
+            return launch_one<RPW, CB, MP, 3>(x, xq_in, wq, sw, sx, inv, 0, M, N, K, out, acc, xq_out, st, srow, zcorr, two);
         return launch_one<RPW, CB, MP, 1>(x, xq_in, wq, sw, sx, inv, 0, M, N, K, out, acc, xq_out, st, srow, zcorr, two);
     }
     else {

@@ -113,3 +113,19 @@ def test_output_over_the_tokens(pq, M, K):
         else:
             pq.pq_linear(y, w, sw, step, 1, out=y, workspace=ws)
         assert np.array_equal(bits(y), bits(want))
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 32, 16), (1, 32768, 528), (2, 544, 272), (3, 10912, 48), (4, 8192, 4112), (4, 8224, 48)])
+def test_up_to_four_tokens(pq, M, K, N):
+    """The fused launch of few tokens, with rows that the registers hold to the last piece, and more than that."""
+    step, x = 0.3719, dev(inputs(M, K, 0.3719, M + K))
+    w, sw = dev(synth.random_packed(N, K, seed=N + K, stream=7)), dev(synth.random_scales(N, seed=N))
+    prev = pq.pq_set_gemm_variant(4)
+    try:
+        out, ws = pq.pq_linear(x, w, sw, step, 1)
+        oa, ob, _ = pq.pq_linear2(x, w, sw, w[:16], sw[:16], step, 1)
+    finally:
+        pq.pq_set_gemm_variant(prev)
+    ref, wr = general(pq, lambda: pq.pq_linear(x, w, sw, step, 1))
+    assert np.array_equal(host(ws)[: M * K // 2], host(wr)[: M * K // 2])
+    assert np.array_equal(bits(out), bits(ref)) and np.array_equal(bits(oa), bits(ref)) and np.array_equal(bits(ob), bits(ref)[:, :16])

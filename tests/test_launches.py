@@ -76,3 +76,9 @@ def test_outputs_that_start_within_a_line(fn, M, K, N):
 def test_near_square_tiles_of_short_rows_where_they_were_measured_faster(fn, M, K, N, other_us, square_us):
     (_, events), = launches([dict(fn=fn, M=M, K=K, N=N)])
     assert kernels(events)[-1].startswith("k_gemm_f6_square<") == (square_us < other_us)
+
+
+def test_unrotated_tokens_have_a_kernel_of_their_own_up_to_what_registers_hold():
+    calls = [dict(fn="linear", M=M, K=K, N=528, h=h, variant=4) for M, K, h in ((1, 32768, 1), (4, 8192, 0), (4, 8224, 1), (1, 32768, 64), (1, 4096, 4096))]
+    modes = [kernels(events)[0].split(", ")[3] for _, events in launches(calls)]
+    assert modes == ["3", "3", "1", "1", "2"]
