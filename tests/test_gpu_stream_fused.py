@@ -1,15 +1,15 @@
 """The layer of 5 to 16 tokens without rotation in one launch (and of two matrices from 2 tokens on): codes and outputs are those
-of the quantizer launch and the tiled product, bit for bit, over all forms that the rule takes.
+of the quantizer launch and the tiled product, bit for bit.  The shapes, and that they take this launch: fused_shapes.py, test_launches.py.
 
-Sizes: rows of one unit of 256 channels to several a wavefront, slices of K that stay empty or end early, wavefronts that share a
-slice, odd and even token counts, one row group to more tasks than a workgroup keeps open, a second matrix that starts inside
-a task.  Inputs: values on rounding ties of the step and one fp16 step beside them, infinities, NaN, zeros and subnormals.
+A second matrix starts inside a task; token counts are odd and even.  Inputs: values on rounding ties of the step and one fp16 step beside
+them, infinities, NaN, zeros and subnormals.
 """
 
 import numpy as np
 import pytest
 import torch
 
+import fused_shapes
 import oracle as O
 from paper_2410_05265_amd import synth
 from pq_testlib import check_end_to_end, dev, host
@@ -44,13 +44,9 @@ def bits(t):
     return host(t).view(np.uint16)
 
 
-ONE = [(5, 256, 16), (16, 768, 272), (7, 1280, 528), (6, 2048, 1040), (9, 2304, 48), (16, 4096, 4096), (13, 4096, 14336), (8, 4352, 4112),
-       (5, 11008, 4096), (11, 1024, 66128), (15, 512, 40000)]
-
-
 @pytest.mark.parametrize("step", [0.25, 0.3719])
-@pytest.mark.parametrize("M,K,N", ONE)
-def test_one_matrix(pq, M, K, N, step):
+@pytest.mark.parametrize("_,M,K,N", fused_shapes.ONE)
+def test_one_matrix(pq, _, M, K, N, step):
     x = dev(inputs(M, K, step, M + K))
     w, sw = dev(synth.random_packed(N, K, seed=N + K, stream=7)), dev(synth.random_scales(N, seed=N))
     out, ws = pq.pq_linear(x, w, sw, step, 1)
@@ -59,9 +55,8 @@ def test_one_matrix(pq, M, K, N, step):
     assert np.array_equal(bits(out), bits(ref))
 
 
-@pytest.mark.parametrize("M,K,Na,Nb", [(2, 28672, 272, 16), (3, 12288, 1040, 2064), (5, 1024, 528, 272), (12, 2048, 4096, 4096), (16, 4096, 11008, 11008),
-                                       (16, 8192, 1008, 528), (6, 256, 16, 33024)])
-def test_two_matrices(pq, M, K, Na, Nb):
+@pytest.mark.parametrize("_,M,K,Na,Nb", fused_shapes.TWO)
+def test_two_matrices(pq, _, M, K, Na, Nb):
     step = 0.3719
     x = dev(inputs(M, K, step, M + K))
     wa, sa = dev(synth.random_packed(Na, K, seed=Na + K, stream=7)), dev(synth.random_scales(Na, seed=Na))

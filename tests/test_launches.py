@@ -4,6 +4,7 @@ import os
 
 import pytest
 
+import fused_shapes
 from launch_log import kernels, launches
 from square_tiles import LARGE, ONE, STREAM_ONE, STREAM_TWO, TWO
 
@@ -82,3 +83,22 @@ def test_unrotated_tokens_have_a_kernel_of_their_own_up_to_what_registers_hold()
     calls = [dict(fn="linear", M=M, K=K, N=528, h=h, variant=4) for M, K, h in ((1, 32768, 1), (4, 8192, 0), (4, 8224, 1), (1, 32768, 64), (1, 4096, 4096))]
     modes = [kernels(events)[0].split(", ")[3] for _, events in launches(calls)]
     assert modes == ["3", "3", "1", "1", "2"]
+
+
+@pytest.mark.parametrize("cases", [fused_shapes.ONE, fused_shapes.TWO])
+def test_fused_launch_of_up_to_16_tokens(cases):
+    done = launches([dict(fn="linear2" if len(c) == 5 else "linear", M=c[1], K=c[2], N=c[3], N2=c[-1]) for c in cases])
+    assert [kernels(events) for _, events in done] == [["k_stream_fused<%d, %d>" % c[0]] for c in cases]
+
+
+def test_every_fused_kernel_runs_several_tasks_of_several_units():
+    """What the shapes above are there for: each kernel, and with more than one unit a wavefront also several tasks a workgroup, so that tasks end
+    inside a round and sums leave before the last one."""
+    seen = set()
+    for c in fused_shapes.ONE + fused_shapes.TWO:
+        P, N = c[2] // 256, sum(c[3:])
+        slices = 16 if P > 8 else (8 if P > 4 else 4)
+        units, tasks = -(-P // slices), -(-(N // 16) // (16 // slices))
+        seen.add((c[0], "units" if units > 1 else "unit", "tasks" if -(-tasks // min(tasks, 256)) > 2 else "task"))
+    assert {k for k, _, _ in seen} == {(2, 8), (4, 8), (2, 16), (4, 16)}
+    assert {((4, 8), "units", "tasks"), ((4, 16), "units", "tasks"), ((4, 8), "unit", "tasks")} <= seen
