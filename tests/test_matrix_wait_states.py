@@ -35,7 +35,7 @@ class Instruction:
     """What an instruction does to the registers, in the terms of the rules above."""
 
     def __init__(self, line, in_asm):
-        self.line = line
+        self.line, self.in_asm = line, in_asm
         op, _, rest = line.partition(" ")
         operands = [registers(o) for o in re.split(r",(?![^\[]*\])", rest)] if rest else []
         self.wait = op == "s_nop"
@@ -94,7 +94,7 @@ def step(pending, ins, report):
     return pending
 
 
-def violations(blocks, labels):
+def violations(blocks, labels, step=step):
     report, entry, todo = [], {0: {}}, [0]
     while todo:
         at = todo.pop()

@@ -9,35 +9,81 @@ import numpy as np
 import pytest
 
 from paper_2410_05265_amd import build
+from test_matrix_wait_states import NO_RESULT, functions, registers, violations
 
 
-@pytest.mark.parametrize("name", ["pq_rotate_quant.hip", "pq_gemm_f6.hip", "pq_decode.hip"])
-def test_no_exchange_follows_its_writer_too_closely(name, tmp_path):
-    """Between a vector instruction that writes a register and one that reads it through an exchange of lanes lie two others (or s_nop
-    for them), along every straight run of the code and across labels."""
-    out = str(tmp_path / "k.s")
-    subprocess.run([build.HIPCC, *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, name), "-o", out], check=True,
-                   stderr=subprocess.DEVNULL)
-    recent, seen = [], 0                                                 # (registers written, wait states since)
-    for line in open(out):
-        line = line.split(";")[0].strip()
-        if not line or line.startswith(".") and not line.endswith(":") or line.endswith(":"):
-            continue
-        op, _, rest = line.partition(" ")
-        if "_dpp" in op:
-            seen += 1
-            src = re.findall(r"v\d+", rest)[1]
-            assert all(src not in regs for regs, age in recent if age < 2), line
-        step = 1
-        if op == "s_nop":
-            step = int(rest, 0) + 1
-        recent = [(regs, age + step) for regs, age in recent if age + step < 2]
-        if op.startswith("v_") and not op.startswith("v_cmp"):
-            m = re.match(r"v(\d+)\b|v\[(\d+):(\d+)\]", rest.strip())
-            if m:
-                lo, hi = (int(m.group(1)),) * 2 if m.group(1) else (int(m.group(2)), int(m.group(3)))
-                recent.append(({"v%d" % r for r in range(lo, hi + 1)}, 0))
-    assert seen > 50
+# every source that the rotation is compiled into
+SOURCES = [os.path.basename(f) for f in build.sources() if '#include "pq_rotate.h"' in open(f).read()]
+# states between a vector instruction that writes a register, or the lanes' mask, and an exchange of lanes that reads it; between a matrix
+# instruction and an exchange in the stages' assembly (the compiler sees to its own)
+AFTER_WRITE, AFTER_MASK, AFTER_MATRIX = 2, 5, 18
+EXCHANGE = ("_dpp", "v_permlane16_swap", "v_permlane32_swap")
+
+
+def step(pending, ins, report):
+    """As its namesake of the matrix instructions: pending maps (register or "mask") to the states that still have to pass."""
+    op, _, rest = ins.line.partition(" ")
+    operands = [registers(o) for o in re.split(r",(?![^\[]*\])", rest)] if rest else []
+    if any(e in op for e in EXCHANGE):
+        reads = operands[0] | operands[1] if "swap" in op else operands[1]
+        for key in reads | {"mask"} | {("matrix", reg) for reg in reads if ins.in_asm}:
+            if key in pending:
+                report.append("%s: %s %d states too early" % (ins.line, key, pending[key]))
+    pending = {k: left - ins.states for k, left in pending.items() if left > ins.states}
+    if op.startswith("v_cmpx"):
+        pending["mask"] = AFTER_MASK
+    elif op.startswith("v_") and not op.startswith(NO_RESULT) and operands:
+        for reg in operands[0] | (operands[1] if "swap" in op else frozenset()):
+            if op.startswith("v_mfma"):
+                pending["matrix", reg] = AFTER_MATRIX
+            else:
+                pending[reg] = AFTER_WRITE
+                pending.pop(("matrix", reg), None)
+    return pending
+
+
+@pytest.fixture(scope="module")
+def compiled(tmp_path_factory):
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("hipcc not installed")
+    folder = tmp_path_factory.mktemp("asm")
+    procs = [(s, subprocess.Popen([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, s), "-o", str(folder / s)],
+                                  stderr=subprocess.PIPE, text=True)) for s in SOURCES]
+    out = {}
+    for s, pr in procs:
+        _, err = pr.communicate()
+        assert pr.returncode == 0, err[-4000:]
+        out[s] = functions((folder / s).read_text())
+    return out
+
+
+def test_sources_are_found():
+    assert {"pq_rotate_quant.hip", "pq_gemm_f6.hip", "pq_decode.hip", "pq_stream_mfma.hip", "pq_calibrate.hip"} <= set(SOURCES)
+
+
+@pytest.mark.parametrize("name", SOURCES)
+def test_no_exchange_follows_its_writer_too_closely(compiled, name):
+    """Along every path through the compiled kernels: the compiler does not see into the stages' assembly, neither what they read nor that
+    they write."""
+    exchanges = 0
+    for kernel, (blocks, labels) in compiled[name].items():
+        exchanges += sum("_dpp" in i.line for b in blocks for i in b)
+        bad = violations(blocks, labels, step)
+        assert not bad, "%s: %d, first %s" % (kernel, len(bad), bad[:3])
+    assert exchanges > 50
+
+
+@pytest.mark.parametrize("lines,bad", [
+    (["v_add_f32_e32 v1, v2, v3", "v_fmac_f32_dpp v1, v1, v4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"], 1),
+    (["v_add_f32_e32 v1, v2, v3", "s_nop 1", "v_fmac_f32_dpp v1, v1, v4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"], 0),
+    (["v_add_f32_e32 v1, v2, v3", "s_nop 0", "s_cbranch_scc1 .LBB0_1", "s_nop 7", ".LBB0_1:", "v_mov_b32_dpp v5, v1 row_half_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1"], 0),
+    (["v_add_f32_e32 v1, v2, v3", "s_cbranch_scc1 .LBB0_1", "s_nop 7", ".LBB0_1:", "v_mov_b32_dpp v5, v1 row_half_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1"], 1),
+    (["v_cmpx_lt_u32_e32 v1, v2", "s_nop 3", "v_mov_b32_dpp v5, v4 row_ror:8 row_mask:0xf bank_mask:0xf"], 1),
+    (["v_mfma_f32_32x32x16_f16 v[0:15], v[16:19], v[20:23], v[0:15]", "s_nop 7", ";;#ASMSTART", "v_mov_b32_dpp v25, v3 row_ror:8 row_mask:0xf bank_mask:0xf"], 1),
+    (["v_mov_b32_dpp v5, v4 row_ror:8 row_mask:0xf bank_mask:0xf", "v_permlane32_swap_b32_e32 v6, v5"], 1)])
+def test_the_count_itself(lines, bad):
+    blocks, labels = functions("_Zk:\n%s\ts_endpgm\n.Lfunc_end0:\n" % "".join(t + "\n" if t.endswith((":", "START")) else "\t%s\n" % t for t in lines))["_Zk"]
+    assert (len(violations(blocks, labels, step)) > 0) == bool(bad)
 
 
 @pytest.mark.gpu
