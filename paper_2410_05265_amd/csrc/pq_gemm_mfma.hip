@@ -928,12 +928,6 @@ int launch_gemm_mfma(const void* xq, const void* wq, const float* sw, float sx, 
     return launch_packed(xq, wq, sw, sx, M, N, K, out, acc, st, nullptr, nullptr);
 }
 
-int gemm_packed_tile(int64_t M, int64_t N, int64_t K)
-{
-    const PackedPlan p = plan_packed(M, N, K);
-    return p.cfg >= 0 || p.n1 > 0 ? 0 : 1000 * p.bm + p.bn;
-}
-
 int set_gemm_tile(int tile)
 {
     if (tile < -1 || tile >= kNumCfg) return -2;

@@ -56,8 +56,6 @@ int launch_calibrate_zp(const void* x, int64_t T, int64_t K, int32_t h, int32_t 
                         float beta_min, float* result, float* ws, hipStream_t st);
 int launch_gemm_simple(const void* xq, const void* wq, const float* sw, float sx, int64_t M,
                        int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st);
-// (gemm_packed_tile: the tile that its kernel takes by size, 1000 * rows + channels; 0: two widths in one launch, or a forced one)
-int gemm_packed_tile(int64_t M, int64_t N, int64_t K);
 int launch_gemm_mfma(const void* xq, const void* wq, const float* sw, float sx, int64_t M,
                      int64_t N, int64_t K, void* out, int32_t* acc, hipStream_t st);
 // The tiled kernel with K split over workgroups where a cost model finds that cheaper (few tokens

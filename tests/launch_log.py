@@ -1,6 +1,7 @@
 """What library calls would launch, read without a GPU: the calls run in a process of their own on a stand-in for the runtime's
 launch entries (launch_log.cpp).  `launches(calls)`: one entry per call, its status and its ("launch" or "allow", kernel, workgroups,
-bytes of dynamic LDS) in order.  A call is a dict: fn ("linear", "linear2", "f6", "f6_two"), M, K, N (N2: of the second matrix), h, variant
+bytes of dynamic LDS) in order.  A call is a dict: fn ("linear", "linear2", "gemm": the product of
+packed codes, "f6": of prepacked ones, "f6_two": the layer of two prepacked matrices), M, K, N (N2: of the second matrix), h, variant
 (pq_set_gemm_variant), over ("out": the output lies over the tokens, "out_b": the second one does), start (bytes that the outputs start behind a line)."""
 
 import ctypes
@@ -52,6 +53,8 @@ def _main():
             rc = pq.pq_linear(x, wa, sa, f32(0.5), h, M, N, K, a, ws, room, p(0))
         elif fn == "linear2":
             rc = pq.pq_linear2(x, wa, sa, N, a, wb, sb, N2, b, f32(0.5), h, M, K, ws, room, p(0))
+        elif fn == "gemm":
+            rc = pq.pq_w4a4_gemm(x, wa, sa, f32(0.5), M, N, K, a, p(0), p(0))
         elif fn == "f6":
             rc = pq.pq_w4a4_gemm_f6(x, wa, sa, f32(0.5), M, N, K, a, p(0), p(0))
         else:

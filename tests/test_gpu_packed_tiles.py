@@ -2,26 +2,13 @@
 zero point, and sampled sums those of the oracle.  Rows and channels end inside a tile and inside a wavefront's 32 x 32 results; fewer
 stages than the ring holds and more; one round of tiles and two."""
 
-import ctypes
-
 import numpy as np
 import pytest
 import torch
 
 import oracle as O
+from packed_tiles import TILES      # (which take their tiles: test_launches.py)
 from pq_testlib import host
-
-# tile (1000 * tokens + channels), tokens, channels out, channels in
-TILES = [(64128, 46, 176, 128), (128128, 129, 11952, 384), (128192, 616, 9776, 128), (128320, 651, 12336, 640), (192128, 262, 13296, 384),
-         (192192, 711, 10992, 512), (192256, 917, 12688, 512), (192320, 1142, 12688, 384), (256128, 653, 8848, 384), (256192, 682, 14064, 768),
-         (256256, 1153, 12144, 384), (320128, 579, 13264, 640), (320192, 856, 14032, 640)]
-
-
-def test_every_tile_has_its_shape():
-    import paper_2410_05265_amd.binding as pq
-    rule = pq.lib()["_ZN2pq16gemm_packed_tileElll"]      # (pq::gemm_packed_tile: the launch's own rule)
-    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int64] * 3
-    assert [rule(M, N, K) for _, M, N, K in TILES] == [c[0] for c in TILES]
 
 
 @pytest.mark.gpu

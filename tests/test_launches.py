@@ -6,6 +6,7 @@ import pytest
 
 import fused_shapes
 from launch_log import kernels, launches
+from packed_tiles import TILES
 from square_tiles import LARGE, ONE, STREAM_ONE, STREAM_TWO, TWO
 
 pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"), reason="no HIP headers")
@@ -102,3 +103,8 @@ def test_every_fused_kernel_runs_several_tasks_of_several_units():
         seen.add((c[0], "units" if units > 1 else "unit", "tasks" if -(-tasks // min(tasks, 256)) > 2 else "task"))
     assert {k for k, _, _ in seen} == {(2, 8), (4, 8), (2, 16), (4, 16)}
     assert {((4, 8), "units", "tasks"), ((4, 16), "units", "tasks"), ((4, 8), "unit", "tasks")} <= seen
+
+
+def test_every_packed_tile_has_its_shape():
+    done = launches([dict(fn="gemm", M=M, K=K, N=N, variant=2) for _, M, N, K in TILES])
+    assert [kernels(events)[0].startswith("k_gemm_dma<%d, %d," % (t // 1000, t % 1000)) for (t, _, _, _), (_, events) in zip(TILES, done)] == [True] * 13

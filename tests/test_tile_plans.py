@@ -31,7 +31,7 @@ def test_square_tiles_where_they_were_measured_faster(b, M, N, K, other_us, squa
     assert b.pq_gemm_square_tiles(M, N, K) == (square_us < other_us)
 
 
-def test_square_tiles_are_for_one_matrix_and_whole_pairs(b):
+def test_square_tiles_are_for_whole_pairs(b):
     assert not b.pq_gemm_square_tiles(2048, 8192, 22144)           # an odd count of 128-channel blocks
     assert b.pq_set_gemm_f6_tile(4) == -1
     try:
