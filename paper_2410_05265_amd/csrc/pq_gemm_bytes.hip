@@ -17,8 +17,10 @@
 // operand i is replaced by the next stage's as soon as its last instruction is issued, the weights are read early and
 // expanded into a second set in the second half.
 //
-// LDS: the 16-byte unit u of an activation row t lies at position u ^ ((t >> 1) & 7), chunk c of a weight row t at
-// c ^ ((t >> 2) & 3): sixteen rows' reads of one unit fall into different banks.
+// LDS: a 16-byte read serves eight lanes a clock, four rows of chunk c and the other four of chunk c + 1 among them (not eight rows of one
+// chunk), and the places are chosen so that those lie in different banks: of an activation row t, the even unit of chunk c at
+// c ^ ((t >> 1) & 7) and the odd one at (c + 4) ^ ((t >> 1) & 7); chunk c of a weight row t at {0, 3, 1, 2}[c] ^ ((t >> 2) & 3).  1500 x 11008 ->
+// 4096: conflicts 39735 -> 758 clocks a CU, LDS busy for 79 -> 40 thousand of 118 thousand clocks; the product 1 % faster, so LDS does not bound it.
 #include "pq_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -78,8 +80,9 @@ __global__ __launch_bounds__(kNW * 64) void k_gemm_bytes(const uint8_t* __restri
         int ra = m0 + blk * 8 + lrow8, rw = n0 + (blk - BLK_A) * 16 + lrow16;
         ra = ra < M ? ra : M - 1;
         rw = rw < N ? rw : N - 1;
-        const uint32_t a = (uint32_t)ra * (uint32_t)K + (((lane & 7) ^ (((blk * 8 + lrow8) >> 1) & 7)) << 4);
-        const uint32_t w = (uint32_t)rw * (uint32_t)(K >> 1) + (((lane & 3) ^ ((lrow16 >> 2) & 3)) << 4);
+        const int ua = (lane & 7) ^ (((blk * 8 + lrow8) >> 1) & 7), uw = (lane & 3) ^ ((lrow16 >> 2) & 3);      // as below, read backwards
+        const uint32_t a = (uint32_t)ra * (uint32_t)K + (((ua & 3) << 1 | ua >> 2) << 4);
+        const uint32_t w = (uint32_t)rw * (uint32_t)(K >> 1) + ((0x1320 >> 4 * uw & 3) << 4);
         goff[i] = blk < BLK_A ? a : w;
     });
     const uint32_t lds0 = (uint32_t)(uintptr_t)PQB_LDS(smem) + wave * 1024;
@@ -96,8 +99,8 @@ __global__ __launch_bounds__(kNW * 64) void k_gemm_bytes(const uint8_t* __restri
     };
     // ---- reader
     const uint32_t row_a = (wm * (TM * 16) + r) * 128, swz = (r >> 1) & 7;
-    const uint32_t rd_a[2] = {row_a + (((2 * g) ^ swz) << 4), row_a + (((2 * g + 1) ^ swz) << 4)};
-    const uint32_t rd_b = BM * 128 + (wn * (TN * 16) + r) * 64 + ((g ^ ((r >> 2) & 3)) << 4);
+    const uint32_t rd_a[2] = {row_a + ((g ^ swz) << 4), row_a + (((g + 4) ^ swz) << 4)};
+    const uint32_t rd_b = BM * 128 + (wn * (TN * 16) + r) * 64 + (((0x2130 >> 4 * g & 3) ^ ((r >> 2) & 3)) << 4);
     auto from_lds = [&](uint32_t off) { return *(__attribute__((address_space(3))) const v4i*)(smem + off); };
 
     v4i acc[TM][TN], xa[2][TM], xb[2][2][TN], packed[TN];            // xa [even, odd]; xb [stage parity][even, odd]
