@@ -135,11 +135,14 @@ bool share_ksplit(int64_t M, int64_t N_a, int64_t N_b, int64_t K, size_t plane_b
 }
 
 // Whether pq_linear takes the fused launch (every workgroup rotates and quantizes the few rows for itself)
-// when the shape allows it, rather than a quantizer launch and a product launch.  Measured with cold weights
-// on 8 to 117 MB matrices: without rotation the fused launch is level or ahead up to 32768 channels in all
-// (the rows then pass through the quantizer in the registers they were loaded into; 4 tokens of 8192: 10.1
-// against 12.6 us); with rotation a CU spends about 0.2 us per 1024 channels, level for one token up to
-// 16384 channels (7.4 us both ways at 14336), behind from two tokens on (11.3 against 10.2 us).
+// when the shape allows it, rather than a quantizer launch and a product launch.  Without rotation the fused launch is level or ahead up
+// to 32768 channels in all (the rows then pass through the quantizer in the registers they were loaded into; 4 tokens of
+// 8192, cold weights: 10.1 against 12.6 us).  With rotation the line was drawn before the one-instruction stages between lanes and before the
+// 4096-point blocks went to the matrix pipe.  Since then, three sets of weights in turn: blocks up to 512 and of 4096 are ahead up to
+// the line and, except 3 and 4 rows of 8192 in blocks of 4096, beyond it (1 x 14336 -> 4096 6.3 against 8.9, 2 x 8192 -> 4096 5.6 against 7.4 in
+// blocks of 128, 3 x 4096 -> 14336 8.4 against 9.9 in blocks of 4096); blocks of 1024 and 2048, which four of the sixteen wavefronts rotate, are
+// level at 4096 channels and behind from there to the line (1 x 8192 -> 4096 10.4 against 7.8).  Moving it changes which of two
+// orders of sums 128-point blocks have, and with that their codes on ties.
 inline bool fused_few_tokens(int64_t M, int64_t K, int32_t had_block)
 {
     const int64_t total = M * K;
