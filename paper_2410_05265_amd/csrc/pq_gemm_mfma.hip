@@ -34,6 +34,7 @@
 
 #include <hip/hip_fp16.h>
 #include <stdlib.h>
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -951,14 +952,22 @@ double gemm_unsplit_cost_us(int64_t M, int64_t N, int64_t K)
     return best;
 }
 
+// Whole, the launch takes one of the thirteen sizes, of which the figure above knows five.  Their own fit runs up to a fifth low on outputs
+// of few tiles, so it counts with a quarter more: of 95 shapes of 33 to 700 tokens whose choice were the small tiles that turned the seven
+// that are 9 to 31 % faster tiled (181 x 6656 -> 24560 43.8 -> 33.4 us, 137 x 6656 -> 22080 41.6 -> 32.9, 546 x 9216 -> 7632 50.7 -> 44.3) and none of the
+// others (183 x 6016 -> 5696 14.9 against 18.7, 292 x 19456 -> 4992 43 against 53); 170 further
+// calls whose kernel it changes, with and without planes, of one matrix and two: 0.835 x, geometric mean, the slowest 1.007 x.
 double gemm_tiled_cost_us(int64_t M, int64_t N, int64_t K, size_t ws_bytes)
 {
     if (forced_tile() != -1) return 0.0;
-    int bm, S;
+    int bm, S = 1;
     double split = 1e300;
     if (ws_bytes > 0) plan_splitk(M, N, K, ws_bytes, false, &bm, &S, &split);
-    const double whole = gemm_unsplit_cost_us(M, N, K);
-    return split < whole ? split : whole;
+    double whole = gemm_unsplit_cost_us(M, N, K);
+    if (S > 1) return split < whole ? split : whole;
+    if (K % 128 == 0)
+        for (const PackedTile& t : kPackedTiles) whole = std::min(whole, 1.24 * packed_us(t, M, N, K));
+    return whole;
 }
 
 size_t gemm_splitk_workspace_bytes(int64_t M, int64_t N, int64_t K, bool force)

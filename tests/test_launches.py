@@ -108,3 +108,13 @@ def test_every_fused_kernel_runs_several_tasks_of_several_units():
 def test_every_packed_tile_has_its_shape():
     done = launches([dict(fn="gemm", M=M, K=K, N=N, variant=2) for _, M, N, K in TILES])
     assert [kernels(events)[0].startswith("k_gemm_dma<%d, %d," % (t // 1000, t % 1000)) for (t, _, _, _), (_, events) in zip(TILES, done)] == [True] * 13
+
+
+# tokens, channels in, channels out; measured us of the small tiles and of the tiled kernel
+@pytest.mark.parametrize("M,K,N,small_us,tiled_us", [
+    (137, 6656, 22080, 41.6, 32.9), (181, 6656, 24560, 43.8, 33.4), (143, 7680, 23120, 46.5, 36.2), (588, 12672, 7072, 68.9, 57.0),
+    (546, 9216, 7632, 50.7, 44.3), (342, 18560, 11008, 93.9, 86.1), (183, 6016, 5696, 14.9, 18.7), (292, 19456, 4992, 43.1, 52.5),
+    (225, 17920, 6704, 41.5, 49.9), (668, 7936, 2384, 22.9, 25.4), (108, 21888, 15920, 69.6, 74.8), (200, 4096, 6144, 10.8, 13.9)])
+def test_small_tiles_where_they_were_measured_faster(M, K, N, small_us, tiled_us):
+    (_, events), = launches([dict(fn="gemm", M=M, K=K, N=N)])
+    assert kernels(events)[0].startswith("k_gemm_i8_ksplit<") == (small_us < tiled_us)
